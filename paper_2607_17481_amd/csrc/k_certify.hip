@@ -29,8 +29,10 @@ namespace pmp {
 // reads it once, with the selected cells.
 
 // Start state: every finite value is a candidate, the histogram is clear.
+// The join's counts (when given) travel with the state, which the host reads.
 __global__ void k_select_init(SelState *__restrict__ st, int64_t need,
-                              unsigned int *__restrict__ hist) {
+                              unsigned int *__restrict__ hist,
+                              const unsigned long long *__restrict__ counts) {
     for (int i = threadIdx.x; i < kSelBins; i += blockDim.x) hist[i] = 0;
     if (threadIdx.x == 0) {
         st->high = 0;
@@ -39,6 +41,8 @@ __global__ void k_select_init(SelState *__restrict__ st, int64_t need,
         st->need_eq = 0;
         st->nless = 0;
         st->done = 0;
+        st->kept = counts ? counts[0] : 0ull;
+        st->nredo = counts ? (uint32_t)counts[1] : 0u;
     }
 }
 
@@ -319,10 +323,11 @@ int64_t select_blocks(int64_t n) { return (n + kSelTile - 1) / kSelTile; }
 void launch_select(const uint64_t *P, int64_t n, int64_t need, SelState *st,
                    unsigned int *hist, uint32_t *cnt, uint32_t *scan_tmp, uint32_t *less,
                    uint64_t *less_val, uint32_t *eq, uint32_t *less_cell, uint32_t *eq_cell,
-                   const uint32_t *cell, hipStream_t s) {
+                   const uint32_t *cell, const unsigned long long *counts, hipStream_t s) {
     static const int shifts[6] = {53, 42, 31, 20, 9, 0};
     static const int widths[6] = {11, 11, 11, 11, 11, 9};
-    hipLaunchKernelGGL(k_select_init, dim3(1), dim3(kBlock), 0, s, st, need, hist);
+    hipLaunchKernelGGL(k_select_init, dim3(1), dim3(kBlock), 0, s, st, need, hist,
+                       counts);
     if (n <= 0) return;
     for (int ps = 0; ps < 6; ++ps) {
         hipLaunchKernelGGL(k_select_hist, dim3(gridcap(n, 4096)), dim3(kBlock), 0, s, P, n,

@@ -3,9 +3,10 @@
 // After the one pass the profile is a sound upper bound (Prop. 1); let T be
 // the k-th value the greedy accepts on it.  A pair at distance d <= T has, by
 // Lemma 2, true features within T sqrt(m/2) of each other, hence working
-// vectors G (the stored features as a sum of two bf16 numbers) within
-//   R = T sqrt(m/2) + e'_i + e'_j,     e' >= ||G - F|| (stored record bound
-// plus the FP32 and bf16 roundings).  The join finds every such pair:
+// vectors G (the stored features rounded to fp16) within
+//   R = T sqrt(m/2) + e'_i + e'_j,     e' >= ||G - F||
+// (the record's bound, the FP32 rounding and the fp16 rounding itself, which
+// k_join_ops measures window by window).  The join finds every such pair:
 //
 //  * grid: each length's windows get coordinates, the projections of their
 //    FP32 feature copies f on the leading principal directions of that
@@ -14,26 +15,29 @@
 //    them, in cells of width h >= R_f, place a pair within R_f in adjacent
 //    cells (or one, in finer cells, when R_f is below the two-coordinate
 //    grid's resolution), and all three must differ by at most R_f;
-//  * tiles: windows sorted by (length, cell) are cut into tiles of 32; a
-//    tile's candidates are the windows of the cells next to its queries' cells
-//    (each a contiguous run of the order), taken 32 at a time;
-//  * filter: for a 32 x 32 tile, <G_q, G_c> comes from six MFMA products in
-//    bf16 with FP32 accumulation (hi.hi + hi.lo + lo.hi), and
+//  * tiles: windows sorted by (length, cell) are cut into blocks of 128
+//    queries, one wavefront each; its candidates are the windows of the cells
+//    next to its queries' cells (each a contiguous run of the order), taken 32
+//    at a time against the four query tiles of 32;
+//  * filter: for a 32 x 32 tile, <G_q, G_c> comes from two fp16 MFMA products
+//    (the products are exact in FP32, which also accumulates them), and
 //      ||dG||^2 = |G_q|^2 + |G_c|^2 - 2 <G_q, G_c>
 //    is bounded below with a rigorous rounding margin; a pair is kept unless
-//    that bound exceeds R^2;
+//    that bound exceeds R^2.  It is a prefilter only: what it rejects provably
+//    lies past T, and what it keeps is decided on the stored records and the
+//    FP64 distance, so its 16 bits touch no result;
 //  * exact: kept pairs pass the exclusion test, the certified Parseval bound
 //    from the stored records (<= T and below one of the two cells) and are
 //    verified with the canonical FP64 distance, lowering both cells.  The
 //    tiles hand their kept pairs to a buffer, and the exact stage runs as a
-//    kernel of its own (k_join_verify) after each chunk of tiles: the tiles
-//    walk in step as a block, so an exact stage inside them would hold the
-//    block's other wavefronts at the next barrier.
+//    kernel of its own (k_join_verify) after each chunk of tiles.
 //
 // Every unordered pair is examined once: a pair whose other end is itself a
-// query and comes earlier in the order is left to that end's tile (both ends
+// query and comes earlier in the order is left to that end's block (both ends
 // see each other, since cell adjacency is symmetric and the filter is
-// conservative on both sides).
+// conservative on both sides).  At a length where every window is a query (no
+// cell at 0: the usual case while T > 0) a block skips the candidates before
+// its own first query altogether.
 #include "pmp_dev.h"
 
 namespace pmp {
@@ -41,41 +45,50 @@ namespace pmp {
 namespace {
 
 constexpr int kJT = kJoinTile;                // queries / candidates per tile
-constexpr int kQueueHigh = 128;               // kept pairs buffered before they are handed on
-constexpr int kQueueCap = kQueueHigh + kJT * kJT;   // room for one more whole tile
+constexpr int kQueueCap = 512;                // group hits buffered before they are resolved
+constexpr int kOutCap = 192;                  // kept pairs buffered before they are handed on
 constexpr int kCovSample = 1024;              // windows per length for the principal directions
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
 
-__device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) {
-    union {
-        uint4 u;
-        bf16x8 b;
-    } c;
-    c.u = v;
-    return c.b;
+// acc + a . b of two fp16 pairs (exact products, FP32 sums).
+__device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float acc) {
+    f16x2 x, y;
+    __builtin_memcpy(&x, &a, 4);
+    __builtin_memcpy(&y, &b, 4);
+    acc = fmaf((float)x[0], (float)y[0], acc);
+    return fmaf((float)x[1], (float)y[1], acc);
 }
 
-// Lower bound (first index with key >= target) in the sorted keys[lo, hi),
-// by a 64-ary search of the whole wavefront (uniform result).
-__device__ __forceinline__ int64_t wave_lower_bound(const uint32_t *__restrict__ keys, int64_t lo,
-                                                    int64_t hi, uint32_t target) {
-    const int lane = lane_id();
-    while (hi - lo > kWave) {
-        const int64_t step = (hi - lo + kWave - 1) / kWave;
-        const int64_t idx = lo + (int64_t)lane * step;
-        const bool below = idx < hi && keys[idx] < target;
-        const int cnt = __popcll(__ballot(below));
+__device__ __forceinline__ f16x8 as_f16x8(uint4 v) {
+    union {
+        uint4 u;
+        f16x8 h;
+    } c;
+    c.u = v;
+    return c.h;
+}
+
+// First position of the sorted keys[lo, hi) with key >= v (incl) or > v, by a
+// 64-ary search of the whole wavefront (uniform arguments and result).
+__device__ __forceinline__ uint32_t wave_first(const uint32_t *__restrict__ keys, uint32_t lo,
+                                               uint32_t hi, uint32_t v, bool incl) {
+    const uint32_t lane = (uint32_t)lane_id();
+    while (hi > lo) {
+        const uint32_t step = (hi - lo + kWave - 1) / kWave;
+        const uint32_t idx = lo + lane * step;
+        const uint32_t key = idx < hi ? keys[idx] : 0xFFFFFFFFu;
+        const bool below = idx < hi && (incl ? key < v : key <= v);
+        const uint32_t cnt = (uint32_t)__popcll(__ballot(below));
         if (cnt == 0) return lo;
-        const int64_t nlo = lo + (int64_t)(cnt - 1) * step + 1;
-        const int64_t nhi = min(hi, lo + (int64_t)cnt * step);
-        lo = nlo;
-        hi = nhi;
+        // keys[lo + (cnt - 1) step] is below, keys[lo + cnt step] is not
+        const uint32_t end = lo + cnt * step;
+        lo += (cnt - 1) * step + 1;
+        hi = end < hi ? end : hi;
     }
-    const int64_t idx = lo + lane;
-    const bool below = idx < hi && keys[idx] < target;
-    return lo + __popcll(__ballot(below));
+    return lo;
 }
 
 __device__ __forceinline__ int wave_min_i(int v) {
@@ -87,22 +100,6 @@ __device__ __forceinline__ int wave_max_i(int v) {
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, kWave));
     return v;
-}
-
-// G of one window, in FP64 (hi + lo is exact).
-__device__ __forceinline__ void load_g(const uint4 *__restrict__ op, double g[2 * kMaxK]) {
-#pragma unroll
-    for (int part = 0; part < 4; ++part) {
-        const uint4 h = op[part], w = op[4 + part];
-        const uint32_t hs[4] = {h.x, h.y, h.z, h.w}, ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            g[8 * part + 2 * e] = (double)__uint_as_float(hs[e] << 16) +
-                                  (double)__uint_as_float(ws[e] << 16);
-            g[8 * part + 2 * e + 1] = (double)__uint_as_float(hs[e] & 0xFFFF0000u) +
-                                      (double)__uint_as_float(ws[e] & 0xFFFF0000u);
-        }
-    }
 }
 
 }  // namespace
@@ -248,7 +245,8 @@ __global__ __launch_bounds__(kBlock) void k_grid_keys(Req q, const GridLen *__re
                                                       uint32_t *__restrict__ gkey,
                                                       uint32_t *__restrict__ gval,
                                                       uint8_t *__restrict__ qf,
-                                                      float4 *__restrict__ gp) {
+                                                      float4 *__restrict__ gp,
+                                                      uint32_t *__restrict__ nonq) {
     const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (k >= N) return;
     const int64_t k_first = (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~(kWave - 1));
@@ -271,26 +269,34 @@ __global__ __launch_bounds__(kBlock) void k_grid_keys(Req q, const GridLen *__re
     const int64_t i = (int64_t)q.cell[k] - q.len[l].cell_base;
     const bool f = q.P[k] != 0ull && (l < l_lim || (l == l_lim && i <= i_lim));
     qf[k] = f;
+    if (!f) nonq[l] = 1u;                         // (every writer stores the same value)
     // the same flag in the sign of the candidate's Gram term, so that a
     // candidate tile reads one 16-byte word per window besides its operands
     gp[k].w = f ? -fabsf(c.w) : fabsf(c.w);
 }
 
 // The join operands and coordinates in sorted (grid) order, so that a tile
-// of the order reads one contiguous block, with no index load before it.
+// of the order reads contiguous blocks, with no index load before them: the
+// operands as two arrays of half rows (32 bytes each, one per matrix product),
+// the Gram terms again on their own.
 __global__ __launch_bounds__(kBlock) void k_join_gather(const uint32_t *__restrict__ gval,
                                                         const uint4 *__restrict__ jop,
                                                         const float4 *__restrict__ gp, int64_t n,
                                                         uint4 *__restrict__ jop_s,
-                                                        float4 *__restrict__ gp_s) {
-    // eight threads per window: one 16-byte part of its operands each
+                                                        float4 *__restrict__ gp_s,
+                                                        float *__restrict__ gw_s) {
+    // four threads per window: one 16-byte part of its operands each
     const int64_t x = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const int64_t pos = x >> 3;
-    const int part = (int)(x & 7);
+    const int64_t pos = x >> 2;
+    const int part = (int)(x & 3);
     if (pos >= n) return;
     const uint32_t k = gval[pos];
-    jop_s[pos * 8 + part] = jop[(int64_t)k * 8 + part];
-    if (part == 0) gp_s[pos] = gp[k];
+    jop_s[(part >> 1) * 2 * n + pos * 2 + (part & 1)] = jop[(int64_t)k * kJoinOp + part];
+    if (part == 0) {
+        const float4 g = gp[k];
+        gp_s[pos] = g;
+        gw_s[pos] = g.w;
+    }
 }
 
 // ------------------------------------------------------------ the tiles
@@ -348,41 +354,73 @@ __device__ __forceinline__ uint32_t join_exact(const Req &q, bool valid, uint32_
     return n_ver;
 }
 
-// A block of kJB wavefronts takes kJB consecutive query tiles of 32 sorted
-// windows of one length.  It walks the candidate runs of the union of their
-// queries' neighbourhoods together, and each candidate tile is loaded once
-// by the whole block into LDS (double-buffered: the next tile's loads are in
-// flight while the current one goes through the matrix cores and the
-// filter) and read from there by every wavefront, so the kJB query tiles,
-// whose neighbourhoods nearly coincide, share its global traffic.  Every
-// wavefront keeps its own queries, filter terms and queue of kept pairs (as
-// window indices (k_q, k_c)).  A full queue is copied to the pair buffer,
-// whose pairs k_join_verify takes after the launch; a wavefront that finds
-// the buffer full runs the exact stage of the rest in place.  The launch
-// covers the blocks [blk0, blk0 + gridDim.x) of the round.
-constexpr int kJB = kJoinBlock;               // query tiles (wavefronts) per block
-constexpr int kJRow = 9;                      // uint4 per LDS operand row (8 + 1: no bank conflicts)
+// One wavefront per block of 128 sorted queries of one length (four tiles of
+// 32, their fp16 operands in registers).  It lists the runs of candidates
+// next to its queries' cells, 64 grid rows at a time: one lane per row finds
+// the row's range of cells and, by binary search in the sorted keys, its run.
+// Then it walks the runs 32 candidates at a time: two 16-byte operand words
+// and one Gram term per lane (the next tile's loads in flight through the
+// current one's products), two products per query tile.  The query's filter
+// term rides in the two operand slots past the features, so a pair is kept
+// iff its accumulator reaches the candidate's Gram term, and most tiles end
+// at one comparison of their largest accumulator.
+//
+// The accumulators are tested four rows at a time (the largest of the four,
+// one bit per lane and group), and the groups that hold a passing pair go to a
+// queue in LDS as (first row, candidate): a step of 4096 pairs keeps about
+// five at noisy data, and resolving them row by row from the accumulators took
+// more issue slots than the products and the test together.  A full queue is
+// resolved one pair per lane: coordinates, order (a candidate that is a query
+// earlier in the order leaves the pair to its own block), then the pair's own
+// product against the same term, by fp16 dot products.  The pairs left become
+// window indices and go to the pair buffer, whose pairs k_join_verify takes
+// after the launch.  A wavefront that finds the buffer
+// full puts its block on the list of overflowed blocks and stops; those are
+// taken again from their start with an emptied buffer (the pairs of the first
+// attempt that reached the buffer are then verified twice, which changes no
+// minimum), or, should one alone overflow it, by the kRedo form, which
+// verifies its pairs in place.  Keeping the exact stage out of the main form
+// keeps the walk in registers.  The main form covers the blocks [blk0, blk0 +
+// gridDim.x) of the round, or those of a list.
+//
+// Wavefronts share nothing and meet no barrier.  The form before shared
+// candidate tiles through LDS among four wavefronts of one query tile each and
+// took six bf16 products a tile; it was bound by its barriers, by a row filter
+// of about 100 VALU instructions a tile and by the mirror image of every pair.
+// Measured (FP32 form, ECG-like, 51 lengths of 100..400): 250,000 samples 27 ->
+// 5.8 ms for all tiles, 1,000,000 samples 280 -> 64 ms.  What bounds it now is
+// the first-level cache: of about 200 accesses a step of 4096 pairs, 36 are the
+// candidates' operands and the rest the rows that resolve() gathers; the matrix
+// cores are busy 15% of the time, the vector units 40%.
+constexpr int kJB = kJoinBlock;               // query tiles per wavefront
+constexpr int kJQ = kJB * kJT;                // queries per wavefront
+constexpr int kXcds = 8;
+constexpr int64_t kJSeg = 128;                // consecutive blocks per XCD (16,384 queries)
+constexpr int kJWaves = 4;                    // wavefronts per SIMD the registers are held to
 
-template <typename FT>
-__global__ __launch_bounds__(kJB * kWave) __attribute__((amdgpu_waves_per_eu(3)))
-void k_join_tiles(Req q, const GridLen *__restrict__ gl, const uint32_t *__restrict__ gkey,
-                  const uint32_t *__restrict__ gval, const uint8_t *__restrict__ qf,
-                  const uint4 *__restrict__ jop_s, const float4 *__restrict__ jmeta,
-                  const float4 *__restrict__ gp_s, int cb1, int cb2, int cb3, double T,
-                  int64_t blk0, uint2 *__restrict__ pairs, unsigned long long *__restrict__ pcount,
-                  int64_t cap) {
-    __shared__ uint2 queue[kJB][kQueueCap];
-    __shared__ uint32_t rowk[kJB][kJT];               // the queries' window indices
-    __shared__ uint32_t ck[2][kJT];                   // the candidates' window indices
-    __shared__ float roww[kJB][kJT];                  // the queries' Gram filter terms
-    __shared__ float4 rowc[kJB][kJT];                 // the queries' principal coordinates
-    __shared__ uint4 cop[2][kJT][kJRow];              // candidate operands, two tiles
-    __shared__ float4 cgp[2][kJT];                    // candidate coordinates and Gram terms
-    __shared__ int red[2][kJB];                       // block reductions
-    const int tid = threadIdx.x;
-    const int wv = tid / kWave;
+struct JoinSmem {
+    uint2 queue[kQueueCap];                   // (first row, candidate) of groups of four rows
+    uint2 outq[kOutCap];                      // kept pairs (k_q, k_c)
+    uint32_t qkey[kJQ];                       // the queries' cells (kNone: not a query)
+    float qv[kJQ];                            // the queries' filter terms
+    uint32_t rbeg[kWave], rend[kWave];        // the non-empty runs of 64 grid rows
+};
+
+template <typename FT, bool kRedo>
+__device__ __forceinline__ void join_block(const Req &q, const GridLen *__restrict__ gl,
+                                           const uint32_t *__restrict__ gkey,
+                                           const uint32_t *__restrict__ gval,
+                                           const uint8_t *__restrict__ qf,
+                                           const uint4 *__restrict__ jop_s,
+                                           const float4 *__restrict__ jmeta,
+                                           const float4 *__restrict__ gp_s,
+                                           const float *__restrict__ gw_s, int64_t nwin,
+                                           const uint32_t *__restrict__ nonq, int cb1, int cb2,
+                                           int cb3, double T, int64_t gb, const JoinOut &out,
+                                           JoinSmem &sm) {
+    uint2 *const queue = sm.queue, *const outq = sm.outq;
+    uint32_t *const qkey = sm.qkey, *const rbeg = sm.rbeg, *const rend = sm.rend;
     const int lane = lane_id();
-    const int64_t gb = blk0 + (int64_t)blockIdx.x;
     int l;
     {
         int lo = 0, hi = q.L - 1;
@@ -393,281 +431,368 @@ void k_join_tiles(Req q, const GridLen *__restrict__ gl, const uint32_t *__restr
         l = lo;
     }
     const GridLen &G = gl[l];
-    const LenInfo L = q.len[l];
-    const int m = L.m;
-    const int64_t pbeg = L.kbase, pend = L.kbase + L.n_index;
-    const int64_t p0 = pbeg + ((gb - G.blk_base) * kJB + wv) * kJT;
+    const int m = q.len[l].m;
+    const int64_t cell_base = q.len[l].cell_base;
+    // positions of the sorted order fit 32 bits (at most 2^31 - 1 cells)
+    const uint32_t pbeg = (uint32_t)q.len[l].kbase;
+    const uint32_t pend = pbeg + (uint32_t)q.len[l].n_index;
+    const uint32_t p0 = pbeg + (uint32_t)((gb - G.blk_base) * kJQ);
     const int i = lane % kJT, hh = lane / kJT;
-    const int64_t pq = p0 + i;
-    const bool validq = pq < pend;
-    const uint32_t kq = validq ? gval[pq] : 0u;
-    const bool isq = validq && qf[kq];
+    const float scale = join_scale(m);
 
-    // block-wide min and max of one wave-uniform value per wavefront
-    auto block_minmax = [&](int vmin, int vmax, int &omin, int &omax) {
-        if (lane == 0) {
-            red[0][wv] = vmin;
-            red[1][wv] = vmax;
-        }
-        __syncthreads();
-        omin = red[0][0];
-        omax = red[1][0];
+    const uint4 *const op0 = jop_s, *const op1 = jop_s + 2 * nwin;
+
+    // ---- query operands (A), their filter terms in slots 30 and 31
+    f16x8 a0[kJB], a1[kJB];
+    const uint32_t kmask = (1u << (cb1 + cb2 + cb3)) - 1u;
+    bool any = false;
 #pragma unroll
-        for (int w = 1; w < kJB; ++w) {
-            omin = min(omin, red[0][w]);
-            omax = max(omax, red[1][w]);
-        }
-        __syncthreads();
-    };
-    {
-        int none, anyq;
-        block_minmax(0, __ballot(isq) ? 1 : 0, none, anyq);
-        if (!anyq) return;                        // uniform over the block
-    }
-
-    // ---- query operands (A) and filter terms
-    bf16x8 aH0, aH1, aL0, aL1;
-    {
-        const uint4 *o = jop_s + pq * 8;
+    for (int t = 0; t < kJB; ++t) {
+        const uint32_t pq = p0 + (uint32_t)(t * kJT + i);
+        const bool validq = pq < pend;
+        const uint32_t kq = validq ? gval[pq] : 0u;
+        const bool isq = validq && qf[kq];
+        any |= __ballot(isq) != 0ull;
         const uint4 z = make_uint4(0, 0, 0, 0);
-        aH0 = as_bf16x8(isq ? o[hh] : z);
-        aH1 = as_bf16x8(isq ? o[2 + hh] : z);
-        aL0 = as_bf16x8(isq ? o[4 + hh] : z);
-        aL1 = as_bf16x8(isq ? o[6 + hh] : z);
+        float vq = -INFINITY;                             // not a query: keeps nothing
+        uint4 w0 = isq ? op0[(int64_t)pq * 2 + hh] : z, w1 = isq ? op1[(int64_t)pq * 2 + hh] : z;
+        if (hh == 1) {
+            // a pair is kept iff <G_q, G_c> + v >= 0.5 |G_c|^2, with v at
+            // least 0.5 (R^2 - |G_q|^2) plus every rounding of the left side
+            float hi = -65504.0f, lo = 0.0f;
+            if (isq) {
+                const float4 mt = jmeta[kq];              // |G|^2, e', |G| bound, 0
+                const double R = (G.Tr + (double)mt.y + (double)q.jemax[l]) * (1.0 + 1e-9);
+                const double nG2 = (double)mt.x * (1.0 - 0x1.0p-23);
+                double v = 0.5 * (R * R * (1.0 + 1e-9) - nG2) + G.eps_c * (double)mt.z + 1e-30;
+                v += 0x1.0p-22 * (fabs(v) + G.nmax2);
+                // the slots' share of the accumulation (at most 34 additions)
+                // and of the split into hi + lo
+                v += 5e-6 * fabs(v) + 0x1.0p-12 * (double)scale;
+                // (past the range every pair passes: |v| / scale is below
+                // 32768 wherever the test decides anything)
+                const float x = (float)fmin(fmax(v / (double)scale, -60000.0), 60000.0);
+                vq = x * scale;
+                hi = half_float(half_bits(x));
+                lo = x - hi;
+                if (fabsf(hi) < 0x1.0p-14f) hi = 0.0f;
+                if (fabsf(lo) < 0x1.0p-14f) lo = 0.0f;
+            }
+            w1.w = half_bits(hi) | (half_bits(lo) << 16);
+        }
+        a0[t] = as_f16x8(w0);
+        a1[t] = as_f16x8(w1);
+        if (hh == 0) qkey[t * kJT + i] = isq ? (gkey[pq] & kmask) : kNone;
+        if (hh == 1) sm.qv[t * kJT + i] = vq;
     }
-    float a = INFINITY;                                   // filter term of query i
-    if (isq) {
-        const float4 mt = jmeta[kq];                      // |G|^2, e', |G| bound, 0
-        const double nG2 = (double)mt.x * (1.0 - 0x1.0p-23);
-        double v = 0.5 * (nG2 - G.R2) - G.eps_c * (double)mt.z - 1e-30;
-        v -= 0x1.0p-22 * (fabs(v) + G.nmax2);
-        a = (float)v;
-    }
-    if (hh == 0) {
-        roww[wv][i] = a;
-        rowk[wv][i] = kq;
-        rowc[wv][i] = isq ? gp_s[pq] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    }
+    if (!any) return;                                     // uniform
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 
-    // ---- the rows of adjacent cells, over the block's queries
-    const uint32_t mask1 = (1u << cb1) - 1u, mask2 = (1u << cb2) - 1u, mask3 = (1u << cb3) - 1u;
-    const uint32_t key_q = validq ? gkey[pq] : 0u;
-    const int c1q = (int)((key_q >> (cb2 + cb3)) & mask1), c2q = (int)((key_q >> cb3) & mask2);
-    const int c3q = (int)(key_q & mask3);
-    int c1min, c1max;
-    block_minmax(wave_min_i(isq ? c1q : INT_MAX), wave_max_i(isq ? c1q : -1), c1min, c1max);
-    const uint32_t lbits = (uint32_t)l << (cb1 + cb2 + cb3);
-    unsigned long long n_pairs = 0, n_kept = 0, n_ver = 0;
-    int qn = 0;                                           // queued pairs (wave-uniform)
+    unsigned long long n_tiles = 0, n_kept = 0, n_ver = 0;
+    int qn = 0, on = 0;                                   // queued groups, kept pairs (uniform)
+    bool over = false;                                    // the buffer ran full (uniform)
 
-    // hand the queued pairs of this wavefront to the pair buffer: one
-    // reservation for the whole queue; the part past the buffer's end gets
-    // the exact stage here
-    auto spill = [&]() {
-        // the queue is written and read by lanes of this wavefront only
+    auto lds_sync = [] {
+        // LDS is written and read by this wavefront only
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        unsigned long long base = 0;
-        if (lane == 0) {
-            base = atomicAdd(pcount, (unsigned long long)qn);
-            n_kept += (unsigned long long)qn;
+    };
+    // hand the kept pairs to the pair buffer (or, kRedo, verify them here)
+    auto hand_on = [&]() {
+        lds_sync();
+        n_kept += (unsigned long long)on;
+        if (kRedo) {
+            for (int b = 0; b < on; b += kWave) {
+                const int e = b + lane;
+                const uint2 pr = e < on ? outq[e] : make_uint2(0u, 0u);
+                n_ver += join_exact<FT, false, true>(q, e < on, pr.x, pr.y, m, cell_base,
+                                                     G.sqrt2m, T);
+            }
+        } else {
+            unsigned long long base = 0;
+            if (lane == 0) base = atomicAdd(out.pcount, (unsigned long long)on);
+            base = (unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)base) |
+                   (unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)) << 32;
+            const unsigned long long cap = (unsigned long long)out.cap;
+            const int fit = base >= cap ? 0 : (int)min((unsigned long long)on, cap - base);
+            for (int e = lane; e < fit; e += kWave) out.pairs[base + e] = outq[e];
+            over |= __builtin_amdgcn_readfirstlane(fit < on ? 1 : 0) != 0;
         }
-        base = __shfl(base, 0, kWave);
-        const int fit = base >= (unsigned long long)cap
-                            ? 0 : (int)min((unsigned long long)qn, (unsigned long long)cap - base);
-        for (int e = lane; e < fit; e += kWave) pairs[base + e] = queue[wv][e];
-        for (int b = fit; b < qn; b += kWave) {
-            const int e = b + lane;
-            const uint2 pr = e < qn ? queue[wv][e] : make_uint2(0u, 0u);
-            n_ver += join_exact<FT, false, true>(q, e < qn, pr.x, pr.y, m, L.cell_base, G.sqrt2m, T);
+        lds_sync();
+        on = 0;
+    };
+    // resolve the queued groups: lane 4 e + r takes row r of entry e
+    auto resolve = [&]() {
+        lds_sync();
+        for (int b = 0; b < qn; b += kWave / 4) {
+            const int e = b + (lane >> 2);
+            bool keep = false;
+            uint32_t pq = 0, pc = 0;
+            if (e < qn) {
+                const uint2 pr = queue[e];
+                pq = pr.x + (uint32_t)(lane & 3);
+                pc = pr.y;
+                if (pq < pend) {
+                    const float4 gq = gp_s[pq], gc = gp_s[pc];
+                    const float v = sm.qv[pq - p0];
+                    keep = fabsf(gq.x - gc.x) <= G.rp && fabsf(gq.y - gc.y) <= G.rp &&
+                           fabsf(gq.z - gc.z) <= G.rp && pq != pc &&
+                           !(signbit(gc.w) && pc < pq);
+                    if (keep) {
+                        // the pair's own product: exact fp16 products summed
+                        // in FP32, within the same rounding bound as the
+                        // matrix products' (the slots past the features out)
+                        float dot = 0.0f;
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) {
+                            const uint4 x = (w < 2 ? op0 : op1)[(int64_t)pq * 2 + (w & 1)];
+                            const uint4 y = (w < 2 ? op0 : op1)[(int64_t)pc * 2 + (w & 1)];
+                            dot = dot2(x.x, y.x, dot);
+                            dot = dot2(x.y, y.y, dot);
+                            dot = dot2(x.z, y.z, dot);
+                            if (w < 3) dot = dot2(x.w, y.w, dot);
+                        }
+                        keep = dot + v >= fabsf(gc.w);
+                    }
+                }
+            }
+            const uint64_t mk = __ballot(keep);
+            if (mk == 0ull) continue;
+            if (keep) outq[on + __popcll(mk & lanemask_lt())] = make_uint2(gval[pq], gval[pc]);
+            on += __popcll(mk);
+            if (on > kOutCap - kWave) hand_on();
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        lds_sync();
         qn = 0;
     };
 
-    // the block's candidate runs (one per grid row next to a query's cell);
-    // every decision below is uniform over the block, so that every
-    // wavefront passes the same barriers
-    int c1p = max(c1min - kJoinNb, 0) - 1;
-    const int c1end = min(c1max + kJoinNb, (int)mask1);
-    int64_t c0 = 0, cend = 0;
-    int c2p = 0, c2end = -1;                              // three coordinates: the row's c2 range
-    // move [c0, cend) to the next non-empty run once the current one is used
-    // up; false when there is none
-    auto next_run = [&]() -> bool {
-        if (cb3 > 0) {
-            // three coordinates: one run per pair of adjacent (c1, c2) cells,
-            // over the c3 cells next to the queries of that pair
-            while (c0 >= cend && (c2p < c2end || c1p < c1end)) {
-                if (c2p >= c2end) {
-                    ++c1p;
-                    const bool near1 = isq && abs(c1q - c1p) <= kJoinNb;
-                    int lo2, hi2;
-                    block_minmax(wave_min_i(near1 ? max(c2q - kJoinNb, 0) : INT_MAX),
-                                 wave_max_i(near1 ? min(c2q + kJoinNb, (int)mask2) : -1), lo2, hi2);
-                    if (lo2 > hi2) continue;
-                    c2p = lo2 - 1;
-                    c2end = hi2;
-                    continue;
-                }
-                ++c2p;
-                const bool near = isq && abs(c1q - c1p) <= kJoinNb && abs(c2q - c2p) <= kJoinNb;
-                int c3lo, c3hi;
-                block_minmax(wave_min_i(near ? max(c3q - kJoinNb, 0) : INT_MAX),
-                             wave_max_i(near ? min(c3q + kJoinNb, (int)mask3) : -1), c3lo, c3hi);
-                if (c3lo > c3hi) continue;
-                const uint32_t rk = lbits | ((uint32_t)c1p << (cb2 + cb3)) | ((uint32_t)c2p << cb3);
-                c0 = wave_lower_bound(gkey, pbeg, pend, rk | (uint32_t)c3lo);
-                cend = wave_lower_bound(gkey, c0, pend, (rk | (uint32_t)c3hi) + 1u);
-            }
-        } else if (cb2 == 0) {
-            // one coordinate: the cells next to the queries' cells form a
-            // single run of the order
-            if (c0 >= cend && c1p < c1end) {
-                const uint32_t klo = lbits | (uint32_t)(c1p + 1);
-                c1p = c1end;
-                c0 = wave_lower_bound(gkey, pbeg, pend, klo);
-                cend = wave_lower_bound(gkey, c0, pend, (lbits | (uint32_t)c1end) + 1u);
-            }
-        } else {
-            while (c0 >= cend && c1p < c1end) {
-                ++c1p;
-                const bool near = isq && abs(c1q - c1p) <= kJoinNb;
-                int c2lo, c2hi;
-                block_minmax(wave_min_i(near ? max(c2q - kJoinNb, 0) : INT_MAX),
-                             wave_max_i(near ? min(c2q + kJoinNb, (int)mask2) : -1), c2lo, c2hi);
-                if (c2lo > c2hi) continue;
-                const uint32_t rk = lbits | ((uint32_t)c1p << cb2);
-                c0 = wave_lower_bound(gkey, pbeg, pend, rk | (uint32_t)c2lo);
-                cend = wave_lower_bound(gkey, c0, pend, (rk | (uint32_t)c2hi) + 1u);
-            }
-        }
-        return c0 < cend;
-    };
-    // a candidate tile is the positions [tc0, min(tc0 + 32, tend)); the block
-    // loads it with one 16-byte part of one candidate per thread (and the
-    // coordinates of one candidate on each of the first 32 threads)
-    const int ld_c = tid / 8, ld_part = tid % 8;
-    auto load_part = [&](bool have_t, int64_t tc0, int64_t tend, uint4 &op, float4 &cg,
-                         uint32_t &kc) {
-        const int64_t pc = tc0 + ld_c;
-        op = have_t && pc < tend ? jop_s[pc * 8 + ld_part] : make_uint4(0, 0, 0, 0);
-        if (tid < kJT) {
-            const int64_t pg = tc0 + tid;
-            const bool in = have_t && pg < tend;
-            cg = in ? gp_s[pg] : make_float4(0.0f, 0.0f, 0.0f, INFINITY);
-            kc = in ? gval[pg] : 0u;
-        }
-    };
-    auto store_part = [&](int buf, const uint4 &op, const float4 &cg, uint32_t kc) {
-        cop[buf][ld_c][ld_part] = op;
-        if (tid < kJT) {
-            cgp[buf][tid] = cg;
-            ck[buf][tid] = kc;
-        }
-    };
-
-    bool have = next_run();
-    int64_t tc0 = c0;
+    // ---- the grid rows next to the queries' cells
+    const uint32_t mask1 = (1u << cb1) - 1u, mask2 = (1u << cb2) - 1u, mask3 = (1u << cb3) - 1u;
+    const uint32_t lbits = (uint32_t)l << (cb1 + cb2 + cb3);
+    // rows are c1 cells with one or two coordinates (one coordinate: a single
+    // row, the whole range), (c1, c2) pairs with three
+    int r1lo, r1hi, r2lo = 0, r2n = 1;
     {
-        uint4 op;
-        float4 cg;
-        uint32_t kc = 0;
-        load_part(have, tc0, cend, op, cg, kc);
-        store_part(0, op, cg, kc);
-    }
-    __syncthreads();
-    // the Gram filter terms of the 16 rows this lane holds, in registers for
-    // the whole walk (rows 8 (r / 4) + 4 hh + r % 4 of the result)
-    float rw[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) rw[r] = roww[wv][8 * (r / 4) + 4 * hh + (r % 4)];
-    int cur = 0;
-    c0 += kJT;
-    bool have1 = have && next_run();
-    while (have) {
-        // the next tile's loads, in flight through this tile's work
-        const int64_t nc0 = c0, nend = cend;
-        uint4 op;
-        float4 cg;
-        uint32_t kcn = 0;
-        load_part(have1, nc0, nend, op, cg, kcn);
-        // this tile: operands from LDS (lane (i, hh) holds candidate tc0 + i)
-        const bf16x8 bH0 = as_bf16x8(cop[cur][i][hh]), bH1 = as_bf16x8(cop[cur][i][2 + hh]);
-        const bf16x8 bL0 = as_bf16x8(cop[cur][i][4 + hh]), bL1 = as_bf16x8(cop[cur][i][6 + hh]);
-        const float4 gc = cgp[cur][i];
-        const float bj = fabsf(gc.w);
-        f32x16 acc = {};
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aH0, bH0, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aH1, bH1, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aH0, bL0, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aH1, bL1, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aL0, bH0, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aL1, bH1, acc, 0, 0, 0);
-        n_pairs += 16;
-        // the Gram test of the 16 rows this lane holds, as a bit mask (bit r:
-        // row 8 (r / 4) + 4 hh + r % 4); most tiles keep nothing
-        uint32_t km = 0;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) km |= (acc[r] >= rw[r] + bj ? 1u : 0u) << r;
-        if (__ballot(km != 0u)) {
-            // keep (row, candidate) unless a coordinate rules it out, the
-            // candidate is a query earlier in the order (its tile takes the
-            // pair) or it is the row itself (positions relative to the query
-            // tile p0); each lane walks only its own passing rows
-            const int pcr = (int)(tc0 + i - p0);
-            const bool qc = gc.w != INFINITY && signbit(gc.w);
-            uint32_t kk = 0;
-            for (uint32_t b = km; b != 0u; b &= b - 1u) {
-                const int r = __builtin_ctz(b);
-                const int row = 8 * (r >> 2) + 4 * hh + (r & 3);
-                const float4 rc = rowc[wv][row];
-                if (fabsf(rc.x - gc.x) <= G.rp && fabsf(rc.y - gc.y) <= G.rp &&
-                    fabsf(rc.z - gc.z) <= G.rp && pcr != row && !(qc && pcr < row))
-                    kk |= 1u << r;
-            }
-            // queue positions: an exclusive prefix sum of the counts
-            const int cnt = __popc(kk);
-            int pre = cnt;
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) {
-                const int v = __shfl_up(pre, off, kWave);
-                if (lane >= off) pre += v;
-            }
-            const int total = __shfl(pre, kWave - 1, kWave);
-            int pos = qn + pre - cnt;
-            const uint32_t kcand = ck[cur][i];
-            for (uint32_t b = kk; b != 0u; b &= b - 1u) {
-                const int r = __builtin_ctz(b);
-                queue[wv][pos++] = make_uint2(rowk[wv][8 * (r >> 2) + 4 * hh + (r & 3)], kcand);
-            }
-            qn += total;
-            if (qn > kQueueHigh) spill();
+        int lo1 = INT_MAX, hi1 = -1, lo2 = INT_MAX, hi2 = -1;
+        for (int x = lane; x < kJQ; x += kWave) {
+            const uint32_t key = qkey[x];
+            if (key == kNone) continue;
+            const int c1 = (int)(key >> (cb2 + cb3)), c2 = (int)((key >> cb3) & mask2);
+            lo1 = min(lo1, c1);
+            hi1 = max(hi1, c1);
+            lo2 = min(lo2, c2);
+            hi2 = max(hi2, c2);
         }
-        // stage the next tile; after the barrier it is the current one
-        store_part(cur ^ 1, op, cg, kcn);
-        __syncthreads();
-        cur ^= 1;
-        have = have1;
-        tc0 = nc0;
-        if (have) {
-            c0 += kJT;
-            have1 = next_run();
+        lo1 = wave_min_i(lo1);
+        hi1 = wave_max_i(hi1);
+        lo2 = wave_min_i(lo2);
+        hi2 = wave_max_i(hi2);
+        r1lo = max(lo1 - kJoinNb, 0);
+        r1hi = min(hi1, (int)mask1 - kJoinNb) + kJoinNb;
+        if (cb3 > 0) {
+            r2lo = max(lo2 - kJoinNb, 0);
+            r2n = min(hi2 + kJoinNb, (int)mask2) - r2lo + 1;
         }
     }
-    if (qn > 0) spill();
+    // every window of the length a query: the candidates before this block's
+    // first query see this block's queries themselves
+    const uint32_t first = nonq[l] ? pbeg : p0;
+    const int nrows = cb2 == 0 ? 1 : (r1hi - r1lo + 1) * r2n;
+
+    for (int row0 = 0; row0 < nrows && !over; row0 += kWave) {
+        // ---- one lane per row: its range of keys, then its run
+        const int row = row0 + lane;
+        uint32_t beg = 0, end = 0;
+        uint32_t klo = 1u, khi = 0u;
+        if (row < nrows) {
+            if (cb2 == 0) {
+                klo = lbits | (uint32_t)r1lo;
+                khi = lbits | (uint32_t)r1hi;
+            } else {
+                const int c1 = r1lo + row / r2n, c2 = r2lo + row % r2n;
+                int lo = INT_MAX, hi = -1;
+#pragma unroll 8
+                for (int x = 0; x < kJQ; ++x) {
+                    const uint32_t key = qkey[x];
+                    const int q1 = (int)(key >> (cb2 + cb3)), q2 = (int)((key >> cb3) & mask2);
+                    const int qx = cb3 > 0 ? (int)(key & mask3) : q2;
+                    const bool near = key != kNone && abs(q1 - c1) <= kJoinNb &&
+                                      (cb3 == 0 || abs(q2 - c2) <= kJoinNb);
+                    lo = near ? min(lo, qx) : lo;
+                    hi = near ? max(hi, qx) : hi;
+                }
+                if (hi >= 0) {
+                    const uint32_t rk = cb3 > 0
+                        ? lbits | ((uint32_t)c1 << (cb2 + cb3)) | ((uint32_t)c2 << cb3)
+                        : lbits | ((uint32_t)c1 << cb2);
+                    klo = rk | (uint32_t)max(lo - kJoinNb, 0);
+                    khi = rk | (uint32_t)min(hi + kJoinNb, (int)(cb3 > 0 ? mask3 : mask2));
+                }
+            }
+        }
+        if (nrows == 1) {
+            // one row: the whole wavefront searches for it
+            klo = __builtin_amdgcn_readfirstlane(klo);
+            khi = __builtin_amdgcn_readfirstlane(khi);
+            const uint32_t b0 = wave_first(gkey, first, pend, klo, true);
+            const uint32_t e0 = wave_first(gkey, b0, pend, khi, false);
+            if (lane == 0) {
+                beg = b0;
+                end = e0;
+            }
+        } else if (klo <= khi) {
+            // first positions with key >= klo and key > khi, together
+            uint32_t lo1 = first, hi1 = pend, lo2 = first, hi2 = pend;
+            while (lo1 < hi1 || lo2 < hi2) {
+                const uint32_t m1 = lo1 + ((hi1 - lo1) >> 1), m2 = lo2 + ((hi2 - lo2) >> 1);
+                const uint32_t v1 = gkey[min(m1, pend - 1u)], v2 = gkey[min(m2, pend - 1u)];
+                if (lo1 < hi1) {
+                    if (v1 < klo) lo1 = m1 + 1u; else hi1 = m1;
+                }
+                if (lo2 < hi2) {
+                    if (v2 <= khi) lo2 = m2 + 1u; else hi2 = m2;
+                }
+            }
+            beg = lo1;
+            end = lo2;
+        }
+        const uint64_t live = __ballot(beg < end);
+        const int nrun = __popcll(live);
+        if (beg < end) {
+            const int at = __popcll(live & lanemask_lt());
+            rbeg[at] = beg;
+            rend[at] = end;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (nrun == 0) continue;
+
+        // ---- the runs, 32 candidates at a time
+        auto load_tile = [&](uint32_t c, uint4 &b0, uint4 &b1, float &w) {
+            const uint32_t pc = min(c + (uint32_t)i, pend - 1u);
+            b0 = op0[(int64_t)pc * 2 + hh];
+            b1 = op1[(int64_t)pc * 2 + hh];
+            w = gw_s[pc];
+        };
+        int run = 0;
+        uint32_t c = __builtin_amdgcn_readfirstlane(rbeg[0]);
+        uint32_t e = __builtin_amdgcn_readfirstlane(rend[0]);
+        uint4 nb0, nb1;
+        float nw;
+        load_tile(c, nb0, nb1, nw);
+        bool more = true;
+        while (more) {
+            const f16x8 b0 = as_f16x8(nb0), b1 = as_f16x8(nb1);
+            // the candidate's Gram term (its sign is the query flag), less
+            // one unit of its bits.  Terms are >= 0, so an accumulator reaches
+            // one iff their bits compare so as signed integers (no NaN occurs,
+            // and an accumulator of -0 needs a filter term of 0, which its
+            // margins exclude)
+            const int bj = (c + (uint32_t)i < e ? __float_as_int(nw) & 0x7FFFFFFF : 0x7F800000) - 1;
+            const uint32_t tc = c;
+            c += kJT;
+            if (c >= e) {
+                if (++run < nrun) {
+                    c = __builtin_amdgcn_readfirstlane(rbeg[run]);
+                    e = __builtin_amdgcn_readfirstlane(rend[run]);
+                } else {
+                    more = false;
+                }
+            }
+            load_tile(c, nb0, nb1, nw);                   // (past the last: read and dropped)
+            n_tiles += kJB;
+            f32x16 acc[kJB];
+#pragma unroll
+            for (int t = 0; t < kJB; ++t) {
+                f32x16 z = {};
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0[t], b0, z, 0, 0, 0);
+            }
+#pragma unroll
+            for (int t = 0; t < kJB; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1[t], b1, acc[t], 0, 0, 0);
+            // the groups of four rows with a passing pair: bit 4 t + g (the
+            // sign of term - 1 - accumulator as integers, shifted in; negative
+            // accumulators count as 0, so the difference does not wrap)
+            uint32_t hit = 0;
+#pragma unroll
+            for (int t = kJB - 1; t >= 0; --t)
+#pragma unroll
+                for (int g = 3; g >= 0; --g) {
+                    int top = 0;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) top = max(top, __float_as_int(acc[t][4 * g + r]));
+                    hit = __builtin_amdgcn_alignbit(hit, (uint32_t)(bj - top), 31);
+                }
+            uint64_t mk = __ballot(hit != 0u);
+            while (mk) {
+                if (qn > kQueueCap - kWave) resolve();
+                if (hit) {
+                    // group g of tile t: rows 32 t + 8 g + 4 hh .. + 3
+                    const uint32_t tg = (uint32_t)__builtin_ctz(hit);
+                    queue[qn + __popcll(mk & lanemask_lt())] =
+                        make_uint2(p0 + 8u * tg + 4u * (uint32_t)hh, tc + (uint32_t)i);
+                    hit &= hit - 1u;
+                }
+                qn += __popcll(mk);
+                mk = __ballot(hit != 0u);
+            }
+            if (over) break;
+        }
+        // (the next rows' runs overwrite rbeg and rend)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (qn > 0 && !over) resolve();
+    if (on > 0 && !over) hand_on();
+    if (over) {
+        // (its counts come from the second attempt)
+        if (lane == 0) out.redo[atomicAdd(out.nredo, 1u)] = (uint32_t)gb;
+        return;
+    }
     // statistics: one atomic per wavefront
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        n_pairs += __shfl_xor(n_pairs, off, kWave);
-        n_kept += __shfl_xor(n_kept, off, kWave);
-        n_ver += __shfl_xor(n_ver, off, kWave);
-    }
+    for (int off = kWave / 2; off > 0; off >>= 1) n_ver += __shfl_xor(n_ver, off, kWave);
     if (lane == 0) {
-        atomicAdd(&q.counters[C_JOIN_PAIRS], n_pairs);
+        atomicAdd(&q.counters[C_JOIN_PAIRS], n_tiles * (unsigned long long)(kJT * kJT));
         if (n_kept) atomicAdd(&q.counters[C_JOIN_CAND], n_kept);
         if (n_ver) atomicAdd(&q.counters[C_JOIN_VER], n_ver);
     }
+}
+
+template <typename FT>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(kJWaves)))
+void k_join_tiles(Req q, const GridLen *__restrict__ gl, const uint32_t *__restrict__ gkey,
+                  const uint32_t *__restrict__ gval, const uint8_t *__restrict__ qf,
+                  const uint4 *__restrict__ jop_s, const float4 *__restrict__ jmeta,
+                  const float4 *__restrict__ gp_s, const float *__restrict__ gw_s, int64_t nwin,
+                  const uint32_t *__restrict__ nonq, int cb1, int cb2, int cb3, double T,
+                  int64_t blk0, int64_t nblocks, const uint32_t *__restrict__ list, JoinOut out) {
+    __shared__ JoinSmem sm;
+    // consecutive blocks share most of their candidates: workgroups go to the
+    // XCDs in turn, so each XCD takes segments of kJSeg consecutive blocks,
+    // whose candidates its L2 then serves again
+    const int64_t seq = (int64_t)(blockIdx.x / kXcds);
+    const int64_t b = ((seq / kJSeg) * kXcds + blockIdx.x % kXcds) * kJSeg + seq % kJSeg;
+    if (b >= nblocks) return;
+    const int64_t gb = list ? (int64_t)list[b] : blk0 + b;
+    join_block<FT, false>(q, gl, gkey, gval, qf, jop_s, jmeta, gp_s, gw_s, nwin, nonq, cb1, cb2,
+                          cb3, T, gb, out, sm);
+}
+
+// Blocks that overflow an empty buffer, wavefronts striding over their list:
+// their pairs are verified in place.
+template <typename FT>
+__global__ __launch_bounds__(kWave)
+void k_join_redo(Req q, const GridLen *__restrict__ gl, const uint32_t *__restrict__ gkey,
+                 const uint32_t *__restrict__ gval, const uint8_t *__restrict__ qf,
+                 const uint4 *__restrict__ jop_s, const float4 *__restrict__ jmeta,
+                 const float4 *__restrict__ gp_s, const float *__restrict__ gw_s, int64_t nwin,
+                 const uint32_t *__restrict__ nonq, int cb1, int cb2, int cb3, double T,
+                 const uint32_t *__restrict__ list, uint32_t n, JoinOut out) {
+    __shared__ JoinSmem sm;
+    for (uint32_t x = blockIdx.x; x < n; x += gridDim.x)
+        join_block<FT, true>(q, gl, gkey, gval, qf, jop_s, jmeta, gp_s, gw_s, nwin, nonq, cb1, cb2,
+                             cb3, T, (int64_t)list[x], out, sm);
 }
 
 // The exact stage of the pairs in the buffer (the first min(*pcount, cap)
@@ -715,33 +840,47 @@ void launch_join_dirs(int precision, const Req &q, int nlen, double *cov, double
 
 void launch_grid_keys(const Req &q, const GridLen *gl, int64_t N, int cb1, int cb2, int cb3,
                       int l_lim, int64_t i_lim, uint32_t *gkey, uint32_t *gval, uint8_t *qf,
-                      float4 *gp, hipStream_t s) {
+                      float4 *gp, uint32_t *nonq, hipStream_t s) {
     if (N <= 0) return;
     hipLaunchKernelGGL(k_grid_keys, dim3(nblk(N)), dim3(kBlock), 0, s, q, gl, N, cb1, cb2, cb3,
-                       l_lim, i_lim, gkey, gval, qf, gp);
+                       l_lim, i_lim, gkey, gval, qf, gp, nonq);
 }
 
 void launch_join_gather(const uint32_t *gval, const uint4 *jop, const float4 *gp, int64_t n,
-                        uint4 *jop_s, float4 *gp_s, hipStream_t s) {
+                        uint4 *jop_s, float4 *gp_s, float *gw_s, hipStream_t s) {
     if (n <= 0) return;
-    hipLaunchKernelGGL(k_join_gather, dim3((unsigned)((n * 8 + kBlock - 1) / kBlock)), dim3(kBlock),
-                       0, s, gval, jop, gp, n, jop_s, gp_s);
+    hipLaunchKernelGGL(k_join_gather, dim3((unsigned)((n * kJoinOp + kBlock - 1) / kBlock)),
+                       dim3(kBlock), 0, s, gval, jop, gp, n, jop_s, gp_s, gw_s);
 }
 
-void launch_join_tiles(int precision, const Req &q, const GridLen *gl, const uint32_t *gkey,
-                       const uint32_t *gval, const uint8_t *qf, const uint4 *jop_s,
-                       const float4 *jmeta, const float4 *gp_s, int64_t blk0, int64_t nblocks,
-                       int cb1, int cb2, int cb3, double T, uint2 *pairs,
-                       unsigned long long *pcount, int64_t cap, hipStream_t s) {
+void launch_join_tiles(const JoinIn &in, int64_t blk0, int64_t nblocks, const uint32_t *list,
+                       const JoinOut &out, hipStream_t s) {
     if (nblocks <= 0) return;
-    if (precision == 0)
-        hipLaunchKernelGGL(k_join_tiles<double>, dim3((unsigned)nblocks), dim3(kJB * kWave), 0, s,
-                           q, gl, gkey, gval, qf, jop_s, jmeta, gp_s, cb1, cb2, cb3, T, blk0,
-                           pairs, pcount, cap);
+    // whole groups of one segment per XCD (workgroups past the last block end
+    // at once); fewer blocks than that spread over the XCDs with the grid
+    const int64_t group = kXcds * kJSeg;
+    const dim3 grid((unsigned)((nblocks + group - 1) / group * group));
+    if (in.precision == 0)
+        hipLaunchKernelGGL(k_join_tiles<double>, grid, dim3(kWave), 0, s, in.q, in.gl, in.gkey,
+                           in.gval, in.qf, in.jop_s, in.jmeta, in.gp_s, in.gw_s, in.nwin, in.nonq,
+                           in.cb1, in.cb2, in.cb3, in.T, blk0, nblocks, list, out);
     else
-        hipLaunchKernelGGL(k_join_tiles<float>, dim3((unsigned)nblocks), dim3(kJB * kWave), 0, s,
-                           q, gl, gkey, gval, qf, jop_s, jmeta, gp_s, cb1, cb2, cb3, T, blk0,
-                           pairs, pcount, cap);
+        hipLaunchKernelGGL(k_join_tiles<float>, grid, dim3(kWave), 0, s, in.q, in.gl, in.gkey,
+                           in.gval, in.qf, in.jop_s, in.jmeta, in.gp_s, in.gw_s, in.nwin, in.nonq,
+                           in.cb1, in.cb2, in.cb3, in.T, blk0, nblocks, list, out);
+}
+
+void launch_join_redo(const JoinIn &in, const uint32_t *list, uint32_t n, hipStream_t s) {
+    if (n == 0) return;
+    const dim3 grid(n < 2048u ? n : 2048u);
+    if (in.precision == 0)
+        hipLaunchKernelGGL(k_join_redo<double>, grid, dim3(kWave), 0, s, in.q, in.gl, in.gkey,
+                           in.gval, in.qf, in.jop_s, in.jmeta, in.gp_s, in.gw_s, in.nwin, in.nonq,
+                           in.cb1, in.cb2, in.cb3, in.T, list, n, JoinOut{});
+    else
+        hipLaunchKernelGGL(k_join_redo<float>, grid, dim3(kWave), 0, s, in.q, in.gl, in.gkey,
+                           in.gval, in.qf, in.jop_s, in.jmeta, in.gp_s, in.gw_s, in.nwin, in.nonq,
+                           in.cb1, in.cb2, in.cb3, in.T, list, n, JoinOut{});
 }
 
 void launch_join_verify(int precision, const Req &q, const GridLen *gl, const uint2 *pairs,

@@ -705,11 +705,9 @@ __device__ __forceinline__ void load_fcopy(const Req &q, int64_t kk, bool valid,
     }
 }
 
-// The FP32 copy as bf16 pairs: G = hi + lo, hi = bf16(f), lo = bf16(f - hi);
-// each component of G is within 2^-17 of f (relative).  n2 = |G|^2 (FP64).
-__device__ __forceinline__ void bf16_pairs(const float f[kFD], uint32_t hw[16], uint32_t lw[16],
-                                           double &n2) {
-    n2 = 0.0;
+// The FP32 copy as bf16 pairs: hi = bf16(f), lo = bf16(f - hi); hi + lo is
+// within 2^-17 of f (relative) in each component.
+__device__ __forceinline__ void bf16_pairs(const float f[kFD], uint32_t hw[16], uint32_t lw[16]) {
 #pragma unroll
     for (int w = 0; w < 16; ++w) {
         uint32_t hp = 0, lp = 0;
@@ -720,8 +718,6 @@ __device__ __forceinline__ void bf16_pairs(const float f[kFD], uint32_t hw[16], 
             const uint32_t hb = bf16_bits(x);
             const float xh = __uint_as_float(hb << 16);
             const uint32_t lb = bf16_bits(x - xh);
-            const double gx = (double)xh + (double)__uint_as_float(lb << 16);
-            n2 = fma(gx, gx, n2);
             hp |= hb << (16 * e);
             lp |= lb << (16 * e);
         }
@@ -734,44 +730,72 @@ __device__ __forceinline__ void bf16_pairs(const float f[kFD], uint32_t hw[16], 
 
 // The threshold join's operands of the indexed windows [k0, k1), one thread
 // each, written only when a join runs and only for the windows it queries
-// (lengths up to the key bound): the bf16 pairs G, their metadata and the
-// principal coordinates of the FP32 copy (FP64 dots) that place the grid.
+// (lengths up to the key bound): the features rounded to fp16 (parts below its
+// normal range as 0), their metadata and the principal coordinates of the FP32
+// copy (FP64 dots) that place the grid.
 template <typename FT>
 __global__ __launch_bounds__(kBlock) void k_join_ops(Req q, int64_t k0, int64_t k1) {
     const int64_t kk = k0 + (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (kk >= k1) return;
+    const bool live = kk < k1;
     const int64_t k_first = k0 + (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~(kWave - 1));
-    const int l = find_len_k_wave(q.len, q.L, k_first, kk);
-    float f[kFD];
-    float erec, nrec;
-    load_fcopy<FT>(q, kk, true, f, erec, nrec);
-    uint32_t hw[16], lw[16];
-    double n2;
-    bf16_pairs(f, hw, lw, n2);
-    const double *u = q.udir + (int64_t)l * kJoinDirs * 32;
-    double p0 = 0.0, p1 = 0.0, p2 = 0.0;
+    if (k_first >= k1) return;
+    const int l = find_len_k_wave(q.len, q.L, k_first, live ? kk : k_first);
+    float ep = 0.0f;
+    if (live) {
+        float f[kFD];
+        float erec, nrec;
+        load_fcopy<FT>(q, kk, true, f, erec, nrec);
+        const uint32_t cw = half_bits(join_scale(q.len[l].m));
+        uint32_t hw[16];
+        double n2 = 0.0, r2 = 0.0;
 #pragma unroll
-    for (int c = 0; c < kFD; ++c) {
-        p0 = fma(u[c], (double)f[c], p0);
-        p1 = fma(u[32 + c], (double)f[c], p1);
-        p2 = fma(u[64 + c], (double)f[c], p2);
-    }
-    // f is within u32 |F~| of the stored record F~, itself within e of F;
-    // so e' = e + (u32 + 2^-17) |F~| bounds |G - F|
-    uint4 *jo = q.jop + kk * 8;
+        for (int w = 0; w < 15; ++w) {
+            uint32_t hp = 0;
 #pragma unroll
-    for (int part = 0; part < 4; ++part) {
-        jo[part] = make_uint4(hw[4 * part], hw[4 * part + 1], hw[4 * part + 2], hw[4 * part + 3]);
-        jo[4 + part] = make_uint4(lw[4 * part], lw[4 * part + 1], lw[4 * part + 2], lw[4 * part + 3]);
+            for (int e = 0; e < 2; ++e) {
+                const float x = fabsf(f[2 * w + e]) < 0x1.0p-14f ? 0.0f : f[2 * w + e];
+                const uint32_t h = half_bits(x);
+                const double g = (double)half_float(h), r = (double)f[2 * w + e] - g;
+                n2 = fma(g, g, n2);
+                r2 = fma(r, r, r2);
+                hp |= h << (16 * e);
+            }
+            hw[w] = hp;
+        }
+        hw[15] = cw | (cw << 16);
+        const double *u = q.udir + (int64_t)l * kJoinDirs * 32;
+        double p0 = 0.0, p1 = 0.0, p2 = 0.0;
+#pragma unroll
+        for (int c = 0; c < kFD; ++c) {
+            p0 = fma(u[c], (double)f[c], p0);
+            p1 = fma(u[32 + c], (double)f[c], p1);
+            p2 = fma(u[64 + c], (double)f[c], p2);
+        }
+        // f is within u32 |F~| of the stored record F~, itself within e of F;
+        // so e' = e + u32 |F~| + |G - f| bounds |G - F|
+        uint4 *jo = q.jop + kk * kJoinOp;
+#pragma unroll
+        for (int part = 0; part < 4; ++part)
+            jo[part] = make_uint4(hw[4 * part], hw[4 * part + 1], hw[4 * part + 2], hw[4 * part + 3]);
+        // w: the join's candidate Gram term 0.5 |G|^2, rounded down (its sign
+        // bit is set per certify round by the grid keys)
+        q.gp[kk] = make_float4((float)p0, (float)p1, (float)p2,
+                               (float)(0.5 * (double)(float)n2 * (1.0 - 0x1.0p-23)));
+        const double epd = ((double)erec + 5.9604644775390625e-08 * (double)nrec +
+                            sqrt(r2) * (1.0 + 1e-12)) * (1.0 + 1e-6) + 1e-30;
+        ep = (float)epd * (1.0f + 2.4e-7f);
+        q.jmeta[kk] = make_float4((float)n2, ep, (float)(sqrt(n2) * (1.0 + 1e-12)) * (1.0f + 2.4e-7f),
+                                  0.0f);
     }
-    // w: the join's candidate Gram term 0.5 |G|^2, rounded down (its sign
-    // bit is set per certify round by the grid keys)
-    q.gp[kk] = make_float4((float)p0, (float)p1, (float)p2,
-                           (float)(0.5 * (double)(float)n2 * (1.0 - 0x1.0p-23)));
-    const double ep =
-        ((double)erec + (5.9604644775390625e-08 + 0x1.0p-17) * (double)nrec) * (1.0 + 1e-6);
-    q.jmeta[kk] = make_float4((float)n2, (float)ep * (1.0f + 2.4e-7f),
-                              (float)((double)nrec * (1.0 + 0x1.0p-16)) * (1.0f + 2.4e-7f), 0.0f);
+    // the largest e' of the length (one atomic per wavefront within a length;
+    // positive floats order like their bits)
+    if (__ballot(live && l != __shfl(l, 0, kWave)) == 0) {
+        for (int off = kWave / 2; off > 0; off >>= 1) ep = fmaxf(ep, __shfl_xor(ep, off, kWave));
+        // (a stale read only costs an atomic)
+        if (lane_id() == 0 && ep > q.jemax[l]) atomicMax((int *)&q.jemax[l], __float_as_int(ep));
+    } else if (live) {
+        atomicMax((int *)&q.jemax[l], __float_as_int(ep));
+    }
 }
 
 namespace {
@@ -817,8 +841,7 @@ __global__ __launch_bounds__(kBlock) void k_keys(Req q, const float *__restrict_
     float erec = 0.0f, nrec = 0.0f;
     load_fcopy<FT>(q, kk, valid, f, erec, nrec);
     uint32_t hw[16], lw[16];
-    double n2;
-    bf16_pairs(f, hw, lw, n2);
+    bf16_pairs(f, hw, lw);
 
     // ---- SimHash projections <g_b, G> of the wavefront's 64 windows on the
     // matrix cores: two blocks of 32 windows x 32 bits (B used) over 32

@@ -76,7 +76,8 @@ struct Req {
     uint64_t *P;           // [N] profile, FP64 bits (atomicMin)
     void    *F;            // [N][kRec] features (float or double)
     uint64_t *keyw;        // [N] key word: signature | probe order << 24
-    uint4   *jop;          // [N][8] join operands: 32 bf16 hi, then 32 bf16 lo (G = hi + lo)
+    uint4   *jop;          // [N][kJoinOp] join operands: 30 fp16 features G, then twice
+                           //     join_scale(m)
     float4  *jmeta;        // [N] |G|^2, e' >= |G - F|, bound on |G|, 0
     float4  *gp;           // [N] principal coordinates of the FP32 feature copy, and
                            //     0.5 |G|^2 (rounded down) with the sign bit = (P != 0)
@@ -92,6 +93,7 @@ struct Req {
     uint32_t *hint;        // [N] start of a partner that lowered the cell
                            // (kNone: none), written when a cell is lowered
     float   *emax;         // [L] largest e_i of each length
+    float   *jemax;        // [L] largest e' of each length's join operands
     unsigned long long *counters;   // stats counters
     int     *bad;          // raised on inputs the library cannot represent
 };
@@ -121,6 +123,20 @@ __device__ __forceinline__ double bitsd(uint64_t b) {
     return __longlong_as_double((long long)b);
 }
 
+// fp16 with round to nearest even, as its 16 bits, and back.
+__device__ __forceinline__ uint32_t half_bits(float x) {
+    const _Float16 h = (_Float16)x;
+    uint16_t u;
+    __builtin_memcpy(&u, &h, 2);
+    return u;
+}
+__device__ __forceinline__ float half_float(uint32_t b) {
+    const uint16_t u = (uint16_t)b;
+    _Float16 h;
+    __builtin_memcpy(&h, &u, 2);
+    return (float)h;
+}
+
 // Length index of a cell (binary search over cell_base, L is small).
 __device__ __forceinline__ int find_len(const LenInfo *len, int L, int64_t cell) {
     int lo = 0, hi = L - 1;
@@ -142,7 +158,8 @@ __device__ __forceinline__ int find_len_k(const LenInfo *len, int L, int64_t k) 
 }
 
 constexpr int kJoinTile = 32;             // windows per threshold-join tile
-constexpr int kJoinBlock = 4;             // join tiles per block (they share candidate tiles)
+constexpr int kJoinBlock = 4;             // query tiles per block (one wavefront)
+constexpr int kJoinOp = 4;                // uint4 words of one window's join operands
 constexpr int kJoinDirs = 3;              // principal directions per length in the join
 constexpr int kJoinNb = 1;                // join grid cells are 1/kJoinNb of the radius wide; a
                                           // pair within it lies at most kJoinNb cells apart
@@ -153,12 +170,23 @@ struct GridLen {
     double qlo;           // grid origin of both coordinates
     double hinv;          // 1 / cell width of the first coordinate (0: one cell)
     double hinv2;         // 1 / cell width of the second and third coordinates
-    double R2;            // squared radius on the join vectors G (+inf: every pair)
+    double Tr;            // T sqrt(m/2), the radius on the true features (+inf: every pair)
     double eps_c;         // MFMA dot-product error per unit |G_q| (times the largest |G_c|)
     double nmax2;         // square of the largest |G|
     float sqrt2m;         // sqrt(2/m) (1 + 1e-7)
     float rp;             // bound on any coordinate difference of a pair within R_f
 };
+
+// The power of two c >= 1 that brings every filter term of the join, at most
+// 2.5 nmax^2 in absolute value (nmax: the largest |G| of length m), into the
+// range of an fp16 number: the two operand slots past the features hold c on
+// the candidate's side and the term over c, as hi + lo, on the query's.
+__device__ __forceinline__ float join_scale(int m) {
+    const float nmax2 = 0.5f * (float)m * (float)m * 1.03f + 2.0f * (float)m + 2.0f;
+    float c = 1.0f;
+    while (32768.0f * c < 2.5f * nmax2) c *= 2.0f;
+    return c;
+}
 
 // State of the device-side radix select (k_certify.hip).
 constexpr int kSelBins = 2048;            // bins of one select pass (11 bits)
@@ -169,6 +197,9 @@ struct SelState {
     int64_t need_eq;      // values equal to the pivot to take, in cell order
     uint32_t nless;       // values below the pivot found by the emit pass
     int32_t done;         // the pivot is known
+    uint64_t kept;        // the join's counts when the selection began: kept pairs,
+    uint32_t nredo;       // overflowed blocks
+    uint32_t pad_;
 };
 
 struct RowReq {
@@ -585,11 +616,11 @@ int64_t select_blocks(int64_t n);
 // pivot go to less (unordered, with their values in less_val), positions
 // equal to it to eq (position order); less_cell / eq_cell hold cell[position].
 // Everything runs on the stream; st holds the counts when the stream reaches
-// the end.
+// the end, with the join's two counts (null: none) as they were at the start.
 void launch_select(const uint64_t *P, int64_t n, int64_t need, SelState *st,
                    unsigned int *hist, uint32_t *cnt, uint32_t *scan_tmp, uint32_t *less,
                    uint64_t *less_val, uint32_t *eq, uint32_t *less_cell, uint32_t *eq_cell,
-                   const uint32_t *cell, hipStream_t s);
+                   const uint32_t *cell, const unsigned long long *counts, hipStream_t s);
 // (k_join.hip)
 size_t join_cov_doubles(int L);
 // principal directions: covariance of a sample, then power iteration (GPU)
@@ -599,22 +630,46 @@ void launch_join_dirs(int precision, const Req &q, int nlen, double *cov, double
                       hipStream_t s);
 // grid keys over cb1 (and cb2, cb3 when nonzero) bits of the principal
 // coordinates, of the first N indexed windows; queries are the cells not at 0
-// with (length, start) <= (l_lim, i_lim)
+// with (length, start) <= (l_lim, i_lim); nonq[l] is set where some window of
+// length l is not one
 void launch_grid_keys(const Req &q, const GridLen *gl, int64_t N, int cb1, int cb2, int cb3,
                       int l_lim, int64_t i_lim, uint32_t *gkey, uint32_t *gval, uint8_t *qf,
-                      float4 *gp, hipStream_t s);
+                      float4 *gp, uint32_t *nonq, hipStream_t s);
 // the join operands and coordinates of the first n sorted positions, in
 // sorted order
 void launch_join_gather(const uint32_t *gval, const uint4 *jop, const float4 *gp, int64_t n,
-                        uint4 *jop_s, float4 *gp_s, hipStream_t s);
-// one block of kJoinBlock query tiles per GridLen block: the blocks
-// [blk0, blk0 + nblocks) of the round; kept pairs go to `pairs` (capacity
-// cap, fill count *pcount), or are verified in place once it is full
-void launch_join_tiles(int precision, const Req &q, const GridLen *gl, const uint32_t *gkey,
-                       const uint32_t *gval, const uint8_t *qf, const uint4 *jop_s,
-                       const float4 *jmeta, const float4 *gp_s, int64_t blk0, int64_t nblocks,
-                       int cb1, int cb2, int cb3, double T, uint2 *pairs,
-                       unsigned long long *pcount, int64_t cap, hipStream_t s);
+                        uint4 *jop_s, float4 *gp_s, float *gw_s, hipStream_t s);
+// What one round's tiles read.
+struct JoinIn {
+    int precision;
+    Req q;
+    const GridLen *gl;
+    const uint32_t *gkey, *gval;
+    const uint8_t *qf;
+    const uint4 *jop_s;
+    const float4 *jmeta, *gp_s;
+    const float *gw_s;
+    int64_t nwin;         // windows in the order
+    const uint32_t *nonq;
+    int cb1, cb2, cb3;
+    double T;
+};
+// Where the tiles' kept pairs go: `pairs` (capacity cap, fill count *pcount);
+// blocks that find it full go to `redo` (*nredo of them, one entry per block
+// of a launch).
+struct JoinOut {
+    uint2 *pairs;
+    unsigned long long *pcount;
+    int64_t cap;
+    uint32_t *redo;
+    uint32_t *nredo;
+};
+// one wavefront of kJoinBlock query tiles per GridLen block: the blocks
+// [blk0, blk0 + nblocks) of the round, or the first nblocks of a list
+void launch_join_tiles(const JoinIn &in, int64_t blk0, int64_t nblocks, const uint32_t *list,
+                       const JoinOut &out, hipStream_t s);
+// the n blocks of a list, their kept pairs verified in place
+void launch_join_redo(const JoinIn &in, const uint32_t *list, uint32_t n, hipStream_t s);
 // the exact stage of the first min(*pcount, cap) pairs of the buffer
 void launch_join_verify(int precision, const Req &q, const GridLen *gl, const uint2 *pairs,
                         const unsigned long long *pcount, int64_t cap, double T, hipStream_t s);

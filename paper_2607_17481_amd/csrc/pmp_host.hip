@@ -426,8 +426,10 @@ struct Bufs {
     uint32_t *jk, *jv, *jk2, *jv2;
     uint4 *jop_s;              // join operands and coordinates in grid order
     float4 *gp_s;
+    float *gw_s;               // and their Gram terms
     uint2 *jpairs;             // the join's kept pairs (k_q, k_c), jcap of them
     unsigned long long *jcount;
+    uint32_t *jredo;           // blocks that found the pair buffer full: two lists
     int64_t jcap;
     // emit stage: cell -> k map, partner hints, sieve segments and
     // directions, completion seeds
@@ -456,7 +458,7 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
         {p.n + 1, p.ntiles + 1, select_blocks(p.cells) + 1, 2 * p.cells + p.L + 1})));
     b.bad = take<int>(a, 1);
     b.counters = take<unsigned long long>(a, C_NCOUNTERS);
-    b.emax = take<float>(a, p.L);
+    b.emax = take<float>(a, 2 * p.L);        // then the join operands' (jemax)
     b.gproj = take<float>(a, (int64_t)p.L * kMaxBits * kFD);
     b.cov = take<double>(a, (int64_t)join_cov_doubles(p.L));
     b.udir = take<double>(a, (int64_t)p.L * kJoinDirs * 32);
@@ -483,8 +485,11 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
 static bool needs_kmap(const Opt &o) { return o.stride > 1; }
 
 // Kept pairs of the join buffered between its tiles and its exact stage:
-// two per indexed window (16 bytes a window), at least 2^16.
-static int64_t join_pair_cap(int64_t N) { return std::max<int64_t>(int64_t(1) << 16, 2 * N); }
+// four per indexed window (32 bytes a window), at least 2^16.
+static int64_t join_pair_cap(int64_t N) { return std::max<int64_t>(int64_t(1) << 16, 4 * N); }
+
+// Blocks of the join over N windows in L lengths, at most.
+static int64_t join_blocks_max(int64_t N, int L) { return N / (kJoinTile * kJoinBlock) + L + 1; }
 
 static void carve2(Arena &a, Bufs &b, const Plan &p, const Opt &o, int k) {
     const int precision = o.precision;
@@ -496,7 +501,7 @@ static void carve2(Arena &a, Bufs &b, const Plan &p, const Opt &o, int k) {
     b.P = take<uint64_t>(a, N);
     b.keyw = take<uint64_t>(a, N);
     b.F = a.take((size_t)N * kRec * (precision == 0 ? 8 : 4));
-    b.jop = take<uint4>(a, N * 8);
+    b.jop = take<uint4>(a, N * kJoinOp);
     b.jmeta = take<float4>(a, N);
     b.qf = take<uint8_t>(a, N);
     b.gp = take<float4>(a, N);
@@ -507,15 +512,18 @@ static void carve2(Arena &a, Bufs &b, const Plan &p, const Opt &o, int k) {
     b.pcell = take<uint32_t>(a, N);
     b.bstart = take<uint32_t>(a, p.nbuckets + 1);
     b.sort_tmp = a.take(sort_temp_bytes(N));
-    b.jop_s = take<uint4>(a, N * 8);
+    b.jop_s = take<uint4>(a, N * kJoinOp);
     b.gp_s = take<float4>(a, N);
+    b.gw_s = take<float>(a, N);
     b.jk = take<uint32_t>(a, N);
     b.jv = take<uint32_t>(a, N);
     b.jk2 = take<uint32_t>(a, N);
     b.jv2 = take<uint32_t>(a, N);
     b.jcap = join_pair_cap(N);
     b.jpairs = take<uint2>(a, b.jcap);
-    b.jcount = take<unsigned long long>(a, 1);
+    // the pair count, the number of overflowed blocks, nonq (u32 per length)
+    b.jcount = take<unsigned long long>(a, 2 + (p.L + 1) / 2);
+    b.jredo = take<uint32_t>(a, 2 * join_blocks_max(N, p.L));
     b.sel_cnt = take<uint32_t>(a, select_blocks(N) + 1);
     b.selblk = (char *)a.take(select_block_bytes(need));
     b.sel = (SelState *)b.selblk;
@@ -561,7 +569,13 @@ static int len_of_cell(const Plan &p, int64_t cell) {
 // state and the selected positions, values and cells, after any copies the
 // caller has already enqueued on the stream (they complete with the same
 // synchronization).
-static int select_topk(const Plan &p, Bufs &b, int k, hipStream_t s, std::vector<Cand> &accepted) {
+// `counts` (when given) receives the join's kept pairs and overflowed blocks.
+struct JoinCounts {
+    unsigned long long kept;
+    uint32_t nredo, pad;
+};
+static int select_topk(const Plan &p, Bufs &b, int k, hipStream_t s, std::vector<Cand> &accepted,
+                       JoinCounts *counts = nullptr) {
     accepted.clear();
     const int64_t N = p.N;
     const int64_t need_all = need_select(k, p.max_m);
@@ -570,12 +584,13 @@ static int select_topk(const Plan &p, Bufs &b, int k, hipStream_t s, std::vector
         return PMP_OK;
     }
     launch_select(b.P, N, need_all, b.sel, b.hist, b.sel_cnt, b.scan_tmp, b.less_k, b.less_val,
-                  b.eq_k, b.less_cell, b.eq_cell, b.cell, s);
+                  b.eq_k, b.less_cell, b.eq_cell, b.cell, counts ? b.jcount : nullptr, s);
     std::vector<char> host(select_block_bytes(need_all));
     HIPCHK(hipMemcpyAsync(host.data(), b.selblk, host.size(), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     SelState st;
     memcpy(&st, host.data(), sizeof(st));
+    if (counts) *counts = {st.kept, st.nredo, 0u};
     if (!st.done) return fail(PMP_EINTERNAL, "selection did not settle");
     if (st.nless > (uint32_t)need_all) return fail(PMP_EINTERNAL, "selection overflow");
     const uint32_t nless = st.nless;
@@ -921,7 +936,7 @@ static int run_pipeline(Run &R, Arena &ar) {
                           hipMemcpyHostToDevice, s));
     const std::vector<LenInfo> len_host = p.len;
     HIPCHK(hipMemcpyAsync(b.len, len_host.data(), p.L * sizeof(LenInfo), hipMemcpyHostToDevice, s));
-    launch_fill_u32((uint32_t *)b.emax, p.L, 0u, s);
+    launch_fill_u32((uint32_t *)b.emax, 2 * p.L, 0u, s);
     launch_fill_u64((uint64_t *)b.counters, C_NCOUNTERS, 0ull, s);
 
     Req q{};
@@ -952,6 +967,7 @@ static int run_pipeline(Run &R, Arena &ar) {
     q.pcell = b.pcell;
     q.gproj = b.gproj;
     q.emax = b.emax;
+    q.jemax = b.emax + p.L;
     q.counters = b.counters;
     q.bad = b.bad;
     q.kmap = b.kmap;
@@ -1106,19 +1122,18 @@ static int run_pipeline(Run &R, Arena &ar) {
         for (;;) {
             ++rounds;
             const double Teff = std::max(T, kEps0);
-            // R: radius on the join vectors G (bf16 pairs); Rf: on the FP32
-            // feature copies f, which place the grid
-            std::vector<double> Rl(p.L), Rf(p.L);
+            // Tl: radius on the true features (the tiles add the errors of
+            // their fp16 vectors); Rf: on the FP32 feature copies f, which
+            // place the grid
+            std::vector<double> Tl(p.L), Rf(p.L);
             bool two_d = true, three_d = true;
             for (int l = 0; l < p.L; ++l) {
                 const double m = p.ms[l];
                 const double nmax = m / std::sqrt(2.0) * 1.01 + 1.0;
-                const double epmax = ((double)emax[l] + (5.9604644775390625e-08 + 0x1.0p-17) * nmax * 1.01) *
-                                         (1.0 + 1e-6) + 1e-30;
                 const double efmax = ((double)emax[l] + 5.9604644775390625e-08 * nmax * 1.01) *
                                          (1.0 + 1e-6) + 1e-30;
                 const double Tr = Teff * std::sqrt(m / 2.0) * (1.0 + 1e-9);
-                Rl[l] = std::isinf(Teff) ? INFINITY : Tr + 2.0 * epmax;
+                Tl[l] = std::isinf(Teff) ? INFINITY : Tr;
                 Rf[l] = std::isinf(Teff) ? INFINITY : Tr + 2.0 * efmax;
                 // (the lengths this round's windows belong to)
                 const double cw = Rf[l] / kJoinNb;           // the cell width the radius asks for
@@ -1138,11 +1153,10 @@ static int run_pipeline(Run &R, Arena &ar) {
                 // least 1/kJoinNb of the radius wide
                 const double hmin = 2.0 * -G.qlo / (double)(1u << cb1) * (1.0 + 1e-9);
                 const double hmin2 = 2.0 * -G.qlo / (double)(1u << std::max(cb2, 1)) * (1.0 + 1e-9);
-                if (std::isinf(Rl[l])) {
-                    G.R2 = INFINITY;
+                G.Tr = Tl[l];
+                if (std::isinf(Tl[l])) {
                     G.hinv = G.hinv2 = 0.0;
                 } else {
-                    G.R2 = Rl[l] * Rl[l] * (1.0 + 1e-9);
                     // coordinates are computed in FP64 from floats: 1e-12 nmax
                     // covers their rounding; cells of 1/kJoinNb of the radius
                     // put a pair within it at most kJoinNb cells apart
@@ -1169,43 +1183,85 @@ static int run_pipeline(Run &R, Arena &ar) {
             if (nq_ops == 0 && Nq > 0) launch_join_dirs(o.precision, q, rec_lim + 1, b.cov, b.udir, s);
             launch_join_ops(o.precision, q, nq_ops, Nq, s);
             nq_ops = std::max(nq_ops, Nq);
-            launch_grid_keys(q, b.gl, Nq, cb1, cb2, cb3, l_lim, i_lim, b.jk, b.jv, b.qf, b.gp, s);
+            uint32_t *const nonq = (uint32_t *)(b.jcount + 2);
+            launch_fill_u64((uint64_t *)b.jcount, 2 + (p.L + 1) / 2, 0ull, s);
+            launch_grid_keys(q, b.gl, Nq, cb1, cb2, cb3, l_lim, i_lim, b.jk, b.jv, b.qf, b.gp, nonq,
+                             s);
             radix_sort_pairs(b.jk, b.jv, b.jk2, b.jv2, Nq, 0, p.len_bits + cb1 + cb2 + cb3,
                              b.sort_tmp, s);
-            launch_join_gather(b.jv, b.jop, b.gp, Nq, b.jop_s, b.gp_s, s);
+            launch_join_gather(b.jv, b.jop, b.gp, Nq, b.jop_s, b.gp_s, b.gw_s, s);
             // the tiles in chunks of blocks, each followed by the exact stage
             // of the pairs it kept (a kernel of its own, at full occupancy).
-            // A chunk is sized to fill at most half the pair buffer at the
-            // largest rate of kept pairs per block seen so far in the round
-            // (the first at 16 pairs per window); a wavefront that still
-            // finds the buffer full verifies the rest of its pairs itself.
-            launch_fill_u64((uint64_t *)b.jcount, 1, 0ull, s);
+            // A chunk is sized to fill three quarters of the pair buffer at
+            // the last chunk's rate of kept pairs per block (the first at 16
+            // pairs per window): rates change slowly over the lengths, and
+            // each chunk's last wavefronts leave the chip part idle.  Blocks that still found
+            // the buffer full are listed and taken again, in chunks too; if
+            // that leaves as many, each overflows the buffer alone and their
+            // pairs are verified in place.  The counts of the last chunk come
+            // back with the selection, which is then repeated if some of its
+            // blocks are still to be taken.
             {
-                const int64_t first = std::max<int64_t>(64, b.jcap / (2 * 16 * win_per_blk));
+                const JoinIn in{o.precision, q, b.gl, b.jk, b.jv, b.qf, b.jop_s, b.jmeta, b.gp_s,
+                                b.gw_s, Nq, nonq, cb1, cb2, cb3, Teff};
+                uint32_t *cur = b.jredo, *nxt = b.jredo + join_blocks_max(N, p.L);
+                JoinCounts cnt{};
                 double rate = 0.0;                       // kept pairs per block
-                for (int64_t b0 = 0; b0 < nbq;) {
+                int64_t nb = 0;
+                auto chunk = [&](int64_t left) {
                     const int64_t lim =
-                        rate > 0.0 ? std::max<int64_t>(64, (int64_t)std::min(0.5 * (double)b.jcap / rate, 1e15))
-                                   : first;
-                    const int64_t nb = std::min(nbq - b0, lim);
-                    launch_join_tiles(o.precision, q, b.gl, b.jk, b.jv, b.qf, b.jop_s, b.jmeta,
-                                      b.gp_s, b0, nb, cb1, cb2, cb3, Teff, b.jpairs, b.jcount,
-                                      b.jcap, s);
+                        rate > 0.0 ? std::max<int64_t>(64, (int64_t)std::min(0.75 * (double)b.jcap / rate, 1e15))
+                                   : std::max<int64_t>(64, b.jcap / (16 * win_per_blk));
+                    return std::min(left, lim);
+                };
+                auto take_chunk = [&](int64_t b0, const uint32_t *list) {
+                    const JoinOut out{b.jpairs, b.jcount, b.jcap, nxt, (uint32_t *)(b.jcount + 1)};
+                    launch_join_tiles(in, b0, nb, list, out, s);
                     launch_join_verify(o.precision, q, b.gl, b.jpairs, b.jcount, b.jcap, Teff, s);
+                };
+                // the counts so far; the pair count starts again
+                auto read_counts = [&]() -> int {
+                    HIPCHK(hipMemcpyAsync(&cnt, b.jcount, sizeof(cnt), hipMemcpyDeviceToHost, s));
+                    HIPCHK(hipStreamSynchronize(s));
+                    rate = (double)(cnt.kept + 1) / (double)nb;
+                    launch_fill_u64((uint64_t *)b.jcount, 1, 0ull, s);
+                    return PMP_OK;
+                };
+                for (int64_t b0 = 0; b0 < nbq; b0 += nb) {
+                    nb = chunk(nbq - b0);
+                    take_chunk(b0, nullptr);
                     HIPCHK(hipGetLastError());
-                    b0 += nb;
-                    if (b0 < nbq) {
-                        unsigned long long kept = 0;
-                        HIPCHK(hipMemcpyAsync(&kept, b.jcount, 8, hipMemcpyDeviceToHost, s));
-                        HIPCHK(hipStreamSynchronize(s));
-                        rate = std::max(rate, (double)(kept + 1) / (double)nb);
-                        launch_fill_u64((uint64_t *)b.jcount, 1, 0ull, s);
+                    if (b0 + nb < nbq) {
+                        rc = read_counts();
+                        if (rc) return rc;
                     }
                 }
+                rc = select_topk(p, b, R.k, s, acc, &cnt);   // synchronizes: gl may be rewritten next
+                if (rc) return rc;
+                const bool again = cnt.nredo > 0;
+                while (cnt.nredo > 0) {
+                    const uint32_t n = cnt.nredo;
+                    rate = (double)(cnt.kept + 1) / (double)std::max<int64_t>(nb, 1);
+                    std::swap(cur, nxt);
+                    launch_fill_u64((uint64_t *)b.jcount, 2, 0ull, s);
+                    for (int64_t b0 = 0; b0 < (int64_t)n; b0 += nb) {
+                        nb = chunk((int64_t)n - b0);
+                        take_chunk(0, cur + b0);
+                        HIPCHK(hipGetLastError());
+                        rc = read_counts();
+                        if (rc) return rc;
+                    }
+                    if (cnt.nredo >= n) {
+                        launch_join_redo(in, nxt, cnt.nredo, s);
+                        HIPCHK(hipGetLastError());
+                        break;
+                    }
+                }
+                if (again) {
+                    rc = select_topk(p, b, R.k, s, acc);
+                    if (rc) return rc;
+                }
             }
-            HIPCHK(hipGetLastError());
-            rc = select_topk(p, b, R.k, s, acc);   // synchronizes: gl may be rewritten next
-            if (rc) return rc;
             if (std::isinf(T)) break;                               // exhaustive
             if (acc.size() == (size_t)R.k) {
                 const Cand &c = acc.back();

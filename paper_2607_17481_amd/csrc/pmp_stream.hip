@@ -442,7 +442,7 @@ int pmp_stream_topk(pmp_stream *s, pmp_motif *out, int32_t *n_out) {
     uint32_t *eq_k = less_cell + need;
     uint32_t *eq_cell = eq_k + need;
     launch_select(s->P, s->cells, need, sel, s->hist, s->sel_cnt, s->scan_tmp, less_k, less_val,
-                  eq_k, less_cell, eq_cell, s->cellid, s->hs);
+                  eq_k, less_cell, eq_cell, s->cellid, nullptr, s->hs);
     HIPCHK(hipGetLastError());
     std::vector<char> host(select_block_bytes(need));
     HIPCHK(hipMemcpyAsync(host.data(), s->selblk, host.size(), hipMemcpyDeviceToHost, s->hs));

@@ -1,0 +1,34 @@
+"""GPU kernels at the sizes where their tiling changes: tile and block edges,
+remainders, the smallest and largest of a range (against the CPU oracle; the
+bars of test_gpu_parity.py)."""
+import numpy as np
+import pytest
+
+from tests import parity
+from tests.test_gpu_parity import PRECS, gpu, run, ws  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+
+def check(gpu, ws, oracle, t, lo, hi, excl, k=20, **opt):  # noqa: F811
+    rows = oracle.pan_profile(t, range(lo, hi + 1), excl)
+    res, st = run(gpu, ws, t, lo, hi, excl, k, **opt)
+    ok, msg = parity.check_topk(res, rows, k, oracle, t, excl=excl)
+    assert ok, msg
+    return st
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("repeat", [False, True])
+@pytest.mark.parametrize("windows", [31, 127, 128, 129, 513, 1025])
+def test_join_blocks(gpu, ws, oracle, windows, repeat, prec):  # noqa: F811
+    """The threshold join's blocks of 128 queries and tiles of 32 candidates:
+    one below, at and above a block; with an exact repeat (cells at 0 are not
+    queries, so a block also scans the candidates before its first query) and
+    without (it skips them)."""
+    lo, hi, excl = 12, 14, 6
+    n = windows + lo - 1
+    t = np.cumsum(np.random.default_rng(windows).standard_normal(n))
+    if repeat:
+        t[n - 16:n - 1] = t[2:17] + 3.0
+    check(gpu, ws, oracle, t, lo, hi, excl, precision=PRECS[prec], anchor_stride=2)
