@@ -41,8 +41,11 @@ __global__ void k_select_init(SelState *__restrict__ st, int64_t need,
         st->need_eq = 0;
         st->nless = 0;
         st->done = 0;
-        st->kept = counts ? counts[0] : 0ull;
-        st->nredo = counts ? (uint32_t)counts[1] : 0u;
+        unsigned long long kept = 0;
+        if (counts)
+            for (int x = 0; x < kCtrSlots; ++x) kept += counts[x * kCtrStride];
+        st->kept = kept;
+        st->nredo = counts ? (uint32_t)counts[kCtrSlots * kCtrStride] : 0u;
     }
 }
 
@@ -298,8 +301,15 @@ __global__ __launch_bounds__(kBlock) void k_count_zero(const uint64_t *__restric
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * kBlock)
         c += P[i] == 0ull;
+    __shared__ unsigned long long wc[kBlock / kWave];
     for (int off = kWave / 2; off > 0; off >>= 1) c += __shfl_xor(c, off, kWave);
-    if (lane_id() == 0 && c) atomicAdd(out, c);
+    if (lane_id() == 0) wc[threadIdx.x / kWave] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        c = 0;
+        for (int k = 0; k < kBlock / kWave; ++k) c += wc[k];
+        if (c) atomicAdd(out, c);
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_fill_u32(uint32_t *__restrict__ p, int64_t n,
@@ -360,7 +370,7 @@ void launch_gather_u32(const uint32_t *src, const uint32_t *idx, int64_t n, uint
 
 void launch_count_zero(const uint64_t *P, int64_t n, unsigned long long *out, hipStream_t s) {
     if (n > 0)
-        hipLaunchKernelGGL(k_count_zero, dim3(gridcap(n, 1024)), dim3(kBlock), 0, s, P, n, out);
+        hipLaunchKernelGGL(k_count_zero, dim3(gridcap(n, 512)), dim3(kBlock), 0, s, P, n, out);
 }
 
 void launch_fill_u64(uint64_t *p, int64_t n, uint64_t v, hipStream_t s) {

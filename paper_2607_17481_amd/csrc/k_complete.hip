@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kWave) void k_hints(Req q) {
                          pr.lim);
     }
     for (int off = kWave / 2; off > 0; off >>= 1) n_ver += __shfl_xor(n_ver, off, kWave);
-    if (lane_id() == 0 && n_ver) atomicAdd(&q.counters[C_HINT_VER], n_ver);
+    if (lane_id() == 0 && n_ver) count_add(q.counters, C_HINT_VER, n_ver);
 }
 
 // ------------------------------------------------------------------ sieve
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kWave) void k_sieve_verify(Req q, const uint32_t *_
                          pr.lim);
     }
     for (int off2 = kWave / 2; off2 > 0; off2 >>= 1) n_ver += __shfl_xor(n_ver, off2, kWave);
-    if (lane_id() == 0 && n_ver) atomicAdd(&q.counters[C_SIEVE_VER], n_ver);
+    if (lane_id() == 0 && n_ver) count_add(q.counters, C_SIEVE_VER, n_ver);
 }
 
 // ------------------------------------------------------- local completion
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(kBlock) void k_complete(Req q, const uint32_t *__re
         n_low += __shfl_xor(n_low, off, kWave);
     }
     if (lane_id() == 0) {
-        if (n_ver) atomicAdd(&q.counters[C_COMPL_VER], n_ver);
+        if (n_ver) count_add(q.counters, C_COMPL_VER, n_ver);
         if (n_low) atomicAdd(&q.counters[C_COMPL_IMPROVED], n_low);
     }
 }

@@ -511,12 +511,13 @@ __device__ __forceinline__ void join_block(const Req &q, const GridLen *__restri
             }
         } else {
             unsigned long long base = 0;
-            if (lane == 0) base = atomicAdd(out.pcount, (unsigned long long)on);
+            const int seg = (int)(blockIdx.x % kCtrSlots);
+            if (lane == 0) base = atomicAdd(&out.pcount[seg * kCtrStride], (unsigned long long)on);
             base = (unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)base) |
                    (unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(base >> 32)) << 32;
-            const unsigned long long cap = (unsigned long long)out.cap;
+            const unsigned long long cap = (unsigned long long)out.segcap;
             const int fit = base >= cap ? 0 : (int)min((unsigned long long)on, cap - base);
-            for (int e = lane; e < fit; e += kWave) out.pairs[base + e] = outq[e];
+            for (int e = lane; e < fit; e += kWave) out.pairs[seg * out.segcap + (int64_t)base + e] = outq[e];
             over |= __builtin_amdgcn_readfirstlane(fit < on ? 1 : 0) != 0;
         }
         lds_sync();
@@ -753,9 +754,9 @@ __device__ __forceinline__ void join_block(const Req &q, const GridLen *__restri
     // statistics: one atomic per wavefront
     for (int off = kWave / 2; off > 0; off >>= 1) n_ver += __shfl_xor(n_ver, off, kWave);
     if (lane == 0) {
-        atomicAdd(&q.counters[C_JOIN_PAIRS], n_tiles * (unsigned long long)(kJT * kJT));
-        if (n_kept) atomicAdd(&q.counters[C_JOIN_CAND], n_kept);
-        if (n_ver) atomicAdd(&q.counters[C_JOIN_VER], n_ver);
+        count_add(q.counters, C_JOIN_PAIRS, n_tiles * (unsigned long long)(kJT * kJT));
+        if (n_kept) count_add(q.counters, C_JOIN_CAND, n_kept);
+        if (n_ver) count_add(q.counters, C_JOIN_VER, n_ver);
     }
 }
 
@@ -795,21 +796,21 @@ void k_join_redo(Req q, const GridLen *__restrict__ gl, const uint32_t *__restri
                              cb3, T, (int64_t)list[x], out, sm);
 }
 
-// The exact stage of the pairs in the buffer (the first min(*pcount, cap)
-// entries), one pair per lane, the wavefronts striding over the buffer.
-// Pairs of one length sit together in the buffer (a queue holds one
-// length), so a wavefront's pairs mostly share their window length.
+// The exact stage of the pairs in the buffer, one pair per lane, each block
+// striding over one segment.  Pairs of one length sit together in the buffer (a
+// queue holds one length), so a wavefront's pairs mostly share their window
+// length.
 template <typename FT>
 __global__ __launch_bounds__(kBlock) void k_join_verify(Req q, const GridLen *__restrict__ gl,
-                                                        const uint2 *__restrict__ pairs,
-                                                        const unsigned long long *__restrict__ pcount,
-                                                        int64_t cap, double T) {
-    const int64_t n = min((int64_t)*pcount, cap);
+                                                        JoinOut out, double T) {
+    const int seg = (int)(blockIdx.x % kCtrSlots);
+    const int64_t n = min((int64_t)out.pcount[seg * kCtrStride], out.segcap);
+    const uint2 *const pairs = out.pairs + seg * out.segcap;
     const int lane = lane_id();
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    const int64_t stride = (int64_t)(gridDim.x / kCtrSlots) * kBlock;
     uint32_t n_ver = 0;
-    for (int64_t base = (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~(kWave - 1)); base < n;
-         base += stride) {
+    for (int64_t base = (int64_t)(blockIdx.x / kCtrSlots) * kBlock + (threadIdx.x & ~(kWave - 1));
+         base < n; base += stride) {
         const int64_t e = base + lane;
         const bool valid = e < n;
         const uint2 pr = valid ? pairs[e] : make_uint2(0u, 0u);
@@ -819,7 +820,7 @@ __global__ __launch_bounds__(kBlock) void k_join_verify(Req q, const GridLen *__
     }
     unsigned long long v = n_ver;
     for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-    if (lane == 0 && v) atomicAdd(&q.counters[C_JOIN_VER], v);
+    if (lane == 0 && v) count_add(q.counters, C_JOIN_VER, v);
 }
 
 // ------------------------------------------------------------ launchers
@@ -883,17 +884,16 @@ void launch_join_redo(const JoinIn &in, const uint32_t *list, uint32_t n, hipStr
                            in.cb1, in.cb2, in.cb3, in.T, list, n, JoinOut{});
 }
 
-void launch_join_verify(int precision, const Req &q, const GridLen *gl, const uint2 *pairs,
-                        const unsigned long long *pcount, int64_t cap, double T, hipStream_t s) {
-    // enough wavefronts to keep every SIMD busy with eight, each striding
-    const int64_t want = (cap + kBlock - 1) / kBlock;
-    const unsigned nb = (unsigned)(want < 2048 ? want : 2048);
+void launch_join_verify(int precision, const Req &q, const GridLen *gl, const JoinOut &out,
+                        double T, hipStream_t s) {
+    // enough wavefronts to keep every SIMD busy with eight, each striding; a
+    // whole number of blocks per segment
+    const int64_t want = (out.segcap + kBlock - 1) / kBlock;
+    const unsigned nb = kCtrSlots * (unsigned)(want < 32 ? want : 32);
     if (precision == 0)
-        hipLaunchKernelGGL(k_join_verify<double>, dim3(nb), dim3(kBlock), 0, s, q, gl, pairs,
-                           pcount, cap, T);
+        hipLaunchKernelGGL(k_join_verify<double>, dim3(nb), dim3(kBlock), 0, s, q, gl, out, T);
     else
-        hipLaunchKernelGGL(k_join_verify<float>, dim3(nb), dim3(kBlock), 0, s, q, gl, pairs,
-                           pcount, cap, T);
+        hipLaunchKernelGGL(k_join_verify<float>, dim3(nb), dim3(kBlock), 0, s, q, gl, out, T);
 }
 
 }  // namespace pmp

@@ -21,12 +21,12 @@
 // top-k built on it by the certificate does not (the role of the fixed merge
 // order of Prop. 5).
 //
-// GPU mapping: one lane per query searches its candidates (lane-parallel
-// bound tests) until every lane still working holds a proposal; a lane that
-// holds one already (and whose own cell is finite) keeps searching for a
-// second meanwhile, so the wait for the slowest lane's search is used.  The
-// exact distances of the proposals are then computed for the whole
-// wavefront (verify_proposals), first slot, then second.
+// GPU mapping: eight lanes per query, eight queries per wavefront.  A query
+// inspects eight candidates at a time, one per lane; their records are read
+// by the eight lanes together (one contiguous row per load) and the eight
+// bounds summed by a transposed reduction.  The survivors are verified by the
+// eight lanes together, smallest bound first, each result tightening the
+// prune of the rest; queries without survivors search on meanwhile.
 //
 // One departure from the paper: a query stops once its own cell reaches 0
 // (the smallest possible value); the remaining candidates could only lower
@@ -35,28 +35,95 @@
 
 namespace pmp {
 
-// The query windows of a wavefront, staged in LDS when they share one length
-// and lie within a short span of the series (dynamic size: kQwinExtra + the
-// longest window, in doubles).  The staged samples are the series' own, so a
-// distance read through them has the same bits.
+// The query windows of a wavefront, staged in LDS when they lie within a
+// short span of the series (dynamic size: kQwinExtra + the longest window, in
+// doubles).  The staged samples are the series' own, so a distance read
+// through them has the same bits.
 extern __shared__ double probe_qwin[];
-constexpr int kQwinExtra = 256;
+constexpr int kQwinExtra = 128;
 struct QwinA {
     int64_t base;
     __device__ __forceinline__ double operator()(int64_t x) const { return probe_qwin[x - base]; }
 };
+
+namespace {
+
+constexpr int kPart = kRec / kGroup;          // record slots per lane of a group
+
+// A lane's part of one record (slots kPart g .. + kPart - 1).
+template <typename FT>
+struct RecPart {
+    FT v[kPart];
+};
+__device__ __forceinline__ RecPart<double> load_part(const double *rec, int g) {
+    const double2 a = ((const double2 *)rec)[2 * g], b = ((const double2 *)rec)[2 * g + 1];
+    return {{a.x, a.y, b.x, b.y}};
+}
+__device__ __forceinline__ RecPart<float> load_part(const float *rec, int g) {
+    const float4 a = ((const float4 *)rec)[g];
+    return {{a.x, a.y, a.z, a.w}};
+}
+
+// The certified bounds of lb_mem for the eight candidates of a group, whose
+// indices sit one per lane (kc; `want`: this lane's is wanted; m8: the wanted
+// ones of the group as a bit mask).  Lane g returns candidate g's bound (0 if
+// not wanted).  fq: this lane's part of the query's record, eq its error.
+template <typename FT>
+__device__ __forceinline__ float group_lb(const FT *__restrict__ F, const RecPart<FT> &fq, FT eq,
+                                          uint32_t kc, bool want, uint32_t m8, int g,
+                                          float sqrt2m) {
+    FT ec = 0;
+    if (want) ec = F[(int64_t)kc * kRec + kSlotErr];
+    FT p[kGroup];
+#pragma unroll
+    for (int c = 0; c < kGroup; ++c) {
+        p[c] = 0;
+        const uint32_t kcc = (uint32_t)__shfl((int)kc, c, kGroup);
+        if ((m8 >> c) & 1u) {
+            const RecPart<FT> r = load_part(F + (int64_t)kcc * kRec, g);
+            const FT e0 = r.v[0] - fq.v[0], e1 = r.v[1] - fq.v[1];
+            FT e2 = r.v[2] - fq.v[2], e3 = r.v[3] - fq.v[3];
+            if (g == kGroup - 1) e2 = e3 = 0;           // the error and the norm
+            p[c] = e0 * e0 + e1 * e1 + e2 * e2 + e3 * e3;
+        }
+    }
+    // transposed reduction: after it lane g holds the sum of candidate g
+    FT h[4], q[2];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const FT send = (g & 4) ? p[c] : p[c + 4], keep = (g & 4) ? p[c + 4] : p[c];
+        h[c] = keep + xor_lane<4>(send);
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const FT send = (g & 2) ? h[c] : h[c + 2], keep = (g & 2) ? h[c + 2] : h[c];
+        q[c] = keep + xor_lane<2>(send);
+    }
+    const FT send = (g & 1) ? q[0] : q[1], keep = (g & 1) ? q[1] : q[0];
+    const FT acc = keep + xor_lane<1>(send);
+    return lb_of(acc, eq + ec, sqrt2m);
+}
+
+}  // namespace
 
 // Queries are taken in (length, start) order (indexed position k), so that
 // neighbouring windows, which tend to cost alike, share a wavefront; only the
 // anchor lengths are probed (Sec. 3.3), each from its first probe block, so a
 // wavefront never spans two lengths.  A block is one wavefront: wavefront
 // times vary over two orders of magnitude, and a single-wave block lets a
-// compute unit start new work as soon as any one wavefront ends, not when a
-// slot for four is free.  Whenever a verification lowers a cell, the partner's
-// start is recorded as the cell's hint (any partner that lowered it will do:
-// the hints only propose pairs at the lengths between anchors).
-// Four wavefronts per SIMD (128 registers, a few spilled) hide more of the
-// candidate chain's latency than three without spills.
+// compute unit start new work as soon as any one wavefront ends.  Whenever a
+// verification lowers a cell, the partner's start is recorded as the cell's
+// hint (any partner that lowered it will do: the hints only propose pairs at
+// the lengths between anchors).
+//
+// What bounds it: the chain of dependent loads of a query (bucket, slot, cell
+// value, record, moments, samples) where few queries are in flight, the record
+// and sample reads where many are.  With one lane per query a wavefront waited
+// for the slowest of 64 chains of up to R candidates; eight lanes shorten a
+// chain eightfold and give eight times the wavefronts.  Measured: random walk
+// 4,000 x 51 (19,700 queries) 3.0 -> 0.63 ms, Wafer-like 40,000 x 41 of 480..520
+// 5.4 -> 1.2 ms, Wafer-like 5M (981,000 queries) 1.69 -> 0.77 ms, ECG-like 1M
+// (5.0e6 queries, FP64) 65 -> 53 ms.
 template <typename FT>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0) {
@@ -64,95 +131,79 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0)
     // the probe): the last length whose first probe block is at or below it
     // (uniform)
     const int64_t gb = blk0 + (int64_t)blockIdx.x;
-    int lb = 0;
+    int l = 0;
     {
         int hi = q.L - 1;
-        while (lb < hi) {
-            const int mid = (lb + hi + 1) >> 1;
-            if (q.len[mid].pblk_base <= gb) lb = mid; else hi = mid - 1;
+        while (l < hi) {
+            const int mid = (l + hi + 1) >> 1;
+            if (q.len[mid].pblk_base <= gb) l = mid; else hi = mid - 1;
         }
     }
-    const int64_t k_first = q.len[lb].kbase + (gb - q.len[lb].pblk_base) * kWave;
-    const int64_t k = k_first + threadIdx.x;
+    const LenInfo &L = q.len[l];
+    const int m = L.m, d = L.depth, probes = L.probes;
+    const int64_t cell_base = L.cell_base;
+    const uint32_t *const bb = bstart + L.bucket_base;
+    const float sqrt2m = (float)sqrt(2.0 / (double)m) * (1.0f + 1e-7f);
+    const FT *const F = (const FT *)q.F;
+    const int g = threadIdx.x & (kGroup - 1), grp = threadIdx.x / kGroup;
+    const int64_t kend = L.kbase + L.n_index;
+    const int64_t k = L.kbase + (gb - L.pblk_base) * kProbeQ + grp;
     uint32_t n_cand = 0, n_ver = 0;
 
-    // ---- per-lane query state
-    bool done = k >= q.len[lb].kbase + q.len[lb].n_index;
-    int l = -1, m = 0, d = 0, probes = 0;
-    int64_t cell_base = 0;
-    uint32_t cq = 0, prefix = 0, lim = 0;
+    // ---- the group's query (every lane of a group holds the same state)
+    bool done = k >= kend;
+    uint32_t prefix = 0, lim = 0;
     int64_t iq = 0;
     uint64_t kw = 0;
     double Pq = 0.0, muq = 0.0, isq = 0.0;
-    float sqrt2m = 0.0f;
-    const uint32_t *bb = bstart;
-    const FT *fq = (const FT *)q.F;
-    if (!done) {
-        l = lb;
-        const LenInfo L = q.len[l];
-        m = L.m;
-        d = L.depth;
-        probes = L.probes;
-        cell_base = L.cell_base;
-        bb = bstart + L.bucket_base;
-        sqrt2m = (float)sqrt(2.0 / (double)m) * (1.0f + 1e-7f);
-        cq = q.cell[k];
-        iq = (int64_t)cq - cell_base;
+    RecPart<FT> fq = {};
+    FT eq = 0;
+    const bool mine = !done;
+    if (mine) {
+        iq = (int64_t)q.cell[k] - cell_base;
         kw = q.keyw[k];
         prefix = d ? (uint32_t)(kw & 0xFFFFFFu) >> (q.B - d) : 0u;
         Pq = bitsd(q.P[k]);
         muq = q.mu[k];
         isq = q.isig[k];
-        fq += k * kRec;
+        fq = load_part(F + k * kRec, g);
+        eq = F[k * kRec + kSlotErr];
         done = Pq == 0.0 || iq - q.excl < 0;
         lim = (uint32_t)(cell_base + iq - q.excl);
     }
-    // ---- stage the query windows (uniform decision): one length, and the
-    // span from the first start to the last window's end fits
-    bool staged = false;
-    int64_t qlo = 0;
+    // ---- stage the query windows (uniform decision): the span from the first
+    // start to the last window's end fits
+    bool staged;
+    const int64_t qlo = __shfl(iq, 0, kWave);
     {
-        const uint64_t valid = __ballot(l >= 0);
-        const int last = 63 - __clzll((long long)valid);
-        const int l0 = __shfl(l, 0, kWave);
-        qlo = __shfl(iq, 0, kWave);
-        const int64_t qhi = __shfl(iq, last, kWave) + __shfl(m, last, kWave);
-        staged = __ballot(l >= 0 && l != l0) == 0 && qhi - qlo <= (int64_t)qcap;
+        const int last = 63 - __clzll((long long)__ballot(mine));
+        const int64_t span = __shfl(iq, last, kWave) + m - qlo;
+        staged = span <= (int64_t)qcap;
         if (staged) {
-            for (int64_t x = lane_id(); x < qhi - qlo; x += kWave) probe_qwin[x] = q.t[qlo + x];
+            for (int64_t x = lane_id(); x < span; x += kWave) probe_qwin[x] = q.t[qlo + x];
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
     }
-    // candidate iterator
+    // candidate iterator of the query
     int pr = -1, budget = q.budget_R;
     int64_t bs = 0, cut = 0, span = 0;
     int take = 0, rec = 0, str = 1, j = 0;
-    // current proposals (two slots), kept in LDS from the search that finds
-    // them to the verification that reads them, so that they hold no
-    // registers through the search loop
-    __shared__ double s_Pc[2][kWave], s_mu[2][kWave], s_is[2][kWave], s_lim[2][kWave];
-    __shared__ int64_t s_ic[2][kWave];
-    __shared__ uint32_t s_c[2][kWave];
-    const int ln = threadIdx.x;
-#pragma unroll
-    for (int sl = 0; sl < 2; ++sl) {
-        s_Pc[sl][ln] = 0.0;
-        s_mu[sl][ln] = 0.0;
-        s_is[sl][ln] = 0.0;
-        s_lim[sl][ln] = INFINITY;
-        s_ic[sl][ln] = 0;
-        s_c[sl][ln] = 0;
-    }
-    bool has = false, has1 = false;
+    // this lane's candidate, while it waits for its verification
+    bool alive = false;
+    uint32_t kc = 0;
+    int64_t ic = 0;
+    double Pc = 0.0, muc = 0.0, isc = 0.0;
+    float lb = 0.0f;
 
+    const int gshift = grp * kGroup;
+    auto group_bits = [&](bool b) -> uint32_t { return (uint32_t)(__ballot(b) >> gshift) & 0xFFu; };
     for (;;) {
-        // ---- the wavefront searches until every lane still working holds a
-        // proposal; a lane that holds one already looks for a second meanwhile
-        while (__ballot(!done && !has) != 0) {
-            // a second proposal only once the query's own cell is finite
-            // (before that, its first distance often ends it: a repeat at 0)
-            if (done || has1 || (has && Pq == INFINITY)) continue;
+        // ---- every query still at work searches until it has a survivor
+        for (;;) {
+            const bool search = !done && group_bits(alive) == 0u;
+            if (__ballot(search) == 0) break;
+            if (!search) continue;
             if (j >= take) {
                 // open the next bucket
                 ++pr;
@@ -165,11 +216,15 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0)
                 bs = bb[b];
                 // the valid entries (cell <= lim) form a prefix of the bucket
                 // (in the own bucket the query and everything after it lie
-                // past the prefix)
+                // past the prefix); the group narrows it down eight ways
                 int64_t lo = bs, hi = (int64_t)bb[b + 1];
                 while (lo < hi) {
-                    const int64_t mid = (lo + hi) >> 1;
-                    if (q.pcell[mid] <= lim) lo = mid + 1; else hi = mid;
+                    const int64_t step = (hi - lo + kGroup - 1) / kGroup;
+                    const int64_t at = lo + g * step;
+                    const int below = __popc(group_bits(at < hi && q.pcell[at] <= lim));
+                    if (below == 0) break;
+                    hi = min(hi, lo + below * step);
+                    lo += (below - 1) * step + 1;
                 }
                 cut = lo;
                 const int64_t cnt = cut - bs;
@@ -184,84 +239,70 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0)
                 budget -= take;
                 continue;
             }
-            const int64_t cs = j < rec ? cut - 1 - j : bs + ((int64_t)(j - rec) * span) / str;
-            ++j;
-            ++n_cand;
-            const uint32_t kc = q.perm[cs];
-            const double Pc = bitsd(q.P[kc]);
-            const double thr = fmax(Pq, Pc);
-            if (thr == 0.0) continue;
-            // no bound can prune below +inf: skip the record reads
-            if (thr != INFINITY) {
-                const float lb = lb_mem<FT>(fq, (const FT *)q.F + (int64_t)kc * kRec, sqrt2m);
-                if ((double)lb >= thr) continue;
+            // the next candidates, one per lane; a single one while the
+            // query's own cell has no value (its first distance often ends
+            // the query: a repeat at 0), and no bound can prune below +inf
+            const bool first = Pq == INFINITY;
+            const int jj = j + g;
+            const bool in = jj < take && (!first || g == 0);
+            j += first ? 1 : kGroup;
+            double thr = 0.0;
+            if (in) {
+                const int64_t cs = jj < rec ? cut - 1 - jj : bs + ((int64_t)(jj - rec) * span) / str;
+                kc = q.perm[cs];
+                ic = (int64_t)q.pcell[cs] - cell_base;
+                Pc = bitsd(q.P[kc]);
+                thr = fmax(Pq, Pc);
+                ++n_cand;
             }
-            {
-                const int sl = has ? 1 : 0;
-                s_lim[sl][ln] = exit_bound(thr);
-                s_c[sl][ln] = kc;
-                s_ic[sl][ln] = (int64_t)q.pcell[cs] - cell_base;
-                s_Pc[sl][ln] = Pc;
-                s_mu[sl][ln] = q.mu[kc];
-                s_is[sl][ln] = q.isig[kc];
-                if (has) has1 = true; else has = true;
+            alive = thr > 0.0;
+            lb = 0.0f;
+            if (!first) {
+                const uint32_t m8 = group_bits(alive);
+                if (m8) {
+                    lb = group_lb<FT>(F, fq, eq, kc, alive, m8, g, sqrt2m);
+                    alive = alive && (double)lb < thr;
+                }
+            }
+            if (alive) {
+                muc = q.mu[kc];
+                isc = q.isig[kc];
             }
         }
-        // ---- the wavefront verifies the first proposals
-        const uint64_t mask = __ballot(has);
-        if (mask == 0) break;
-        const double pPc = s_Pc[0][ln], pmu = s_mu[0][ln], pis = s_is[0][ln], plim = s_lim[0][ln];
-        const int64_t pic = s_ic[0][ln];
-        const uint32_t pc = s_c[0][ln];
-        auto on_result = [&](double dd) {
-            ++n_ver;
+        if (__ballot(alive) == 0) break;
+        // ---- every query verifies its survivor of the smallest bound
+        const bool go = group_bits(alive) != 0u;
+        uint32_t key = alive ? (__float_as_uint(lb) & ~7u) | (uint32_t)g : 0xFFFFFFFFu;
+        key = min(key, xor_lane<1>(key));
+        key = min(key, xor_lane<2>(key));
+        key = min(key, xor_lane<4>(key));
+        const int sel = (int)(key & 7u);
+        const uint32_t vk = (uint32_t)__shfl((int)kc, sel, kGroup);
+        const int64_t vi = __shfl(ic, sel, kGroup);
+        const double vP = __shfl(Pc, sel, kGroup);
+        const double vmu = __shfl(muc, sel, kGroup), vis = __shfl(isc, sel, kGroup);
+        const double lim2 = exit_bound(fmax(Pq, vP));
+        const int vm = go ? m : 0;
+        const double dd = snap(staged
+            ? group_zdist_a(QwinA{qlo}, q.t, iq, muq, isq, vi, vmu, vis, vm, lim2)
+            : group_zdist_a(SeriesA{q.t}, q.t, iq, muq, isq, vi, vmu, vis, vm, lim2));
+        if (go) {
             const unsigned long long db = (unsigned long long)dbits(dd);
-            if (dd < Pq) {
-                atomicMin((unsigned long long *)&q.P[k], db);
-                Pq = dd;
-                q.hint[k] = (uint32_t)pic;
+            if (g == 0) {
+                ++n_ver;
+                if (dd < Pq) {
+                    atomicMin((unsigned long long *)&q.P[k], db);
+                    q.hint[k] = (uint32_t)vi;
+                }
+                if (dd < vP) {
+                    atomicMin((unsigned long long *)&q.P[vk], db);
+                    q.hint[vk] = (uint32_t)iq;
+                }
             }
-            if (dd < pPc) {
-                atomicMin((unsigned long long *)&q.P[pc], db);
-                q.hint[pc] = (uint32_t)iq;
-            }
-            has = false;
+            Pq = fmin(Pq, dd);
             if (Pq == 0.0) done = true;
-        };
-        if (staged)
-            verify_proposals(mask, QwinA{qlo}, q.t, iq, muq, isq, pic, pmu, pis, m, on_result, plim);
-        else
-            verify_proposals(mask, SeriesA{q.t}, q.t, iq, muq, isq, pic, pmu, pis, m, on_result,
-                             plim);
-        // the second slot (a lane whose own cell reached 0 drops it)
-        const uint64_t mask1 = __ballot(has1 && !done);
-        auto on_result1 = [&](double dd) {
-            const double pPc1 = s_Pc[1][ln];
-            const uint32_t pc1 = s_c[1][ln];
-            ++n_ver;
-            const unsigned long long db = (unsigned long long)dbits(dd);
-            if (dd < Pq) {
-                atomicMin((unsigned long long *)&q.P[k], db);
-                Pq = dd;
-                q.hint[k] = (uint32_t)s_ic[1][ln];
-            }
-            if (dd < pPc1) {
-                atomicMin((unsigned long long *)&q.P[pc1], db);
-                q.hint[pc1] = (uint32_t)iq;
-            }
-            if (Pq == 0.0) done = true;
-        };
-        if (mask1) {
-            const double pmu1 = s_mu[1][ln], pis1 = s_is[1][ln], plim1 = s_lim[1][ln];
-            const int64_t pic1 = s_ic[1][ln];
-            if (staged)
-                verify_proposals(mask1, QwinA{qlo}, q.t, iq, muq, isq, pic1, pmu1, pis1, m, on_result1,
-                                 plim1);
-            else
-                verify_proposals(mask1, SeriesA{q.t}, q.t, iq, muq, isq, pic1, pmu1, pis1, m,
-                                 on_result1, plim1);
+            if (g == sel || done || (double)lb >= fmax(Pq, Pc)) alive = false;
         }
-        has1 = false;
     }
     // stats: one atomic per wave
     unsigned long long a = n_cand, v = n_ver;
@@ -270,8 +311,8 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0)
         v += __shfl_xor(v, off, kWave);
     }
     if (lane_id() == 0) {
-        if (a) atomicAdd(&q.counters[C_PASS_CAND], a);
-        if (v) atomicAdd(&q.counters[C_PASS_VER], v);
+        if (a) count_add(q.counters, C_PASS_CAND, a);
+        if (v) count_add(q.counters, C_PASS_VER, v);
     }
 }
 

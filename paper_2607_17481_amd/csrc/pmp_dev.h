@@ -18,6 +18,7 @@ constexpr int    kSlotErr    = 30;        // record slot of the error bound e_i
 constexpr int    kSlotNorm   = 31;        // record slot of ||F||
 constexpr int    kMaxBits    = 24;        // SimHash bits B (Sec. 4: B = 24)
 constexpr int    kProbeSlots = 8;         // Hamming-1 probes kept per key word
+constexpr int    kProbeQ     = 8;         // queries per probe wavefront (eight lanes each)
 constexpr int    kMaxM       = 2048;      // longest window supported
 constexpr int    kTileW      = 1024;      // windows per sketch tile
 constexpr int    kSegW       = 64;        // windows per sliding-DFT segment
@@ -42,7 +43,7 @@ struct LenInfo {
     int64_t blk_base;     // first block of this length in k_keys (anchors own blocks)
     // anchor lengths (Sec. 3.3): the one pass probes only these.  pblk_base
     // is non-decreasing over the lengths: an anchor owns probe blocks
-    // [pblk_base, pblk_base + ceil(n_index / 64)), a non-anchor none.
+    // [pblk_base, pblk_base + ceil(n_index / kProbeQ)), a non-anchor none.
     // Likewise hblk_base for the hint blocks of the non-anchor lengths.
     int32_t anchor;       // 1: an anchor length
     int32_t a_lo, a_hi;   // a non-anchor's nearest anchors below and above
@@ -94,7 +95,7 @@ struct Req {
                            // (kNone: none), written when a cell is lowered
     float   *emax;         // [L] largest e_i of each length
     float   *jemax;        // [L] largest e' of each length's join operands
-    unsigned long long *counters;   // stats counters
+    unsigned long long *counters;   // stats counters: kCtrSlots sets, kCtrStride apart
     int     *bad;          // raised on inputs the library cannot represent
 };
 
@@ -104,6 +105,15 @@ enum Counter {
 };
 
 constexpr uint32_t kNone = 0xFFFFFFFFu;      // no entry (kmap, hint)
+
+// Counters that every wavefront adds to are kept in kCtrSlots sets, one per
+// residue of the block index and each in a cache line of its own, and summed
+// by whoever reads them: atomics on one address follow each other at about
+// 8 ns, which a million wavefronts would wait for (measured: the probe of 1e6
+// windows at 8 per wavefront took 2.7 ms with one set of counters).  Blocks go
+// to the eight XCDs in turn, so a set belongs to one of them.
+constexpr int kCtrSlots = 64;
+constexpr int kCtrStride = 16;               // in 64-bit words: 128 bytes
 
 // ------------------------------------------------------------- helpers
 
@@ -135,6 +145,36 @@ __device__ __forceinline__ float half_float(uint32_t b) {
     _Float16 h;
     __builtin_memcpy(&h, &u, 2);
     return (float)h;
+}
+
+// The value of lane (l ^ X), X in {1, 2, 4}, through the data-parallel
+// primitives (no LDS round trip as in a general shuffle).
+template <int X>
+__device__ __forceinline__ int xor_lane(int v) {
+    static_assert(X == 1 || X == 2 || X == 4, "within a group of eight lanes");
+    if (X == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);   // quad 1 0 3 2
+    if (X == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);   // quad 2 3 0 1
+    // l ^ 3 within quads, then l ^ 7 within halves of a row
+    v = __builtin_amdgcn_update_dpp(0, v, 0x1B, 0xF, 0xF, true);
+    return __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true);
+}
+template <int X>
+__device__ __forceinline__ uint32_t xor_lane(uint32_t v) {
+    return (uint32_t)xor_lane<X>((int)v);
+}
+template <int X>
+__device__ __forceinline__ float xor_lane(float v) {
+    return __int_as_float(xor_lane<X>(__float_as_int(v)));
+}
+template <int X>
+__device__ __forceinline__ double xor_lane(double v) {
+    return __hiloint2double(xor_lane<X>(__double2hiint(v)), xor_lane<X>(__double2loint(v)));
+}
+
+// Adds to this block's set of a counter.
+__device__ __forceinline__ void count_add(unsigned long long *counters, int c,
+                                          unsigned long long v) {
+    atomicAdd(&counters[(blockIdx.x % kCtrSlots) * kCtrStride + c], v);
 }
 
 // Length index of a cell (binary search over cell_base, L is small).
@@ -264,13 +304,15 @@ __device__ __forceinline__ double group_zdist_a(A qa, const double *__restrict__
         // compute the same total)
         if (lim2 != INFINITY && (r0 | (kGroup - 1)) + 1 + (kB - 1) * kGroup < m) {
             double sp = acc;
-#pragma unroll
-            for (int off = 1; off < kGroup; off <<= 1) sp += __shfl_xor(sp, off, kGroup);
+            sp += xor_lane<1>(sp);
+            sp += xor_lane<2>(sp);
+            sp += xor_lane<4>(sp);
             if (sp >= lim2) return INFINITY;
         }
     }
-#pragma unroll
-    for (int off = 1; off < kGroup; off <<= 1) acc += __shfl_xor(acc, off, kGroup);
+    acc += xor_lane<1>(acc);
+    acc += xor_lane<2>(acc);
+    acc += xor_lane<4>(acc);
     return sqrt(acc);
 }
 __device__ __forceinline__ double group_zdist(const double *__restrict__ t, int64_t a, double mua,
@@ -377,6 +419,20 @@ __device__ __forceinline__ double window_moments(const double *x, int m, double 
     return sqrt(((a0 + a1) + (a2 + a3)) / (double)m);
 }
 
+// The bound from the squared distance of two feature records and the sum of
+// their errors.
+template <typename FT>
+__device__ __forceinline__ float lb_of(FT acc, FT es, float sqrt2m) {
+    const FT nd = sqrt(acc);
+    if (sizeof(FT) == 4) {
+        float v = (float)nd * (1.0f - 1e-5f) - (float)es * (1.0f + 1e-5f);
+        return v > 0.0f ? v * sqrt2m * (1.0f - 1e-6f) : 0.0f;
+    } else {
+        double v = (double)nd * (1.0 - 1e-12) - (double)es * (1.0 + 1e-12);
+        return v > 0.0 ? __double2float_rd(v * (double)sqrt2m * (1.0 - 1e-6)) : 0.0f;
+    }
+}
+
 // Certified lower bound on d_m(q, c) from two stored feature records: the
 // Parseval bound (Lemma 2) of the true features is at least
 //   sqrt(2/m) (||F~q - F~c|| - e_q - e_c),
@@ -415,15 +471,7 @@ __device__ __forceinline__ float lb_mem(const FT *__restrict__ fq, const FT *__r
         acc = fmaf(e0, e0, acc);
         acc = fmaf(e1, e1, acc);
     }
-    const FT nd = sqrt(acc);
-    const FT es = fq[kSlotErr] + fc[kSlotErr];
-    if (sizeof(FT) == 4) {
-        float v = (float)nd * (1.0f - 1e-5f) - (float)es * (1.0f + 1e-5f);
-        return v > 0.0f ? v * sqrt2m * (1.0f - 1e-6f) : 0.0f;
-    } else {
-        double v = (double)nd * (1.0 - 1e-12) - (double)es * (1.0 + 1e-12);
-        return v > 0.0 ? __double2float_rd(v * (double)sqrt2m * (1.0 - 1e-6)) : 0.0f;
-    }
+    return lb_of(acc, fq[kSlotErr] + fc[kSlotErr], sqrt2m);
 }
 
 // Verification of the proposals of a wavefront.  Every lane whose bit is set
@@ -588,7 +636,7 @@ void launch_sketch_mfma(int precision, const Req &q, const uint32_t *E, const ui
 void launch_bucket_bounds(const Req &q, int64_t N, int64_t nbuckets, uint32_t *bstart,
                           hipStream_t s);
 // (k_probe.hip)
-// one wavefront per 64 indexed windows of each anchor length (LenInfo.pblk_base):
+// one wavefront per kProbeQ indexed windows of each anchor length (LenInfo.pblk_base):
 // the probe blocks [blk0, blk0 + nblocks)
 void launch_probe(int precision, const Req &q, const uint32_t *bstart, int64_t blk0,
                   int64_t nblocks, int max_m, hipStream_t s);
@@ -654,13 +702,15 @@ struct JoinIn {
     int cb1, cb2, cb3;
     double T;
 };
-// Where the tiles' kept pairs go: `pairs` (capacity cap, fill count *pcount);
-// blocks that find it full go to `redo` (*nredo of them, one entry per block
-// of a launch).
+// Where the tiles' kept pairs go: kCtrSlots segments of segcap pairs each,
+// their fill counts kCtrStride apart in pcount (a block writes to the segment
+// of its index, so that reservations do not queue on one address); blocks that
+// find theirs full go to `redo` (*nredo of them, one entry per block of a
+// launch).
 struct JoinOut {
     uint2 *pairs;
     unsigned long long *pcount;
-    int64_t cap;
+    int64_t segcap;
     uint32_t *redo;
     uint32_t *nredo;
 };
@@ -670,9 +720,9 @@ void launch_join_tiles(const JoinIn &in, int64_t blk0, int64_t nblocks, const ui
                        const JoinOut &out, hipStream_t s);
 // the n blocks of a list, their kept pairs verified in place
 void launch_join_redo(const JoinIn &in, const uint32_t *list, uint32_t n, hipStream_t s);
-// the exact stage of the first min(*pcount, cap) pairs of the buffer
-void launch_join_verify(int precision, const Req &q, const GridLen *gl, const uint2 *pairs,
-                        const unsigned long long *pcount, int64_t cap, double T, hipStream_t s);
+// the exact stage of the pairs in the buffer's segments
+void launch_join_verify(int precision, const Req &q, const GridLen *gl, const JoinOut &out,
+                        double T, hipStream_t s);
 void launch_rows(const Req &q, const RowReq *rr, int nrows, int64_t maxN,
                  unsigned long long *out_min, unsigned long long *out_arg, hipStream_t s);
 void launch_stream_basis(const SAnchor *anc, int na, int64_t elems, double *basis,

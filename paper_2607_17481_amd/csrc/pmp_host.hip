@@ -381,7 +381,7 @@ static void plan_index(Plan &p, const std::vector<int64_t> &cnt, const Opt &o, i
         L.pblk_base = p.nprobe_blocks;
         L.hblk_base = p.nhint_blocks;
         if (L.anchor)
-            p.nprobe_blocks += (L.n_index + kWave - 1) / kWave;
+            p.nprobe_blocks += (L.n_index + kProbeQ - 1) / kProbeQ;
         else
             p.nhint_blocks += (L.n_index + kWave - 1) / kWave;
         L.bucket_base = bb;
@@ -457,7 +457,7 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
     b.scan_tmp = (uint32_t *)a.take(scan_temp_bytes(std::max<int64_t>(
         {p.n + 1, p.ntiles + 1, select_blocks(p.cells) + 1, 2 * p.cells + p.L + 1})));
     b.bad = take<int>(a, 1);
-    b.counters = take<unsigned long long>(a, C_NCOUNTERS);
+    b.counters = take<unsigned long long>(a, kCtrSlots * kCtrStride);
     b.emax = take<float>(a, 2 * p.L);        // then the join operands' (jemax)
     b.gproj = take<float>(a, (int64_t)p.L * kMaxBits * kFD);
     b.cov = take<double>(a, (int64_t)join_cov_doubles(p.L));
@@ -486,6 +486,7 @@ static bool needs_kmap(const Opt &o) { return o.stride > 1; }
 
 // Kept pairs of the join buffered between its tiles and its exact stage:
 // four per indexed window (32 bytes a window), at least 2^16.
+constexpr int kJoinCounts = kCtrSlots * kCtrStride + 1;
 static int64_t join_pair_cap(int64_t N) { return std::max<int64_t>(int64_t(1) << 16, 4 * N); }
 
 // Blocks of the join over N windows in L lengths, at most.
@@ -521,8 +522,8 @@ static void carve2(Arena &a, Bufs &b, const Plan &p, const Opt &o, int k) {
     b.jv2 = take<uint32_t>(a, N);
     b.jcap = join_pair_cap(N);
     b.jpairs = take<uint2>(a, b.jcap);
-    // the pair count, the number of overflowed blocks, nonq (u32 per length)
-    b.jcount = take<unsigned long long>(a, 2 + (p.L + 1) / 2);
+    // the segments' pair counts, the number of overflowed blocks, nonq (u32 per length)
+    b.jcount = take<unsigned long long>(a, kJoinCounts + (p.L + 1) / 2);
     b.jredo = take<uint32_t>(a, 2 * join_blocks_max(N, p.L));
     b.sel_cnt = take<uint32_t>(a, select_blocks(N) + 1);
     b.selblk = (char *)a.take(select_block_bytes(need));
@@ -937,7 +938,7 @@ static int run_pipeline(Run &R, Arena &ar) {
     const std::vector<LenInfo> len_host = p.len;
     HIPCHK(hipMemcpyAsync(b.len, len_host.data(), p.L * sizeof(LenInfo), hipMemcpyHostToDevice, s));
     launch_fill_u32((uint32_t *)b.emax, 2 * p.L, 0u, s);
-    launch_fill_u64((uint64_t *)b.counters, C_NCOUNTERS, 0ull, s);
+    launch_fill_u64((uint64_t *)b.counters, kCtrSlots * kCtrStride, 0ull, s);
 
     Req q{};
     q.t = R.t;
@@ -1183,8 +1184,8 @@ static int run_pipeline(Run &R, Arena &ar) {
             if (nq_ops == 0 && Nq > 0) launch_join_dirs(o.precision, q, rec_lim + 1, b.cov, b.udir, s);
             launch_join_ops(o.precision, q, nq_ops, Nq, s);
             nq_ops = std::max(nq_ops, Nq);
-            uint32_t *const nonq = (uint32_t *)(b.jcount + 2);
-            launch_fill_u64((uint64_t *)b.jcount, 2 + (p.L + 1) / 2, 0ull, s);
+            uint32_t *const nonq = (uint32_t *)(b.jcount + kJoinCounts);
+            launch_fill_u64((uint64_t *)b.jcount, kJoinCounts + (p.L + 1) / 2, 0ull, s);
             launch_grid_keys(q, b.gl, Nq, cb1, cb2, cb3, l_lim, i_lim, b.jk, b.jv, b.qf, b.gp, nonq,
                              s);
             radix_sort_pairs(b.jk, b.jv, b.jk2, b.jv2, Nq, 0, p.len_bits + cb1 + cb2 + cb3,
@@ -1215,16 +1216,21 @@ static int run_pipeline(Run &R, Arena &ar) {
                     return std::min(left, lim);
                 };
                 auto take_chunk = [&](int64_t b0, const uint32_t *list) {
-                    const JoinOut out{b.jpairs, b.jcount, b.jcap, nxt, (uint32_t *)(b.jcount + 1)};
+                    const JoinOut out{b.jpairs, b.jcount, std::max<int64_t>(1, b.jcap / kCtrSlots), nxt,
+                                      (uint32_t *)(b.jcount + kJoinCounts - 1)};
                     launch_join_tiles(in, b0, nb, list, out, s);
-                    launch_join_verify(o.precision, q, b.gl, b.jpairs, b.jcount, b.jcap, Teff, s);
+                    launch_join_verify(o.precision, q, b.gl, out, Teff, s);
                 };
                 // the counts so far; the pair count starts again
                 auto read_counts = [&]() -> int {
-                    HIPCHK(hipMemcpyAsync(&cnt, b.jcount, sizeof(cnt), hipMemcpyDeviceToHost, s));
+                    std::vector<unsigned long long> v(kJoinCounts);
+                    HIPCHK(hipMemcpyAsync(v.data(), b.jcount, v.size() * 8, hipMemcpyDeviceToHost, s));
                     HIPCHK(hipStreamSynchronize(s));
+                    cnt.kept = 0;
+                    for (int x = 0; x < kCtrSlots; ++x) cnt.kept += v[x * kCtrStride];
+                    cnt.nredo = (uint32_t)v[kJoinCounts - 1];
                     rate = (double)(cnt.kept + 1) / (double)nb;
-                    launch_fill_u64((uint64_t *)b.jcount, 1, 0ull, s);
+                    launch_fill_u64((uint64_t *)b.jcount, kJoinCounts - 1, 0ull, s);
                     return PMP_OK;
                 };
                 for (int64_t b0 = 0; b0 < nbq; b0 += nb) {
@@ -1243,7 +1249,7 @@ static int run_pipeline(Run &R, Arena &ar) {
                     const uint32_t n = cnt.nredo;
                     rate = (double)(cnt.kept + 1) / (double)std::max<int64_t>(nb, 1);
                     std::swap(cur, nxt);
-                    launch_fill_u64((uint64_t *)b.jcount, 2, 0ull, s);
+                    launch_fill_u64((uint64_t *)b.jcount, kJoinCounts, 0ull, s);
                     for (int64_t b0 = 0; b0 < (int64_t)n; b0 += nb) {
                         nb = chunk((int64_t)n - b0);
                         take_chunk(0, cur + b0);
@@ -1291,7 +1297,7 @@ static int run_pipeline(Run &R, Arena &ar) {
         memcpy(&rr[x].target, &d, 8);
     }
     std::vector<unsigned long long> rmin(nacc), rarg(nacc);
-    std::vector<unsigned long long> ctr(C_NCOUNTERS);
+    std::vector<unsigned long long> sets(kCtrSlots * kCtrStride), ctr(C_NCOUNTERS);
     if (nacc) {
         HIPCHK(hipMemcpyAsync(b.rows, rr.data(), nacc * sizeof(RowReq), hipMemcpyHostToDevice, s));
         launch_fill_u64((uint64_t *)b.row_min, nacc, kInfBits, s);
@@ -1304,7 +1310,7 @@ static int run_pipeline(Run &R, Arena &ar) {
     }
     tm.mark(7, s);
     if (R.st)
-        HIPCHK(hipMemcpyAsync(ctr.data(), b.counters, C_NCOUNTERS * 8, hipMemcpyDeviceToHost, s));
+        HIPCHK(hipMemcpyAsync(sets.data(), b.counters, sets.size() * 8, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     HIPCHK(hipGetLastError());
     if (nacc) {
@@ -1380,6 +1386,8 @@ static int run_pipeline(Run &R, Arena &ar) {
     }
 
     if (R.st) {
+        for (int x = 0; x < kCtrSlots; ++x)
+            for (int c = 0; c < C_NCOUNTERS; ++c) ctr[c] += sets[x * kCtrStride + c];
         pmp_stats *st = R.st;
         st->K = K;
         st->lengths = p.L;

@@ -32,3 +32,18 @@ def test_join_blocks(gpu, ws, oracle, windows, repeat, prec):  # noqa: F811
     if repeat:
         t[n - 16:n - 1] = t[2:17] + 3.0
     check(gpu, ws, oracle, t, lo, hi, excl, precision=PRECS[prec], anchor_stride=2)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "bf16"])
+@pytest.mark.parametrize("windows", [2, 7, 8, 9, 17, 64, 65])
+def test_probe_groups(gpu, ws, oracle, windows, prec):  # noqa: F811
+    """The probe's wavefronts of eight queries with eight lanes each: fewer
+    queries than one wavefront takes, one below, at and above a multiple; flat
+    stretches keep the windows of a wavefront apart (they are then read from
+    the series, not from the staged copy)."""
+    lo, hi, excl = 8, 9, 1
+    n = windows + lo - 1
+    t = np.random.default_rng(windows).standard_normal(n)
+    check(gpu, ws, oracle, t, lo, hi, excl, k=5, precision=PRECS[prec])
+    gaps = np.concatenate([np.concatenate([t, np.full(200, t[-1])]), t * 0.5 + 1.0])
+    check(gpu, ws, oracle, gaps, lo, hi, excl, k=5, precision=PRECS[prec])
