@@ -29,6 +29,7 @@
 //    their hint.  The seeds are the current top-k cells, re-selected every
 //    round, for at most P_max rounds or until no cell improves.
 #include "pmp_dev.h"
+#include "quant.h"
 
 namespace pmp {
 
@@ -140,6 +141,98 @@ __global__ __launch_bounds__(kWave) void k_hints(Req q) {
                              lower_pair(q, (uint32_t)k, i, pr.kb, pr.ib, dd);
                          },
                          pr.lim);
+    }
+    for (int off = kWave / 2; off > 0; off >>= 1) n_ver += __shfl_xor(n_ver, off, kWave);
+    if (lane_id() == 0 && n_ver) count_add(q.counters, C_HINT_VER, n_ver);
+}
+
+// The hints once a k-th value `cut` is known that no cell above it can undercut:
+// only partners within it are of interest, so the 16-bit prefilter (four lanes
+// per pair) tests every pair against the cut and the two cells first, and the
+// few that pass are verified as above.  A pair's record bound is left out: it
+// costs two record reads and rules out little that the prefilter keeps.
+// Measured (ECG-like 1M, 46 lengths between anchors): 39 -> 1.2 ms.
+__global__ __launch_bounds__(kWave) void k_hints_cut(Req q, double cut, Quant x) {
+    const int64_t blk = blockIdx.x;
+    int l = 0;
+    {
+        int hi = q.L - 1;
+        while (l < hi) {
+            const int mid = (l + hi + 1) >> 1;
+            if (q.len[mid].hblk_base <= blk) l = mid; else hi = mid - 1;
+        }
+    }
+    const LenInfo L = q.len[l];
+    const int64_t k = L.kbase + (blk - L.hblk_base) * kWave + threadIdx.x;
+    const bool live = !L.anchor && k < L.kbase + L.n_index;
+    const int m = L.m;
+    const int lane = lane_id(), g = lane & 3;
+    int64_t i = 0;
+    float4 wi = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (live) {
+        wi = x.xw[k];
+        i = (int64_t)__float_as_uint(wi.x);
+    }
+    uint32_t jprev = kNone;
+    unsigned long long n_ver = 0;
+    for (int side = 0; side < 2; ++side) {
+        const int a = side ? L.a_hi : L.a_lo;
+        uint32_t j = kNone, kj = kNone;
+        if (live && a >= 0) {
+            const LenInfo &A = q.len[a];
+            if (i < A.W) {
+                const uint32_t ka = q.kmap[A.cell_base + i];
+                if (ka != kNone) j = q.hint[ka];
+            }
+            if (j != kNone && j != jprev && (int64_t)j < L.W) {
+                const int64_t gap = (int64_t)j > i ? (int64_t)j - i : i - (int64_t)j;
+                if (gap >= q.excl) kj = q.kmap[L.cell_base + j];
+            }
+            jprev = j;
+        }
+        float aj = 0.0f, b = 0.0f, lim = 0.0f;
+        bool sum = false, pass = false;
+        double thr = 0.0;
+        if (kj != kNone) {
+            thr = fmin(cut, fmax(bitsd(q.P[k]), bitsd(q.P[kj])));
+            if (thr > 0.0) {
+                const float4 wj = x.xw[kj];
+                aj = wj.y;
+                b = wi.z - wj.z;
+                sum = quant_limit(wi, wj, m, thr, lim);
+                pass = !sum;
+            }
+        }
+        if (__ballot(sum) != 0) {
+#pragma unroll 1
+            for (int rnd = 0; rnd < 4; ++rnd) {
+                const int src = 16 * rnd + (lane >> 2);
+                const bool go = __shfl(sum ? 1 : 0, src, kWave) != 0;
+                if (__ballot(go) == 0) continue;
+                const uint32_t gi = (uint32_t)__shfl((int)i, src, kWave);
+                const uint32_t gj = (uint32_t)__shfl((int)j, src, kWave);
+                const float gai = __shfl(wi.y, src, kWave), gaj = __shfl(aj, src, kWave);
+                const float gb = __shfl(b, src, kWave), glim = __shfl(lim, src, kWave);
+                const bool in = go && quant_below<4>(x.x16, x.pitch, gi, gj, gai, gaj, gb, m, glim, g);
+                const uint64_t mk = __ballot(in);
+                if ((lane >> 4) == rnd && sum) pass = (mk >> (4 * (lane & 15))) & 1ull;
+            }
+        }
+        const uint64_t mask = __ballot(pass);
+        if (mask == 0) continue;
+        double mua = 0.0, isa = 0.0, mub = 0.0, isb = 0.0;
+        if (pass) {
+            mua = q.mu[k];
+            isa = q.isig[k];
+            mub = q.mu[kj];
+            isb = q.isig[kj];
+        }
+        verify_proposals(mask, SeriesA{q.t}, q.t, i, mua, isa, (int64_t)j, mub, isb, m,
+                         [&](double dd) {
+                             ++n_ver;
+                             lower_pair(q, (uint32_t)k, i, kj, (int64_t)j, dd);
+                         },
+                         exit_bound(thr));
     }
     for (int off = kWave / 2; off > 0; off >>= 1) n_ver += __shfl_xor(n_ver, off, kWave);
     if (lane_id() == 0 && n_ver) count_add(q.counters, C_HINT_VER, n_ver);
@@ -315,9 +408,12 @@ __global__ __launch_bounds__(kBlock) void k_complete(Req q, const uint32_t *__re
 
 static inline unsigned nblk(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-void launch_hints(int precision, const Req &q, int64_t nblocks, hipStream_t s) {
+void launch_hints(int precision, const Req &q, int64_t nblocks, double cut, const Quant &x,
+                  hipStream_t s) {
     if (nblocks <= 0) return;
-    if (precision == 0)
+    if (x.x16 && cut < INFINITY)
+        hipLaunchKernelGGL(k_hints_cut, dim3((unsigned)nblocks), dim3(kWave), 0, s, q, cut, x);
+    else if (precision == 0)
         hipLaunchKernelGGL(k_hints<double>, dim3((unsigned)nblocks), dim3(kWave), 0, s, q);
     else
         hipLaunchKernelGGL(k_hints<float>, dim3((unsigned)nblocks), dim3(kWave), 0, s, q);

@@ -39,6 +39,7 @@
 // cell at 0: the usual case while T > 0) a block skips the candidates before
 // its own first query altogether.
 #include "pmp_dev.h"
+#include "quant.h"
 
 namespace pmp {
 
@@ -823,6 +824,150 @@ __global__ __launch_bounds__(kBlock) void k_join_verify(Req q, const GridLen *__
     if (lane == 0 && v) count_add(q.counters, C_JOIN_VER, v);
 }
 
+// ------------------------------------------- the exact stage's prefilter (quant.h)
+
+// Ordered bits of a finite double: unsigned order is numeric order.
+__device__ __forceinline__ unsigned long long order_bits(double x) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+    return (u >> 63) ? ~u : u | 0x8000000000000000ull;
+}
+__device__ __forceinline__ double order_value(unsigned long long u) {
+    return __longlong_as_double((long long)((u >> 63) ? u & 0x7FFFFFFFFFFFFFFFull : ~u));
+}
+
+// mm[0] = smallest, mm[1] = largest sample (ordered bits; mm starts as all
+// ones and 0).
+__global__ __launch_bounds__(kBlock) void k_quant_range(const double *__restrict__ t, int64_t n,
+                                                        unsigned long long *__restrict__ mm) {
+    __shared__ unsigned long long lo[kBlock / kWave], hi[kBlock / kWave];
+    unsigned long long a = ~0ull, b = 0ull;
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * kBlock) {
+        const unsigned long long u = order_bits(t[i]);
+        a = u < a ? u : a;
+        b = u > b ? u : b;
+    }
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        const unsigned long long x = __shfl_xor(a, off, kWave), y = __shfl_xor(b, off, kWave);
+        a = x < a ? x : a;
+        b = y > b ? y : b;
+    }
+    if (lane_id() == 0) {
+        lo[threadIdx.x / kWave] = a;
+        hi[threadIdx.x / kWave] = b;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kBlock / kWave; ++w) {
+            a = lo[w] < a ? lo[w] : a;
+            b = hi[w] > b ? hi[w] : b;
+        }
+        atomicMin(&mm[0], a);
+        atomicMax(&mm[1], b);
+    }
+}
+
+// The series' centre c and half range from k_quant_range's result.
+__device__ __forceinline__ double2 quant_scale(const unsigned long long *__restrict__ mm) {
+    const double lo = order_value(mm[0]), hi = order_value(mm[1]);
+    const double c = 0.5 * lo + 0.5 * hi;
+    return make_double2(c, fmax(hi - c, c - lo) * (1.0 + 1e-12));
+}
+
+// The 16-bit series, twice: x[r] and, for windows at odd starts, x[r + 1], so
+// that every window begins on a 4-byte boundary (16-byte loads need that).
+// Entries past the series are 0.
+__global__ __launch_bounds__(kBlock) void k_quantize(const double *__restrict__ t, int64_t n,
+                                                     const unsigned long long *__restrict__ mm,
+                                                     int16_t *__restrict__ x16, int64_t pitch) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i >= pitch) return;
+    const double2 cs = quant_scale(mm);
+    const int16_t v = i < n ? (int16_t)rint((t[i] - cs.x) / cs.y * 32767.0) : (int16_t)0;
+    x16[i] = v;
+    if (i > 0) x16[pitch + i - 1] = v;
+    if (i == pitch - 1) x16[pitch + i] = 0;
+}
+
+// Per indexed window: its start, s / sigma, (c - mu) / sigma and delta.
+__global__ __launch_bounds__(kBlock) void k_quant_windows(Req q, int64_t k0, int64_t k1,
+                                                          const unsigned long long *__restrict__ mm,
+                                                          float4 *__restrict__ xw) {
+    const int64_t k = k0 + (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (k >= k1) return;
+    const int64_t k_first = k0 + (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~(kWave - 1));
+    const int l = find_len_k_wave(q.len, q.L, k_first, k);
+    const double2 cs = quant_scale(mm);
+    const double is = q.isig[k];
+    const uint32_t start = (uint32_t)((int64_t)q.cell[k] - q.len[l].cell_base);
+    const double delta = (0x1.0p-16 * (1.0 + 1e-4) + 0x1.0p-21) * cs.y * is;
+    xw[k] = make_float4(__uint_as_float(start), (float)(cs.y * is / 32767.0),
+                        (float)((cs.x - q.mu[k]) * is), (float)(delta * (1.0 + 1e-6)));
+}
+
+// The exact stage with the prefilter in front: one pair per lane for the
+// pairs' data, four lanes per pair for the 16-bit sums (64 bytes of each
+// window per load), then join_exact for the survivors.
+template <typename FT>
+__global__ __launch_bounds__(kBlock) void k_join_verify_q(Req q, const GridLen *__restrict__ gl,
+                                                          JoinOut out, double T,
+                                                          const int16_t *__restrict__ x16,
+                                                          int64_t pitch,
+                                                          const float4 *__restrict__ xw) {
+    const int seg = (int)(blockIdx.x % kCtrSlots);
+    const int64_t n = min((int64_t)out.pcount[seg * kCtrStride], out.segcap);
+    const uint2 *const pairs = out.pairs + seg * out.segcap;
+    const int lane = lane_id();
+    const int g = lane & 3;
+    const int64_t stride = (int64_t)(gridDim.x / kCtrSlots) * kBlock;
+    uint32_t n_ver = 0;
+    for (int64_t base = (int64_t)(blockIdx.x / kCtrSlots) * kBlock + (threadIdx.x & ~(kWave - 1));
+         base < n; base += stride) {
+        const int64_t e = base + lane;
+        const bool valid = e < n;
+        const uint2 pr = valid ? pairs[e] : make_uint2(0u, 0u);
+        int l = 0, m = 0;
+        uint32_t si = 0, sj = 0;
+        float ai = 0.0f, aj = 0.0f, b = 0.0f, lim = 0.0f;
+        bool live = false, pass = false;      // needs the sums; goes on to the exact stage
+        if (valid) {
+            l = find_len_k(q.len, q.L, (int64_t)pr.x);
+            m = q.len[l].m;
+            const float4 wi = xw[pr.x], wj = xw[pr.y];
+            si = __float_as_uint(wi.x);
+            sj = __float_as_uint(wj.x);
+            ai = wi.y;
+            aj = wj.y;
+            b = wi.z - wj.z;
+            const uint32_t gap = si > sj ? si - sj : sj - si;
+            if (gap >= (uint32_t)q.excl) {
+                live = quant_limit(wi, wj, m, T, lim);
+                pass = !live;
+            }
+        }
+#pragma unroll 1
+        for (int rnd = 0; rnd < 4; ++rnd) {
+            // lanes 4 p .. 4 p + 3 take the pair of lane 16 rnd + p
+            const int src = 16 * rnd + (lane >> 2);
+            const bool go = __shfl(live ? 1 : 0, src, kWave) != 0;
+            if (__ballot(go) == 0) continue;
+            const uint32_t gi = (uint32_t)__shfl((int)si, src, kWave);
+            const uint32_t gj = (uint32_t)__shfl((int)sj, src, kWave);
+            const float gai = __shfl(ai, src, kWave), gaj = __shfl(aj, src, kWave);
+            const float gb = __shfl(b, src, kWave), glim = __shfl(lim, src, kWave);
+            const int gm = __shfl(m, src, kWave);
+            const bool in = go && quant_below<4>(x16, pitch, gi, gj, gai, gaj, gb, gm, glim, g);
+            const uint64_t mk = __ballot(in);
+            if ((lane >> 4) == rnd && live) pass = (mk >> (4 * (lane & 15))) & 1ull;
+        }
+        if (__ballot(pass) == 0) continue;
+        n_ver += join_exact<FT, true>(q, pass, pr.x, pr.y, m, q.len[l].cell_base, gl[l].sqrt2m, T);
+    }
+    unsigned long long v = n_ver;
+    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+    if (lane == 0 && v) count_add(q.counters, C_JOIN_VER, v);
+}
+
 // ------------------------------------------------------------ launchers
 
 static inline unsigned nblk(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
@@ -885,15 +1030,39 @@ void launch_join_redo(const JoinIn &in, const uint32_t *list, uint32_t n, hipStr
 }
 
 void launch_join_verify(int precision, const Req &q, const GridLen *gl, const JoinOut &out,
-                        double T, hipStream_t s) {
+                        double T, const Quant &x, hipStream_t s) {
     // enough wavefronts to keep every SIMD busy with eight, each striding; a
     // whole number of blocks per segment
     const int64_t want = (out.segcap + kBlock - 1) / kBlock;
     const unsigned nb = kCtrSlots * (unsigned)(want < 32 ? want : 32);
-    if (precision == 0)
+    if (x.x16 && precision == 0)
+        hipLaunchKernelGGL(k_join_verify_q<double>, dim3(nb), dim3(kBlock), 0, s, q, gl, out, T,
+                           x.x16, x.pitch, x.xw);
+    else if (x.x16)
+        hipLaunchKernelGGL(k_join_verify_q<float>, dim3(nb), dim3(kBlock), 0, s, q, gl, out, T,
+                           x.x16, x.pitch, x.xw);
+    else if (precision == 0)
         hipLaunchKernelGGL(k_join_verify<double>, dim3(nb), dim3(kBlock), 0, s, q, gl, out, T);
     else
         hipLaunchKernelGGL(k_join_verify<float>, dim3(nb), dim3(kBlock), 0, s, q, gl, out, T);
+}
+
+// room past a window's last sample for whole loads of the prefilter
+int64_t quant_pitch(int64_t n) { return (n + 64 + 7) & ~(int64_t)7; }
+
+void launch_quant_series(const double *t, int64_t n, const Quant &x, hipStream_t s) {
+    launch_fill_u64((uint64_t *)x.mm, 1, ~0ull, s);
+    launch_fill_u64((uint64_t *)x.mm + 1, 1, 0ull, s);
+    const unsigned nb = nblk(n);
+    hipLaunchKernelGGL(k_quant_range, dim3(nb < 256 ? nb : 256), dim3(kBlock), 0, s, t, n, x.mm);
+    hipLaunchKernelGGL(k_quantize, dim3(nblk(x.pitch)), dim3(kBlock), 0, s, t, n,
+                       (const unsigned long long *)x.mm, x.x16, x.pitch);
+}
+
+void launch_quant_windows(const Req &q, int64_t k0, int64_t k1, const Quant &x, hipStream_t s) {
+    if (k1 <= k0) return;
+    hipLaunchKernelGGL(k_quant_windows, dim3(nblk(k1 - k0)), dim3(kBlock), 0, s, q, k0, k1,
+                       (const unsigned long long *)x.mm, x.xw);
 }
 
 }  // namespace pmp

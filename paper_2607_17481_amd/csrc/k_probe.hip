@@ -32,6 +32,7 @@
 // (the smallest possible value); the remaining candidates could only lower
 // their own cells, which their own queries, or the certificate, cover.
 #include "pmp_dev.h"
+#include "quant.h"
 
 namespace pmp {
 
@@ -124,9 +125,16 @@ __device__ __forceinline__ float group_lb(const FT *__restrict__ F, const RecPar
 // 4,000 x 51 (19,700 queries) 3.0 -> 0.63 ms, Wafer-like 40,000 x 41 of 480..520
 // 5.4 -> 1.2 ms, Wafer-like 5M (981,000 queries) 1.69 -> 0.77 ms, ECG-like 1M
 // (5.0e6 queries, FP64) 65 -> 53 ms.
-template <typename FT>
+//
+// kCut: only pairs at or below `cut` are of interest (the caller holds a k-th
+// value that cells above it cannot undercut).  The bound and the 16-bit
+// prefilter then test every pair against the smaller of the cut and the two
+// cells, so that nearly all pairs of noisy windows end without a distance:
+// at ECG-like 1M the four anchors after the first take 9.5 ms instead of 44.
+template <typename FT, bool kCut>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
-void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0) {
+void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0, double cut,
+             Quant x) {
     // the anchor length of this block (blocks [blk0, blk0 + gridDim.x) of
     // the probe): the last length whose first probe block is at or below it
     // (uniform)
@@ -158,6 +166,7 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0)
     double Pq = 0.0, muq = 0.0, isq = 0.0;
     RecPart<FT> fq = {};
     FT eq = 0;
+    float4 wq = make_float4(0.0f, 0.0f, 0.0f, 0.0f), wc = wq;   // prefilter: query, candidate
     const bool mine = !done;
     if (mine) {
         iq = (int64_t)q.cell[k] - cell_base;
@@ -168,6 +177,7 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0)
         isq = q.isig[k];
         fq = load_part(F + k * kRec, g);
         eq = F[k * kRec + kSlotErr];
+        if (kCut) wq = x.xw[k];
         done = Pq == 0.0 || iq - q.excl < 0;
         lim = (uint32_t)(cell_base + iq - q.excl);
     }
@@ -187,7 +197,7 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0)
     }
     // candidate iterator of the query
     int pr = -1, budget = q.budget_R;
-    int64_t bs = 0, cut = 0, span = 0;
+    int64_t bs = 0, vend = 0, span = 0;
     int take = 0, rec = 0, str = 1, j = 0;
     // this lane's candidate, while it waits for its verification
     bool alive = false;
@@ -226,8 +236,8 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0)
                     hi = min(hi, lo + below * step);
                     lo += (below - 1) * step + 1;
                 }
-                cut = lo;
-                const int64_t cnt = cut - bs;
+                vend = lo;
+                const int64_t cnt = vend - bs;
                 j = 0;
                 if (cnt <= 0) { take = 0; continue; }
                 if (cnt <= budget) {
@@ -242,17 +252,18 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0)
             // the next candidates, one per lane; a single one while the
             // query's own cell has no value (its first distance often ends
             // the query: a repeat at 0), and no bound can prune below +inf
-            const bool first = Pq == INFINITY;
+            const bool first = !kCut && Pq == INFINITY;
             const int jj = j + g;
             const bool in = jj < take && (!first || g == 0);
             j += first ? 1 : kGroup;
             double thr = 0.0;
             if (in) {
-                const int64_t cs = jj < rec ? cut - 1 - jj : bs + ((int64_t)(jj - rec) * span) / str;
+                const int64_t cs = jj < rec ? vend - 1 - jj : bs + ((int64_t)(jj - rec) * span) / str;
                 kc = q.perm[cs];
                 ic = (int64_t)q.pcell[cs] - cell_base;
                 Pc = bitsd(q.P[kc]);
                 thr = fmax(Pq, Pc);
+                if (kCut) thr = fmin(thr, cut);
                 ++n_cand;
             }
             alive = thr > 0.0;
@@ -264,7 +275,9 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0)
                     alive = alive && (double)lb < thr;
                 }
             }
-            if (alive) {
+            if (alive && kCut) {
+                wc = x.xw[kc];
+            } else if (alive) {
                 muc = q.mu[kc];
                 isc = q.isig[kc];
             }
@@ -280,15 +293,35 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0)
         const uint32_t vk = (uint32_t)__shfl((int)kc, sel, kGroup);
         const int64_t vi = __shfl(ic, sel, kGroup);
         const double vP = __shfl(Pc, sel, kGroup);
-        const double vmu = __shfl(muc, sel, kGroup), vis = __shfl(isc, sel, kGroup);
-        const double lim2 = exit_bound(fmax(Pq, vP));
-        const int vm = go ? m : 0;
-        const double dd = snap(staged
-            ? group_zdist_a(QwinA{qlo}, q.t, iq, muq, isq, vi, vmu, vis, vm, lim2)
-            : group_zdist_a(SeriesA{q.t}, q.t, iq, muq, isq, vi, vmu, vis, vm, lim2));
+        double vmu = 0.0, vis = 0.0, thr = fmax(Pq, vP);
+        bool exact = go;
+        if (kCut) {
+            thr = fmin(thr, cut);
+            const float4 wv = make_float4(__shfl(wc.x, sel, kGroup), __shfl(wc.y, sel, kGroup),
+                                          __shfl(wc.z, sel, kGroup), __shfl(wc.w, sel, kGroup));
+            float qlim;
+            if (go && quant_limit(wq, wv, m, thr, qlim))
+                exact = quant_below<8>(x.x16, x.pitch, (uint32_t)iq, (uint32_t)vi, wq.y, wv.y,
+                                       wq.z - wv.z, m, qlim, g);
+            if (exact) {
+                vmu = q.mu[vk];
+                vis = q.isig[vk];
+            }
+        } else {
+            vmu = __shfl(muc, sel, kGroup);
+            vis = __shfl(isc, sel, kGroup);
+        }
+        const double lim2 = exit_bound(thr);
+        const int vm = exact ? m : 0;
+        double dd = INFINITY;
+        if (!kCut || __ballot(exact))
+            dd = snap(staged
+                ? group_zdist_a(QwinA{qlo}, q.t, iq, muq, isq, vi, vmu, vis, vm, lim2)
+                : group_zdist_a(SeriesA{q.t}, q.t, iq, muq, isq, vi, vmu, vis, vm, lim2));
+        if (!exact) dd = INFINITY;
         if (go) {
             const unsigned long long db = (unsigned long long)dbits(dd);
-            if (g == 0) {
+            if (g == 0 && exact) {
                 ++n_ver;
                 if (dd < Pq) {
                     atomicMin((unsigned long long *)&q.P[k], db);
@@ -330,15 +363,23 @@ __global__ __launch_bounds__(kBlock) void k_hot_buckets(const uint32_t *__restri
 static inline unsigned nblk(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 void launch_probe(int precision, const Req &q, const uint32_t *bstart, int64_t blk0,
-                  int64_t nblocks, int max_m, hipStream_t s) {
+                  int64_t nblocks, int max_m, double cut, const Quant &x, hipStream_t s) {
     if (nblocks <= 0) return;
     const dim3 grid((unsigned)nblocks);
     const int qcap = kQwinExtra + max_m;
     const size_t lds = (size_t)qcap * sizeof(double);
-    if (precision == 0)
-        hipLaunchKernelGGL(k_probe<double>, grid, dim3(kWave), lds, s, q, bstart, qcap, blk0);
+    if (precision == 0 && x.x16)
+        hipLaunchKernelGGL((k_probe<double, true>), grid, dim3(kWave), lds, s, q, bstart, qcap, blk0,
+                           cut, x);
+    else if (x.x16)
+        hipLaunchKernelGGL((k_probe<float, true>), grid, dim3(kWave), lds, s, q, bstart, qcap, blk0,
+                           cut, x);
+    else if (precision == 0)
+        hipLaunchKernelGGL((k_probe<double, false>), grid, dim3(kWave), lds, s, q, bstart, qcap,
+                           blk0, INFINITY, x);
     else
-        hipLaunchKernelGGL(k_probe<float>, grid, dim3(kWave), lds, s, q, bstart, qcap, blk0);
+        hipLaunchKernelGGL((k_probe<float, false>), grid, dim3(kWave), lds, s, q, bstart, qcap, blk0,
+                           INFINITY, x);
 }
 
 void launch_hot_buckets(const uint32_t *bstart, int64_t nb, int R, unsigned long long *cnt,

@@ -598,6 +598,16 @@ struct StreamDev {
 };
 enum { CS_CAND = 0, CS_VER, CS_UPD, CS_DROP, kStreamCounters };
 
+// The 16-bit copy of the series for the prefilter of exact distances (quant.h;
+// x16 null: none): two arrays of `pitch` entries, the range of the samples
+// they were made from, and per indexed window what the sums need.
+struct Quant {
+    int16_t *x16;
+    int64_t pitch;
+    unsigned long long *mm;
+    float4 *xw;
+};
+
 // --------------------------------------------------- host-side launchers
 // (k_scan.hip)
 size_t scan_temp_bytes(int64_t n);
@@ -638,14 +648,18 @@ void launch_bucket_bounds(const Req &q, int64_t N, int64_t nbuckets, uint32_t *b
 // (k_probe.hip)
 // one wavefront per kProbeQ indexed windows of each anchor length (LenInfo.pblk_base):
 // the probe blocks [blk0, blk0 + nblocks)
+// cut: pairs above it are of no interest (+inf: none), x: the prefilter for
+// them (x16 null with cut = +inf)
 void launch_probe(int precision, const Req &q, const uint32_t *bstart, int64_t blk0,
-                  int64_t nblocks, int max_m, hipStream_t s);
+                  int64_t nblocks, int max_m, double cut, const Quant &x, hipStream_t s);
 void launch_hot_buckets(const uint32_t *bstart, int64_t nb, int R, unsigned long long *cnt,
                         hipStream_t s);
 // (k_complete.hip): the emit stage
 // the hints: one wavefront per 64 indexed windows of each length between
 // anchors (LenInfo.hblk_base)
-void launch_hints(int precision, const Req &q, int64_t nblocks, hipStream_t s);
+// (cut and x as in launch_probe)
+void launch_hints(int precision, const Req &q, int64_t nblocks, double cut, const Quant &x,
+                  hipStream_t s);
 void launch_sieve_count(const Req &q, const uint32_t *bstart, int64_t nbuckets, int R,
                         uint32_t *cnt, hipStream_t s);
 void launch_sieve_keys(int precision, const Req &q, const uint32_t *bstart, const uint32_t *off,
@@ -720,9 +734,13 @@ void launch_join_tiles(const JoinIn &in, int64_t blk0, int64_t nblocks, const ui
                        const JoinOut &out, hipStream_t s);
 // the n blocks of a list, their kept pairs verified in place
 void launch_join_redo(const JoinIn &in, const uint32_t *list, uint32_t n, hipStream_t s);
-// the exact stage of the pairs in the buffer's segments
+int64_t quant_pitch(int64_t n);
+void launch_quant_series(const double *t, int64_t n, const Quant &x, hipStream_t s);
+void launch_quant_windows(const Req &q, int64_t k0, int64_t k1, const Quant &x, hipStream_t s);
+// the exact stage of the pairs in the buffer's segments, behind the prefilter
+// when x holds one
 void launch_join_verify(int precision, const Req &q, const GridLen *gl, const JoinOut &out,
-                        double T, hipStream_t s);
+                        double T, const Quant &x, hipStream_t s);
 void launch_rows(const Req &q, const RowReq *rr, int nrows, int64_t maxN,
                  unsigned long long *out_min, unsigned long long *out_arg, hipStream_t s);
 void launch_stream_basis(const SAnchor *anc, int na, int64_t elems, double *basis,

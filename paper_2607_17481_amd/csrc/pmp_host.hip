@@ -435,6 +435,9 @@ struct Bufs {
     // directions, completion seeds
     uint32_t *kmap, *hint, *scnt, *stotal, *sseg, *seeds;
     float *sdir;
+    int16_t *x16;              // the exact stage's prefilter (Quant)
+    unsigned long long *xmm;
+    float4 *xw;
     uint32_t *sel_cnt;
     // the selection's results, one contiguous block read back at once:
     // state, then less_val, less_k, less_cell, eq_k, eq_cell (need each)
@@ -477,6 +480,8 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
     b.row_arg = take<unsigned long long>(a, k);
     b.cal_starts = take<int64_t>(a, 3 * 256);
     b.cal_win = take<double>(a, (int64_t)3 * 256 * p.max_m);
+    b.x16 = take<int16_t>(a, 2 * quant_pitch(p.n));
+    b.xmm = take<unsigned long long>(a, 2);
     b.sdir = take<float>(a, (int64_t)p.L * kFD);
     b.seeds = take<uint32_t>(a, k);
     b.stotal = take<uint32_t>(a, 1);
@@ -486,6 +491,11 @@ static bool needs_kmap(const Opt &o) { return o.stride > 1; }
 
 // Kept pairs of the join buffered between its tiles and its exact stage:
 // four per indexed window (32 bytes a window), at least 2^16.
+// Indexed windows from which a request uses the 16-bit prefilter: below, its
+// data and the selection for the cut (about 0.1 ms) cost more than the exact
+// distances they save.
+constexpr int64_t kQuantMin = (int64_t)1 << 20;
+constexpr double kProbeCut = 1.25;   // the probe's cut over the first anchor's k-th value
 constexpr int kJoinCounts = kCtrSlots * kCtrStride + 1;
 static int64_t join_pair_cap(int64_t N) { return std::max<int64_t>(int64_t(1) << 16, 4 * N); }
 
@@ -520,6 +530,7 @@ static void carve2(Arena &a, Bufs &b, const Plan &p, const Opt &o, int k) {
     b.jv = take<uint32_t>(a, N);
     b.jk2 = take<uint32_t>(a, N);
     b.jv2 = take<uint32_t>(a, N);
+    b.xw = take<float4>(a, N);
     b.jcap = join_pair_cap(N);
     b.jpairs = take<uint2>(a, b.jcap);
     // the segments' pair counts, the number of overflowed blocks, nonq (u32 per length)
@@ -702,7 +713,7 @@ static void launch_records(const Plan &p, Bufs &b, const Req &q, const Opt &o, i
 // only), the last length whose records exist when this returns
 static int emit_stage(const Plan &p, Bufs &b, Req &q, const Opt &o, int k, hipStream_t s,
                       Timer &tm, std::vector<Cand> &acc, bool &selected, int &rounds, bool lazy,
-                      int &rec_lim) {
+                      int &rec_lim, const Quant &qx) {
     rounds = 0;
     tm.mark(9, s);
     tm.mark(10, s);
@@ -743,7 +754,11 @@ static int emit_stage(const Plan &p, Bufs &b, Req &q, const Opt &o, int k, hipSt
     // k-th cell's come first
     const int64_t hint_blocks = zero_kth ? p.len[acc.back().l].hblk_base : p.nhint_blocks;
     if (hint_blocks > 0) {
-        launch_hints(o.precision, q, hint_blocks, s);
+        // with a k-th value and a certificate to follow, only cells at or
+        // below it matter
+        const bool cut = qx.x16 && acc.size() == (size_t)k && acc.back().d > kEps0;
+        launch_hints(o.precision, q, hint_blocks, cut ? acc.back().d * (1.0 + 1e-9) : INFINITY,
+                     cut ? qx : Quant{}, s);
         selected = false;
     }
     tm.mark(10, s);
@@ -1012,6 +1027,7 @@ static int run_pipeline(Run &R, Arena &ar) {
     // the selection after the first anchor's probe, when it settled the top-k
     std::vector<Cand> acc0;
     bool have_acc0 = false;
+    Quant qx{};                              // the prefilter of exact distances, once made
     // The first anchor length alone first.  When its cells already give k
     // accepted cells at 0, every cell of a longer length comes after the k-th
     // in the (P, m, i) order and can change nothing: the other anchors'
@@ -1021,7 +1037,7 @@ static int run_pipeline(Run &R, Arena &ar) {
         for (int l = 1; l < p.L && a1 < 0; ++l)
             if (p.len[l].anchor) a1 = l;
         const int64_t first = a1 < 0 ? p.nprobe_blocks : p.len[a1].pblk_base;
-        launch_probe(o.precision, q, b.bstart, 0, first, p.max_m, s);
+        launch_probe(o.precision, q, b.bstart, 0, first, p.max_m, INFINITY, Quant{}, s);
         bool rest = first < p.nprobe_blocks;
         if (rest && o.certify) {
             // fewer than k zeros at the first length (counted on the device,
@@ -1039,8 +1055,25 @@ static int run_pipeline(Run &R, Arena &ar) {
                 have_acc0 = !rest;
             }
         }
+        // A large request that the first anchor does not settle makes the
+        // prefilter's data now (4 launches, 32 bytes a window) and takes the
+        // k-th value so far as a cut: the certificate finds every cell at or
+        // below the final k-th value whatever the one pass left undone, so
+        // pairs above it serve nothing.  The factor keeps partners that are
+        // slightly farther at an anchor than at the lengths beside it as
+        // hints for those.
+        double cut = INFINITY;
+        if (rest && o.certify && N >= kQuantMin && p.anchors < p.L) {
+            qx = Quant{b.x16, quant_pitch(R.n), b.xmm, b.xw};
+            launch_quant_series(R.t, R.n, qx, s);
+            launch_quant_windows(q, 0, N, qx, s);
+            const int rc = select_topk(p, b, R.k, s, acc0);
+            if (rc) return rc;
+            if (acc0.size() == (size_t)R.k && acc0.back().d > kEps0) cut = kProbeCut * acc0.back().d;
+        }
         if (rest)
-            launch_probe(o.precision, q, b.bstart, first, p.nprobe_blocks - first, p.max_m, s);
+            launch_probe(o.precision, q, b.bstart, first, p.nprobe_blocks - first, p.max_m, cut,
+                         cut < INFINITY ? qx : Quant{}, s);
     }
     tm.mark(5, s);
     HIPCHK(hipGetLastError());
@@ -1066,7 +1099,7 @@ static int run_pipeline(Run &R, Arena &ar) {
         acc = acc0;
         selected = true;
     }
-    int rc = emit_stage(p, b, q, o, R.k, s, tm, acc, selected, crounds, lazy, rec_lim);
+    int rc = emit_stage(p, b, q, o, R.k, s, tm, acc, selected, crounds, lazy, rec_lim, qx);
     if (rc) return rc;
     tm.mark(8, s);
     // the largest feature errors again, with the records the emit stage added
@@ -1183,6 +1216,15 @@ static int run_pipeline(Run &R, Arena &ar) {
             // have none yet (the principal directions first, once)
             if (nq_ops == 0 && Nq > 0) launch_join_dirs(o.precision, q, rec_lim + 1, b.cov, b.udir, s);
             launch_join_ops(o.precision, q, nq_ops, Nq, s);
+            // the exact stage's prefilter while T > 0 (made by the probe, or
+            // here when every length is an anchor)
+            const bool pre = std::isfinite(T) && T > kEps0 && Nq >= kQuantMin;
+            if (pre && !qx.x16) {
+                qx = Quant{b.x16, quant_pitch(R.n), b.xmm, b.xw};
+                launch_quant_series(R.t, R.n, qx, s);
+                launch_quant_windows(q, 0, N, qx, s);
+            }
+            const Quant xuse = pre ? qx : Quant{};
             nq_ops = std::max(nq_ops, Nq);
             uint32_t *const nonq = (uint32_t *)(b.jcount + kJoinCounts);
             launch_fill_u64((uint64_t *)b.jcount, kJoinCounts + (p.L + 1) / 2, 0ull, s);
@@ -1219,7 +1261,7 @@ static int run_pipeline(Run &R, Arena &ar) {
                     const JoinOut out{b.jpairs, b.jcount, std::max<int64_t>(1, b.jcap / kCtrSlots), nxt,
                                       (uint32_t *)(b.jcount + kJoinCounts - 1)};
                     launch_join_tiles(in, b0, nb, list, out, s);
-                    launch_join_verify(o.precision, q, b.gl, out, Teff, s);
+                    launch_join_verify(o.precision, q, b.gl, out, Teff, xuse, s);
                 };
                 // the counts so far; the pair count starts again
                 auto read_counts = [&]() -> int {

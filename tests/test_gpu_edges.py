@@ -4,6 +4,7 @@ bars of test_gpu_parity.py)."""
 import numpy as np
 import pytest
 
+from paper_2607_17481_amd import synth
 from tests import parity
 from tests.test_gpu_parity import PRECS, gpu, run, ws  # noqa: F401  (fixtures)
 
@@ -47,3 +48,31 @@ def test_probe_groups(gpu, ws, oracle, windows, prec):  # noqa: F811
     check(gpu, ws, oracle, t, lo, hi, excl, k=5, precision=PRECS[prec])
     gaps = np.concatenate([np.concatenate([t, np.full(200, t[-1])]), t * 0.5 + 1.0])
     check(gpu, ws, oracle, gaps, lo, hi, excl, k=5, precision=PRECS[prec])
+
+
+_LARGE_ROWS: dict = {}
+
+
+@pytest.mark.parametrize("prec,stride", [("fp64", 16), ("fp32", 16), ("fp64", 1)])
+@pytest.mark.parametrize("kind", ["ecg", "walk", "far", "tiny"])
+def test_prefiltered_requests(gpu, ws, oracle, kind, prec, stride):  # noqa: F811
+    """Requests of more than 2^20 windows, whose exact distances stand behind
+    the 16-bit prefilter: a noisy series (nearly every pair ends there), a
+    random walk (window spreads far below the series' range, so most pairs
+    pass by it), the noisy series on a far offset and scaled by 2^-400."""
+    if kind == "walk":
+        t = np.cumsum(np.random.default_rng(4).standard_normal(27001))
+    else:
+        t = synth.ecg_like(27001, 9)
+        if kind == "far":
+            t = t * 3.0 + 1e5
+    lo, hi, excl = 61, 100, 50
+    ref = "ecg" if kind == "tiny" else kind       # an exact scaling keeps every distance
+    if ref not in _LARGE_ROWS:
+        _LARGE_ROWS[ref] = oracle.pan_profile_v2(t, range(lo, hi + 1), excl)
+    if kind == "tiny":
+        t = t * 2.0 ** -400
+    res, st = run(gpu, ws, t, lo, hi, excl, precision=PRECS[prec], anchor_stride=stride)
+    assert st["indexed_cells"] > 1 << 20
+    ok, msg = parity.check_topk(res, _LARGE_ROWS[ref], 20, oracle, t, excl=excl)
+    assert ok, msg
