@@ -22,41 +22,95 @@ namespace pmp {
 
 // ---------------------------------------------------------------- select
 
-// The radix select runs on the device from start to end: six passes of a
-// histogram over 11 (the last 9) bits of the FP64 bit pattern, each followed
-// by one block that picks the bin holding the `remaining`-th smallest value
-// and narrows the prefix `high`.  The state lives in a SelState; the host
-// reads it once, with the selected cells.
+// The radix select runs on the device from start to end: up to six passes of a
+// histogram over 11 (the last 9) bits of the FP64 bit pattern, whose last block
+// picks the bin holding the `remaining`-th smallest value and narrows the
+// prefix `high`.  It is over as soon as the cells at or below that bin fit the
+// output (usually after two or three passes; the greedy sorts out the rest),
+// and the passes after that return at once.  The state lives in a SelState,
+// whose ticket and histogram every pass leaves cleared for the next.
+//
+// What bounds it: launches and the reads of P.  With a pick kernel per pass,
+// always six passes, a three-kernel scan for ties and the greedy on the host
+// (a copy and a sort of k (m_max + 1) cells), a selection took about 0.3 ms at
+// 200,000 cells and 0.6 ms at windows of 400; it now takes 0.1 ms there, half
+// of it the greedy's chain of rounds.
 
-// Start state: every finite value is a candidate, the histogram is clear.
-// The join's counts (when given) travel with the state, which the host reads.
-__global__ void k_select_init(SelState *__restrict__ st, int64_t need,
-                              unsigned int *__restrict__ hist,
-                              const unsigned long long *__restrict__ counts) {
-    for (int i = threadIdx.x; i < kSelBins; i += blockDim.x) hist[i] = 0;
-    if (threadIdx.x == 0) {
-        st->high = 0;
-        st->pivot = kInfBits;
-        st->remaining = need;
-        st->need_eq = 0;
-        st->nless = 0;
-        st->done = 0;
-        unsigned long long kept = 0;
-        if (counts)
-            for (int x = 0; x < kCtrSlots; ++x) kept += counts[x * kCtrStride];
-        st->kept = kept;
-        st->nredo = counts ? (uint32_t)counts[kCtrSlots * kCtrStride] : 0u;
+// Arrival of a block at the end of a kernel: true in the last one (uniform).
+// Everything the blocks wrote before is visible to it.
+__device__ __forceinline__ bool last_block(SelState *st) {
+    __shared__ int last;
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(&st->ticket, 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (last) {
+        __threadfence();
+        if (threadIdx.x == 0) st->ticket = 0;
     }
+    return last != 0;
+}
+
+// The histogram as one block of kBlock threads sees it: eight bins a thread
+// and the sums before them.
+struct SelPick {
+    static constexpr int kPer = kSelBins / kBlock;
+    unsigned int hv[kPer];
+    unsigned long long before, upto, total;
+    // true in the one thread whose bins hold the rem-th value: the bin, the
+    // count before it and in it
+    __device__ __forceinline__ bool holds(unsigned long long rem, int &bin,
+                                          unsigned long long &cum, unsigned int &in_bin) const {
+        if (!(before < rem && upto >= rem)) return false;
+        cum = before;
+        bin = threadIdx.x * kPer;
+        in_bin = 0;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            in_bin = hv[u];
+            if (cum + hv[u] >= rem) { bin = threadIdx.x * kPer + u; break; }
+            cum += hv[u];
+        }
+        return true;
+    }
+};
+__device__ __forceinline__ SelPick pick_bin(const unsigned int *hist, int nbins) {
+    __shared__ unsigned long long part[kBlock];
+    SelPick p;
+    unsigned long long mine = 0;
+#pragma unroll
+    for (int u = 0; u < SelPick::kPer; ++u) {
+        const int b = threadIdx.x * SelPick::kPer + u;
+        p.hv[u] = b < nbins
+                      ? __hip_atomic_load(&hist[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        mine += p.hv[u];
+    }
+    part[threadIdx.x] = mine;
+    __syncthreads();
+    // inclusive scan of the per-thread sums (Hillis-Steele)
+    for (int off = 1; off < kBlock; off <<= 1) {
+        const unsigned long long x = threadIdx.x >= off ? part[threadIdx.x - off] : 0ull;
+        __syncthreads();
+        part[threadIdx.x] += x;
+        __syncthreads();
+    }
+    p.upto = part[threadIdx.x];
+    p.before = p.upto - mine;
+    p.total = part[kBlock - 1];
+    return p;
 }
 
 // Histogram of bits [shift, shift + nbits) of P over cells whose bits above
-// shift + nbits equal the state's prefix.
+// shift + nbits equal the state's prefix, then (last block) the bin of the
+// remaining-th value.  Pass 0 also settles two cases: fewer finite values than
+// wanted (take them all), and a first bin of 0, whose values are exact zeros
+// (the snap leaves nothing between 0 and 1e-6).
 __global__ __launch_bounds__(kBlock) void k_select_hist(const uint64_t *__restrict__ P,
-                                                        int64_t n, int shift, int nbits,
-                                                        const SelState *__restrict__ st,
-                                                        unsigned int *__restrict__ hist) {
-    if (st->done) return;
-    const uint64_t high = st->high;
+                                                        int64_t n, int shift, int nbits, int pass,
+                                                        int last, int64_t need, int64_t cap,
+                                                        SelState *st, unsigned int *hist) {
+    if (pass > 0 && st->done) return;
+    const uint64_t high = pass > 0 ? st->high : 0ull;
     __shared__ unsigned int h[kSelBins];
     for (int i = threadIdx.x; i < (1 << nbits); i += kBlock) h[i] = 0;
     __syncthreads();
@@ -71,151 +125,269 @@ __global__ __launch_bounds__(kBlock) void k_select_hist(const uint64_t *__restri
     __syncthreads();
     for (int i = threadIdx.x; i < (1 << nbits); i += kBlock)
         if (h[i]) atomicAdd(&hist[i], h[i]);
-}
+    if (!last_block(st)) return;
 
-// One block of kBlock threads: the bin of the remaining-th value, then the
-// histogram is cleared for the next pass.  Pass 0 also settles two cases:
-// fewer finite values than wanted (take them all), and a first bin of 0,
-// whose values are exact zeros (the snap leaves nothing between 0 and 1e-6).
-__global__ __launch_bounds__(kBlock) void k_select_pick(unsigned int *__restrict__ hist,
-                                                        int nbits, int pass, int last,
-                                                        SelState *__restrict__ st) {
-    __shared__ unsigned long long part[kBlock];
-    constexpr int kPer = kSelBins / kBlock;
-    const int nb = 1 << nbits;
-    const int done = st->done;
-    unsigned long long mine = 0;
-    unsigned int hv[kPer];
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-        const int b = threadIdx.x * kPer + u;
-        hv[u] = (!done && b < nb) ? hist[b] : 0u;
-        mine += hv[u];
-    }
-    part[threadIdx.x] = mine;
-    __syncthreads();
-    // inclusive scan of the per-thread sums (Hillis-Steele)
-    for (int off = 1; off < kBlock; off <<= 1) {
-        const unsigned long long x = threadIdx.x >= off ? part[threadIdx.x - off] : 0ull;
-        __syncthreads();
-        part[threadIdx.x] += x;
-        __syncthreads();
-    }
-    if (!done) {
-        const unsigned long long total = part[kBlock - 1];
-        const unsigned long long rem = (unsigned long long)st->remaining;
-        if (pass == 0 && total < rem) {
-            if (threadIdx.x == 0) {          // fewer finite cells than needed: take all
-                st->pivot = kInfBits;
-                st->need_eq = 0;
+    const SelPick pk = pick_bin(hist, 1 << nbits);
+    const int64_t remaining = pass > 0 ? st->remaining : need;
+    const unsigned long long rem = (unsigned long long)remaining;
+    __syncthreads();                                       // the state is rewritten below
+    if (pass == 0 && pk.total < rem) {
+        if (threadIdx.x == 0) {              // fewer finite cells than needed: take all
+            st->pivot = kInfBits;
+            st->need_eq = 0;
+            st->nless = 0;
+            st->done = 1;
+        }
+    } else {
+        int bin;
+        unsigned int in_bin;
+        unsigned long long cum;
+        if (pk.holds(rem, bin, cum, in_bin)) {             // exactly one thread
+            const unsigned long long r2 = rem - cum;       // still wanted within the bin
+            const uint64_t hi = (high << nbits) | (uint64_t)bin;
+            // cells below the bin: those the earlier passes passed by, and cum
+            const int64_t below = need - remaining + (int64_t)cum;
+            st->remaining = (int64_t)r2;
+            st->high = hi;
+            st->below = below;
+            st->tie_lo = 0;
+            st->tie_hi = n;
+            st->pos_limit = 0;
+            st->need_eq = 0;
+            st->nless = 0;
+            st->done = 0;
+            if (pass == 0 && bin == 0) {
+                st->pivot = 0;
+                st->need_eq = (int64_t)r2;
                 st->done = 1;
-            }
-        } else {
-            unsigned long long cum = threadIdx.x ? part[threadIdx.x - 1] : 0ull;
-            if (cum < rem && part[threadIdx.x] >= rem) {   // exactly one thread
-                int bin = threadIdx.x * kPer;
-#pragma unroll
-                for (int u = 0; u < kPer; ++u) {
-                    if (cum + hv[u] >= rem) { bin = threadIdx.x * kPer + u; break; }
-                    cum += hv[u];
-                }
-                const unsigned long long r2 = rem - cum;
-                const uint64_t high = (st->high << nbits) | (uint64_t)bin;
-                st->remaining = (int64_t)r2;
-                st->high = high;
-                if (pass == 0 && bin == 0) {
-                    st->pivot = 0;
-                    st->need_eq = (int64_t)r2;
-                    st->done = 1;
-                } else if (last) {
-                    st->pivot = high;
-                    st->need_eq = (int64_t)r2;
-                    st->done = 1;
-                }
+            } else if (last) {
+                st->pivot = hi;
+                st->need_eq = (int64_t)r2;
+                st->done = 1;
+            } else if (below + (int64_t)in_bin <= cap) {
+                st->pivot = (hi + 1) << shift;             // the whole bin
+                st->done = 1;
             }
         }
     }
-    __syncthreads();
     for (int i = threadIdx.x; i < kSelBins; i += kBlock) hist[i] = 0;
 }
 
-// Per-block counts of cells equal to the pivot (for the ordered compaction).
+// Ties at the pivot: the first need_eq of them in position order are wanted,
+// i.e. those before some position.  Level 0 counts them over 2048 bins of all
+// positions, level 1 over bins of the one bin that holds the last wanted tie,
+// unless that bin fits the output as it is.
+__global__ __launch_bounds__(kBlock) void k_select_ties(const uint64_t *__restrict__ P, int64_t n,
+                                                        int64_t cap, SelState *st,
+                                                        unsigned int *hist) {
+    if (st->need_eq == 0 || st->pos_limit > 0) return;
+    const uint64_t pivot = st->pivot;
+    const int64_t lo = st->tie_lo, hi = st->tie_hi;
+    const int64_t width = (hi - lo + kSelBins - 1) / kSelBins;
+    __shared__ unsigned int h[kSelBins];
+    for (int i = threadIdx.x; i < kSelBins; i += kBlock) h[i] = 0;
+    __syncthreads();
+    for (int64_t i = lo + (int64_t)blockIdx.x * kBlock + threadIdx.x; i < hi;
+         i += (int64_t)gridDim.x * kBlock)
+        if (P[i] == pivot) atomicAdd(&h[(i - lo) / width], 1u);
+    __syncthreads();
+    for (int i = threadIdx.x; i < kSelBins; i += kBlock)
+        if (h[i]) atomicAdd(&hist[i], h[i]);
+    if (!last_block(st)) return;
+    const SelPick pk = pick_bin(hist, kSelBins);
+    const int64_t need_eq = st->need_eq, below = st->below;
+    __syncthreads();
+    int bin;
+    unsigned int in_bin;
+    unsigned long long cum;
+    if (pk.holds((unsigned long long)need_eq, bin, cum, in_bin)) {
+        const int64_t b0 = lo + bin * width, b1 = min(b0 + width, n);
+        if (below + (int64_t)cum + (int64_t)in_bin <= cap) {
+            st->pos_limit = b1;
+        } else {
+            st->tie_lo = b0;
+            st->tie_hi = b1;
+            st->below = below + (int64_t)cum;
+            st->need_eq = need_eq - (int64_t)cum;
+        }
+    }
+    for (int i = threadIdx.x; i < kSelBins; i += kBlock) hist[i] = 0;
+}
+
+// The selected cells: those below the pivot and the ties before the position
+// limit (any order, one reservation per block).
 constexpr int kSelTile = kBlock * 16;
 
-__global__ __launch_bounds__(kBlock) void k_select_count(const uint64_t *__restrict__ P, int64_t n,
-                                                         const SelState *__restrict__ st,
-                                                         uint32_t *__restrict__ cnt) {
-    __shared__ uint32_t wc[kBlock / kWave];
+__global__ __launch_bounds__(kBlock) void k_select_emit(const uint64_t *__restrict__ P, int64_t n,
+                                                        SelState *__restrict__ st,
+                                                        uint32_t *__restrict__ sel,
+                                                        uint64_t *__restrict__ sel_val,
+                                                        uint32_t cap) {
+    __shared__ uint32_t found[kSelTile];
+    __shared__ uint32_t nfound, at;
     const uint64_t pivot = st->pivot;
-    int64_t base = (int64_t)blockIdx.x * kSelTile;
-    uint32_t c = 0;
-    for (int r = 0; r < 16; ++r) {
-        int64_t i = base + (int64_t)r * kBlock + threadIdx.x;
-        if (i < n && P[i] == pivot) ++c;
-    }
-    for (int off = kWave / 2; off > 0; off >>= 1) c += __shfl_xor(c, off, kWave);
-    if (lane_id() == 0) wc[threadIdx.x / kWave] = c;
+    const int64_t limit = st->need_eq > 0 ? st->pos_limit : 0;
+    const int64_t base = (int64_t)blockIdx.x * kSelTile;
+    if (pivot == 0 && base >= limit) return;               // nothing lies below 0
+    if (threadIdx.x == 0) nfound = 0;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t s = 0;
-        for (int k = 0; k < kBlock / kWave; ++k) s += wc[k];
-        cnt[blockIdx.x] = s;
+    uint64_t v[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int64_t i = base + (int64_t)r * kBlock + threadIdx.x;
+        v[r] = i < n ? P[i] : kInfBits;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int64_t i = base + (int64_t)r * kBlock + threadIdx.x;
+        if (v[r] < kInfBits && (v[r] < pivot || (v[r] == pivot && i < limit)))
+            found[atomicAdd(&nfound, 1u)] = (uint32_t)(r * kBlock + threadIdx.x);
+    }
+    __syncthreads();
+    const uint32_t nf = nfound;
+    if (nf == 0) return;
+    if (threadIdx.x == 0) at = atomicAdd(&st->nless, nf);
+    __syncthreads();
+    for (uint32_t x = threadIdx.x; x < nf; x += kBlock) {
+        const uint32_t p = at + x;
+        if (p < cap) {
+            const int64_t i = base + found[x];
+            sel[p] = (uint32_t)i;
+            sel_val[p] = P[i];
+        }
     }
 }
 
-// Cells below the pivot are appended (any order); cells equal to the pivot are
-// written in natural order up to `need` of them.
-__global__ __launch_bounds__(kBlock) void k_select_emit(const uint64_t *__restrict__ P, int64_t n,
-                                                        SelState *__restrict__ st,
-                                                        const uint32_t *__restrict__ off,
-                                                        uint32_t *__restrict__ less,
-                                                        uint64_t *__restrict__ less_val,
-                                                        uint32_t cap,
-                                                        uint32_t *__restrict__ eq) {
-    __shared__ uint32_t wc[kBlock / kWave];
-    const uint64_t pivot = st->pivot;
-    const uint32_t need = (uint32_t)st->need_eq;
-    uint32_t *nless = &st->nless;
-    int64_t base = (int64_t)blockIdx.x * kSelTile;
-    uint32_t run = off[blockIdx.x];
-    if (run >= need) {
-        // still emit the cells below the pivot
-        for (int r = 0; r < 16; ++r) {
-            int64_t i = base + (int64_t)r * kBlock + threadIdx.x;
-            if (i < n && P[i] < pivot) {
-                uint32_t p = atomicAdd(nless, 1u);
-                if (p < cap) {
-                    less[p] = (uint32_t)i;
-                    less_val[p] = P[i];
-                }
-            }
-        }
+// The greedy of Sec. 2 over the selected cells (one block): up to k times the
+// smallest (value, position) still in is accepted and every cell of its length
+// within m/2 of it goes.  Positions follow the (length, start) order.  Also
+// the cells of all selected positions when the host is to run the greedy
+// (k = 0: more than one block's registers hold).  The join's counts (when
+// given) travel with the state, which the host reads.
+constexpr int kGreedyThreads = 1024;
+
+// Smallest value over the wavefront, in every lane (all 64 lanes active), by
+// shifts within rows of 16 and row broadcasts.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, kCtrl, kRows, 0xF, false);
+}
+template <int kCtrl, int kRows>
+__device__ __forceinline__ void min_step(uint32_t &v) {
+    v = min(v, dpp_u32<kCtrl, kRows>(v));
+}
+template <int kCtrl, int kRows>
+__device__ __forceinline__ void min_step(unsigned long long &v) {
+    const unsigned long long o =
+        (unsigned long long)dpp_u32<kCtrl, kRows>((uint32_t)(v >> 32)) << 32 |
+        dpp_u32<kCtrl, kRows>((uint32_t)v);
+    v = o < v ? o : v;
+}
+template <typename T>
+__device__ __forceinline__ void wave_min_steps(T &v) {
+    min_step<0x111, 0xF>(v);
+    min_step<0x112, 0xF>(v);
+    min_step<0x114, 0xF>(v);
+    min_step<0x118, 0xF>(v);
+    min_step<0x142, 0xA>(v);
+    min_step<0x143, 0xC>(v);
+}
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
+    wave_min_steps(v);
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v) {
+    wave_min_steps(v);
+    return (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), 63) << 32 |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
+}
+
+constexpr int kGreedyPer = kGreedyMax / kGreedyThreads;
+
+__global__ __launch_bounds__(kGreedyThreads) void k_select_greedy(
+    SelState *__restrict__ st, const uint32_t *__restrict__ sel,
+    const uint64_t *__restrict__ sel_val, int64_t cap, const uint32_t *__restrict__ cell,
+    LenView lv, int k, uint32_t *__restrict__ sel_cell, SelCell *__restrict__ acc,
+    const unsigned long long *__restrict__ counts) {
+    __shared__ unsigned long long wv[2][kGreedyThreads / kWave];
+    __shared__ uint32_t wp[2][kGreedyThreads / kWave];
+    __shared__ int4 win[2];                                // cell, length index, m
+    __shared__ unsigned long long kept;
+    const int tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
+    if (tid == 0) kept = 0;
+    __syncthreads();
+    if (counts && tid < kCtrSlots) atomicAdd(&kept, counts[tid * kCtrStride]);
+    __syncthreads();
+    const int64_t nl = (int64_t)st->nless < cap ? (int64_t)st->nless : cap;
+    if (tid == 0) {
+        st->kept = kept;
+        st->nredo = counts ? (uint32_t)counts[kCtrSlots * kCtrStride] : 0u;
+        st->naccept = 0;
+    }
+    if (k == 0) {
+        for (int64_t x = tid; x < nl; x += kGreedyThreads) sel_cell[x] = cell[sel[x]];
         return;
     }
-    for (int r = 0; r < 16; ++r) {
-        int64_t i = base + (int64_t)r * kBlock + threadIdx.x;
-        const bool ok = i < n;
-        const uint64_t v = ok ? P[i] : kInfBits;
-        if (ok && v < pivot) {
-            uint32_t p = atomicAdd(nless, 1u);
-            if (p < cap) {
-                less[p] = (uint32_t)i;
-                less_val[p] = v;
+    // every entry with its cell and length, in registers
+    unsigned long long v[kGreedyPer];
+    uint32_t p[kGreedyPer], c[kGreedyPer];
+    int l[kGreedyPer];
+    const int nu = (int)((nl + kGreedyThreads - 1) / kGreedyThreads);     // entries per thread
+#pragma unroll
+    for (int u = 0; u < kGreedyPer; ++u) {
+        const int64_t x = (int64_t)u * kGreedyThreads + tid;
+        v[u] = ~0ull;                                      // none
+        p[u] = kNone;
+        c[u] = 0;
+        l[u] = -1;
+        if (x < nl) {
+            v[u] = sel_val[x];
+            p[u] = sel[x];
+            c[u] = cell[p[u]];
+            l[u] = lv.find((int64_t)c[u]);
+        }
+    }
+    for (int r = 0; r < k; ++r) {
+        unsigned long long bv = ~0ull;
+        uint32_t bp = kNone;
+#pragma unroll
+        for (int u = 0; u < kGreedyPer; ++u)
+            if (u < nu && (v[u] < bv || (v[u] == bv && p[u] < bp))) {
+                bv = v[u];
+                bp = p[u];
+            }
+        const unsigned long long mv = wave_min_u64(bv);
+        const uint32_t mp = wave_min_u32(bv == mv ? bp : kNone);
+        // (two sets of the wavefronts' results in turn: one barrier a round
+        // suffices for them)
+        if (lane == 0) {
+            wv[r & 1][w] = mv;
+            wp[r & 1][w] = mp;
+        }
+        __syncthreads();
+        const unsigned long long xv = lane < kGreedyThreads / kWave ? wv[r & 1][lane] : ~0ull;
+        bv = wave_min_u64(xv);
+        bp = wave_min_u32(lane < kGreedyThreads / kWave && xv == bv ? wp[r & 1][lane] : kNone);
+        if (bp == kNone) break;                            // (uniform) nothing is left
+        // the thread that holds the cell publishes it
+#pragma unroll
+        for (int u = 0; u < kGreedyPer; ++u)
+            if (u < nu && p[u] == bp) {
+                win[r & 1] = make_int4((int)c[u], l[u], lv.m(l[u]), 0);
+                acc[r] = SelCell{bv, bp, c[u]};
+                st->naccept = r + 1;
+            }
+        __syncthreads();
+        const int4 x = win[r & 1];
+#pragma unroll
+        for (int u = 0; u < kGreedyPer; ++u) {
+            const int64_t d = (int64_t)c[u] - (int64_t)(uint32_t)x.x;
+            if (u < nu && l[u] == x.y && 2 * (d < 0 ? -d : d) <= x.z) {
+                v[u] = ~0ull;
+                p[u] = kNone;
+                l[u] = -1;
             }
         }
-        const bool e = ok && v == pivot;
-        const uint64_t bal = __ballot(e);
-        if (lane_id() == 0) wc[threadIdx.x / kWave] = (uint32_t)__popcll(bal);
-        __syncthreads();
-        uint32_t pos = run + (uint32_t)__popcll(bal & lanemask_lt());
-        uint32_t tot = 0;
-        for (int k = 0; k < kBlock / kWave; ++k) {
-            if (k < (int)(threadIdx.x / kWave)) pos += wc[k];
-            tot += wc[k];
-        }
-        if (e && pos < need) eq[pos] = (uint32_t)i;
-        run += tot;
-        __syncthreads();
     }
 }
 
@@ -259,21 +431,6 @@ __global__ __launch_bounds__(kBlock) void k_rows(Req q, const RowReq *__restrict
         atomicMin(&out_min[blockIdx.y], best);
         if (arg != ~0ull) atomicMin(&out_arg[blockIdx.y], arg);
     }
-}
-
-// Cells of the selected positions: the first min(nless, cap) of `less` and
-// the first need_eq of `eq`.
-__global__ __launch_bounds__(kBlock) void k_select_cells(const uint32_t *__restrict__ cell,
-                                                         const SelState *__restrict__ st,
-                                                         const uint32_t *__restrict__ less,
-                                                         const uint32_t *__restrict__ eq,
-                                                         int64_t cap, uint32_t *__restrict__ less_cell,
-                                                         uint32_t *__restrict__ eq_cell) {
-    const int64_t x = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (x >= cap) return;
-    const int64_t nl = (int64_t)st->nless < cap ? (int64_t)st->nless : cap;
-    if (x < nl) less_cell[x] = cell[less[x]];
-    if (x < st->need_eq) eq_cell[x] = cell[eq[x]];
 }
 
 // out[x] = src[idx[x]]
@@ -328,32 +485,25 @@ static inline unsigned gridcap(int64_t n, int64_t cap) {
     return (unsigned)(b < cap ? b : cap);
 }
 
-int64_t select_blocks(int64_t n) { return (n + kSelTile - 1) / kSelTile; }
-
-void launch_select(const uint64_t *P, int64_t n, int64_t need, SelState *st,
-                   unsigned int *hist, uint32_t *cnt, uint32_t *scan_tmp, uint32_t *less,
-                   uint64_t *less_val, uint32_t *eq, uint32_t *less_cell, uint32_t *eq_cell,
-                   const uint32_t *cell, const unsigned long long *counts, hipStream_t s) {
+void launch_select(const Select &x, const uint64_t *P, int64_t n, const uint32_t *cell,
+                   const LenView &lv, const unsigned long long *counts, hipStream_t s) {
     static const int shifts[6] = {53, 42, 31, 20, 9, 0};
     static const int widths[6] = {11, 11, 11, 11, 11, 9};
-    hipLaunchKernelGGL(k_select_init, dim3(1), dim3(kBlock), 0, s, st, need, hist,
-                       counts);
     if (n <= 0) return;
-    for (int ps = 0; ps < 6; ++ps) {
-        hipLaunchKernelGGL(k_select_hist, dim3(gridcap(n, 4096)), dim3(kBlock), 0, s, P, n,
-                           shifts[ps], widths[ps], (const SelState *)st, hist);
-        hipLaunchKernelGGL(k_select_pick, dim3(1), dim3(kBlock), 0, s, hist, widths[ps], ps,
-                           ps == 5 ? 1 : 0, st);
-    }
-    const int64_t nsb = select_blocks(n);
-    hipLaunchKernelGGL(k_select_count, dim3((unsigned)nsb), dim3(kBlock), 0, s, P, n,
-                       (const SelState *)st, cnt);
-    scan_exclusive_u32(cnt, cnt, nsb, nullptr, scan_tmp, s);
-    hipLaunchKernelGGL(k_select_emit, dim3((unsigned)nsb), dim3(kBlock), 0, s, P, n, st,
-                       (const uint32_t *)cnt, less, less_val, (uint32_t)need, eq);
-    hipLaunchKernelGGL(k_select_cells, dim3(nblk(need)), dim3(kBlock), 0, s, cell,
-                       (const SelState *)st, (const uint32_t *)less, (const uint32_t *)eq, need,
-                       less_cell, eq_cell);
+    // (each block ends with a fence and a ticket: eight turns a thread at
+    // least, and no more blocks than fill the chip)
+    const unsigned nb = gridcap((n + 7) / 8, 1024);
+    for (int ps = 0; ps < 6; ++ps)
+        hipLaunchKernelGGL(k_select_hist, dim3(nb), dim3(kBlock), 0, s, P, n, shifts[ps], widths[ps],
+                           ps, ps == 5 ? 1 : 0, x.need, x.cap, x.st, x.hist);
+    for (int level = 0; level < 2; ++level)
+        hipLaunchKernelGGL(k_select_ties, dim3(level && nb > 32 ? 32u : nb), dim3(kBlock), 0, s,
+                           P, n, x.cap, x.st, x.hist);
+    hipLaunchKernelGGL(k_select_emit, dim3((unsigned)((n + kSelTile - 1) / kSelTile)), dim3(kBlock),
+                       0, s, P, n, x.st, x.sel, x.sel_val, (uint32_t)x.cap);
+    hipLaunchKernelGGL(k_select_greedy, dim3(1), dim3(kGreedyThreads), 0, s, x.st,
+                       (const uint32_t *)x.sel, (const uint64_t *)x.sel_val, x.cap, cell, lv,
+                       x.on_device() ? x.k : 0, x.sel_cell, x.acc, counts);
 }
 
 void launch_rows(const Req &q, const RowReq *rr, int nrows, int64_t maxN,

@@ -232,14 +232,63 @@ __device__ __forceinline__ float join_scale(int m) {
 constexpr int kSelBins = 2048;            // bins of one select pass (11 bits)
 struct SelState {
     uint64_t high;        // bits of the selected prefix so far
-    uint64_t pivot;       // FP64 bits of the boundary value (kInfBits: take all)
+    uint64_t pivot;       // cells below it are taken (kInfBits: every value)
     int64_t remaining;    // values still wanted at or below the prefix
-    int64_t need_eq;      // values equal to the pivot to take, in cell order
-    uint32_t nless;       // values below the pivot found by the emit pass
+    int64_t below;        // values known to lie below the pivot (or, with ties, before tie_lo)
+    int64_t need_eq;      // values equal to the pivot to take, in position order
+    int64_t tie_lo, tie_hi;   // positions among which the last of them lies
+    int64_t pos_limit;    // ties before this position are taken (0: not known yet)
+    uint32_t nless;       // cells found by the emit pass
     int32_t done;         // the pivot is known
-    uint64_t kept;        // the join's counts when the selection began: kept pairs,
+    uint64_t kept;        // the join's counts when the greedy ran: kept pairs,
     uint32_t nredo;       // overflowed blocks
-    uint32_t pad_;
+    uint32_t ticket;      // blocks of the running pass that have arrived (0 between passes)
+    int32_t naccept;      // cells accepted by the device's greedy
+    int32_t pad_;
+};
+// A selected cell: its value's bits, position and cell.
+struct SelCell {
+    uint64_t v;
+    uint32_t k, cell;
+};
+// Where the lengths' cells begin, for the greedy: first cell and window length
+// of each, read out of an array of any record type.
+struct LenView {
+    const char *base;     // record of length 0
+    int64_t stride;       // bytes from one record to the next
+    int32_t off_cell, off_m;   // offsets of the first cell (int64) and the length (int32)
+    int32_t L;
+    __device__ __forceinline__ int64_t cell0(int l) const {
+        return *(const int64_t *)(base + l * stride + off_cell);
+    }
+    __device__ __forceinline__ int m(int l) const {
+        return *(const int32_t *)(base + l * stride + off_m);
+    }
+    __device__ __forceinline__ int find(int64_t cell) const {
+        int lo = 0, hi = L - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (cell0(mid) <= cell) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    }
+};
+// One selection's buffers.  The greedy runs on the device while the selected
+// cells fit one block's registers and k rounds of it are short against a copy
+// and a sort on the host (about 1 us each); otherwise the host reads all of
+// them.
+constexpr int kGreedyMax = 16384;         // selected cells the device's greedy holds
+constexpr int kGreedyRounds = 128;
+constexpr int64_t kSelSlack = 2048;       // cells beyond `need` that the select may take
+struct Select {
+    SelState *st;
+    SelCell *acc;         // [k] accepted cells (device greedy)
+    uint64_t *sel_val;    // [cap] selected cells: value bits, position, cell
+    uint32_t *sel, *sel_cell;
+    unsigned int *hist;   // [kSelBins], zero between selections (as st->ticket)
+    int64_t need, cap;
+    int k;
+    bool on_device() const { return cap <= kGreedyMax && k <= kGreedyRounds; }
 };
 
 struct RowReq {
@@ -673,16 +722,13 @@ void launch_sieve_verify(int precision, const Req &q, const uint32_t *bstart, co
 void launch_complete(int precision, const Req &q, const uint32_t *seeds, int nseeds, int dm,
                      int dp, hipStream_t s);
 // (k_certify.hip)
-int64_t select_blocks(int64_t n);
-// The first `need` values of P in (value, position) order: positions below the
-// pivot go to less (unordered, with their values in less_val), positions
-// equal to it to eq (position order); less_cell / eq_cell hold cell[position].
-// Everything runs on the stream; st holds the counts when the stream reaches
-// the end, with the join's two counts (null: none) as they were at the start.
-void launch_select(const uint64_t *P, int64_t n, int64_t need, SelState *st,
-                   unsigned int *hist, uint32_t *cnt, uint32_t *scan_tmp, uint32_t *less,
-                   uint64_t *less_val, uint32_t *eq, uint32_t *less_cell, uint32_t *eq_cell,
-                   const uint32_t *cell, const unsigned long long *counts, hipStream_t s);
+// The first `need` values of P[0 .. n) in (value, position) order (perhaps a
+// few more, st->nless of them, unordered in sel / sel_val), then the greedy over
+// them, or with on_device() false the cells of all of them.  Everything runs on
+// the stream; the state holds the counts when the stream reaches the end, with
+// the join's counts (null: none).
+void launch_select(const Select &x, const uint64_t *P, int64_t n, const uint32_t *cell,
+                   const LenView &lv, const unsigned long long *counts, hipStream_t s);
 // (k_join.hip)
 size_t join_cov_doubles(int L);
 // principal directions: covariance of a sample, then power iteration (GPU)

@@ -8,6 +8,8 @@
 #include "pmp_dev.h"
 
 #include <cstddef>
+#include <functional>
+#include <vector>
 #include <cstdint>
 
 namespace pmp {
@@ -63,7 +65,18 @@ int kprime_of(int K, int m);
 // indices.
 int64_t need_select(int k, int m_max);
 constexpr size_t kSelHead = 256;          // SelState, padded
-size_t select_block_bytes(int64_t need);
+size_t select_block_bytes(int64_t need, int k);
+// A selection's buffers laid out in one block: state, accepted cells, then the
+// selected cells.
+Select select_buffers(char *blk, unsigned int *hist, int64_t need, int k);
+// Bytes of the block that the host reads back.
+size_t select_read_bytes(const Select &x);
+// The accepted cells in order (val, position k, cell), from the block as read
+// back; length_of gives a cell's length index, m_of its window length.
+// PMP_EINTERNAL when the selection did not settle.
+int select_result(const Select &x, const char *host, SelState &st, std::vector<SelCell> &out,
+                  const std::function<int(uint32_t)> &length_of,
+                  const std::function<int(int)> &m_of);
 
 }  // namespace pmp
 

@@ -438,29 +438,81 @@ struct Bufs {
     int16_t *x16;              // the exact stage's prefilter (Quant)
     unsigned long long *xmm;
     float4 *xw;
-    uint32_t *sel_cnt;
-    // the selection's results, one contiguous block read back at once:
-    // state, then less_val, less_k, less_cell, eq_k, eq_cell (need each)
+    // the selection: one contiguous block, of which the host reads the front
     char *selblk;
-    SelState *sel;
-    uint64_t *less_val;
-    uint32_t *less_k, *less_cell, *eq_k, *eq_cell;
+    Select sel;
 };
 
 int64_t need_select(int k, int m_max) { return (int64_t)k * (m_max + 1); }
-size_t select_block_bytes(int64_t need) { return kSelHead + (size_t)need * 24; }
+size_t select_block_bytes(int64_t need, int k) {
+    return kSelHead + (size_t)k * sizeof(SelCell) + (size_t)(need + kSelSlack) * 16;
+}
+Select select_buffers(char *blk, unsigned int *hist, int64_t need, int k) {
+    Select x{};
+    x.need = need;
+    x.cap = need + kSelSlack;
+    x.k = k;
+    x.hist = hist;
+    x.st = (SelState *)blk;
+    x.acc = (SelCell *)(blk + kSelHead);
+    x.sel_val = (uint64_t *)(x.acc + k);
+    x.sel = (uint32_t *)(x.sel_val + x.cap);
+    x.sel_cell = x.sel + x.cap;
+    return x;
+}
+size_t select_read_bytes(const Select &x) {
+    return x.on_device() ? kSelHead + (size_t)x.k * sizeof(SelCell) : select_block_bytes(x.need, x.k);
+}
+int select_result(const Select &x, const char *host, SelState &st, std::vector<SelCell> &out,
+                  const std::function<int(uint32_t)> &length_of,
+                  const std::function<int(int)> &m_of) {
+    out.clear();
+    memcpy(&st, host, sizeof(st));
+    if (!st.done) return fail(PMP_EINTERNAL, "selection did not settle");
+    if ((int64_t)st.nless > x.cap) return fail(PMP_EINTERNAL, "selection overflow");
+    const SelCell *acc = (const SelCell *)(host + kSelHead);
+    if (x.on_device()) {
+        out.assign(acc, acc + st.naccept);
+        return PMP_OK;
+    }
+    const uint64_t *lv = (const uint64_t *)(acc + x.k);
+    const uint32_t *lk = (const uint32_t *)(lv + x.cap);
+    const uint32_t *lc = lk + x.cap;
+    // position order is the (length, start) order; non-negative doubles order
+    // like their bits
+    std::vector<SelCell> c(st.nless);
+    for (uint32_t y = 0; y < st.nless; ++y) c[y] = {lv[y], lk[y], lc[y]};
+    std::sort(c.begin(), c.end(), [](const SelCell &a, const SelCell &b) {
+        return a.v != b.v ? a.v < b.v : a.k < b.k;
+    });
+    // greedy (Sec. 2): skip a cell within m/2 of an accepted cell of its length
+    std::vector<int> ls;
+    for (const SelCell &y : c) {
+        const int l = length_of(y.cell), m = m_of(l);
+        bool skip = false;
+        for (size_t a = 0; a < out.size() && !skip; ++a)
+            skip = ls[a] == l && 2 * std::llabs((int64_t)out[a].cell - (int64_t)y.cell) <= m;
+        if (skip) continue;
+        out.push_back(y);
+        ls.push_back(l);
+        if ((int)out.size() == x.k) break;
+    }
+    return PMP_OK;
+}
 
 static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
     b.len = take<LenInfo>(a, p.L);
     b.flags = take<uint32_t>(a, p.n + 1);
     b.E = take<uint32_t>(a, p.n + 1);
     b.tile_off = take<uint32_t>(a, p.ntiles + 1);
-    // the scans run over n + 1 change points, the tiles, the selection's
-    // blocks and the sieve's buckets (at most 2 W + 1 per length)
+    // the scans run over n + 1 change points, the tiles and the sieve's
+    // buckets (at most 2 W + 1 per length)
     b.scan_tmp = (uint32_t *)a.take(scan_temp_bytes(std::max<int64_t>(
-        {p.n + 1, p.ntiles + 1, select_blocks(p.cells) + 1, 2 * p.cells + p.L + 1})));
+        {p.n + 1, p.ntiles + 1, 2 * p.cells + p.L + 1})));
     b.bad = take<int>(a, 1);
-    b.counters = take<unsigned long long>(a, kCtrSlots * kCtrStride);
+    // (the counters, then the selection's histogram: cleared together)
+    b.counters = take<unsigned long long>(a, kCtrSlots * kCtrStride + kSelBins / 2);
+    b.hist = (unsigned int *)(b.counters + kCtrSlots * kCtrStride);
     b.emax = take<float>(a, 2 * p.L);        // then the join operands' (jemax)
     b.gproj = take<float>(a, (int64_t)p.L * kMaxBits * kFD);
     b.cov = take<double>(a, (int64_t)join_cov_doubles(p.L));
@@ -474,7 +526,6 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
         b.bl = take<uint16_t>(a, ne);
     }
     b.gl = take<GridLen>(a, p.L);
-    b.hist = take<unsigned int>(a, kSelBins);
     b.rows = take<RowReq>(a, k);
     b.row_min = take<unsigned long long>(a, k);
     b.row_arg = take<unsigned long long>(a, k);
@@ -536,14 +587,8 @@ static void carve2(Arena &a, Bufs &b, const Plan &p, const Opt &o, int k) {
     // the segments' pair counts, the number of overflowed blocks, nonq (u32 per length)
     b.jcount = take<unsigned long long>(a, kJoinCounts + (p.L + 1) / 2);
     b.jredo = take<uint32_t>(a, 2 * join_blocks_max(N, p.L));
-    b.sel_cnt = take<uint32_t>(a, select_blocks(N) + 1);
-    b.selblk = (char *)a.take(select_block_bytes(need));
-    b.sel = (SelState *)b.selblk;
-    b.less_val = (uint64_t *)(b.selblk + kSelHead);
-    b.less_k = (uint32_t *)(b.less_val + need);
-    b.less_cell = b.less_k + need;
-    b.eq_k = b.less_cell + need;
-    b.eq_cell = b.eq_k + need;
+    b.selblk = (char *)a.take(select_block_bytes(need, k));
+    b.sel = select_buffers(b.selblk, b.hist, need, k);
     b.kmap = needs_kmap(o) ? take<uint32_t>(a, p.cells) : nullptr;
     b.hint = take<uint32_t>(a, N);
     b.scnt = o.sieve_w > 0 ? take<uint32_t>(a, p.nbuckets + 1) : nullptr;
@@ -559,12 +604,6 @@ struct Cand {
     uint32_t k;
 };
 
-static bool cand_less(const Cand &a, const Cand &b, const Plan &p) {
-    if (a.d != b.d) return a.d < b.d;
-    if (p.ms[a.l] != p.ms[b.l]) return p.ms[a.l] < p.ms[b.l];
-    return a.i < b.i;
-}
-
 static int len_of_cell(const Plan &p, int64_t cell) {
     int lo = 0, hi = p.L - 1;
     while (lo < hi) {
@@ -574,69 +613,43 @@ static int len_of_cell(const Plan &p, int64_t cell) {
     return lo;
 }
 
-// The first `need` cells of the (P, m, i) order, sorted, then the greedy of
-// Sec. 2 over them.  P is indexed by k, whose order is the (m, i) order of the
-// non-constant windows; constant windows have no cell value.
-// The selection runs on the device (launch_select); one read-back brings the
-// state and the selected positions, values and cells, after any copies the
-// caller has already enqueued on the stream (they complete with the same
-// synchronization).
-// `counts` (when given) receives the join's kept pairs and overflowed blocks.
+// The greedy of Sec. 2 over the upper profile: P is indexed by k, whose order
+// is the (m, i) order of the non-constant windows; constant windows have no
+// cell value.  The selection runs on the device (launch_select); one read-back
+// brings the accepted cells, after any copies the caller has already enqueued
+// on the stream (they complete with the same synchronization).  `counts` (when
+// given) receives the join's kept pairs and overflowed blocks.  Only the first n
+// positions are looked at (0: all), for callers that know that no cell after
+// them can be accepted.
 struct JoinCounts {
     unsigned long long kept;
     uint32_t nredo, pad;
 };
 static int select_topk(const Plan &p, Bufs &b, int k, hipStream_t s, std::vector<Cand> &accepted,
-                       JoinCounts *counts = nullptr) {
+                       int64_t n = 0, JoinCounts *counts = nullptr) {
     accepted.clear();
-    const int64_t N = p.N;
-    const int64_t need_all = need_select(k, p.max_m);
-    if (N == 0) {
+    if (p.N == 0) {
         HIPCHK(hipStreamSynchronize(s));
         return PMP_OK;
     }
-    launch_select(b.P, N, need_all, b.sel, b.hist, b.sel_cnt, b.scan_tmp, b.less_k, b.less_val,
-                  b.eq_k, b.less_cell, b.eq_cell, b.cell, counts ? b.jcount : nullptr, s);
-    std::vector<char> host(select_block_bytes(need_all));
+    const LenView lv{(const char *)b.len, (int64_t)sizeof(LenInfo),
+                     (int32_t)offsetof(LenInfo, cell_base), (int32_t)offsetof(LenInfo, m), p.L};
+    launch_select(b.sel, b.P, n > 0 ? n : p.N, b.cell, lv, counts ? b.jcount : nullptr, s);
+    std::vector<char> host(select_read_bytes(b.sel));
     HIPCHK(hipMemcpyAsync(host.data(), b.selblk, host.size(), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     SelState st;
-    memcpy(&st, host.data(), sizeof(st));
+    std::vector<SelCell> acc;
+    const int rc = select_result(b.sel, host.data(), st, acc,
+                                 [&](uint32_t c) { return len_of_cell(p, c); },
+                                 [&](int l) { return p.ms[l]; });
     if (counts) *counts = {st.kept, st.nredo, 0u};
-    if (!st.done) return fail(PMP_EINTERNAL, "selection did not settle");
-    if (st.nless > (uint32_t)need_all) return fail(PMP_EINTERNAL, "selection overflow");
-    const uint32_t nless = st.nless;
-    const int64_t need_eq = st.need_eq;
-    const uint64_t pivot = st.pivot;
-    const uint64_t *lv = (const uint64_t *)(host.data() + kSelHead);
-    const uint32_t *lk = (const uint32_t *)(lv + need_all);
-    const uint32_t *lc = lk + need_all;
-    const uint32_t *ek = lc + need_all;
-    const uint32_t *ec = ek + need_all;
-    std::vector<Cand> c;
-    c.reserve(nless + need_eq);
-    for (uint32_t x = 0; x < nless; ++x) {
+    if (rc) return rc;
+    for (const SelCell &c : acc) {
         double d;
-        memcpy(&d, &lv[x], 8);
-        const int l = len_of_cell(p, lc[x]);
-        c.push_back({d, l, (int64_t)lc[x] - p.len[l].cell_base, lk[x]});
-    }
-    std::sort(c.begin(), c.end(), [&](const Cand &a, const Cand &bb) { return cand_less(a, bb, p); });
-    double pv;
-    memcpy(&pv, &pivot, 8);
-    for (int64_t x = 0; x < need_eq; ++x) {
-        const int l = len_of_cell(p, ec[x]);
-        c.push_back({pv, l, (int64_t)ec[x] - p.len[l].cell_base, ek[x]});
-    }
-    // greedy (Sec. 2): skip a cell within m/2 of an accepted cell of its length
-    for (const Cand &x : c) {
-        const int m = p.ms[x.l];
-        bool skip = false;
-        for (const Cand &a : accepted)
-            if (a.l == x.l && 2 * std::llabs(a.i - x.i) <= m) { skip = true; break; }
-        if (skip) continue;
-        accepted.push_back(x);
-        if ((int)accepted.size() == k) break;
+        memcpy(&d, &c.v, 8);
+        const int l = len_of_cell(p, c.cell);
+        accepted.push_back({d, l, (int64_t)c.cell - p.len[l].cell_base, c.k});
     }
     return PMP_OK;
 }
@@ -953,7 +966,8 @@ static int run_pipeline(Run &R, Arena &ar) {
     const std::vector<LenInfo> len_host = p.len;
     HIPCHK(hipMemcpyAsync(b.len, len_host.data(), p.L * sizeof(LenInfo), hipMemcpyHostToDevice, s));
     launch_fill_u32((uint32_t *)b.emax, 2 * p.L, 0u, s);
-    launch_fill_u64((uint64_t *)b.counters, kCtrSlots * kCtrStride, 0ull, s);
+    launch_fill_u64((uint64_t *)b.counters, kCtrSlots * kCtrStride + kSelBins / 2, 0ull, s);
+    launch_fill_u64((uint64_t *)b.sel.st, sizeof(SelState) / 8, 0ull, s);
 
     Req q{};
     q.t = R.t;
@@ -1049,7 +1063,8 @@ static int run_pipeline(Run &R, Arena &ar) {
             HIPCHK(hipMemcpyAsync(&zeros, b.jcount, 8, hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
             if (zeros >= (unsigned long long)R.k) {
-                const int rc = select_topk(p, b, R.k, s, acc0);
+                // (no other length has a value yet)
+                const int rc = select_topk(p, b, R.k, s, acc0, p.len[0].n_index);
                 if (rc) return rc;
                 rest = !(acc0.size() == (size_t)R.k && acc0.back().d == 0.0);
                 have_acc0 = !rest;
@@ -1067,7 +1082,7 @@ static int run_pipeline(Run &R, Arena &ar) {
             qx = Quant{b.x16, quant_pitch(R.n), b.xmm, b.xw};
             launch_quant_series(R.t, R.n, qx, s);
             launch_quant_windows(q, 0, N, qx, s);
-            const int rc = select_topk(p, b, R.k, s, acc0);
+            const int rc = select_topk(p, b, R.k, s, acc0, p.len[0].n_index);
             if (rc) return rc;
             if (acc0.size() == (size_t)R.k && acc0.back().d > kEps0) cut = kProbeCut * acc0.back().d;
         }
@@ -1284,7 +1299,9 @@ static int run_pipeline(Run &R, Arena &ar) {
                         if (rc) return rc;
                     }
                 }
-                rc = select_topk(p, b, R.k, s, acc, &cnt);   // synchronizes: gl may be rewritten next
+                // (a k-th value of 0 keeps the answer within the round's
+                // lengths; synchronizes: gl may be rewritten next)
+                rc = select_topk(p, b, R.k, s, acc, Nq, &cnt);
                 if (rc) return rc;
                 const bool again = cnt.nredo > 0;
                 while (cnt.nredo > 0) {
@@ -1306,7 +1323,7 @@ static int run_pipeline(Run &R, Arena &ar) {
                     }
                 }
                 if (again) {
-                    rc = select_topk(p, b, R.k, s, acc);
+                    rc = select_topk(p, b, R.k, s, acc, Nq);
                     if (rc) return rc;
                 }
             }

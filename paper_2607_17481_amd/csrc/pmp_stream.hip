@@ -61,8 +61,7 @@ struct pmp_stream {
     // selection (one-pass top-k)
     char *selblk = nullptr;
     unsigned int *hist = nullptr;
-    uint32_t *sel_cnt = nullptr, *scan_tmp = nullptr;
-    int64_t need = 0;
+    Select sel{};
     // exact queries: workspace grown on demand
     void *ws = nullptr;
     size_t ws_bytes = 0;
@@ -313,7 +312,7 @@ int pmp_stream_create(int device, int64_t capacity, int32_t m_min, int32_t m_max
     s->E.assign((size_t)capacity + 1, 0u);
     s->listcap = std::max(1, na * batch);
     s->updcap = (uint32_t)std::min<int64_t>((int64_t)s->listcap * s->R, UINT32_MAX);
-    s->need = need_select(k, s->max_am);
+    const int64_t need = need_select(k, s->max_am);
 
 #define SCHK(x)            \
     do {                   \
@@ -354,10 +353,9 @@ int pmp_stream_create(int device, int64_t capacity, int32_t m_min, int32_t m_max
     SCHK(dalloc(s, &s->bmarg, (int64_t)s->listcap * kMaxBits));
     SCHK(dalloc(s, &s->upd, s->updcap));
     SCHK(dalloc(s, &s->nupd, 1));
-    SCHK(dalloc(s, &s->selblk, (int64_t)select_block_bytes(s->need)));
+    SCHK(dalloc(s, &s->selblk, (int64_t)select_block_bytes(need, k)));
     SCHK(dalloc(s, &s->hist, kSelBins));
-    SCHK(dalloc(s, &s->sel_cnt, select_blocks(cb) + 1));
-    SCHK(dalloc(s, &s->scan_tmp, (int64_t)scan_temp_bytes(select_blocks(cb) + 1) / 4 + 1));
+    s->sel = select_buffers(s->selblk, s->hist, need, k);
 #undef SCHK
     auto hchk = [&](hipError_t e, const char *what) {
         if (e == hipSuccess) return PMP_OK;
@@ -392,6 +390,8 @@ int pmp_stream_create(int device, int64_t capacity, int32_t m_min, int32_t m_max
     launch_fill_u64(s->P, cb, kInfBits, s->hs);
     launch_fill_u32((uint32_t *)s->I, cb, 0xFFFFFFFFu, s->hs);
     launch_fill_u32(s->nupd, 1, 0u, s->hs);
+    launch_fill_u32(s->hist, kSelBins, 0u, s->hs);
+    launch_fill_u64((uint64_t *)s->sel.st, sizeof(SelState) / 8, 0ull, s->hs);
     launch_fill_u64((uint64_t *)s->counters, kStreamCounters, 0ull, s->hs);
     launch_iota_u32(s->cellid, cb, s->hs);
     if ((rc = hchk(hipGetLastError(), "launch"))) return rc;
@@ -434,69 +434,35 @@ int pmp_stream_topk(pmp_stream *s, pmp_motif *out, int32_t *n_out) {
     if (!s || !out || !n_out) return fail(PMP_EINVAL, "bad arguments");
     HIPCHK(hipSetDevice(s->device));
     *n_out = 0;
-    const int64_t need = s->need;
-    SelState *sel = (SelState *)s->selblk;
-    uint64_t *less_val = (uint64_t *)(s->selblk + kSelHead);
-    uint32_t *less_k = (uint32_t *)(less_val + need);
-    uint32_t *less_cell = less_k + need;
-    uint32_t *eq_k = less_cell + need;
-    uint32_t *eq_cell = eq_k + need;
-    launch_select(s->P, s->cells, need, sel, s->hist, s->sel_cnt, s->scan_tmp, less_k, less_val,
-                  eq_k, less_cell, eq_cell, s->cellid, nullptr, s->hs);
+    const LenView lv{(const char *)s->d_anc, (int64_t)sizeof(SAnchor),
+                     (int32_t)offsetof(SAnchor, cbase), (int32_t)offsetof(SAnchor, m),
+                     (int32_t)s->anc.size()};
+    launch_select(s->sel, s->P, s->cells, s->cellid, lv, nullptr, s->hs);
     HIPCHK(hipGetLastError());
-    std::vector<char> host(select_block_bytes(need));
+    std::vector<char> host(select_read_bytes(s->sel));
     HIPCHK(hipMemcpyAsync(host.data(), s->selblk, host.size(), hipMemcpyDeviceToHost, s->hs));
     HIPCHK(hipStreamSynchronize(s->hs));
-    SelState st;
-    std::memcpy(&st, host.data(), sizeof(st));
-    if (!st.done || st.nless > (uint32_t)need) return fail(PMP_EINTERNAL, "stream selection failed");
-    const uint64_t *lv = (const uint64_t *)(host.data() + kSelHead);
-    const uint32_t *lc = (const uint32_t *)(lv + need) + need;
-    const uint32_t *ec = lc + 2 * need;
-    struct C {
-        double d;
-        int a;
-        int64_t q;
-    };
     auto anchor_of = [&](uint32_t cell) {
         int a = 0;
         while (a + 1 < (int)s->anc.size() && s->anc[a + 1].cbase <= (int64_t)cell) ++a;
         return a;
     };
-    std::vector<C> c;
-    for (uint32_t x = 0; x < st.nless; ++x) {
+    SelState st;
+    std::vector<SelCell> sel;
+    const int rc = select_result(s->sel, host.data(), st, sel, anchor_of,
+                                 [&](int a) { return s->anc[a].m; });
+    if (rc) return rc;
+    struct C {
         double d;
-        std::memcpy(&d, &lv[x], 8);
-        const int a = anchor_of(lc[x]);
-        c.push_back({d, a, (int64_t)lc[x] - s->anc[a].cbase});
-    }
-    // key (P, m, i): anchors are in ascending m and cells ascending within
-    std::sort(c.begin(), c.end(), [](const C &x, const C &y) {
-        if (x.d != y.d) return x.d < y.d;
-        if (x.a != y.a) return x.a < y.a;
-        return x.q < y.q;
-    });
-    if (st.pivot != kInfBits) {
-        double pv;
-        std::memcpy(&pv, &st.pivot, 8);
-        for (int64_t x = 0; x < st.need_eq; ++x) {
-            const int a = anchor_of(ec[x]);
-            c.push_back({pv, a, (int64_t)ec[x] - s->anc[a].cbase});
-        }
-    }
-    // greedy (Sec. 2): skip a cell within m/2 of an accepted cell of its length
+        int a;
+        int64_t q;
+    };
     std::vector<C> acc;
-    for (const C &x : c) {
-        if (!std::isfinite(x.d)) break;
-        bool skip = false;
-        for (const C &y : acc)
-            if (y.a == x.a && 2 * std::llabs(y.q - x.q) <= s->anc[x.a].m) {
-                skip = true;
-                break;
-            }
-        if (skip) continue;
-        acc.push_back(x);
-        if ((int)acc.size() == s->k) break;
+    for (const SelCell &x : sel) {
+        double d;
+        std::memcpy(&d, &x.v, 8);
+        const int a = anchor_of(x.cell);
+        acc.push_back({d, a, (int64_t)x.cell - s->anc[a].cbase});
     }
     for (size_t x = 0; x < acc.size(); ++x) {
         int32_t nb = -1;

@@ -76,3 +76,18 @@ def test_prefiltered_requests(gpu, ws, oracle, kind, prec, stride):  # noqa: F81
     assert st["indexed_cells"] > 1 << 20
     ok, msg = parity.check_topk(res, _LARGE_ROWS[ref], 20, oracle, t, excl=excl)
     assert ok, msg
+
+
+@pytest.mark.parametrize("lo,hi,k", [(8, 9, 1), (8, 9, 128), (8, 9, 129), (110, 111, 128),
+                                     (111, 112, 128)])
+@pytest.mark.parametrize("kind", ["walk", "tied", "short"])
+def test_selection_forms(gpu, ws, oracle, kind, lo, hi, k):  # noqa: F811
+    """The greedy on the device and, for more than 128 motifs or 14336 cells, on
+    the host; distances that differ, that fall on a few equal values (a series
+    of two levels) and fewer cells than motifs."""
+    rng = np.random.default_rng(k + hi)
+    n = 3000 if kind != "short" else 2 * hi
+    t = np.cumsum(rng.standard_normal(n))
+    if kind == "tied":
+        t = np.sign(rng.standard_normal(n))
+    check(gpu, ws, oracle, t, lo, hi, 5, k=k)
