@@ -219,12 +219,11 @@ __global__ __launch_bounds__(kBlock) void k_select_ties(const uint64_t *__restri
 constexpr int kSelTile = kBlock * 16;
 
 __global__ __launch_bounds__(kBlock) void k_select_emit(const uint64_t *__restrict__ P, int64_t n,
-                                                        SelState *__restrict__ st,
-                                                        uint32_t *__restrict__ sel,
-                                                        uint64_t *__restrict__ sel_val,
-                                                        uint32_t cap) {
+                                                        const uint32_t *__restrict__ cell,
+                                                        LenView lv, Select out) {
     __shared__ uint32_t found[kSelTile];
     __shared__ uint32_t nfound, at;
+    SelState *st = out.st;
     const uint64_t pivot = st->pivot;
     const int64_t limit = st->need_eq > 0 ? st->pos_limit : 0;
     const int64_t base = (int64_t)blockIdx.x * kSelTile;
@@ -250,20 +249,23 @@ __global__ __launch_bounds__(kBlock) void k_select_emit(const uint64_t *__restri
     __syncthreads();
     for (uint32_t x = threadIdx.x; x < nf; x += kBlock) {
         const uint32_t p = at + x;
-        if (p < cap) {
+        if ((int64_t)p < out.cap) {
             const int64_t i = base + found[x];
-            sel[p] = (uint32_t)i;
-            sel_val[p] = P[i];
+            const uint32_t c = cell[i];
+            const int l = lv.find((int64_t)c);
+            out.sel[p] = (uint32_t)i;
+            out.sel_val[p] = P[i];
+            out.sel_cell[p] = c;
+            out.sel_len[p] = make_int2(l, lv.m(l));
         }
     }
 }
 
 // The greedy of Sec. 2 over the selected cells (one block): up to k times the
 // smallest (value, position) still in is accepted and every cell of its length
-// within m/2 of it goes.  Positions follow the (length, start) order.  Also
-// the cells of all selected positions when the host is to run the greedy
-// (k = 0: more than one block's registers hold).  The join's counts (when
-// given) travel with the state, which the host reads.
+// within m/2 of it goes.  Positions follow the (length, start) order.  k = 0:
+// the host runs the greedy (more than one block's registers hold).  The join's
+// counts (when given) travel with the state, which the host reads.
 constexpr int kGreedyThreads = 1024;
 
 // Smallest value over the wavefront, in every lane (all 64 lanes active), by
@@ -305,33 +307,28 @@ __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v)
 constexpr int kGreedyPer = kGreedyMax / kGreedyThreads;
 
 __global__ __launch_bounds__(kGreedyThreads) void k_select_greedy(
-    SelState *__restrict__ st, const uint32_t *__restrict__ sel,
-    const uint64_t *__restrict__ sel_val, int64_t cap, const uint32_t *__restrict__ cell,
-    LenView lv, int k, uint32_t *__restrict__ sel_cell, SelCell *__restrict__ acc,
-    const unsigned long long *__restrict__ counts) {
+    Select in, int k, SelCell *__restrict__ acc, const unsigned long long *__restrict__ counts) {
     __shared__ unsigned long long wv[2][kGreedyThreads / kWave];
     __shared__ uint32_t wp[2][kGreedyThreads / kWave];
     __shared__ int4 win[2];                                // cell, length index, m
     __shared__ unsigned long long kept;
     const int tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
+    SelState *st = in.st;
     if (tid == 0) kept = 0;
     __syncthreads();
     if (counts && tid < kCtrSlots) atomicAdd(&kept, counts[tid * kCtrStride]);
     __syncthreads();
-    const int64_t nl = (int64_t)st->nless < cap ? (int64_t)st->nless : cap;
+    const int64_t nl = (int64_t)st->nless < in.cap ? (int64_t)st->nless : in.cap;
     if (tid == 0) {
         st->kept = kept;
         st->nredo = counts ? (uint32_t)counts[kCtrSlots * kCtrStride] : 0u;
         st->naccept = 0;
     }
-    if (k == 0) {
-        for (int64_t x = tid; x < nl; x += kGreedyThreads) sel_cell[x] = cell[sel[x]];
-        return;
-    }
+    if (k == 0) return;
     // every entry with its cell and length, in registers
     unsigned long long v[kGreedyPer];
     uint32_t p[kGreedyPer], c[kGreedyPer];
-    int l[kGreedyPer];
+    int l[kGreedyPer], m[kGreedyPer];
     const int nu = (int)((nl + kGreedyThreads - 1) / kGreedyThreads);     // entries per thread
 #pragma unroll
     for (int u = 0; u < kGreedyPer; ++u) {
@@ -340,11 +337,14 @@ __global__ __launch_bounds__(kGreedyThreads) void k_select_greedy(
         p[u] = kNone;
         c[u] = 0;
         l[u] = -1;
+        m[u] = 0;
         if (x < nl) {
-            v[u] = sel_val[x];
-            p[u] = sel[x];
-            c[u] = cell[p[u]];
-            l[u] = lv.find((int64_t)c[u]);
+            v[u] = in.sel_val[x];
+            p[u] = in.sel[x];
+            c[u] = in.sel_cell[x];
+            const int2 lm = in.sel_len[x];
+            l[u] = lm.x;
+            m[u] = lm.y;
         }
     }
     for (int r = 0; r < k; ++r) {
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(kGreedyThreads) void k_select_greedy(
 #pragma unroll
         for (int u = 0; u < kGreedyPer; ++u)
             if (u < nu && p[u] == bp) {
-                win[r & 1] = make_int4((int)c[u], l[u], lv.m(l[u]), 0);
+                win[r & 1] = make_int4((int)c[u], l[u], m[u], 0);
                 acc[r] = SelCell{bv, bp, c[u]};
                 st->naccept = r + 1;
             }
@@ -433,16 +433,6 @@ __global__ __launch_bounds__(kBlock) void k_rows(Req q, const RowReq *__restrict
     }
 }
 
-// out[x] = src[idx[x]]
-__global__ __launch_bounds__(kBlock) void k_gather_u32(const uint32_t *__restrict__ src,
-                                                       const uint32_t *__restrict__ idx, int64_t n,
-                                                       uint32_t *__restrict__ out) {
-    const int64_t x = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (x < n) out[x] = src[idx[x]];
-}
-
-// ------------------------------------------------------------ utilities
-
 __global__ __launch_bounds__(kBlock) void k_fill_u64(uint64_t *__restrict__ p, int64_t n,
                                                      uint64_t v) {
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
@@ -500,10 +490,9 @@ void launch_select(const Select &x, const uint64_t *P, int64_t n, const uint32_t
         hipLaunchKernelGGL(k_select_ties, dim3(level && nb > 32 ? 32u : nb), dim3(kBlock), 0, s,
                            P, n, x.cap, x.st, x.hist);
     hipLaunchKernelGGL(k_select_emit, dim3((unsigned)((n + kSelTile - 1) / kSelTile)), dim3(kBlock),
-                       0, s, P, n, x.st, x.sel, x.sel_val, (uint32_t)x.cap);
-    hipLaunchKernelGGL(k_select_greedy, dim3(1), dim3(kGreedyThreads), 0, s, x.st,
-                       (const uint32_t *)x.sel, (const uint64_t *)x.sel_val, x.cap, cell, lv,
-                       x.on_device() ? x.k : 0, x.sel_cell, x.acc, counts);
+                       0, s, P, n, cell, lv, x);
+    hipLaunchKernelGGL(k_select_greedy, dim3(1), dim3(kGreedyThreads), 0, s, x,
+                       x.on_device() ? x.k : 0, x.acc, counts);
 }
 
 void launch_rows(const Req &q, const RowReq *rr, int nrows, int64_t maxN,
@@ -511,11 +500,6 @@ void launch_rows(const Req &q, const RowReq *rr, int nrows, int64_t maxN,
     if (nrows <= 0) return;
     hipLaunchKernelGGL(k_rows, dim3(gridcap(maxN, 1024), (unsigned)nrows), dim3(kBlock), 0, s,
                        q, rr, out_min, out_arg);
-}
-
-void launch_gather_u32(const uint32_t *src, const uint32_t *idx, int64_t n, uint32_t *out,
-                       hipStream_t s) {
-    if (n > 0) hipLaunchKernelGGL(k_gather_u32, dim3(nblk(n)), dim3(kBlock), 0, s, src, idx, n, out);
 }
 
 void launch_count_zero(const uint64_t *P, int64_t n, unsigned long long *out, hipStream_t s) {

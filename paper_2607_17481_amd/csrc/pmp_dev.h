@@ -283,8 +283,9 @@ constexpr int64_t kSelSlack = 2048;       // cells beyond `need` that the select
 struct Select {
     SelState *st;
     SelCell *acc;         // [k] accepted cells (device greedy)
-    uint64_t *sel_val;    // [cap] selected cells: value bits, position, cell
+    uint64_t *sel_val;    // [cap] selected cells: value bits, position, cell,
     uint32_t *sel, *sel_cell;
+    int2 *sel_len;        // index and window length of its length
     unsigned int *hist;   // [kSelBins], zero between selections (as st->ticket)
     int64_t need, cap;
     int k;
@@ -802,7 +803,5 @@ void launch_fill_u64(uint64_t *p, int64_t n, uint64_t v, hipStream_t s);
 // *out += the number of zeros among P[0 .. n)
 void launch_count_zero(const uint64_t *P, int64_t n, unsigned long long *out, hipStream_t s);
 void launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s);
-void launch_gather_u32(const uint32_t *src, const uint32_t *idx, int64_t n, uint32_t *out,
-                       hipStream_t s);
 
 }  // namespace pmp

@@ -445,7 +445,7 @@ struct Bufs {
 
 int64_t need_select(int k, int m_max) { return (int64_t)k * (m_max + 1); }
 size_t select_block_bytes(int64_t need, int k) {
-    return kSelHead + (size_t)k * sizeof(SelCell) + (size_t)(need + kSelSlack) * 16;
+    return kSelHead + (size_t)k * sizeof(SelCell) + (size_t)(need + kSelSlack) * 24;
 }
 Select select_buffers(char *blk, unsigned int *hist, int64_t need, int k) {
     Select x{};
@@ -458,10 +458,11 @@ Select select_buffers(char *blk, unsigned int *hist, int64_t need, int k) {
     x.sel_val = (uint64_t *)(x.acc + k);
     x.sel = (uint32_t *)(x.sel_val + x.cap);
     x.sel_cell = x.sel + x.cap;
+    x.sel_len = (int2 *)(x.sel_cell + x.cap);
     return x;
 }
 size_t select_read_bytes(const Select &x) {
-    return x.on_device() ? kSelHead + (size_t)x.k * sizeof(SelCell) : select_block_bytes(x.need, x.k);
+    return kSelHead + (size_t)x.k * sizeof(SelCell) + (x.on_device() ? 0 : (size_t)x.cap * 16);
 }
 int select_result(const Select &x, const char *host, SelState &st, std::vector<SelCell> &out,
                   const std::function<int(uint32_t)> &length_of,
