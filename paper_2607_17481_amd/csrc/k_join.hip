@@ -48,7 +48,10 @@ namespace {
 constexpr int kJT = kJoinTile;                // queries / candidates per tile
 constexpr int kQueueCap = 512;                // group hits buffered before they are resolved
 constexpr int kOutCap = 192;                  // kept pairs buffered before they are handed on
-constexpr int kCovSample = 1024;              // windows per length for the principal directions
+constexpr int kCovSample = 1024;              // windows per length for the directions
+constexpr int kCovRows = 72;                  // of them per block of k_join_cov
+constexpr int kCovParts = (kCovSample + kCovRows - 1) / kCovRows;
+constexpr int kCovLd = 32 + 528;              // one block's sums and products (a <= b)
 
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -107,24 +110,47 @@ __device__ __forceinline__ int wave_max_i(int v) {
 
 // ------------------------------------------------- principal directions
 
-// Mean and second moments of the FP32 feature copies over an even sample of
-// each length's windows: out[l] = {count, sum[32], sum of products [32 x 32]
-// (upper)}.
+// Sums and second moments of the FP32 feature copies over an even sample of
+// each length's windows, kCovRows windows a block: {sum[32], products[528]}, the
+// products a <= b row by row.  A length's blocks write their sums one after
+// the other from cov_base() on: a block's 4480 bytes lie in the 64 bytes that
+// each of its 72 windows has in the sorted operands (filled later), and one
+// block's more per length for the remainder.
+//
+// One block per length took 190 us whatever the request (1024 samples in turn,
+// five FP64 sums a thread); fifteen blocks take 15 us, and k_pca adds them up.
+__host__ __device__ inline int64_t cov_base(int64_t kbase, int l) {
+    return kbase * (int64_t)(kJoinOp * sizeof(uint4) / sizeof(double)) + (int64_t)l * kCovLd;
+}
+static_assert(kCovRows * kJoinOp * sizeof(uint4) >= kCovLd * sizeof(double), "block sums fit");
+
 template <typename FT>
 __global__ __launch_bounds__(kBlock) void k_join_cov(Req q, double *__restrict__ out) {
-    __shared__ float rows[64][2 * kMaxK + 1];
-    const int l = blockIdx.x;
-    const LenInfo L = q.len[l];
-    const int64_t n = L.n_index;
+    __shared__ float rows[kCovRows][2 * kMaxK + 1];
+    const int l = blockIdx.y, part = blockIdx.x;
+    const LenInfo &L = q.len[l];
+    const int64_t n = L.n_index, kbase = L.kbase;
     const int S = (int)min<int64_t>(n, kCovSample);
-    double *o = out + (int64_t)l * (1 + 32 + 32 * 32);
+    const int s0 = part * kCovRows, rn = min(kCovRows, S - s0);
+    if (rn <= 0) return;
+    double *o = out + cov_base(kbase, l) + (int64_t)part * kCovLd;
+    for (int x = threadIdx.x; x < kCovRows * 32; x += kBlock) {
+        const int r = x / 32, c = x % 32;
+        float v = 0.0f;
+        if (r < rn && c < 2 * (kMaxK - 1)) {
+            const int64_t k = kbase + (int64_t)(((double)(s0 + r) + 0.5) * (double)n / (double)S);
+            v = (float)((const FT *)q.F)[k * kRec + c];
+        }
+        rows[r][c] = v;
+    }
+    if (threadIdx.x < kCovRows) rows[threadIdx.x][32] = 1.0f;
     // thread -> pairs (a <= b < 32) of the upper triangle, or a sum entry
-    double acc[5] = {0, 0, 0, 0, 0};
-    int pa[5], pb[5];
+    double acc[3] = {0, 0, 0};
+    int pa[3], pb[3];
 #pragma unroll
-    for (int x = 0; x < 5; ++x) {
-        int p = threadIdx.x + x * kBlock;           // 0 .. 1279: 528 pairs, then 32 sums
-        pa[x] = -1;
+    for (int x = 0; x < 3; ++x) {
+        int p = threadIdx.x + x * kBlock;           // 528 pairs, then 32 sums
+        pa[x] = 0;
         pb[x] = -1;
         if (p < 528) {
             int a = 0;
@@ -136,101 +162,172 @@ __global__ __launch_bounds__(kBlock) void k_join_cov(Req q, double *__restrict__
             pb[x] = 32;                              // the sum entry
         }
     }
-    for (int s0 = 0; s0 < S; s0 += 64) {
-        __syncthreads();
-        for (int x = threadIdx.x; x < 64 * 32; x += kBlock) {
-            const int r = x / 32, c = x % 32;
-            float v = 0.0f;
-            if (s0 + r < S && c < 2 * (kMaxK - 1)) {
-                const int64_t k = L.kbase + (int64_t)(((double)(s0 + r) + 0.5) * (double)n / (double)S);
-                v = (float)((const FT *)q.F)[k * kRec + c];
-            }
-            rows[r][c] = v;
-        }
-        if (threadIdx.x < 64) rows[threadIdx.x][32] = 1.0f;
-        __syncthreads();
-        const int rn = min(64, S - s0);
-        for (int r = 0; r < rn; ++r) {
+    __syncthreads();
+    for (int r = 0; r < rn; ++r) {
 #pragma unroll
-            for (int x = 0; x < 5; ++x)
-                if (pa[x] >= 0) acc[x] = fma((double)rows[r][pa[x]], (double)rows[r][pb[x]], acc[x]);
-        }
+        for (int x = 0; x < 3; ++x)
+            acc[x] = fma((double)rows[r][pa[x]], (double)rows[r][max(pb[x], 0)], acc[x]);
     }
-    if (threadIdx.x == 0) o[0] = (double)S;
 #pragma unroll
-    for (int x = 0; x < 5; ++x) {
-        if (pa[x] < 0) continue;
-        if (pb[x] == 32) o[1 + pa[x]] = acc[x];
-        else o[33 + pa[x] * 32 + pb[x]] = acc[x];
+    for (int x = 0; x < 3; ++x) {
+        const int p = threadIdx.x + x * kBlock;
+        if (p < 528) o[32 + p] = acc[x];
+        else if (p < 528 + 32) o[p - 528] = acc[x];
     }
 }
 
 namespace {
+// Sum over the wavefront, in every lane (all 64 lanes active), by shifts within
+// rows of 16 and row broadcasts.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ void sum_step(double &v) {
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, kRows, 0xF, false);
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, kRows, 0xF, false);
+    v += __hiloint2double(hi, lo);
+}
 __device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-    return v;
+    sum_step<0x111, 0xF>(v);
+    sum_step<0x112, 0xF>(v);
+    sum_step<0x114, 0xF>(v);
+    sum_step<0x118, 0xF>(v);
+    sum_step<0x142, 0xA>(v);
+    sum_step<0x143, 0xC>(v);
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                            __builtin_amdgcn_readlane(__double2loint(v), 63));
 }
 }  // namespace
 
-// The kJoinDirs leading principal directions of each length's sample (power
-// iteration on the covariance, each deflated against the ones before), made
-// orthonormal in FP64; one wavefront per length, lane i holds component i.
-// Any orthonormal set keeps the threshold join exact; the leading directions
-// make its cells selective.  udir[l][v][0..31] (components 30, 31 are 0).
-__global__ __launch_bounds__(kWave) void k_pca(const double *__restrict__ cov, int L,
-                                               double *__restrict__ udir) {
+// The kJoinDirs leading principal directions of each length's sample, made
+// orthonormal in FP64; one block per length.  The covariance over its trace is
+// squared twice by the whole block, then one wavefront (lane i holds component
+// i of every direction) iterates all directions together, 16 products with the
+// fourth power, set apart after every second and made orthonormal at the end.  Any orthonormal set
+// keeps the threshold join exact; the leading directions make its cells
+// selective.  udir[l][v][0..31] (components 30, 31 are 0).
+//
+// A serial chain: 64 products per direction in turn, with sums over the
+// wavefront by general shuffles in each, took 180 us; this takes 55.
+__global__ __launch_bounds__(kBlock) void k_pca(Req q, const double *__restrict__ cov, int L,
+                                                double *__restrict__ udir) {
     constexpr int D = 2 * (kMaxK - 1);
-    __shared__ double C[D][D + 1];
-    __shared__ double xs[32];
+    __shared__ double A[2][D][D + 1];
+    __shared__ double sums[32];
+    __shared__ double xs[kJoinDirs][32];
+    __shared__ double trace;
     const int l = blockIdx.x;
     if (l >= L) return;
-    const int i = threadIdx.x;
-    const double *c = cov + (int64_t)l * (1 + 32 + 32 * 32);
-    const double S = c[0];
-    if (i < D)
-        for (int b = 0; b < D; ++b) {
-            const int lo = min(i, b), hi = max(i, b);
-            C[i][b] = S >= 2.0 ? c[33 + lo * 32 + hi] / S - (c[1 + i] / S) * (c[1 + b] / S) : 0.0;
-        }
+    const int tid = threadIdx.x;
+    const double *c = cov + cov_base(q.len[l].kbase, l);
+    const int n = (int)min<int64_t>(q.len[l].n_index, kCovSample);
+    const int parts = (n + kCovRows - 1) / kCovRows;
+    auto total = [&](int x) {
+        double v[kCovParts], s = 0.0;
+#pragma unroll
+        for (int p = 0; p < kCovParts; ++p) v[p] = p < parts ? c[p * kCovLd + x] : 0.0;
+#pragma unroll
+        for (int p = 0; p < kCovParts; ++p) s += v[p];
+        return s;
+    };
+    if (tid < 32) sums[tid] = total(tid);
     __syncthreads();
-    double u[kJoinDirs];
-    for (int v = 0; v < kJoinDirs; ++v) {
-        double x = i < D ? 1.0 + 0.37 * ((i * (v + 3)) % 7) - 0.5 * (i % (v + 2)) : 0.0;
-        // deflate against the directions before, then normalize
-        for (int w = 0; w < v; ++w) x -= wave_sum_d(x * u[w]) * u[w];
-        double nn = sqrt(wave_sum_d(x * x));
-        if (nn > 1e-300) {
-            x /= nn;
-            for (int it = 0; it < 64; ++it) {
-                __syncthreads();
-                if (i < 32) xs[i] = x;
-                __syncthreads();
-                double y = 0.0;
-                if (i < D)
-                    for (int j = 0; j < D; ++j) y = fma(C[i][j], xs[j], y);
-                for (int w = 0; w < v; ++w) y -= wave_sum_d(y * u[w]) * u[w];
-                const double ny = sqrt(wave_sum_d(y * y));
-                if (!(ny > 1e-300)) break;
-                x = y / ny;
-            }
-        }
-        // exact orthonormality against the ones before (twice, for
-        // rounding); a degenerate vector falls back to a unit vector
-        for (int e = 0;; ++e) {
-            for (int r = 0; r < 2; ++r)
-                for (int w = 0; w < v; ++w) x -= wave_sum_d(x * u[w]) * u[w];
-            const double nx = sqrt(wave_sum_d(x * x));
-            if (nx > 1e-300) { x /= nx; break; }
-            x = i == e ? 1.0 : 0.0;
-        }
-        for (int r = 0; r < 2; ++r) {
-            for (int w = 0; w < v; ++w) x -= wave_sum_d(x * u[w]) * u[w];
-            x /= sqrt(wave_sum_d(x * x));
-        }
-        u[v] = i < D ? x : 0.0;
-        if (i < 32) udir[((int64_t)l * kJoinDirs + v) * 32 + i] = u[v];
+    const double S = (double)n;
+    for (int x = tid; x < D * D; x += kBlock) {
+        const int i = x / D, b = x % D, lo = min(i, b), hi = max(i, b);
+        const double s = total(32 + lo * 32 - lo * (lo - 1) / 2 + hi - lo);
+        A[0][i][b] = n >= 2 ? s / S - (sums[i] / S) * (sums[b] / S) : 0.0;
     }
+    __syncthreads();
+    if (tid < kWave) {
+        const double t = wave_sum_d(tid < D ? A[0][tid][tid] : 0.0);
+        if (tid == 0) trace = t;
+    }
+    __syncthreads();
+    const double inv = trace > 1e-300 ? 1.0 / trace : 0.0;
+    for (int x = tid; x < D * D; x += kBlock) A[0][x / D][x % D] *= inv;
+    __syncthreads();
+    for (int sq = 0; sq < 2; ++sq) {
+        for (int x = tid; x < D * D; x += kBlock) {
+            const int i = x / D, b = x % D;
+            double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+            for (int j = 0; j < D; j += 2) {               // (symmetric: row b is column b)
+                s0 = fma(A[sq][i][j], A[sq][b][j], s0);
+                s1 = fma(A[sq][i][j + 1], A[sq][b][j + 1], s1);
+            }
+            A[sq ^ 1][i][b] = s0 + s1;
+        }
+        __syncthreads();
+    }
+    if (tid >= kWave) return;
+    // ---- one wavefront; A[0] holds the fourth power
+    const int i = tid;
+    double row[D];
+#pragma unroll
+    for (int j = 0; j < D; ++j) row[j] = i < D ? A[0][i][j] : 0.0;
+    double u[kJoinDirs];
+#pragma unroll
+    for (int v = 0; v < kJoinDirs; ++v)
+        u[v] = i < D ? 1.0 + 0.37 * ((i * (v + 3)) % 7) - 0.5 * (i % (v + 2)) : 0.0;
+    // each direction against the ones before (twice, for rounding), then to
+    // length 1; a degenerate one falls back to a unit vector
+    auto orthonormal = [&]() {
+#pragma unroll
+        for (int v = 0; v < kJoinDirs; ++v) {
+            double x = u[v];
+            for (int e = 0;; ++e) {
+                const double n0 = sqrt(wave_sum_d(x * x));
+                if (n0 > 1e-300) {
+                    x /= n0;
+#pragma unroll
+                    for (int w = 0; w < 2 * v; ++w) x -= wave_sum_d(x * u[w % v]) * u[w % v];
+                    // (what is left of a dependent vector is rounding)
+                    const double n1 = sqrt(wave_sum_d(x * x));
+                    if (n1 > 1e-12) { x /= n1; break; }
+                }
+                x = i == e ? 1.0 : 0.0;
+            }
+#pragma unroll
+            for (int w = 0; w < 2 * v; ++w) x -= wave_sum_d(x * u[w % v]) * u[w % v];
+            x /= sqrt(wave_sum_d(x * x));
+            u[v] = i < D ? x : 0.0;
+        }
+    };
+    // between the products: once against the ones before, and to length 1
+    // (what vanishes stays 0, for the last pass to replace)
+    auto separate = [&]() {
+#pragma unroll
+        for (int v = 0; v < kJoinDirs; ++v) {
+#pragma unroll
+            for (int w = 0; w < v; ++w) u[v] -= wave_sum_d(u[v] * u[w]) * u[w];
+            const double n2 = wave_sum_d(u[v] * u[v]);
+            u[v] = n2 > 1e-280 ? u[v] * rsqrt(n2) : 0.0;
+        }
+    };
+    separate();
+    for (int it = 0; it < 16; ++it) {
+        if (i < 32)
+#pragma unroll
+            for (int v = 0; v < kJoinDirs; ++v) xs[v][i] = u[v];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int v = 0; v < kJoinDirs; ++v) {
+            double y0 = 0.0, y1 = 0.0;
+#pragma unroll
+            for (int j = 0; j < D; j += 2) {
+                y0 = fma(row[j], xs[v][j], y0);
+                y1 = fma(row[j + 1], xs[v][j + 1], y1);
+            }
+            u[v] = y0 + y1;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (it & 1) separate();
+    }
+    orthonormal();
+    if (i < 32)
+#pragma unroll
+        for (int v = 0; v < kJoinDirs; ++v) udir[((int64_t)l * kJoinDirs + v) * 32 + i] = u[v];
 }
 
 // ------------------------------------------------------------ grid keys
@@ -972,16 +1069,16 @@ __global__ __launch_bounds__(kBlock) void k_join_verify_q(Req q, const GridLen *
 
 static inline unsigned nblk(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-size_t join_cov_doubles(int L) { return (size_t)L * (1 + 32 + 32 * 32); }
+size_t join_sorted_bytes(int64_t N, int L) { return (size_t)cov_base(N, L) * sizeof(double); }
 
 void launch_join_dirs(int precision, const Req &q, int nlen, double *cov, double *udir,
                       hipStream_t s) {
     if (nlen <= 0) return;
     if (precision == 0)
-        hipLaunchKernelGGL(k_join_cov<double>, dim3((unsigned)nlen), dim3(kBlock), 0, s, q, cov);
+        hipLaunchKernelGGL(k_join_cov<double>, dim3(kCovParts, (unsigned)nlen), dim3(kBlock), 0, s, q, cov);
     else
-        hipLaunchKernelGGL(k_join_cov<float>, dim3((unsigned)nlen), dim3(kBlock), 0, s, q, cov);
-    hipLaunchKernelGGL(k_pca, dim3((unsigned)nlen), dim3(kWave), 0, s, cov, nlen, udir);
+        hipLaunchKernelGGL(k_join_cov<float>, dim3(kCovParts, (unsigned)nlen), dim3(kBlock), 0, s, q, cov);
+    hipLaunchKernelGGL(k_pca, dim3((unsigned)nlen), dim3(kBlock), 0, s, q, cov, nlen, udir);
 }
 
 void launch_grid_keys(const Req &q, const GridLen *gl, int64_t N, int cb1, int cb2, int cb3,

@@ -731,7 +731,9 @@ void launch_complete(int precision, const Req &q, const uint32_t *seeds, int nse
 void launch_select(const Select &x, const uint64_t *P, int64_t n, const uint32_t *cell,
                    const LenView &lv, const unsigned long long *counts, hipStream_t s);
 // (k_join.hip)
-size_t join_cov_doubles(int L);
+// Bytes of the sorted operands of N windows of L lengths; the directions'
+// sample sums lie there before.
+size_t join_sorted_bytes(int64_t N, int L);
 // principal directions: covariance of a sample, then power iteration (GPU)
 // principal directions of the lengths [0, nlen) (the lengths whose records
 // exist)

@@ -516,7 +516,6 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
     b.hist = (unsigned int *)(b.counters + kCtrSlots * kCtrStride);
     b.emax = take<float>(a, 2 * p.L);        // then the join operands' (jemax)
     b.gproj = take<float>(a, (int64_t)p.L * kMaxBits * kFD);
-    b.cov = take<double>(a, (int64_t)join_cov_doubles(p.L));
     b.udir = take<double>(a, (int64_t)p.L * kJoinDirs * 32);
     {
         std::vector<int64_t> base;
@@ -575,7 +574,8 @@ static void carve2(Arena &a, Bufs &b, const Plan &p, const Opt &o, int k) {
     b.pcell = take<uint32_t>(a, N);
     b.bstart = take<uint32_t>(a, p.nbuckets + 1);
     b.sort_tmp = a.take(sort_temp_bytes(N));
-    b.jop_s = take<uint4>(a, N * kJoinOp);
+    b.jop_s = (uint4 *)a.take(join_sorted_bytes(N, p.L));
+    b.cov = (double *)b.jop_s;
     b.gp_s = take<float4>(a, N);
     b.gw_s = take<float>(a, N);
     b.jk = take<uint32_t>(a, N);
