@@ -10,6 +10,8 @@
 // directory sorted by window start.
 #include "pmp_dev.h"
 
+#include <algorithm>
+
 namespace pmp {
 
 namespace {
@@ -40,6 +42,46 @@ __device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *lds /* >= 4 */, u
     __syncthreads();
     excl = wbase + x - v;
     return total;
+}
+
+// The whole scan by one block, for inputs of a few thousand: one launch for
+// three.
+constexpr int64_t kScanOne = 16384;
+__global__ __launch_bounds__(1024) void k_scan_one(const uint32_t *in, uint32_t *out, int64_t n,
+                                                   uint32_t *__restrict__ total) {
+    __shared__ uint32_t lds[1024 / kWave];
+    const int lane = lane_id(), w = threadIdx.x / kWave;
+    constexpr int kPer = (int)(kScanOne / 1024);
+    // a contiguous share per thread
+    const int per = (int)((n + 1023) / 1024);
+    const int64_t base = (int64_t)threadIdx.x * per;
+    uint32_t v[kPer], s = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        v[k] = k < per && base + k < n ? in[base + k] : 0u;
+        s += v[k];
+    }
+    uint32_t x = s;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t y = __shfl_up(x, off, kWave);
+        if (lane >= off) x += y;
+    }
+    if (lane == kWave - 1) lds[w] = x;
+    __syncthreads();
+    uint32_t run = x - s, tot = 0;
+#pragma unroll
+    for (int i = 0; i < 1024 / kWave; ++i) {
+        const uint32_t y = lds[i];
+        if (i < w) run += y;
+        tot += y;
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        if (k < per && base + k < n) out[base + k] = run;
+        run += v[k];
+    }
+    if (threadIdx.x == 0 && total) *total = tot;
 }
 
 __global__ __launch_bounds__(kBlock) void k_scan_reduce(const uint32_t *__restrict__ in,
@@ -119,26 +161,40 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(const uint32_t *__restric
 
 constexpr int kSortRounds = 8;                       // items per thread
 constexpr int kSortTile = kBlock * kSortRounds;      // 2048 per tile
-constexpr int kSortSub = 4;                          // consecutive tiles per block
-constexpr int kSortChunk = kSortTile * kSortSub;     // keys per block
 constexpr int kRadix = 256;
 
+// Consecutive tiles per block: four amortize a block's counts over 8192 keys
+// once that fills the chip; below, one tile a block gives four times the
+// blocks (200,000 keys: 98 instead of 25, a pass 50 -> 19 us with the scan in
+// the histogram).
+constexpr int kSortSub = 4;
+constexpr int64_t kSortSmall = (int64_t)1 << 20;
+inline int sort_sub(int64_t n) { return n < kSortSmall ? 1 : kSortSub; }
+
+// Histograms of up to this many blocks are scanned by their own last block; more
+// by the three-kernel scan.
+constexpr int64_t kSortFused = 256;
+
+// Digit counts per block, for the block's `sub` tiles.  Fused form (ticket not
+// null): counts are laid out by block, and the last block to arrive turns them
+// into offsets; otherwise they are laid out by digit, for a scan of its own.
 __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t *__restrict__ keys,
-                                                       int64_t n, int shift, int nbits,
-                                                       uint32_t *__restrict__ counts,
-                                                       int64_t nblocks) {
+                                                       int64_t n, int shift, int nbits, int sub_n,
+                                                       uint32_t *counts,
+                                                       uint32_t *__restrict__ offs,
+                                                       int64_t nblocks, uint32_t *ticket) {
     __shared__ uint32_t h[kRadix];
     h[threadIdx.x] = 0;
     __syncthreads();
     const uint32_t mask = (1u << nbits) - 1u;
     const int lane = lane_id();
-    // the block's kSortSub tiles; wavefront w counts the slice [w, w + 1) *
-    // kSortTile / 4 of each.  Equal digits of a round are matched by ballots
+    // the block's tiles; wavefront w counts the slice [w, w + 1) * kSortTile /
+    // 4 of each.  Equal digits of a round are matched by ballots
     // (one per digit bit) and counted by one lane, so a tile whose keys share
     // a digit (as they do after the lower passes) costs one LDS atomic per
     // round, not 64
-    for (int sub = 0; sub < kSortSub; ++sub) {
-        const int64_t base = (int64_t)blockIdx.x * kSortChunk + (int64_t)sub * kSortTile +
+    for (int sub = 0; sub < sub_n; ++sub) {
+        const int64_t base = ((int64_t)blockIdx.x * sub_n + sub) * kSortTile +
                              (int64_t)(threadIdx.x / kWave) * (kSortTile / (kBlock / kWave));
         if (base >= n) break;
         uint32_t key[kSortRounds];
@@ -161,13 +217,38 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t *__restric
         }
     }
     __syncthreads();
-    // digit-major so that the exclusive scan gives each (digit, block) its
-    // first output position
-    counts[(int64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
+    if (!ticket) {
+        // digit-major so that the exclusive scan gives each (digit, block) its
+        // first output position
+        counts[(int64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
+        return;
+    }
+    counts[(int64_t)blockIdx.x * kRadix + threadIdx.x] = h[threadIdx.x];
+    __shared__ int last;
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    if (threadIdx.x == 0) *ticket = 0;
+    // thread d: the digit's total, the digits' exclusive scan, then the digit's
+    // first position in every block
+    uint32_t sum = 0;
+#pragma unroll 16
+    for (int64_t b = 0; b < nblocks; ++b) sum += counts[b * kRadix + threadIdx.x];
+    __shared__ uint32_t lds[kBlock / kWave];
+    uint32_t run;
+    block_exclusive_scan(sum, lds, run);
+#pragma unroll 16
+    for (int64_t b = 0; b < nblocks; ++b) {
+        const uint32_t v = counts[b * kRadix + threadIdx.x];
+        offs[b * kRadix + threadIdx.x] = run;
+        run += v;
+    }
 }
 
-// kSortSub consecutive tiles of kSortTile keys per block, in order; in each
-// tile wavefront w takes the contiguous slice [w, w + 1) * kSortTile / 4 in
+// sub_n consecutive tiles of kSortTile keys per block, in order; in each tile wavefront w takes the contiguous slice [w, w + 1) * kSortTile / 4 in
 // kSortRounds rounds of 64.  Pass 1 ranks each key among the equal digits of
 // its round (one ballot per digit bit) and counts each wavefront's digits;
 // after one block barrier every (wavefront, digit) knows its first output
@@ -178,16 +259,17 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t *__restric
 __global__ __launch_bounds__(kBlock) void k_radix_scatter(
     const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
     uint32_t *__restrict__ kout, uint32_t *__restrict__ vout, int64_t n, int shift, int nbits,
-    const uint32_t *__restrict__ offs, int64_t nblocks) {
+    int sub_n, const uint32_t *__restrict__ offs, int64_t nblocks, bool by_block) {
     constexpr int kW = kBlock / kWave;
     __shared__ uint32_t wcnt[kW][kRadix];
     const int lane = lane_id();
     const int w = threadIdx.x / kWave;
     const uint32_t mask = (1u << nbits) - 1u;
     // thread d: the next output position of digit d
-    uint32_t run = offs[(int64_t)threadIdx.x * nblocks + blockIdx.x];
-    for (int sub = 0; sub < kSortSub; ++sub) {
-        const int64_t tbase = (int64_t)blockIdx.x * kSortChunk + (int64_t)sub * kSortTile;
+    uint32_t run = by_block ? offs[(int64_t)blockIdx.x * kRadix + threadIdx.x]
+                            : offs[(int64_t)threadIdx.x * nblocks + blockIdx.x];
+    for (int sub = 0; sub < sub_n; ++sub) {
+        const int64_t tbase = ((int64_t)blockIdx.x * sub_n + sub) * kSortTile;
         if (tbase >= n) break;
         for (int q = 0; q < kW; ++q) wcnt[q][threadIdx.x] = 0;
         __syncthreads();
@@ -258,6 +340,10 @@ void scan_exclusive_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *
         if (total) launch_fill_u32(total, 1, 0u, s);
         return;
     }
+    if (n <= kScanOne) {
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(1024), 0, s, in, out, n, total);
+        return;
+    }
     int64_t nb = cdiv(n, kScanTile);
     uint32_t *sums = (uint32_t *)temp;
     hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kBlock), 0, s, in, n, sums);
@@ -267,15 +353,19 @@ void scan_exclusive_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *
 }
 
 size_t sort_temp_bytes(int64_t n) {
-    int64_t nb = cdiv(n, kSortChunk);
+    // (a smaller n in the same buffers may take more blocks, below kSortSmall)
+    int64_t nb = std::max(cdiv(n, (int64_t)kSortTile * sort_sub(n)),
+                          cdiv(std::min(n, kSortSmall), kSortTile));
     size_t counts = (size_t)(nb * kRadix) * sizeof(uint32_t);
     return 2 * counts + scan_temp_bytes(nb * kRadix) + 256;
 }
 
 int radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1, int64_t n,
-                     int lo, int hi, void *temp, hipStream_t s, bool copy_back) {
+                     int lo, int hi, void *temp, uint32_t *ticket, hipStream_t s, bool copy_back) {
     if (n <= 1 || hi <= lo) return 0;
-    int64_t nb = cdiv(n, kSortChunk);
+    const int sub = sort_sub(n);
+    int64_t nb = cdiv(n, (int64_t)kSortTile * sub);
+    const bool fused = nb <= kSortFused;
     uint32_t *counts = (uint32_t *)temp;
     uint32_t *offs = counts + nb * kRadix;
     void *stemp = (void *)(offs + nb * kRadix);
@@ -284,10 +374,10 @@ int radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1, int
     for (int shift = lo; shift < hi; shift += 8, ++passes) {
         int nbits = hi - shift < 8 ? hi - shift : 8;
         hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)nb), dim3(kBlock), 0, s, ka, n, shift,
-                           nbits, counts, nb);
-        scan_exclusive_u32(counts, offs, nb * kRadix, nullptr, stemp, s);
+                           nbits, sub, counts, offs, nb, fused ? ticket : nullptr);
+        if (!fused) scan_exclusive_u32(counts, offs, nb * kRadix, nullptr, stemp, s);
         hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)nb), dim3(kBlock), 0, s, ka, va, kb,
-                           vb, n, shift, nbits, (const uint32_t *)offs, nb);
+                           vb, n, shift, nbits, sub, (const uint32_t *)offs, nb, fused);
         uint32_t *t;
         t = ka; ka = kb; kb = t;
         t = va; va = vb; vb = t;

@@ -668,9 +668,10 @@ size_t sort_temp_bytes(int64_t n);
 // Stable LSD radix sort of (key, val) pairs on key bits [lo, hi).  Result in
 // (k0, v0), or, after an odd number of passes with copy_back false, in
 // (k1, v1): the return value is 1 then, 0 otherwise.  (k1, v1) are scratch
-// of the same size.
+// of the same size.  ticket: a word that is 0 before and after.
 int radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1, int64_t n,
-                     int lo, int hi, void *temp, hipStream_t s, bool copy_back = true);
+                     int lo, int hi, void *temp, uint32_t *ticket, hipStream_t s,
+                     bool copy_back = true);
 
 // (k_sketch.hip)
 void launch_changepoints(const double *t, int64_t n, uint32_t *flag, int *bad, hipStream_t s);

@@ -423,6 +423,7 @@ struct Bufs {
     float4 *gp;
     uint32_t *skey, *sval, *skey2, *sval2, *pcell, *bstart;
     void *sort_tmp;
+    uint32_t *sort_ticket;
     uint32_t *jk, *jv, *jk2, *jv2;
     uint4 *jop_s;              // join operands and coordinates in grid order
     float4 *gp_s;
@@ -442,6 +443,8 @@ struct Bufs {
     char *selblk;
     Select sel;
 };
+
+constexpr int kClearWords = kCtrSlots * kCtrStride + kSelBins / 2 + 1;
 
 int64_t need_select(int k, int m_max) { return (int64_t)k * (m_max + 1); }
 size_t select_block_bytes(int64_t need, int k) {
@@ -511,9 +514,11 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
     b.scan_tmp = (uint32_t *)a.take(scan_temp_bytes(std::max<int64_t>(
         {p.n + 1, p.ntiles + 1, 2 * p.cells + p.L + 1})));
     b.bad = take<int>(a, 1);
-    // (the counters, then the selection's histogram: cleared together)
-    b.counters = take<unsigned long long>(a, kCtrSlots * kCtrStride + kSelBins / 2);
+    // (the counters, the selection's histogram and the sort's ticket: cleared
+    // together)
+    b.counters = take<unsigned long long>(a, kClearWords);
     b.hist = (unsigned int *)(b.counters + kCtrSlots * kCtrStride);
+    b.sort_ticket = (uint32_t *)(b.counters + kClearWords - 1);
     b.emax = take<float>(a, 2 * p.L);        // then the join operands' (jemax)
     b.gproj = take<float>(a, (int64_t)p.L * kMaxBits * kFD);
     b.udir = take<double>(a, (int64_t)p.L * kJoinDirs * 32);
@@ -696,11 +701,11 @@ static int run_sieve(const Plan &p, Bufs &b, const Req &q, const Opt &o, hipStre
                                           (long long)p.N);
     launch_sieve_keys(o.precision, q, b.bstart, b.scnt, p.nbuckets, total, b.sdir, b.jk, b.jv,
                       b.sseg, s);
-    radix_sort_pairs(b.jk, b.jv, b.jk2, b.jv2, total, 0, 32, b.sort_tmp, s);
+    radix_sort_pairs(b.jk, b.jv, b.jk2, b.jv2, total, 0, 32, b.sort_tmp, b.sort_ticket, s);
     launch_sieve_regroup(b.jv, b.sseg, total, b.jk, s);
     int bits = 1;
     while (((int64_t)1 << bits) < p.nbuckets) ++bits;
-    radix_sort_pairs(b.jk, b.jv, b.jk2, b.jv2, total, 0, bits, b.sort_tmp, s);
+    radix_sort_pairs(b.jk, b.jv, b.jk2, b.jv2, total, 0, bits, b.sort_tmp, b.sort_ticket, s);
     launch_sieve_verify(o.precision, q, b.bstart, b.scnt, b.jv, b.sseg, total, o.sieve_w, s);
     return PMP_OK;
 }
@@ -967,7 +972,7 @@ static int run_pipeline(Run &R, Arena &ar) {
     const std::vector<LenInfo> len_host = p.len;
     HIPCHK(hipMemcpyAsync(b.len, len_host.data(), p.L * sizeof(LenInfo), hipMemcpyHostToDevice, s));
     launch_fill_u32((uint32_t *)b.emax, 2 * p.L, 0u, s);
-    launch_fill_u64((uint64_t *)b.counters, kCtrSlots * kCtrStride + kSelBins / 2, 0ull, s);
+    launch_fill_u64((uint64_t *)b.counters, kClearWords, 0ull, s);
     launch_fill_u64((uint64_t *)b.sel.st, sizeof(SelState) / 8, 0ull, s);
 
     Req q{};
@@ -1028,7 +1033,7 @@ static int run_pipeline(Run &R, Arena &ar) {
     launch_keys(o.precision, q, p.nkblocks, s);
     tm.mark(2, s);
     if (radix_sort_pairs(b.skey, b.sval, b.skey2, b.sval2, p.Na, 0, p.key_shift + p.len_bits,
-                         b.sort_tmp, s, false)) {
+                         b.sort_tmp, b.sort_ticket, s, false)) {
         // an odd number of passes leaves the sorted pairs in the scratch pair
         q.skey = b.skey2;
         q.sval = b.sval2;
@@ -1247,7 +1252,7 @@ static int run_pipeline(Run &R, Arena &ar) {
             launch_grid_keys(q, b.gl, Nq, cb1, cb2, cb3, l_lim, i_lim, b.jk, b.jv, b.qf, b.gp, nonq,
                              s);
             radix_sort_pairs(b.jk, b.jv, b.jk2, b.jv2, Nq, 0, p.len_bits + cb1 + cb2 + cb3,
-                             b.sort_tmp, s);
+                             b.sort_tmp, b.sort_ticket, s);
             launch_join_gather(b.jv, b.jop, b.gp, Nq, b.jop_s, b.gp_s, b.gw_s, s);
             // the tiles in chunks of blocks, each followed by the exact stage
             // of the pairs it kept (a kernel of its own, at full occupancy).

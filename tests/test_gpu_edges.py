@@ -91,3 +91,16 @@ def test_selection_forms(gpu, ws, oracle, kind, lo, hi, k):  # noqa: F811
     if kind == "tied":
         t = np.sign(rng.standard_normal(n))
     check(gpu, ws, oracle, t, lo, hi, 5, k=k)
+
+
+@pytest.mark.parametrize("n,lo,hi", [(2055, 8, 8), (2056, 8, 8), (16383, 16, 17), (16384, 16, 17),
+                                     (20000, 41, 70)])
+def test_scan_and_sort_sizes(gpu, ws, oracle, n, lo, hi):  # noqa: F811
+    """Scans of one block (to 16384 entries) and of three kernels; sorts of one
+    full tile and one key more, of several blocks that the histogram's last
+    block scans, and of more than those (the join's 599,000 keys)."""
+    t = np.cumsum(np.random.default_rng(n).standard_normal(n))
+    rows = oracle.pan_profile_v2(t, range(lo, hi + 1), lo)
+    res, _ = run(gpu, ws, t, lo, hi, lo)
+    ok, msg = parity.check_topk(res, rows, 20, oracle, t, excl=lo)
+    assert ok, msg
