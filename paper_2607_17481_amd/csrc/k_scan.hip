@@ -248,7 +248,8 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t *__restric
     }
 }
 
-// sub_n consecutive tiles of kSortTile keys per block, in order; in each tile wavefront w takes the contiguous slice [w, w + 1) * kSortTile / 4 in
+// sub_n consecutive tiles of kSortTile keys per block, in order; in each tile
+// wavefront w takes the contiguous slice [w, w + 1) * kSortTile / 4 in
 // kSortRounds rounds of 64.  Pass 1 ranks each key among the equal digits of
 // its round (one ballot per digit bit) and counts each wavefront's digits;
 // after one block barrier every (wavefront, digit) knows its first output

@@ -731,6 +731,31 @@ void launch_complete(int precision, const Req &q, const uint32_t *seeds, int nse
 // the join's counts (null: none).
 void launch_select(const Select &x, const uint64_t *P, int64_t n, const uint32_t *cell,
                    const LenView &lv, const unsigned long long *counts, hipStream_t s);
+// Spectral width from samples (Sec. 3.2; k_sketch.hip): up to kWidthSets
+// lengths, up to kWidthWin windows of each.
+constexpr int kWidthSets = 3, kWidthWin = 256, kWidthMin = 4;
+struct WidthSets {
+    int32_t sets;
+    int32_t m[kWidthSets];
+    int64_t W[kWidthSets];
+};
+// What the choice of K needs of one length's samples at one candidate K.
+struct WidthSums {
+    double energy;         // retained energy, summed over the windows
+    double coll;           // collision probability, summed over the pairs
+    int64_t pairs, windows;
+};
+__host__ __device__ inline int64_t width_start(int64_t W, int j) {
+    return W <= kWidthWin ? j : (int64_t)((double)j * (double)(W - 1) / 255.0);
+}
+__host__ __device__ inline int width_kprime(int K, int m) {
+    const int half = (m + 1) / 2 - 1, kp = K - 1 < half ? K - 1 : half;
+    return kp < 0 ? 0 : kp;
+}
+constexpr int64_t kWidthSpec = (int64_t)kWidthSets * kWidthWin * kMaxK;   // double2 of scratch
+// out[set][K - kWidthMin], K = kWidthMin .. kMaxK
+void launch_width(const double *t, const WidthSets &w, int B, double2 *spec, WidthSums *out,
+                  hipStream_t s);
 // (k_join.hip)
 // Bytes of the sorted operands of N windows of L lengths; the directions'
 // sample sums lie there before.

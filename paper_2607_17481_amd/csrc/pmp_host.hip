@@ -120,11 +120,7 @@ void projections(uint64_t seed, int m, float *out) {
     std::memcpy(out, it->second.data(), it->second.size() * sizeof(float));
 }
 
-int kprime_of(int K, int m) {
-    int half = (m + 1) / 2 - 1;
-    int kp = std::min(K - 1, half);
-    return kp < 0 ? 0 : kp;
-}
+int kprime_of(int K, int m) { return width_kprime(K, m); }
 
 // ----------------------------------------------- spectral width (Sec. 3.2)
 
@@ -132,10 +128,26 @@ int kprime_of(int K, int m) {
 // normalized spectral energy on average, and whose expected accidental
 // collision count n E[(1 - theta_K / pi)^B] stays within 2 gamma alpha, at
 // each of the sampled lengths.  Near-duplicate pairs (angle below 1e-3 rad at
-// the full width) are left out of the collision estimate.
+// the full width) are left out of the collision estimate.  sums: [set][K - 4].
+static int choose_width(const WidthSums *sums, const int *ms, int sets, int64_t n, int alpha,
+                        int gamma) {
+    const double eta = 0.85;
+    for (int K = kWidthMin; K <= kMaxK; ++K) {
+        bool ok = true;
+        for (int s = 0; s < sets && ok; ++s) {
+            const WidthSums &x = sums[s * (kMaxK - kWidthMin + 1) + K - kWidthMin];
+            if (x.windows == 0) continue;
+            if (x.energy / (double)x.windows < eta) ok = false;
+            else if (x.pairs && (double)n * x.coll / (double)x.pairs > 2.0 * gamma * alpha) ok = false;
+        }
+        if (ok) return K;
+    }
+    return kMaxK;
+}
+
+// The same from host samples (the entry that only asks for K).
 static int calibrate(const std::vector<std::vector<std::vector<double>>> &sets,
                      const std::vector<int> &ms, int64_t n, int alpha, int gamma, int B) {
-    const double eta = 0.85;
     // per sampled window: prefix sums over the bins k = 1..K' of its energy
     // (e[k]), and per consecutive pair those of the dot product and of both
     // energies, so that each candidate K costs O(1) per window and pair
@@ -221,18 +233,15 @@ static int calibrate(const std::vector<std::vector<std::vector<double>>> &sets,
         };
         for (size_t w = 0; w < np; ++w) P.dup[w] = angle(w, kpf) < 1e-3;
     }
-    for (int K = 4; K <= kMaxK; ++K) {
-        bool ok = true;
-        for (size_t s = 0; s < sets.size() && ok; ++s) {
+    std::vector<WidthSums> sums(sets.size() * (kMaxK - kWidthMin + 1));
+    for (int K = kWidthMin; K <= kMaxK; ++K) {
+        for (size_t s = 0; s < sets.size(); ++s) {
             const int m = ms[s];
             const int kp = kprime_of(K, m);
             const auto &v = spec[s];
             const Pre &P = pre[s];
-            if (v.empty()) continue;
             double e = 0.0;
             for (size_t w = 0; w < v.size(); ++w) e += 2.0 * P.e[w * (kMaxK + 1) + kp] / ((double)m * m);
-            e /= (double)v.size();
-            if (e < eta) { ok = false; break; }
             double coll = 0.0;
             int pairs = 0;
             for (size_t w = 0; w + 1 < v.size(); ++w) {
@@ -248,28 +257,11 @@ static int calibrate(const std::vector<std::vector<std::vector<double>>> &sets,
                 coll += std::pow(1.0 - th / M_PI, (double)B);
                 ++pairs;
             }
-            if (pairs && (double)n * coll / pairs > 2.0 * gamma * alpha) ok = false;
+            sums[s * (kMaxK - kWidthMin + 1) + K - kWidthMin] =
+                WidthSums{e, coll, pairs, (int64_t)v.size()};
         }
-        if (ok) return K;
     }
-    return kMaxK;
-}
-
-static std::vector<int64_t> sample_starts(int64_t W) {
-    std::vector<int64_t> v;
-    if (W <= 256) {
-        for (int64_t i = 0; i < W; ++i) v.push_back(i);
-    } else {
-        for (int j = 0; j < 256; ++j) v.push_back((int64_t)((double)j * (double)(W - 1) / 255.0));
-    }
-    return v;
-}
-
-__global__ void k_gather_windows(const double *__restrict__ t, const int64_t *__restrict__ starts,
-                                 int count, int m, double *__restrict__ out) {
-    const int w = blockIdx.x;
-    if (w >= count) return;
-    for (int r = threadIdx.x; r < m; r += blockDim.x) out[(int64_t)w * m + r] = t[starts[w] + r];
+    return choose_width(sums.data(), ms.data(), (int)sets.size(), n, alpha, gamma);
 }
 
 // ------------------------------------------------------------ workspace
@@ -410,8 +402,8 @@ struct Bufs {
     unsigned int *hist;
     RowReq *rows;
     unsigned long long *row_min, *row_arg;
-    int64_t *cal_starts;
-    double *cal_win;
+    double2 *wspec;            // spectral width: sampled spectra and their sums
+    WidthSums *wsums;
     // phase 2: sized by the indexed windows N
     uint32_t *cell;
     double *mu, *isig;
@@ -534,8 +526,8 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
     b.rows = take<RowReq>(a, k);
     b.row_min = take<unsigned long long>(a, k);
     b.row_arg = take<unsigned long long>(a, k);
-    b.cal_starts = take<int64_t>(a, 3 * 256);
-    b.cal_win = take<double>(a, (int64_t)3 * 256 * p.max_m);
+    b.wspec = take<double2>(a, kWidthSpec);
+    b.wsums = take<WidthSums>(a, kWidthSets * (kMaxK - kWidthMin + 1));
     b.x16 = take<int16_t>(a, 2 * quant_pitch(p.n));
     b.xmm = take<unsigned long long>(a, 2);
     b.sdir = take<float>(a, (int64_t)p.L * kFD);
@@ -814,6 +806,19 @@ static int emit_stage(const Plan &p, Bufs &b, Req &q, const Opt &o, int k, hipSt
 
 // ------------------------------------------------------------- pipeline
 
+// The sampled lengths: the first, the middle and the last.
+static WidthSets width_sets(const Plan &p) {
+    WidthSets w{};
+    const int idx[3] = {0, (p.L - 1) / 2, p.L - 1};
+    for (int a = 0; a < 3; ++a) {
+        if (a > 0 && idx[a] == idx[a - 1]) continue;
+        w.m[w.sets] = p.ms[idx[a]];
+        w.W[w.sets] = p.n - p.ms[idx[a]] + 1;
+        ++w.sets;
+    }
+    return w;
+}
+
 static int check_args(int64_t n, int m_min, int m_max, int k, int excl, int budget) {
     if (n < 3) return fail(PMP_EINVAL, "series must have at least 3 samples");
     if (!(3 <= m_min && m_min <= m_max && (int64_t)m_max <= n))
@@ -907,43 +912,16 @@ static int run_pipeline(Run &R, Arena &ar) {
     HIPCHK(hipMemcpyAsync(&bad, b.bad, sizeof(int), hipMemcpyDeviceToHost, s));
     HIPCHK(hipMemcpyAsync(toff.data(), b.tile_off, (p.ntiles + 1) * sizeof(uint32_t),
                           hipMemcpyDeviceToHost, s));
-    // calibration samples
-    std::vector<int> cal_m;
-    std::vector<std::vector<int64_t>> cal_st;
-    std::vector<int64_t> cal_all(3 * 256, 0);   // lives until the sync below
-    std::vector<double> cal_host;
+    const WidthSets ws = width_sets(p);
+    WidthSums wsums[kWidthSets * (kMaxK - kWidthMin + 1)];
     if (o.K == 0) {
-        int idx[3] = {0, (p.L - 1) / 2, p.L - 1};
-        for (int a = 0; a < 3; ++a) {
-            if (a > 0 && idx[a] == idx[a - 1]) continue;
-            cal_m.push_back(p.ms[idx[a]]);
-            cal_st.push_back(sample_starts(p.len[idx[a]].W));
-        }
-        for (size_t a = 0; a < cal_m.size(); ++a)
-            for (size_t w = 0; w < cal_st[a].size(); ++w) cal_all[a * 256 + w] = cal_st[a][w];
-        HIPCHK(hipMemcpyAsync(b.cal_starts, cal_all.data(), cal_all.size() * sizeof(int64_t),
-                              hipMemcpyHostToDevice, s));
-        for (size_t a = 0; a < cal_m.size(); ++a)
-            hipLaunchKernelGGL(k_gather_windows, dim3((unsigned)cal_st[a].size()), dim3(256), 0, s,
-                               R.t, (const int64_t *)b.cal_starts + a * 256,
-                               (int)cal_st[a].size(), cal_m[a],
-                               b.cal_win + (int64_t)a * 256 * p.max_m);
-        cal_host.resize((size_t)3 * 256 * p.max_m);
-        HIPCHK(hipMemcpyAsync(cal_host.data(), b.cal_win, cal_host.size() * sizeof(double),
-                              hipMemcpyDeviceToHost, s));
+        launch_width(R.t, ws, o.B, b.wspec, b.wsums, s);
+        HIPCHK(hipMemcpyAsync(wsums, b.wsums, sizeof(wsums), hipMemcpyDeviceToHost, s));
     }
     HIPCHK(hipStreamSynchronize(s));
     if (bad) return fail(PMP_EINVAL, "series contains a non-finite sample");
     int K = o.K;
-    if (K == 0) {
-        std::vector<std::vector<std::vector<double>>> sets(cal_m.size());
-        for (size_t a = 0; a < cal_m.size(); ++a)
-            for (size_t w = 0; w < cal_st[a].size(); ++w) {
-                const double *src = cal_host.data() + (a * 256 + w) * p.max_m;
-                sets[a].emplace_back(src, src + cal_m[a]);
-            }
-        K = calibrate(sets, cal_m, R.n, R.budget, o.gamma, o.B);
-    }
+    if (K == 0) K = choose_width(wsums, ws.m, ws.sets, R.n, R.budget, o.gamma);
     std::vector<int64_t> cnt(p.L);
     for (int l = 0; l < p.L; ++l) {
         const int64_t t1 = l + 1 < p.L ? p.len[l + 1].tile_base : p.ntiles;
@@ -1702,17 +1680,14 @@ int pmp_calibrate_width(const double *series, int64_t n, int32_t m_min, int32_t 
     if (m_step < 1 || gamma < 1 || bits < 1 || bits > kMaxBits) return fail(PMP_EINVAL, "bad option");
     Plan p;
     plan_lengths(p, n, m_min, m_max, m_step);
-    int idx[3] = {0, (p.L - 1) / 2, p.L - 1};
-    std::vector<int> ms;
-    std::vector<std::vector<std::vector<double>>> sets;
-    for (int a = 0; a < 3; ++a) {
-        if (a > 0 && idx[a] == idx[a - 1]) continue;
-        const int m = p.ms[idx[a]];
-        ms.push_back(m);
-        std::vector<std::vector<double>> set;
-        for (int64_t i : sample_starts(n - m + 1)) set.emplace_back(series + i, series + i + m);
-        sets.push_back(std::move(set));
-    }
+    const WidthSets ws = width_sets(p);
+    const std::vector<int> ms(ws.m, ws.m + ws.sets);
+    std::vector<std::vector<std::vector<double>>> sets(ws.sets);
+    for (int a = 0; a < ws.sets; ++a)
+        for (int j = 0; j < (int)std::min<int64_t>(ws.W[a], kWidthWin); ++j) {
+            const double *w = series + width_start(ws.W[a], j);
+            sets[a].emplace_back(w, w + ws.m[a]);
+        }
     *K = calibrate(sets, ms, n, budget, gamma, bits);
     return PMP_OK;
 }

@@ -104,3 +104,20 @@ def test_scan_and_sort_sizes(gpu, ws, oracle, n, lo, hi):  # noqa: F811
     res, _ = run(gpu, ws, t, lo, hi, lo)
     ok, msg = parity.check_topk(res, rows, 20, oracle, t, excl=lo)
     assert ok, msg
+
+
+@pytest.mark.parametrize("kind", ["walk", "noise", "flat", "few"])
+def test_width_matches_the_host(gpu, ws, kind):  # noqa: F811
+    """The spectral width chosen on the device equals the host's: smooth and
+    white series, constant windows among the samples, fewer windows than
+    samples."""
+    rng = np.random.default_rng(5)
+    t = rng.standard_normal(3000)
+    if kind != "noise":
+        t = np.cumsum(t)
+    if kind == "flat":
+        t[500:1500] = 0.1
+    if kind == "few":
+        t = t[:150]
+    _, st = run(gpu, ws, t, 20, 100, 10, 5)
+    assert st["K"] == gpu.calibrate_width(t, 20, 100)
