@@ -323,6 +323,7 @@ __global__ __launch_bounds__(kGreedyThreads) void k_select_greedy(
         st->kept = kept;
         st->nredo = counts ? (uint32_t)counts[kCtrSlots * kCtrStride] : 0u;
         st->naccept = 0;
+        st->improved = in.improved ? *in.improved : 0ull;
     }
     if (k == 0) return;
     // every entry with its cell and length, in registers

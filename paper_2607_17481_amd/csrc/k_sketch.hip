@@ -70,21 +70,42 @@ __device__ __forceinline__ uint32_t bf16_bits(float x) {
 
 // Non-constant windows per tile: window [i, i+m) is constant iff no change
 // point lies in (i, i+m), i.e. E[i+m] == E[i+1] for the exclusive prefix E.
+// Block (x, y): the tiles of starts [x, x + 1) * kTileW at `group` lengths,
+// which all read the same stretch of E, staged in LDS.  One length a block
+// read E once per length from memory (5M samples at 51 lengths: 300 us, now
+// 125); few blocks still take one length each, to fill the chip.
+constexpr int kCountGroup = 16;               // lengths per block at most
+
 __global__ __launch_bounds__(kBlock) void k_tile_counts(const LenInfo *__restrict__ len, int L,
-                                                        const uint32_t *__restrict__ E,
+                                                        const uint32_t *__restrict__ E, int group,
+                                                        int64_t ntiles,
                                                         uint32_t *__restrict__ tile_cnt) {
-    __shared__ uint32_t ws[kBlock / kWave];
-    const int64_t tile = blockIdx.x;
-    const int l = find_tile_len(len, L, tile);
-    const int m = len[l].m;
-    const int64_t i0 = (tile - len[l].tile_base) * kTileW;
-    const int nw = (int)min<int64_t>(kTileW, len[l].W - i0);
-    uint32_t c = 0;
-    for (int w = threadIdx.x; w < nw; w += kBlock) c += E[i0 + w + m] != E[i0 + w + 1];
-    for (int off = kWave / 2; off > 0; off >>= 1) c += __shfl_xor(c, off, kWave);
-    if (lane_id() == 0) ws[threadIdx.x / kWave] = c;
+    __shared__ uint32_t e[kTileW + kMaxM + 1];
+    __shared__ uint32_t cnt[kCountGroup];
+    const int l0 = blockIdx.y * group, l1 = min(L, l0 + group);
+    const int64_t i0 = (int64_t)blockIdx.x * kTileW;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) tile_cnt[ntiles] = 0;
+    // (the lengths ascend, so their window counts descend)
+    if (i0 >= len[l0].W) return;
+    const int64_t n1 = len[l0].W + len[l0].m;               // entries of E: n + 1
+    const int span = (int)min<int64_t>(kTileW + len[l1 - 1].m, n1 - i0);
+    for (int x = threadIdx.x; x < span; x += kBlock) e[x] = E[i0 + x];
+    if (threadIdx.x < kCountGroup) cnt[threadIdx.x] = 0;
     __syncthreads();
-    if (threadIdx.x == 0) tile_cnt[tile] = ws[0] + ws[1] + ws[2] + ws[3];
+    for (int l = l0; l < l1; ++l) {
+        const int m = len[l].m;
+        const int nw = (int)min<int64_t>(kTileW, len[l].W - i0);
+        uint32_t c = 0;
+        for (int w0 = 0; w0 < nw; w0 += kBlock) {
+            const int w = w0 + threadIdx.x;
+            c += (uint32_t)__popcll(__ballot(w < nw && e[w + m] != e[w + 1]));
+        }
+        if (lane_id() == 0 && c) atomicAdd(&cnt[l - l0], c);
+    }
+    __syncthreads();
+    const int l = l0 + threadIdx.x;
+    if (threadIdx.x < kCountGroup && l < l1 && i0 < len[l].W)
+        tile_cnt[len[l].tile_base + blockIdx.x] = cnt[threadIdx.x];
 }
 
 // ---------------------------------------------------------------- sketch
@@ -825,7 +846,7 @@ __global__ __launch_bounds__(kBlock) void k_keys(Req q, const float *__restrict_
     const int tid = threadIdx.x;
     for (int x = tid; x < 32 * 32; x += kBlock) {
         const int bt = x / 32, c = x % 32;
-        const float gv = bt < q.B && c < kFD ? gproj[((int64_t)l * q.B + bt) * kFD + c] : 0.0f;
+        const float gv = bt < q.B && c < kFD ? gproj[((int64_t)q.len[l].aidx * q.B + bt) * kFD + c] : 0.0f;
         const uint32_t h = bf16_bits(gv);
         sm.gh[bt][c] = (uint16_t)h;
         sm.gl[bt][c] = (uint16_t)bf16_bits(gv - __uint_as_float(h << 16));
@@ -957,10 +978,12 @@ void launch_changepoints(const double *t, int64_t n, uint32_t *flag, int *bad, h
     hipLaunchKernelGGL(k_changepoints, dim3(nblk(n + 1)), dim3(kBlock), 0, s, t, n, flag, bad);
 }
 
-void launch_tile_counts(const LenInfo *len, int L, const uint32_t *E, int64_t ntiles,
-                        uint32_t *tile_cnt, hipStream_t s) {
-    hipLaunchKernelGGL(k_tile_counts, dim3((unsigned)ntiles), dim3(kBlock), 0, s, len, L, E,
-                       tile_cnt);
+void launch_tile_counts(const LenInfo *len, int L, const uint32_t *E, int64_t starts, int max_m,
+                        int64_t ntiles, uint32_t *tile_cnt, hipStream_t s) {
+    const int64_t tiles = (starts + kTileW - 1) / kTileW;
+    const int group = (int)std::min<int64_t>(std::max<int64_t>(ntiles / 2048, 1), kCountGroup);
+    hipLaunchKernelGGL(k_tile_counts, dim3((unsigned)tiles, (unsigned)((L + group - 1) / group)),
+                       dim3(kBlock), 0, s, len, L, E, group, ntiles, tile_cnt);
 }
 
 void launch_sketch(int precision, const Req &q, const uint32_t *E, const uint32_t *tile_off,

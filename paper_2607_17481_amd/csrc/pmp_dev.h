@@ -48,7 +48,7 @@ struct LenInfo {
     int32_t anchor;       // 1: an anchor length
     int32_t a_lo, a_hi;   // a non-anchor's nearest anchors below and above
                           // (indices; -1: none)
-    int32_t pad_;
+    int32_t aidx;         // an anchor's number among the anchors (its projections)
     int64_t pblk_base;    // first probe block of this length
     int64_t hblk_base;    // first hint block of this length
     // Keys and buckets exist at the anchor lengths only (nothing else reads
@@ -245,6 +245,7 @@ struct SelState {
     uint32_t ticket;      // blocks of the running pass that have arrived (0 between passes)
     int32_t naccept;      // cells accepted by the device's greedy
     int32_t pad_;
+    uint64_t improved;    // *Select::improved
 };
 // A selected cell: its value's bits, position and cell.
 struct SelCell {
@@ -287,6 +288,7 @@ struct Select {
     uint32_t *sel, *sel_cell;
     int2 *sel_len;        // index and window length of its length
     unsigned int *hist;   // [kSelBins], zero between selections (as st->ticket)
+    const unsigned long long *improved;   // a counter that travels with the state, or null
     int64_t need, cap;
     int k;
     bool on_device() const { return cap <= kGreedyMax && k <= kGreedyRounds; }
@@ -675,8 +677,9 @@ int radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1, int
 
 // (k_sketch.hip)
 void launch_changepoints(const double *t, int64_t n, uint32_t *flag, int *bad, hipStream_t s);
-void launch_tile_counts(const LenInfo *len, int L, const uint32_t *E, int64_t ntiles,
-                        uint32_t *tile_cnt, hipStream_t s);
+// (also clears tile_cnt[ntiles]; starts = windows of the shortest length)
+void launch_tile_counts(const LenInfo *len, int L, const uint32_t *E, int64_t starts, int max_m,
+                        int64_t ntiles, uint32_t *tile_cnt, hipStream_t s);
 // Which tiles of [0, ntiles) the sketch gives records: every length
 // (kSketchAll), the anchor lengths only, the moments and positions of every
 // tile still written (kSketchAnchors), or the lengths between anchors, whose
@@ -756,6 +759,14 @@ constexpr int64_t kWidthSpec = (int64_t)kWidthSets * kWidthWin * kMaxK;   // dou
 // out[set][K - kWidthMin], K = kWidthMin .. kMaxK
 void launch_width(const double *t, const WidthSets &w, int B, double2 *spec, WidthSums *out,
                   hipStream_t s);
+// Small host data to the device through kernel arguments, read when the call
+// returns; also clears `zero_words` words at `zero` (null: none).  False: too
+// long for that, nothing was done.  (k_scan.hip)
+bool launch_upload(void *dst, const void *src, size_t bytes, uint32_t *zero, int64_t zero_words,
+                   hipStream_t s);
+// offs[l] = tile_off at length l's first tile, offs[L] at the end
+void launch_len_offsets(const LenInfo *len, int L, const uint32_t *tile_off, int64_t ntiles,
+                        uint32_t *offs, hipStream_t s);
 // (k_join.hip)
 // Bytes of the sorted operands of N windows of L lengths; the directions'
 // sample sums lie there before.

@@ -338,9 +338,9 @@ static void plan_index(Plan &p, const std::vector<int64_t> &cnt, const Opt &o, i
     for (int l = 0; l < p.L; ++l) {
         LenInfo &L = p.len[l];
         L.anchor = (l % o.stride == 0 || l == p.L - 1) ? 1 : 0;
+        L.aidx = p.anchors;
         p.anchors += L.anchor;
         L.a_lo = L.a_hi = -1;
-        L.pad_ = 0;
     }
     for (int l = 0; l < p.L; ++l) {
         if (p.len[l].anchor) continue;
@@ -392,8 +392,15 @@ struct Bufs {
     // phase 1: sized by the series and the lengths
     LenInfo *len;
     uint32_t *flags, *E, *scan_tmp, *tile_off;
+    // what the host reads back, in one piece: after the index counts from
+    // `head` to `emax`, with every selection from `bad` on
+    char *head;
+    uint32_t *loff;            // [L + 1] indexed windows before each length
     int *bad;
     unsigned long long *counters;
+    int bad_h = 0;             // the host's copies
+    unsigned long long improved_h = 0;
+    std::vector<float> emax_h;
     float *emax, *gproj;
     double *cov, *udir;
     GridLen *gl;
@@ -496,6 +503,9 @@ int select_result(const Select &x, const char *host, SelState &st, std::vector<S
     return PMP_OK;
 }
 
+// bad (8 bytes), then both lists of feature errors
+static size_t head_bytes(int L) { return 8 + (size_t)L * 8; }
+
 static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
     b.len = take<LenInfo>(a, p.L);
     b.flags = take<uint32_t>(a, p.n + 1);
@@ -505,13 +515,28 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
     // buckets (at most 2 W + 1 per length)
     b.scan_tmp = (uint32_t *)a.take(scan_temp_bytes(std::max<int64_t>(
         {p.n + 1, p.ntiles + 1, 2 * p.cells + p.L + 1})));
-    b.bad = take<int>(a, 1);
+    // [wsums | loff | bad | emax | the selection's results]
+    const size_t hw = kWidthSets * (kMaxK - kWidthMin + 1) * sizeof(WidthSums);
+    const size_t ho = ((size_t)(p.L + 1) * 4 + 7) & ~(size_t)7, he = head_bytes(p.L);
+    const int64_t need = need_select(k, p.max_m);
+    b.head = (char *)a.take(hw + ho + he + select_block_bytes(need, k));
+    b.wsums = (WidthSums *)b.head;
+    b.loff = (uint32_t *)(b.head + hw);
+    b.bad = (int *)(b.head + hw + ho);
+    b.emax = (float *)(b.bad + 2);           // then the join operands' (jemax)
+    b.selblk = (char *)b.bad + he;
+    b.emax_h.assign(p.L, 0.0f);
+    // the rows' requests and results, then the counters (read with the results)
     // (the counters, the selection's histogram and the sort's ticket: cleared
     // together)
-    b.counters = take<unsigned long long>(a, kClearWords);
+    b.rows = (RowReq *)a.take((size_t)k * (sizeof(RowReq) + 16) + kClearWords * 8);
+    b.row_min = (unsigned long long *)(b.rows + k);
+    b.row_arg = b.row_min + k;
+    b.counters = b.row_arg + k;
     b.hist = (unsigned int *)(b.counters + kCtrSlots * kCtrStride);
     b.sort_ticket = (uint32_t *)(b.counters + kClearWords - 1);
-    b.emax = take<float>(a, 2 * p.L);        // then the join operands' (jemax)
+    b.sel = select_buffers(b.selblk, b.hist, need, k);
+    b.sel.improved = &b.counters[C_COMPL_IMPROVED];
     b.gproj = take<float>(a, (int64_t)p.L * kMaxBits * kFD);
     b.udir = take<double>(a, (int64_t)p.L * kJoinDirs * 32);
     {
@@ -523,11 +548,7 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
         b.bl = take<uint16_t>(a, ne);
     }
     b.gl = take<GridLen>(a, p.L);
-    b.rows = take<RowReq>(a, k);
-    b.row_min = take<unsigned long long>(a, k);
-    b.row_arg = take<unsigned long long>(a, k);
     b.wspec = take<double2>(a, kWidthSpec);
-    b.wsums = take<WidthSums>(a, kWidthSets * (kMaxK - kWidthMin + 1));
     b.x16 = take<int16_t>(a, 2 * quant_pitch(p.n));
     b.xmm = take<unsigned long long>(a, 2);
     b.sdir = take<float>(a, (int64_t)p.L * kFD);
@@ -550,10 +571,9 @@ static int64_t join_pair_cap(int64_t N) { return std::max<int64_t>(int64_t(1) <<
 // Blocks of the join over N windows in L lengths, at most.
 static int64_t join_blocks_max(int64_t N, int L) { return N / (kJoinTile * kJoinBlock) + L + 1; }
 
-static void carve2(Arena &a, Bufs &b, const Plan &p, const Opt &o, int k) {
+static void carve2(Arena &a, Bufs &b, const Plan &p, const Opt &o) {
     const int precision = o.precision;
     const int64_t N = std::max<int64_t>(p.N, 1);
-    const int64_t need = need_select(k, p.max_m);
     b.cell = take<uint32_t>(a, N);
     b.mu = take<double>(a, N);
     b.isig = take<double>(a, N);
@@ -585,8 +605,6 @@ static void carve2(Arena &a, Bufs &b, const Plan &p, const Opt &o, int k) {
     // the segments' pair counts, the number of overflowed blocks, nonq (u32 per length)
     b.jcount = take<unsigned long long>(a, kJoinCounts + (p.L + 1) / 2);
     b.jredo = take<uint32_t>(a, 2 * join_blocks_max(N, p.L));
-    b.selblk = (char *)a.take(select_block_bytes(need, k));
-    b.sel = select_buffers(b.selblk, b.hist, need, k);
     b.kmap = needs_kmap(o) ? take<uint32_t>(a, p.cells) : nullptr;
     b.hint = take<uint32_t>(a, N);
     b.scnt = o.sieve_w > 0 ? take<uint32_t>(a, p.nbuckets + 1) : nullptr;
@@ -611,11 +629,21 @@ static int len_of_cell(const Plan &p, int64_t cell) {
     return lo;
 }
 
+// Host data to the device, in stream order: through kernel arguments when
+// short, else by a copy (the source lives until the next synchronization).
+// Also clears `zero_words` words at `zero`.
+static hipError_t upload(void *dst, const void *src, size_t bytes, hipStream_t s,
+                         uint32_t *zero = nullptr, int64_t zero_words = 0) {
+    if (launch_upload(dst, src, bytes, zero, zero_words, s)) return hipSuccess;
+    if (zero_words > 0) launch_fill_u32(zero, zero_words, 0u, s);
+    return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+}
+
 // The greedy of Sec. 2 over the upper profile: P is indexed by k, whose order
 // is the (m, i) order of the non-constant windows; constant windows have no
 // cell value.  The selection runs on the device (launch_select); one read-back
-// brings the accepted cells, after any copies the caller has already enqueued
-// on the stream (they complete with the same synchronization).  `counts` (when
+// brings the accepted cells, and with them the flag of bad windows, the feature
+// errors and the completion's counter (bad_h, emax_h, improved_h).  `counts` (when
 // given) receives the join's kept pairs and overflowed blocks.  Only the first n
 // positions are looked at (0: all), for callers that know that no cell after
 // them can be accepted.
@@ -633,15 +661,19 @@ static int select_topk(const Plan &p, Bufs &b, int k, hipStream_t s, std::vector
     const LenView lv{(const char *)b.len, (int64_t)sizeof(LenInfo),
                      (int32_t)offsetof(LenInfo, cell_base), (int32_t)offsetof(LenInfo, m), p.L};
     launch_select(b.sel, b.P, n > 0 ? n : p.N, b.cell, lv, counts ? b.jcount : nullptr, s);
-    std::vector<char> host(select_read_bytes(b.sel));
-    HIPCHK(hipMemcpyAsync(host.data(), b.selblk, host.size(), hipMemcpyDeviceToHost, s));
+    const size_t he = head_bytes(p.L);
+    std::vector<char> host(he + select_read_bytes(b.sel));
+    HIPCHK(hipMemcpyAsync(host.data(), b.bad, host.size(), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
+    memcpy(&b.bad_h, host.data(), sizeof(int));
+    memcpy(b.emax_h.data(), host.data() + 8, p.L * sizeof(float));
     SelState st;
     std::vector<SelCell> acc;
-    const int rc = select_result(b.sel, host.data(), st, acc,
+    const int rc = select_result(b.sel, host.data() + he, st, acc,
                                  [&](uint32_t c) { return len_of_cell(p, c); },
                                  [&](int l) { return p.ms[l]; });
     if (counts) *counts = {st.kept, st.nredo, 0u};
+    b.improved_h = st.improved;
     if (rc) return rc;
     for (const SelCell &c : acc) {
         double d;
@@ -735,8 +767,7 @@ static int emit_stage(const Plan &p, Bufs &b, Req &q, const Opt &o, int k, hipSt
         // past the signature rows)
         for (int l = 0; l < p.L; ++l)
             for (int c = 0; c < kFD; ++c) dir[(size_t)l * kFD + c] = (float)gauss(o.seed, p.ms[l], 32, c);
-        HIPCHK(hipMemcpyAsync(b.sdir, dir.data(), dir.size() * sizeof(float), hipMemcpyHostToDevice,
-                              s));
+        HIPCHK(upload(b.sdir, dir.data(), dir.size() * sizeof(float), s));
         const int rc = run_sieve(p, b, q, o, s);
         if (rc) return rc;
     }
@@ -776,9 +807,8 @@ static int emit_stage(const Plan &p, Bufs &b, Req &q, const Opt &o, int k, hipSt
     if (o.compl_rounds == 0 || zero_kth) return PMP_OK;
     std::vector<uint32_t> seeds;
     std::vector<Cand> prev;
-    unsigned long long improved = 1;
     for (int r = 0; r <= o.compl_rounds; ++r) {
-        const int rc = select_topk(p, b, k, s, acc);   // also completes the copy of `improved`
+        const int rc = select_topk(p, b, k, s, acc);
         if (rc) return rc;
         selected = true;
         // stop once a round lowers no cell or leaves the selected cells and
@@ -787,17 +817,14 @@ static int emit_stage(const Plan &p, Bufs &b, Req &q, const Opt &o, int k, hipSt
         bool same = r > 0 && prev.size() == acc.size();
         for (size_t x = 0; same && x < acc.size(); ++x)
             same = prev[x].k == acc[x].k && prev[x].d == acc[x].d;
-        if (r == o.compl_rounds || improved == 0 || acc.empty() || same) break;
+        if (r == o.compl_rounds || (r > 0 && b.improved_h == 0) || acc.empty() || same) break;
         if (acc.size() == (size_t)k && acc.back().d == 0.0) break;
         prev = acc;
         seeds.resize(acc.size());
         for (size_t x = 0; x < acc.size(); ++x) seeds[x] = acc[x].k;
-        HIPCHK(hipMemcpyAsync(b.seeds, seeds.data(), seeds.size() * sizeof(uint32_t),
-                              hipMemcpyHostToDevice, s));
-        launch_fill_u64((uint64_t *)&b.counters[C_COMPL_IMPROVED], 1, 0ull, s);
+        HIPCHK(upload(b.seeds, seeds.data(), seeds.size() * sizeof(uint32_t), s,
+                      (uint32_t *)&b.counters[C_COMPL_IMPROVED], 2));
         launch_complete(o.precision, q, b.seeds, (int)seeds.size(), o.compl_dm, o.compl_dp, s);
-        HIPCHK(hipMemcpyAsync(&improved, &b.counters[C_COMPL_IMPROVED], sizeof(improved),
-                              hipMemcpyDeviceToHost, s));
         selected = false;
         ++rounds;
     }
@@ -840,7 +867,7 @@ static size_t upper_bytes(int64_t n, int m_min, int m_max, const Opt &o, int k) 
     a.sizing = true;
     Bufs b;
     carve1(a, b, p, k);
-    carve2(a, b, p, o, k);
+    carve2(a, b, p, o);
     return a.off + 4096;
 }
 
@@ -900,58 +927,51 @@ static int run_pipeline(Run &R, Arena &ar) {
     tm.mark(0, s);
 
     // ---- validation, change points, index counts per tile
-    launch_fill_u32((uint32_t *)b.bad, 1, 0u, s);
+    HIPCHK(upload(b.len, p.len.data(), p.L * sizeof(LenInfo), s, (uint32_t *)b.bad,
+                  (int64_t)(head_bytes(p.L) + sizeof(SelState)) / 4));
     launch_changepoints(R.t, R.n, b.flags, b.bad, s);
     scan_exclusive_u32(b.flags, b.E, R.n + 1, nullptr, b.scan_tmp, s);
-    HIPCHK(hipMemcpyAsync(b.len, p.len.data(), p.L * sizeof(LenInfo), hipMemcpyHostToDevice, s));
-    launch_tile_counts(b.len, p.L, b.E, p.ntiles, b.tile_off, s);
-    launch_fill_u32(b.tile_off + p.ntiles, 1, 0u, s);
+    launch_tile_counts(b.len, p.L, b.E, p.n - p.ms[0] + 1, p.max_m, p.ntiles, b.tile_off, s);
     scan_exclusive_u32(b.tile_off, b.tile_off, p.ntiles + 1, nullptr, b.scan_tmp, s);
-    int bad = 0;
-    std::vector<uint32_t> toff(p.ntiles + 1);
-    HIPCHK(hipMemcpyAsync(&bad, b.bad, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(toff.data(), b.tile_off, (p.ntiles + 1) * sizeof(uint32_t),
-                          hipMemcpyDeviceToHost, s));
+    launch_len_offsets(b.len, p.L, b.tile_off, p.ntiles, b.loff, s);
     const WidthSets ws = width_sets(p);
-    WidthSums wsums[kWidthSets * (kMaxK - kWidthMin + 1)];
-    if (o.K == 0) {
-        launch_width(R.t, ws, o.B, b.wspec, b.wsums, s);
-        HIPCHK(hipMemcpyAsync(wsums, b.wsums, sizeof(wsums), hipMemcpyDeviceToHost, s));
-    }
+    if (o.K == 0) launch_width(R.t, ws, o.B, b.wspec, b.wsums, s);
+    std::vector<char> head((char *)b.emax - b.head);
+    HIPCHK(hipMemcpyAsync(head.data(), b.head, head.size(), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
+    const WidthSums *wsums = (const WidthSums *)head.data();
+    const uint32_t *loff = (const uint32_t *)(head.data() + ((char *)b.loff - b.head));
+    int bad;
+    memcpy(&bad, head.data() + ((char *)b.bad - b.head), sizeof(int));
     if (bad) return fail(PMP_EINVAL, "series contains a non-finite sample");
     int K = o.K;
     if (K == 0) K = choose_width(wsums, ws.m, ws.sets, R.n, R.budget, o.gamma);
     std::vector<int64_t> cnt(p.L);
-    for (int l = 0; l < p.L; ++l) {
-        const int64_t t1 = l + 1 < p.L ? p.len[l + 1].tile_base : p.ntiles;
-        cnt[l] = (int64_t)toff[t1] - (int64_t)toff[p.len[l].tile_base];
-    }
+    for (int l = 0; l < p.L; ++l) cnt[l] = (int64_t)loff[l + 1] - (int64_t)loff[l];
     plan_index(p, cnt, o, R.budget, K);
-    if (p.N != (int64_t)toff[p.ntiles]) return fail(PMP_EINTERNAL, "index count mismatch");
-    carve2(ar, b, p, o, R.k);
+    if (p.N != (int64_t)loff[p.L]) return fail(PMP_EINTERNAL, "index count mismatch");
+    carve2(ar, b, p, o);
     if (ar.off > ar.cap) return fail(PMP_ENOMEM, "workspace too small (%zu < %zu)", ar.cap, ar.off);
     if (R.dbg && R.dbg->join_pair_cap > 0) b.jcap = std::min(b.jcap, R.dbg->join_pair_cap);
     const int64_t N = p.N;
 
     // ---- per-request constants (the host vectors live until the next
     // synchronization, at the first selection)
-    std::vector<float> gproj_host((size_t)p.L * o.B * kFD);
+    // (the projections of the anchor lengths: no other has keys)
+    std::vector<float> gproj_host((size_t)p.anchors * o.B * kFD);
     {
         std::vector<float> one((size_t)kMaxBits * kFD);
         for (int l = 0; l < p.L; ++l) {
+            if (!p.len[l].anchor) continue;
             projections(o.seed, p.ms[l], one.data());
-            std::memcpy(gproj_host.data() + (size_t)l * o.B * kFD, one.data(),
+            std::memcpy(gproj_host.data() + (size_t)p.len[l].aidx * o.B * kFD, one.data(),
                         (size_t)o.B * kFD * sizeof(float));
         }
     }
-    HIPCHK(hipMemcpyAsync(b.gproj, gproj_host.data(), gproj_host.size() * sizeof(float),
-                          hipMemcpyHostToDevice, s));
     const std::vector<LenInfo> len_host = p.len;
-    HIPCHK(hipMemcpyAsync(b.len, len_host.data(), p.L * sizeof(LenInfo), hipMemcpyHostToDevice, s));
-    launch_fill_u32((uint32_t *)b.emax, 2 * p.L, 0u, s);
-    launch_fill_u64((uint64_t *)b.counters, kClearWords, 0ull, s);
-    launch_fill_u64((uint64_t *)b.sel.st, sizeof(SelState) / 8, 0ull, s);
+    HIPCHK(upload(b.len, len_host.data(), p.L * sizeof(LenInfo), s, (uint32_t *)b.counters,
+                  kClearWords * 2));
+    HIPCHK(upload(b.gproj, gproj_host.data(), gproj_host.size() * sizeof(float), s));
 
     Req q{};
     q.t = R.t;
@@ -999,8 +1019,7 @@ static int run_pipeline(Run &R, Arena &ar) {
     int rec_lim = p.L - 1;
     if (o.precision != 0) {
         // precision forms: the projection on the matrix cores
-        HIPCHK(hipMemcpyAsync(b.bbase, bbase.data(), (p.L + 1) * sizeof(int64_t),
-                              hipMemcpyHostToDevice, s));
+        HIPCHK(upload(b.bbase, bbase.data(), (p.L + 1) * sizeof(int64_t), s));
         launch_basis(b.len, p.L, b.bbase, b.bh, b.bm, b.bl, p.max_m, s);
     }
     launch_records(p, b, q, o, p.ntiles, lazy ? kSketchAnchors : kSketchAll, s);
@@ -1087,9 +1106,6 @@ static int run_pipeline(Run &R, Arena &ar) {
     // ---- emit stage (Sec. 3.6, Algorithm 2); the flag of unrepresentable
     // windows and the largest feature errors come back with the first
     // selection
-    std::vector<float> emax(p.L);
-    HIPCHK(hipMemcpyAsync(&bad, b.bad, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(emax.data(), b.emax, p.L * sizeof(float), hipMemcpyDeviceToHost, s));
     std::vector<Cand> acc;
     int crounds = 0;
     bool selected = false;
@@ -1101,16 +1117,19 @@ static int run_pipeline(Run &R, Arena &ar) {
     int rc = emit_stage(p, b, q, o, R.k, s, tm, acc, selected, crounds, lazy, rec_lim, qx);
     if (rc) return rc;
     tm.mark(8, s);
-    // the largest feature errors again, with the records the emit stage added
-    if (lazy) HIPCHK(hipMemcpyAsync(emax.data(), b.emax, p.L * sizeof(float), hipMemcpyDeviceToHost, s));
     if (!selected) {
         rc = select_topk(p, b, R.k, s, acc);
         if (rc) return rc;
     } else {
-        // the copies of the flag and the feature errors complete here
+        // the feature errors again, with the records the emit stage added
+        std::vector<char> host(8 + p.L * sizeof(float));
+        HIPCHK(hipMemcpyAsync(host.data(), b.bad, host.size(), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
+        memcpy(&b.bad_h, host.data(), sizeof(int));
+        memcpy(b.emax_h.data(), host.data() + 8, p.L * sizeof(float));
     }
-    if (bad) return fail(PMP_EINVAL, "series has windows whose standard deviation underflows");
+    const std::vector<float> &emax = b.emax_h;
+    if (b.bad_h) return fail(PMP_EINVAL, "series has windows whose standard deviation underflows");
     int rounds = 0;
     double T = acc.size() == (size_t)R.k ? acc.back().d : INFINITY;
     if (R.dbg && R.dbg->t_start_scale > 0.0 && std::isfinite(T)) T *= R.dbg->t_start_scale;
@@ -1205,7 +1224,7 @@ static int run_pipeline(Run &R, Arena &ar) {
                 G.nmax2 = nmax * nmax;
                 G.sqrt2m = (float)std::sqrt(2.0 / m) * (1.0f + 1e-7f);
             }
-            HIPCHK(hipMemcpyAsync(b.gl, gl.data(), p.L * sizeof(GridLen), hipMemcpyHostToDevice, s));
+            HIPCHK(upload(b.gl, gl.data(), p.L * sizeof(GridLen), s));
             // windows and tiles of the lengths up to the bound (sorted by
             // length first, so they are a prefix)
             const int64_t Nq = p.len[l_lim].kbase + p.len[l_lim].n_index;
@@ -1329,7 +1348,12 @@ static int run_pipeline(Run &R, Arena &ar) {
 
     // ---- exact rows of the reported cells
     const int nacc = (int)acc.size();
-    std::vector<RowReq> rr(nacc);
+    // requests for k rows, then their initial minima and neighbours
+    std::vector<char> rbuf((size_t)R.k * (sizeof(RowReq) + 16), 0);
+    RowReq *rr = (RowReq *)rbuf.data();
+    uint64_t *r0 = (uint64_t *)(rr + R.k);
+    std::fill(r0, r0 + R.k, kInfBits);
+    std::fill(r0 + R.k, r0 + 2 * R.k, ~0ull);
     int64_t maxN = 1;
     for (int l = 0; l < p.L; ++l) maxN = std::max(maxN, p.len[l].n_index);
     for (int x = 0; x < nacc; ++x) {
@@ -1339,22 +1363,20 @@ static int run_pipeline(Run &R, Arena &ar) {
         double d = acc[x].d;
         memcpy(&rr[x].target, &d, 8);
     }
-    std::vector<unsigned long long> rmin(nacc), rarg(nacc);
-    std::vector<unsigned long long> sets(kCtrSlots * kCtrStride), ctr(C_NCOUNTERS);
+    // (the rows' results and the counters lie one after the other)
+    std::vector<unsigned long long> back(2 * (size_t)R.k + (R.st ? kCtrSlots * kCtrStride : 0));
     if (nacc) {
-        HIPCHK(hipMemcpyAsync(b.rows, rr.data(), nacc * sizeof(RowReq), hipMemcpyHostToDevice, s));
-        launch_fill_u64((uint64_t *)b.row_min, nacc, kInfBits, s);
-        launch_fill_u64((uint64_t *)b.row_arg, nacc, ~0ull, s);
+        HIPCHK(upload(b.rows, rbuf.data(), rbuf.size(), s));
         // each reported cell's exact row: its minimum (checked against the
         // certified value) and the smallest neighbour attaining that value
         launch_rows(q, b.rows, nacc, maxN, b.row_min, b.row_arg, s);
-        HIPCHK(hipMemcpyAsync(rmin.data(), b.row_min, nacc * 8, hipMemcpyDeviceToHost, s));
-        HIPCHK(hipMemcpyAsync(rarg.data(), b.row_arg, nacc * 8, hipMemcpyDeviceToHost, s));
     }
     tm.mark(7, s);
-    if (R.st)
-        HIPCHK(hipMemcpyAsync(sets.data(), b.counters, sets.size() * 8, hipMemcpyDeviceToHost, s));
+    if (nacc || R.st)
+        HIPCHK(hipMemcpyAsync(back.data(), b.row_min, back.size() * 8, hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
+    const unsigned long long *rmin = back.data(), *rarg = rmin + R.k, *sets = rarg + R.k;
+    std::vector<unsigned long long> ctr(C_NCOUNTERS);
     HIPCHK(hipGetLastError());
     if (nacc) {
         if (o.certify) {
