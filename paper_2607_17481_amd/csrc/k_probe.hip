@@ -131,14 +131,21 @@ __device__ __forceinline__ float group_lb(const FT *__restrict__ F, const RecPar
 // prefilter then test every pair against the smaller of the cut and the two
 // cells, so that nearly all pairs of noisy windows end without a distance:
 // at ECG-like 1M the four anchors after the first take 9.5 ms instead of 44.
-template <typename FT, bool kCut>
+//
+// kTeam: lanes per query.  Eight are enough while the queries fill the chip;
+// with fewer, a query takes up to the whole wavefront: its lanes look at that
+// many candidates at once and every eight of them verify their own survivor.
+// (A survivor verified beside another that would have ruled it out is work for
+// nothing, about 5 % of the verifications, on lanes that were idle.)
+template <typename FT, bool kCut, int kTeam>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0, double cut,
              Quant x) {
     // the anchor length of this block (blocks [blk0, blk0 + gridDim.x) of
     // the probe): the last length whose first probe block is at or below it
     // (uniform)
-    const int64_t gb = blk0 + (int64_t)blockIdx.x;
+    constexpr int kSplit = kTeam / kGroup;       // wavefronts per probe block of kProbeQ queries
+    const int64_t gb = blk0 + (int64_t)blockIdx.x / kSplit;
     int l = 0;
     {
         int hi = q.L - 1;
@@ -154,11 +161,15 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0,
     const float sqrt2m = (float)sqrt(2.0 / (double)m) * (1.0f + 1e-7f);
     const FT *const F = (const FT *)q.F;
     const int g = threadIdx.x & (kGroup - 1), grp = threadIdx.x / kGroup;
+    const int tl = threadIdx.x & (kTeam - 1);    // lane in the team
     const int64_t kend = L.kbase + L.n_index;
-    const int64_t k = L.kbase + (gb - L.pblk_base) * kProbeQ + grp;
+    const int64_t k0 = L.kbase + (gb - L.pblk_base) * kProbeQ +
+                       (int64_t)(blockIdx.x % kSplit) * (kWave / kTeam);
+    if (k0 >= kend) return;
+    const int64_t k = k0 + threadIdx.x / kTeam;
     uint32_t n_cand = 0, n_ver = 0;
 
-    // ---- the group's query (every lane of a group holds the same state)
+    // ---- the team's query (every lane of a team holds the same state)
     bool done = k >= kend;
     uint32_t prefix = 0, lim = 0;
     int64_t iq = 0;
@@ -208,10 +219,15 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0,
 
     const int gshift = grp * kGroup;
     auto group_bits = [&](bool b) -> uint32_t { return (uint32_t)(__ballot(b) >> gshift) & 0xFFu; };
+    auto team_bits = [&](bool b) -> uint64_t {
+        const uint64_t x = __ballot(b);
+        return kTeam == kWave ? x
+                              : (x >> (threadIdx.x & ~(kTeam - 1))) & ((1ull << (kTeam & 63)) - 1ull);
+    };
     for (;;) {
         // ---- every query still at work searches until it has a survivor
         for (;;) {
-            const bool search = !done && group_bits(alive) == 0u;
+            const bool search = !done && team_bits(alive) == 0ull;
             if (__ballot(search) == 0) break;
             if (!search) continue;
             if (j >= take) {
@@ -226,12 +242,12 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0,
                 bs = bb[b];
                 // the valid entries (cell <= lim) form a prefix of the bucket
                 // (in the own bucket the query and everything after it lie
-                // past the prefix); the group narrows it down eight ways
+                // past the prefix); the team narrows it down kTeam ways
                 int64_t lo = bs, hi = (int64_t)bb[b + 1];
                 while (lo < hi) {
-                    const int64_t step = (hi - lo + kGroup - 1) / kGroup;
-                    const int64_t at = lo + g * step;
-                    const int below = __popc(group_bits(at < hi && q.pcell[at] <= lim));
+                    const int64_t step = (hi - lo + kTeam - 1) / kTeam;
+                    const int64_t at = lo + tl * step;
+                    const int below = __popcll(team_bits(at < hi && q.pcell[at] <= lim));
                     if (below == 0) break;
                     hi = min(hi, lo + below * step);
                     lo += (below - 1) * step + 1;
@@ -253,9 +269,9 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0,
             // query's own cell has no value (its first distance often ends
             // the query: a repeat at 0), and no bound can prune below +inf
             const bool first = !kCut && Pq == INFINITY;
-            const int jj = j + g;
-            const bool in = jj < take && (!first || g == 0);
-            j += first ? 1 : kGroup;
+            const int jj = j + tl;
+            const bool in = jj < take && (!first || tl == 0);
+            j += first ? 1 : kTeam;
             double thr = 0.0;
             if (in) {
                 const int64_t cs = jj < rec ? vend - 1 - jj : bs + ((int64_t)(jj - rec) * span) / str;
@@ -283,7 +299,7 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0,
             }
         }
         if (__ballot(alive) == 0) break;
-        // ---- every query verifies its survivor of the smallest bound
+        // ---- every group of eight lanes verifies its survivor of the smallest bound
         const bool go = group_bits(alive) != 0u;
         uint32_t key = alive ? (__float_as_uint(lb) & ~7u) | (uint32_t)g : 0xFFFFFFFFu;
         key = min(key, xor_lane<1>(key));
@@ -319,11 +335,14 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0,
                 ? group_zdist_a(QwinA{qlo}, q.t, iq, muq, isq, vi, vmu, vis, vm, lim2)
                 : group_zdist_a(SeriesA{q.t}, q.t, iq, muq, isq, vi, vmu, vis, vm, lim2));
         if (!exact) dd = INFINITY;
-        if (go) {
+        double best = dd;                                  // the team's smallest
+#pragma unroll
+        for (int off = kGroup; off < kTeam; off <<= 1) best = fmin(best, __shfl_xor(best, off, kWave));
+        {
             const unsigned long long db = (unsigned long long)dbits(dd);
             if (g == 0 && exact) {
                 ++n_ver;
-                if (dd < Pq) {
+                if (dd < Pq && dd == best) {
                     atomicMin((unsigned long long *)&q.P[k], db);
                     q.hint[k] = (uint32_t)vi;
                 }
@@ -332,7 +351,7 @@ void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0,
                     q.hint[vk] = (uint32_t)iq;
                 }
             }
-            Pq = fmin(Pq, dd);
+            Pq = fmin(Pq, best);
             if (Pq == 0.0) done = true;
             if (g == sel || done || (double)lb >= fmax(Pq, Pc)) alive = false;
         }
@@ -362,24 +381,41 @@ __global__ __launch_bounds__(kBlock) void k_hot_buckets(const uint32_t *__restri
 
 static inline unsigned nblk(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
+// Lanes per query: the fewest that give every SIMD of the chip four wavefronts.
+// Measured on random walks with 51 lengths, one anchor's launch: 4,000 queries
+// 249 us at 8 lanes, 87 at 64; above 32,768 queries more lanes only add the
+// verifications that another would have spared.
+constexpr int64_t kProbeWaves = 4096;
+
+template <typename FT, int kTeam>
+static void launch_probe_team(const Req &q, const uint32_t *bstart, int64_t blk0, int64_t nblocks,
+                              int qcap, const Quant &x, hipStream_t s) {
+    hipLaunchKernelGGL((k_probe<FT, false, kTeam>), dim3((unsigned)(nblocks * (kTeam / kGroup))),
+                       dim3(kWave), (size_t)qcap * sizeof(double), s, q, bstart, qcap, blk0,
+                       INFINITY, x);
+}
+template <typename FT>
+static void launch_probe_ft(const Req &q, const uint32_t *bstart, int64_t blk0, int64_t nblocks,
+                            int qcap, double cut, const Quant &x, hipStream_t s) {
+    if (x.x16)                    // (over 2^20 windows: the queries fill the chip)
+        hipLaunchKernelGGL((k_probe<FT, true, kGroup>), dim3((unsigned)nblocks), dim3(kWave),
+                           (size_t)qcap * sizeof(double), s, q, bstart, qcap, blk0, cut, x);
+    else if (nblocks * 8 <= kProbeWaves)
+        launch_probe_team<FT, 64>(q, bstart, blk0, nblocks, qcap, x, s);
+    else if (nblocks * 4 <= kProbeWaves)
+        launch_probe_team<FT, 32>(q, bstart, blk0, nblocks, qcap, x, s);
+    else if (nblocks * 2 <= kProbeWaves)
+        launch_probe_team<FT, 16>(q, bstart, blk0, nblocks, qcap, x, s);
+    else
+        launch_probe_team<FT, 8>(q, bstart, blk0, nblocks, qcap, x, s);
+}
+
 void launch_probe(int precision, const Req &q, const uint32_t *bstart, int64_t blk0,
                   int64_t nblocks, int max_m, double cut, const Quant &x, hipStream_t s) {
     if (nblocks <= 0) return;
-    const dim3 grid((unsigned)nblocks);
     const int qcap = kQwinExtra + max_m;
-    const size_t lds = (size_t)qcap * sizeof(double);
-    if (precision == 0 && x.x16)
-        hipLaunchKernelGGL((k_probe<double, true>), grid, dim3(kWave), lds, s, q, bstart, qcap, blk0,
-                           cut, x);
-    else if (x.x16)
-        hipLaunchKernelGGL((k_probe<float, true>), grid, dim3(kWave), lds, s, q, bstart, qcap, blk0,
-                           cut, x);
-    else if (precision == 0)
-        hipLaunchKernelGGL((k_probe<double, false>), grid, dim3(kWave), lds, s, q, bstart, qcap,
-                           blk0, INFINITY, x);
-    else
-        hipLaunchKernelGGL((k_probe<float, false>), grid, dim3(kWave), lds, s, q, bstart, qcap, blk0,
-                           INFINITY, x);
+    if (precision == 0) launch_probe_ft<double>(q, bstart, blk0, nblocks, qcap, cut, x, s);
+    else launch_probe_ft<float>(q, bstart, blk0, nblocks, qcap, cut, x, s);
 }
 
 void launch_hot_buckets(const uint32_t *bstart, int64_t nb, int R, unsigned long long *cnt,
