@@ -47,66 +47,6 @@ struct QwinA {
     __device__ __forceinline__ double operator()(int64_t x) const { return probe_qwin[x - base]; }
 };
 
-namespace {
-
-constexpr int kPart = kRec / kGroup;          // record slots per lane of a group
-
-// A lane's part of one record (slots kPart g .. + kPart - 1).
-template <typename FT>
-struct RecPart {
-    FT v[kPart];
-};
-__device__ __forceinline__ RecPart<double> load_part(const double *rec, int g) {
-    const double2 a = ((const double2 *)rec)[2 * g], b = ((const double2 *)rec)[2 * g + 1];
-    return {{a.x, a.y, b.x, b.y}};
-}
-__device__ __forceinline__ RecPart<float> load_part(const float *rec, int g) {
-    const float4 a = ((const float4 *)rec)[g];
-    return {{a.x, a.y, a.z, a.w}};
-}
-
-// The certified bounds of lb_mem for the eight candidates of a group, whose
-// indices sit one per lane (kc; `want`: this lane's is wanted; m8: the wanted
-// ones of the group as a bit mask).  Lane g returns candidate g's bound (0 if
-// not wanted).  fq: this lane's part of the query's record, eq its error.
-template <typename FT>
-__device__ __forceinline__ float group_lb(const FT *__restrict__ F, const RecPart<FT> &fq, FT eq,
-                                          uint32_t kc, bool want, uint32_t m8, int g,
-                                          float sqrt2m) {
-    FT ec = 0;
-    if (want) ec = F[(int64_t)kc * kRec + kSlotErr];
-    FT p[kGroup];
-#pragma unroll
-    for (int c = 0; c < kGroup; ++c) {
-        p[c] = 0;
-        const uint32_t kcc = (uint32_t)__shfl((int)kc, c, kGroup);
-        if ((m8 >> c) & 1u) {
-            const RecPart<FT> r = load_part(F + (int64_t)kcc * kRec, g);
-            const FT e0 = r.v[0] - fq.v[0], e1 = r.v[1] - fq.v[1];
-            FT e2 = r.v[2] - fq.v[2], e3 = r.v[3] - fq.v[3];
-            if (g == kGroup - 1) e2 = e3 = 0;           // the error and the norm
-            p[c] = e0 * e0 + e1 * e1 + e2 * e2 + e3 * e3;
-        }
-    }
-    // transposed reduction: after it lane g holds the sum of candidate g
-    FT h[4], q[2];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const FT send = (g & 4) ? p[c] : p[c + 4], keep = (g & 4) ? p[c + 4] : p[c];
-        h[c] = keep + xor_lane<4>(send);
-    }
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        const FT send = (g & 2) ? h[c] : h[c + 2], keep = (g & 2) ? h[c + 2] : h[c];
-        q[c] = keep + xor_lane<2>(send);
-    }
-    const FT send = (g & 1) ? q[0] : q[1], keep = (g & 1) ? q[1] : q[0];
-    const FT acc = keep + xor_lane<1>(send);
-    return lb_of(acc, eq + ec, sqrt2m);
-}
-
-}  // namespace
-
 // Queries are taken in (length, start) order (indexed position k), so that
 // neighbouring windows, which tend to cost alike, share a wavefront; only the
 // anchor lengths are probed (Sec. 3.3), each from its first probe block, so a

@@ -8,20 +8,19 @@
 //            normalized spectral features F (Sec. 3.2) by a direct FP64 DFT
 //            against a per-anchor basis table, their error bound, SimHash
 //            key and projection margins (Sec. 3.4);
-//   probe    one wavefront per completed window: its exact-prefix bucket and
+//   probe    one block per completed window: its exact-prefix bucket and
 //            the h Hamming-1 buckets of its smallest-margin prefix bits, at
 //            most R candidates (the rest of the budget spent half on a
 //            bucket's most recent entries, half at even intervals over it),
 //            the Parseval prune against max(best_q, P[c]) (Lemma 2), exact
 //            FP64 distances of the survivors; the query's own best is
 //            written, the candidates' improvements are buffered;
-//   apply    one block merges the buffered improvements into the profile;
+//   finish   one block merges the buffered improvements into the profile;
 //            equal distances resolve to the smallest query start, so the
 //            result does not depend on the order the searches ran in
-//            (Prop. 5);
-//   runs     the batch's windows of each anchor become a new sorted run of
-//            its directory, and the newest runs are merged as a binary
-//            counter.
+//            (Prop. 5); one block per anchor makes the batch's windows a new
+//            sorted run of its directory and merges the newest runs as a
+//            binary counter (large merges in launches of their own).
 // The directory of an anchor is its indexed windows in arrival order, cut
 // into runs sorted by (key, start).  A bucket at depth d is the d-bit key
 // prefix, so it is one contiguous range of every run, found by binary
@@ -63,8 +62,8 @@ constexpr int kFDs = 2 * (kMaxK - 1);          // 30 feature reals
 
 }  // namespace
 
-// Basis tables: anchor a, row c (bin k = c / 2 + 1; even rows cos, odd rows
-// -sin), sample r: the value at the exact phase ((k r) mod m) / m.
+// Basis tables: anchor a, sample r, feature c (bin k = c / 2 + 1; even ones
+// cos, odd ones -sin): the value at the exact phase ((k r) mod m) / m.
 __global__ __launch_bounds__(kBlock) void k_stream_basis(const SAnchor *__restrict__ anc, int na,
                                                          double *__restrict__ basis) {
     const int a = blockIdx.y;
@@ -72,7 +71,7 @@ __global__ __launch_bounds__(kBlock) void k_stream_basis(const SAnchor *__restri
     const int m = anc[a].m, kp = anc[a].kprime;
     const int64_t o = anc[a].bbase;
     for (int x = blockIdx.x * kBlock + threadIdx.x; x < 2 * kp * m; x += gridDim.x * kBlock) {
-        const int c = x / m, r = x % m;
+        const int r = x / (2 * kp), c = x % (2 * kp);
         const int k = c / 2 + 1;
         const int64_t j = ((int64_t)k * r) % m;
         double sn, cs;
@@ -81,7 +80,11 @@ __global__ __launch_bounds__(kBlock) void k_stream_basis(const SAnchor *__restri
     }
 }
 
-// One completed non-constant window per block (one wavefront).
+// One completed non-constant window per block (one wavefront).  Two serial
+// chains over the window bound it (the moments' and the features' sums, whose
+// order is part of the result); the features' table is laid out by sample, so
+// that a step reads one line instead of one per feature (ECG-like batches of
+// 500 windows: 26 us).
 __global__ __launch_bounds__(kWave) void k_stream_windows(StreamDev S) {
     extern __shared__ double ys[];                 // the window's samples, then y = x - mu
     __shared__ double s_mu, s_is;
@@ -113,9 +116,11 @@ __global__ __launch_bounds__(kWave) void k_stream_windows(StreamDev S) {
     // feature c = lane: X_c = sum_r y_r B[c][r], in order, then F = X / sigma
     double f = 0.0;
     if (lane < 2 * kp) {
-        const double *b = S.basis + A.bbase + (int64_t)lane * m;
+        const double *b = S.basis + A.bbase + lane;
+        const int ld = 2 * kp;
         double x = 0.0;
-        for (int r = 0; r < m; ++r) x = fma(ys[r], b[r], x);
+#pragma unroll 8
+        for (int r = 0; r < m; ++r) x = fma(ys[r], b[(int64_t)r * ld], x);
         f = x * is;
     }
     const double nrm = sqrt(wave_sum(lane < kFDs ? f * f : 0.0)) * (1.0 + 1e-15);
@@ -158,29 +163,56 @@ __global__ __launch_bounds__(kWave) void k_stream_windows(StreamDev S) {
     }
 }
 
-// One completed window per block (one wavefront): candidates, prune, verify.
-__global__ __launch_bounds__(kWave) void k_stream_probe(StreamDev S) {
-    __shared__ uint32_t roff[kStreamMaxRuns];      // bucket offset of each run (exclusive scan)
-    __shared__ uint32_t rlo[kStreamMaxRuns];       // the bucket's first position in each run
+// One completed window per block of kProbeWaves wavefronts: candidates, prune,
+// verify.  Every wavefront follows the same candidates, 64 a turn, of which each
+// group of eight lanes takes two: it reads their records and evaluates its
+// survivors; the block's best goes through LDS after every turn.
+//
+// A chain of dependent loads bounds it (a batch completes a few hundred windows,
+// too few to hide one behind another): bounds of the buckets in the runs, entry,
+// cell value, record, samples.  With one wavefront a window that searched a
+// bucket's runs when it came to the bucket, read a record per lane and took up
+// to eight turns of verification per 64 candidates, an ECG-like batch of 500
+// windows took 97 us; with all buckets searched at once, records read by groups
+// and 32 pairs verified at a time it takes 53.
+constexpr int kProbeWaves = 4;
+constexpr int kTurn = kWave;                          // candidates per turn
+constexpr int kPerGroup = kTurn / (kProbeWaves * kPerRound);   // of them per group of lanes
+
+__global__ __launch_bounds__(kProbeWaves *kWave) void k_stream_probe(StreamDev S) {
+    extern __shared__ double qwin[];               // the query's samples
+    __shared__ uint32_t roff[kProbeSlots + 1][kStreamMaxRuns];   // bucket: offset of each run's part
+    __shared__ uint32_t rlo[kProbeSlots + 1][kStreamMaxRuns];    // and its first position in the run
+    __shared__ uint32_t tot[kProbeSlots + 1], pre[kProbeSlots + 1];
+    __shared__ int nbk;
+    __shared__ double wbest[2][kProbeWaves];
+    __shared__ int32_t wbestc[2][kProbeWaves];
+    __shared__ uint32_t wver[kProbeWaves];
     const int j = blockIdx.x;
-    const int lane = threadIdx.x;
+    const int tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
+    const int g = lane & (kGroup - 1), grp = lane / kGroup;
     const int a = S.la[j];
     const int64_t q = S.lq[j];
     const SAnchor &A = S.anc[a];
     const int m = A.m, d = A.depth, nr = A.nruns;
-    const int64_t cq = A.cbase + q;
-    const double *Fq = S.F + cq * kRec;
+    const int64_t cbase = A.cbase, cq = cbase + q;
+    const double *F = S.F + cbase * kRec;
+    const RecPart<double> fq = load_part(S.F + cq * kRec, g);
+    const double eq = S.F[cq * kRec + kSlotErr];
     const double muq = S.mu[cq], isq = S.isig[cq];
     const float sqrt2m = (float)sqrt(2.0 / (double)m) * (1.0f + 1e-7f);
     const uint32_t key = S.bkey[j];
+    const int sh = S.B - d;
+    for (int r = tid; r < m; r += kProbeWaves * kWave) qwin[r] = S.t[q + r];
 
-    // Hamming-1 probes: the h prefix bits of smallest margin, in that order
-    int pbit[kProbeSlots];
-    {
+    // the buckets: the key's own prefix, then the Hamming-1 probes, the h
+    // prefix bits of smallest margin in that order
+    if (w == 0) {
+        const uint32_t pfx = d > 0 ? key >> sh : 0u;
+        if (lane == 0) pre[0] = pfx;
         float mg = lane < d ? S.bmarg[(int64_t)j * kMaxBits + lane] : INFINITY;
-        for (int x = 0; x < kProbeSlots; ++x) {
-            pbit[x] = -1;
-            if (x >= A.probes) continue;
+        int n = 1;
+        for (int x = 0; x < kProbeSlots && x < A.probes; ++x) {
             // smallest (margin, bit) over the lanes still in
             float bm = mg;
             int bl = lane < d ? lane : kWave;
@@ -194,169 +226,219 @@ __global__ __launch_bounds__(kWave) void k_stream_probe(StreamDev S) {
                 }
             }
             if (bl >= d) break;
-            pbit[x] = bl;
+            if (lane == 0) pre[n] = pfx ^ (1u << (d - 1 - bl));
             if (lane == bl) mg = INFINITY;
+            ++n;
         }
+        if (lane == 0) nbk = n;
     }
-
-    double best = INFINITY;                         // wave-uniform
-    int32_t bestc = -1;
-    unsigned long long n_cand = 0, n_ver = 0;
-    int brem = S.R;
-    const int sh = S.B - d;
-    const uint32_t pfx = d > 0 ? key >> sh : 0u;
-
-    // inspect one candidate per lane (c < 0: none)
-    auto inspect = [&](int32_t c) {
-        const bool valid = c >= 0 && q - (int64_t)c >= S.excl;
-        int64_t cc = 0;
-        double Pc = INFINITY, thr = INFINITY, muc = 0.0, isc = 0.0;
-        bool prop = false;
-        if (valid) {
-            ++n_cand;
-            cc = A.cbase + c;
-            Pc = bitsd(S.P[cc]);
-            thr = fmax(best, Pc);
-            const float lb = lb_mem<double>(Fq, S.F + cc * kRec, sqrt2m);
-            prop = (double)lb < thr;
-            if (prop) {
-                muc = S.mu[cc];
-                isc = S.isig[cc];
-            }
-        }
-        const uint64_t mask = __ballot(prop);
-        double lb_d = INFINITY;
-        int32_t lb_c = -1;
-        if (mask)
-            verify_proposals(mask, SeriesA{S.t}, S.t, q, muq, isq, (int64_t)c, muc, isc, m,
-                             [&](double dd) {
-                ++n_ver;
-                if (dd < Pc) {
-                    const uint32_t slot = atomicAdd(S.nupd, 1u);
-                    if (slot < S.updcap)
-                        S.upd[slot] = SUpdate{(uint32_t)cc, (int32_t)q, dbits(dd)};
-                    else
-                        atomicAdd(&S.counters[CS_DROP], 1ull);
-                }
-                if (dd < INFINITY) {
-                    lb_d = dd;
-                    lb_c = c;
-                }
-            }, exit_bound(thr));
-        // the query's best over the round: smallest (distance, start)
-#pragma unroll
-        for (int off = kWave / 2; off > 0; off >>= 1) {
-            const double od = __shfl_xor(lb_d, off, kWave);
-            const int32_t oc = __shfl_xor(lb_c, off, kWave);
-            if (od < lb_d || (od == lb_d && (uint32_t)oc < (uint32_t)lb_c)) {
-                lb_d = od;
-                lb_c = oc;
-            }
-        }
-        if (lb_c >= 0 && (lb_d < best || (lb_d == best && lb_c < bestc))) {
-            best = lb_d;
-            bestc = lb_c;
-        }
-        return valid;
-    };
-
-    for (int pi = 0; pi <= A.probes && brem > 0; ++pi) {
-        uint32_t p = pfx;
-        if (pi > 0) {
-            if (pbit[pi - 1] < 0) break;
-            p ^= 1u << (d - 1 - pbit[pi - 1]);
-        }
+    __syncthreads();
+    const int nb = nbk;
+    const uint32_t *keys = S.skey + cbase;
+    for (int x = tid; x < nb * nr; x += kProbeWaves * kWave) {
+        const int pi = x / nr, r = x - pi * nr;
+        const uint32_t p = pre[pi], e = A.runs[r + 1];
         const uint32_t klo = d > 0 ? p << sh : 0u;
         const uint32_t khi = d > 0 ? (p + 1u) << sh : 1u << S.B;
-        uint32_t lo = 0, sz = 0;
-        if (lane < nr) {
-            const uint32_t *keys = S.skey + A.cbase;
-            lo = lower_bound_u32(keys, A.runs[lane], A.runs[lane + 1], klo);
-            sz = lower_bound_u32(keys, lo, A.runs[lane + 1], khi) - lo;
+        // both ends of the range in one chain
+        uint32_t l0 = A.runs[r], h0 = e, l1 = l0, h1 = e;
+        while (l0 < h0 || l1 < h1) {
+            const uint32_t m0 = l0 + ((h0 - l0) >> 1), m1 = l1 + ((h1 - l1) >> 1);
+            const uint32_t k0 = l0 < h0 ? keys[m0] : 0u, k1 = l1 < h1 ? keys[m1] : 0u;
+            if (l0 < h0) {
+                if (k0 < klo) l0 = m0 + 1; else h0 = m0;
+            }
+            if (l1 < h1) {
+                if (k1 < khi) l1 = m1 + 1; else h1 = m1;
+            }
         }
+        rlo[pi][r] = l0;
+        roff[pi][r] = l1 - l0;
+    }
+    __syncthreads();
+    for (int pi = w; pi < nb; pi += kProbeWaves) {
+        const uint32_t sz = lane < nr ? roff[pi][lane] : 0u;
         uint32_t incl = sz;
 #pragma unroll
         for (int off = 1; off < kWave; off <<= 1) {
             const uint32_t y = __shfl_up(incl, off, kWave);
             if (lane >= off) incl += y;
         }
-        const uint32_t total = __shfl(incl, kWave - 1, kWave);
-        if (lane < nr) {
-            roff[lane] = incl - sz;
-            rlo[lane] = lo;
+        if (lane < nr) roff[pi][lane] = incl - sz;
+        if (lane == kWave - 1) tot[pi] = incl;
+    }
+    __syncthreads();
+
+    double best = INFINITY;                         // the same in the whole block
+    int32_t bestc = -1;
+    unsigned long long n_cand = 0;
+    uint32_t n_ver = 0;
+    int brem = S.R, turn = 0;
+    struct QueryA {
+        const double *w;
+        int64_t base;
+        __device__ __forceinline__ double operator()(int64_t x) const { return w[x - base]; }
+    };
+    const QueryA qa{qwin, q};
+
+    // one turn: one candidate per lane, the same in every wavefront (c < 0:
+    // none); returns how many are valid
+    auto inspect = [&](int32_t c) -> int {
+        const uint64_t vmask = __ballot(c >= 0 && q - (int64_t)c >= S.excl);
+        const int nv = __popcll(vmask);
+        if (nv == 0) return 0;                      // (uniform in the block)
+        n_cand += (unsigned long long)nv;
+        // this lane's candidate: the g-th of its group's kPerGroup
+        const int src = (w * kPerRound + grp) * kPerGroup + (g < kPerGroup ? g : 0);
+        const int32_t cm = __shfl(c, src, kWave);
+        const bool mine = g < kPerGroup && ((vmask >> src) & 1ull);
+        double Pc = INFINITY, thr = INFINITY, muc = 0.0, isc = 0.0;
+        if (mine) {
+            Pc = bitsd(S.P[cbase + cm]);
+            thr = fmax(best, Pc);
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        auto group_bits = [&](bool b) -> uint32_t {
+            return (uint32_t)(__ballot(b) >> (grp * kGroup)) & 0xFFu;
+        };
+        const uint32_t m8 = group_bits(mine);
+        float lb = 0.0f;
+        if (m8) lb = group_lb<double>(F, fq, eq, (uint32_t)cm, mine, m8, g, sqrt2m);
+        const bool prop = mine && (double)lb < thr;
+        if (prop) {
+            muc = S.mu[cbase + cm];
+            isc = S.isig[cbase + cm];
+        }
+        const uint32_t p8 = group_bits(prop);
+        double lb_d = INFINITY;
+        int32_t lb_c = -1;
+#pragma unroll
+        for (int x = 0; x < kPerGroup; ++x) {
+            if (__ballot((p8 >> x) & 1u) == 0) continue;
+            const bool go = (p8 >> x) & 1u;
+            const int32_t vc = __shfl(cm, x, kGroup);
+            const double vP = __shfl(Pc, x, kGroup), vthr = __shfl(thr, x, kGroup);
+            const double vmu = __shfl(muc, x, kGroup), vis = __shfl(isc, x, kGroup);
+            const double dd = snap(group_zdist_a(qa, S.t, q, muq, isq, go ? (int64_t)vc : q, vmu, vis,
+                                                 go ? m : 0, exit_bound(vthr)));
+            if (go && g == 0) {
+                ++n_ver;
+                if (dd < vP) {
+                    const uint32_t slot = atomicAdd(S.nupd, 1u);
+                    if (slot < S.updcap)
+                        S.upd[slot] = SUpdate{(uint32_t)(cbase + vc), (int32_t)q, dbits(dd)};
+                    else
+                        count_add(S.counters, CS_DROP, 1ull);
+                }
+                if (dd < lb_d || (dd < INFINITY && dd == lb_d && vc < lb_c)) {
+                    lb_d = dd;
+                    lb_c = vc;
+                }
+            }
+        }
+        // the query's best over the turn: smallest (distance, start)
+        auto take = [](double &bd, int32_t &bc, double od, int32_t oc) {
+            if (od < bd || (od == bd && (uint32_t)oc < (uint32_t)bc)) {
+                bd = od;
+                bc = oc;
+            }
+        };
+#pragma unroll
+        for (int off = kGroup; off < kWave; off <<= 1)
+            take(lb_d, lb_c, __shfl_xor(lb_d, off, kWave), __shfl_xor(lb_c, off, kWave));
+        // (two sets in turn: one barrier a turn)
+        if (lane == 0) {
+            wbest[turn & 1][w] = lb_d;
+            wbestc[turn & 1][w] = lb_c;
+        }
+        __syncthreads();
+        lb_d = wbest[turn & 1][0];
+        lb_c = wbestc[turn & 1][0];
+#pragma unroll
+        for (int v = 1; v < kProbeWaves; ++v) take(lb_d, lb_c, wbest[turn & 1][v], wbestc[turn & 1][v]);
+        ++turn;
+        if (lb_c >= 0 && (lb_d < best || (lb_d == best && lb_c < bestc))) {
+            best = lb_d;
+            bestc = lb_c;
+        }
+        return nv;
+    };
+
+    for (int pi = 0; pi < nb && brem > 0; ++pi) {
+        const uint32_t total = tot[pi];
         if (total == 0) continue;
         // bucket position (runs oldest first) -> window start
         auto entry = [&](uint32_t pos) -> int32_t {
             int rl = 0, rh = nr - 1;
             while (rl < rh) {
                 const int mid = (rl + rh + 1) >> 1;
-                if (roff[mid] <= pos) rl = mid; else rh = mid - 1;
+                if (roff[pi][mid] <= pos) rl = mid; else rh = mid - 1;
             }
-            return (int32_t)S.perm[A.cbase + rlo[rl] + (pos - roff[rl])];
+            return (int32_t)S.perm[cbase + rlo[pi][rl] + (pos - roff[pi][rl])];
         };
         if (total <= (uint32_t)brem) {
             int used = 0;
-            for (uint32_t base = 0; base < total; base += kWave) {
+            for (uint32_t base = 0; base < total; base += kTurn) {
                 const uint32_t pos = base + lane;
-                used += __popcll(__ballot(inspect(pos < total ? entry(pos) : -1)));
+                used += inspect(pos < total ? entry(pos) : -1);
             }
             brem -= used;
         } else {
             // more entries than budget: half on the most recent, half at
             // even intervals over the older rest
             const int nrec = brem / 2, nstr = brem - nrec;
-            for (int base = 0; base < nrec; base += kWave) {
+            for (int base = 0; base < nrec; base += kTurn) {
                 const int x = base + lane;
                 inspect(x < nrec ? entry(total - 1u - (uint32_t)x) : -1);
             }
             const uint64_t span = total - (uint32_t)nrec;
-            for (int base = 0; base < nstr; base += kWave) {
+            for (int base = 0; base < nstr; base += kTurn) {
                 const int x = base + lane;
                 inspect(x < nstr ? entry((uint32_t)((uint64_t)x * span / (uint64_t)nstr)) : -1);
             }
             brem = 0;
         }
     }
-    if (lane == 0) {
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) n_ver += __shfl_xor(n_ver, off, kWave);
+    if (lane == 0) wver[w] = n_ver;
+    __syncthreads();
+    if (tid == 0) {
         S.P[cq] = dbits(best);
         S.I[cq] = bestc;
-    }
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        n_cand += __shfl_xor(n_cand, off, kWave);
-        n_ver += __shfl_xor(n_ver, off, kWave);
-    }
-    if (lane == 0) {
-        if (n_cand) atomicAdd(&S.counters[CS_CAND], n_cand);
-        if (n_ver) atomicAdd(&S.counters[CS_VER], n_ver);
+        uint32_t v = 0;
+        for (int x = 0; x < kProbeWaves; ++x) v += wver[x];
+        if (n_cand) count_add(S.counters, CS_CAND, n_cand);
+        if (v) count_add(S.counters, CS_VER, (unsigned long long)v);
     }
 }
 
-// The batch's buffered improvements into the profile (one block).  Every
-// buffered distance is below its cell's value when the searches started, so
-// each touched cell drops to the smallest one; its neighbour is the smallest
-// query start among those reaching that value.
-__global__ __launch_bounds__(1024) void k_stream_apply(StreamDev S) {
+// The end of a batch, a block per anchor and one more, all independent: the
+// anchors' directories and the buffered improvements.  As launches of their own
+// the new runs, merges, copies back and improvements took 9 + 8 + 5 + 5.5 us of
+// an ECG-like batch, and 5 us of host time each; together KSF.
+constexpr int kFinish = 1024;
+
+// The buffered improvements into the profile.  Every buffered distance is
+// below its cell's value when the searches started, so each touched cell drops
+// to the smallest one; its neighbour is the smallest query start among those
+// reaching that value.
+__device__ __forceinline__ void stream_apply(const StreamDev &S) {
     const uint32_t n = min(*S.nupd, S.updcap);
-    for (uint32_t x = threadIdx.x; x < n; x += blockDim.x)
+    for (uint32_t x = threadIdx.x; x < n; x += kFinish)
         __hip_atomic_store(&S.Icand[S.upd[x].cell], INT_MAX, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    for (uint32_t x = threadIdx.x; x < n; x += blockDim.x)
+    for (uint32_t x = threadIdx.x; x < n; x += kFinish)
         atomicMin((unsigned long long *)&S.P[S.upd[x].cell], (unsigned long long)S.upd[x].d);
     __syncthreads();
     // values other threads changed by atomics are read at device scope (not
     // from this compute unit's cache)
-    for (uint32_t x = threadIdx.x; x < n; x += blockDim.x) {
+    for (uint32_t x = threadIdx.x; x < n; x += kFinish) {
         const SUpdate u = S.upd[x];
         if (__hip_atomic_load(&S.P[u.cell], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == u.d)
             atomicMin(&S.Icand[u.cell], u.j);
     }
     __syncthreads();
-    for (uint32_t x = threadIdx.x; x < n; x += blockDim.x) {
+    for (uint32_t x = threadIdx.x; x < n; x += kFinish) {
         const uint32_t c = S.upd[x].cell;
         S.I[c] = __hip_atomic_load(&S.Icand[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -367,28 +449,66 @@ __global__ __launch_bounds__(1024) void k_stream_apply(StreamDev S) {
     }
 }
 
-// The batch's windows of each anchor as a new run, sorted by (key, start)
-// (one block per anchor; the list holds an anchor's windows in start order).
-__global__ __launch_bounds__(kBlock) void k_stream_newruns(StreamDev S) {
+// Block a < na: the batch's windows of anchor a as a new run, sorted by (key,
+// start) (the list holds an anchor's windows in start order), then the merge of
+// its newest runs (binary counter) if one block holds it: each element's place
+// is its rank in its own run plus, in every other run, the entries before it (an
+// older run's equal keys come first).  Larger merges: k_stream_merge.
+__global__ __launch_bounds__(kFinish) void k_stream_finish(StreamDev S, int na,
+                                                           const SMerge *__restrict__ mg) {
+    __shared__ uint32_t mk[kStreamMergeLds], mp[kStreamMergeLds];
+    if ((int)blockIdx.x == na) {
+        stream_apply(S);
+        return;
+    }
     const SAnchor &A = S.anc[blockIdx.x];
     const int nn = A.nnew;
-    for (int i = threadIdx.x; i < nn; i += kBlock) {
-        const uint32_t ki = S.bkey[A.j0 + i];
+    for (int i0 = 0; i0 < nn; i0 += kFinish) {
+        const int i = i0 + threadIdx.x;
+        const uint32_t ki = i < nn ? S.bkey[A.j0 + i] : 0u;
         int rank = 0;
-        for (int x = 0; x < nn; ++x) {
-            const uint32_t kx = S.bkey[A.j0 + x];
-            rank += kx < ki || (kx == ki && x < i);
+        for (int x0 = 0; x0 < nn; x0 += (int)kStreamMergeLds) {
+            const int xn = min(nn - x0, (int)kStreamMergeLds);
+            __syncthreads();
+            for (int x = threadIdx.x; x < xn; x += kFinish) mk[x] = S.bkey[A.j0 + x0 + x];
+            __syncthreads();
+            for (int x = 0; x < xn; ++x) {
+                const uint32_t kx = mk[x];
+                rank += kx < ki || (kx == ki && x0 + x < i);
+            }
         }
-        const int64_t pos = A.cbase + A.nidx + rank;
-        S.skey[pos] = ki;
-        S.perm[pos] = (uint32_t)S.lq[A.j0 + i];
+        if (i < nn) {
+            const int64_t pos = A.cbase + A.nidx + rank;
+            S.skey[pos] = ki;
+            S.perm[pos] = (uint32_t)S.lq[A.j0 + i];
+        }
+    }
+    if (A.merge < 0) return;
+    __syncthreads();                               // (the new run is read back)
+    const SMerge &M = mg[A.merge];
+    const uint32_t r0 = M.runs[0], n = M.runs[M.nruns] - r0;
+    for (uint32_t x = threadIdx.x; x < n; x += kFinish) {
+        mk[x] = S.skey[M.cbase + r0 + x];
+        mp[x] = S.perm[M.cbase + r0 + x];
+    }
+    __syncthreads();
+    for (uint32_t x = threadIdx.x; x < n; x += kFinish) {
+        const uint32_t k = mk[x];
+        int r = 0;
+        while (r + 1 < M.nruns && M.runs[r + 1] - r0 <= x) ++r;
+        uint32_t out = x - (M.runs[r] - r0);
+        for (int o = 0; o < M.nruns; ++o) {
+            if (o == r) continue;
+            const uint32_t b0 = M.runs[o] - r0, b1 = M.runs[o + 1] - r0;
+            out += (o < r ? upper_bound_u32(mk, b0, b1, k) : lower_bound_u32(mk, b0, b1, k)) - b0;
+        }
+        S.skey[M.cbase + r0 + out] = k;
+        S.perm[M.cbase + r0 + out] = mp[x];
     }
 }
 
-// Merges of the newest runs of an anchor into one (binary counter): each
-// element's place is its rank in its own run plus, in every other run, the
-// entries before it (an older run's equal keys come first).  Written to the
-// scratch arrays, then copied back.
+// The merges of more entries than one block holds, placed likewise.  Written to
+// the scratch arrays, then copied back.
 __global__ __launch_bounds__(kBlock) void k_stream_merge(StreamDev S, const SMerge *__restrict__ mg,
                                                          int nmerge, int64_t nthreads) {
     const int64_t x = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -454,18 +574,15 @@ void launch_stream_windows(const StreamDev &S, int max_m, hipStream_t s) {
                        (size_t)max_m * sizeof(double), s, S);
 }
 
-void launch_stream_probe(const StreamDev &S, hipStream_t s) {
+void launch_stream_probe(const StreamDev &S, int max_m, hipStream_t s) {
     if (S.nlist <= 0) return;
-    hipLaunchKernelGGL(k_stream_probe, dim3((unsigned)S.nlist), dim3(kWave), 0, s, S);
+    hipLaunchKernelGGL(k_stream_probe, dim3((unsigned)S.nlist), dim3(kProbeWaves * kWave),
+                       (size_t)max_m * sizeof(double), s, S);
 }
 
-void launch_stream_apply(const StreamDev &S, hipStream_t s) {
-    hipLaunchKernelGGL(k_stream_apply, dim3(1), dim3(1024), 0, s, S);
-}
-
-void launch_stream_newruns(const StreamDev &S, int na, hipStream_t s) {
-    if (na <= 0) return;
-    hipLaunchKernelGGL(k_stream_newruns, dim3((unsigned)na), dim3(kBlock), 0, s, S);
+void launch_stream_finish(const StreamDev &S, int na, const SMerge *mg, hipStream_t s) {
+    if (S.nlist <= 0) return;
+    hipLaunchKernelGGL(k_stream_finish, dim3((unsigned)na + 1), dim3(kFinish), 0, s, S, na, mg);
 }
 
 void launch_stream_merge(const StreamDev &S, const SMerge *mg, int nmerge, int64_t nthreads,

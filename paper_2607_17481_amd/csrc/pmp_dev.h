@@ -526,6 +526,62 @@ __device__ __forceinline__ float lb_mem(const FT *__restrict__ fq, const FT *__r
     return lb_of(acc, fq[kSlotErr] + fc[kSlotErr], sqrt2m);
 }
 
+constexpr int kPart = kRec / kGroup;          // record slots per lane of a group
+
+// A lane's part of one record (slots kPart g .. + kPart - 1).
+template <typename FT>
+struct RecPart {
+    FT v[kPart];
+};
+__device__ __forceinline__ RecPart<double> load_part(const double *rec, int g) {
+    const double2 a = ((const double2 *)rec)[2 * g], b = ((const double2 *)rec)[2 * g + 1];
+    return {{a.x, a.y, b.x, b.y}};
+}
+__device__ __forceinline__ RecPart<float> load_part(const float *rec, int g) {
+    const float4 a = ((const float4 *)rec)[g];
+    return {{a.x, a.y, a.z, a.w}};
+}
+
+// The certified bounds of lb_mem for the eight candidates of a group, whose
+// indices sit one per lane (kc; `want`: this lane's is wanted; m8: the wanted
+// ones of the group as a bit mask).  Lane g returns candidate g's bound (0 if
+// not wanted).  fq: this lane's part of the query's record, eq its error.
+template <typename FT>
+__device__ __forceinline__ float group_lb(const FT *__restrict__ F, const RecPart<FT> &fq, FT eq,
+                                          uint32_t kc, bool want, uint32_t m8, int g,
+                                          float sqrt2m) {
+    FT ec = 0;
+    if (want) ec = F[(int64_t)kc * kRec + kSlotErr];
+    FT p[kGroup];
+#pragma unroll
+    for (int c = 0; c < kGroup; ++c) {
+        p[c] = 0;
+        const uint32_t kcc = (uint32_t)__shfl((int)kc, c, kGroup);
+        if ((m8 >> c) & 1u) {
+            const RecPart<FT> r = load_part(F + (int64_t)kcc * kRec, g);
+            const FT e0 = r.v[0] - fq.v[0], e1 = r.v[1] - fq.v[1];
+            FT e2 = r.v[2] - fq.v[2], e3 = r.v[3] - fq.v[3];
+            if (g == kGroup - 1) e2 = e3 = 0;           // the error and the norm
+            p[c] = e0 * e0 + e1 * e1 + e2 * e2 + e3 * e3;
+        }
+    }
+    // transposed reduction: after it lane g holds the sum of candidate g
+    FT h[4], q[2];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const FT send = (g & 4) ? p[c] : p[c + 4], keep = (g & 4) ? p[c + 4] : p[c];
+        h[c] = keep + xor_lane<4>(send);
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const FT send = (g & 2) ? h[c] : h[c + 2], keep = (g & 2) ? h[c + 2] : h[c];
+        q[c] = keep + xor_lane<2>(send);
+    }
+    const FT send = (g & 1) ? q[0] : q[1], keep = (g & 1) ? q[1] : q[0];
+    const FT acc = keep + xor_lane<1>(send);
+    return lb_of(acc, eq + ec, sqrt2m);
+}
+
 // Verification of the proposals of a wavefront.  Every lane whose bit is set
 // in `mask` has a proposal (a, b: window starts; mua, ia, mub, ib: moments;
 // m; lim2: the squared distance at or above which the result is of no use,
@@ -594,16 +650,19 @@ __device__ __forceinline__ void verify_proposals(uint64_t mask, A qa, const doub
 // arrival order, cut into sorted runs: run r holds the indexed positions
 // [runs[r], runs[r + 1]), sorted by (SimHash key, start).
 constexpr int kStreamMaxRuns = 48;
+constexpr uint32_t kStreamMergeLds = 4096;    // entries of a merge that one block holds
 struct SAnchor {
     int32_t m, kprime;
     int64_t cbase;        // first cell
-    int64_t bbase;        // offset of the basis table (2 K' rows of m doubles)
+    int64_t bbase;        // offset of the basis table (m rows of 2 K' doubles)
     int32_t nidx;         // indexed windows before this batch
     int32_t nnew;         // indexed windows this batch completes
     int32_t j0;           // first entry of the batch list that is this anchor's
     int32_t depth;        // directory depth d (Prop. 4)
     int32_t probes;       // Hamming-1 probes h
     int32_t nruns;
+    int32_t merge;        // the merge that k_stream_finish does for it (-1: none)
+    int32_t pad_;
     uint32_t runs[kStreamMaxRuns + 1];
 };
 
@@ -646,7 +705,7 @@ struct StreamDev {
     SUpdate *upd;
     uint32_t *nupd;
     uint32_t updcap;
-    unsigned long long *counters;   // kStreamCounters
+    unsigned long long *counters;   // kCtrSlots sets, kCtrStride apart (count_add)
 };
 enum { CS_CAND = 0, CS_VER, CS_UPD, CS_DROP, kStreamCounters };
 
@@ -832,9 +891,8 @@ void launch_rows(const Req &q, const RowReq *rr, int nrows, int64_t maxN,
 void launch_stream_basis(const SAnchor *anc, int na, int64_t elems, double *basis,
                          hipStream_t s);
 void launch_stream_windows(const StreamDev &S, int max_m, hipStream_t s);
-void launch_stream_probe(const StreamDev &S, hipStream_t s);
-void launch_stream_apply(const StreamDev &S, hipStream_t s);
-void launch_stream_newruns(const StreamDev &S, int na, hipStream_t s);
+void launch_stream_probe(const StreamDev &S, int max_m, hipStream_t s);
+void launch_stream_finish(const StreamDev &S, int na, const SMerge *mg, hipStream_t s);
 void launch_stream_merge(const StreamDev &S, const SMerge *mg, int nmerge, int64_t nthreads,
                          hipStream_t s);
 void launch_iota_u32(uint32_t *p, int64_t n, hipStream_t s);

@@ -153,7 +153,7 @@ int run_batch(pmp_stream *s, int64_t end) {
     std::vector<int32_t> la, lq;
     la.reserve((size_t)na * (t1 - t0));
     lq.reserve((size_t)na * (t1 - t0));
-    std::vector<SMerge> merges;
+    std::vector<SMerge> merges, small;               // launches of their own; in one block
     for (int a = 0; a < na; ++a) {
         SAnchor &A = s->anc[a];
         const int m = A.m;
@@ -184,6 +184,7 @@ int run_batch(pmp_stream *s, int64_t end) {
     int64_t nthreads = 0;
     for (int a = 0; a < na; ++a) {
         SAnchor &A = s->anc[a];
+        A.merge = -1;
         if (A.nnew == 0) continue;
         std::vector<uint32_t> &rb = s->runs[a];
         rb.push_back((uint32_t)(A.nidx + A.nnew));
@@ -198,12 +199,21 @@ int run_batch(pmp_stream *s, int64_t end) {
             M.first = nthreads;
             M.nruns = last - first + 1;
             for (int r = 0; r <= M.nruns; ++r) M.runs[r] = rb[first + r];
-            nthreads += M.runs[M.nruns] - M.runs[0];
-            merges.push_back(M);
+            if (M.runs[M.nruns] - M.runs[0] <= kStreamMergeLds) {
+                A.merge = (int32_t)small.size();         // (after the others, below)
+                small.push_back(M);
+            } else {
+                nthreads += M.runs[M.nruns] - M.runs[0];
+                merges.push_back(M);
+            }
             rb.erase(rb.begin() + first + 1, rb.end() - 1);
         }
         if ((int)rb.size() - 1 > kStreamMaxRuns) return fail(PMP_EINTERNAL, "stream run table overflow");
     }
+    const int nlarge = (int)merges.size();
+    for (SAnchor &A : s->anc)
+        if (A.merge >= 0) A.merge += nlarge;
+    merges.insert(merges.end(), small.begin(), small.end());
     // one upload: anchors, list, merges
     const size_t b_anc = (size_t)na * sizeof(SAnchor);
     const size_t b_list = (size_t)2 * s->listcap * sizeof(int32_t);
@@ -222,10 +232,9 @@ int run_batch(pmp_stream *s, int64_t end) {
 
     const StreamDev S = dev_args(s, nlist);
     launch_stream_windows(S, s->max_am, s->hs);
-    launch_stream_probe(S, s->hs);
-    if (nlist > 0) launch_stream_apply(S, s->hs);
-    launch_stream_newruns(S, na, s->hs);
-    launch_stream_merge(S, s->d_merge, (int)merges.size(), nthreads, s->hs);
+    launch_stream_probe(S, s->max_am, s->hs);
+    launch_stream_finish(S, na, s->d_merge, s->hs);
+    launch_stream_merge(S, s->d_merge, nlarge, nthreads, s->hs);
     HIPCHK(hipGetLastError());
     for (int a = 0; a < na; ++a) s->anc[a].nidx += s->anc[a].nnew;
     s->windows += (uint64_t)nlist;
@@ -336,7 +345,7 @@ int pmp_stream_create(int device, int64_t capacity, int32_t m_min, int32_t m_max
     SCHK(dalloc(s, &s->cellid, cb));
     SCHK(dalloc(s, &s->basis, bb));
     SCHK(dalloc(s, &s->gproj, (int64_t)na * kMaxBits * kFD));
-    SCHK(dalloc(s, &s->counters, kStreamCounters));
+    SCHK(dalloc(s, &s->counters, kCtrSlots * kCtrStride));
     {
         // anchors, batch list and merge descriptors in one block
         char *blk = nullptr;
@@ -392,7 +401,7 @@ int pmp_stream_create(int device, int64_t capacity, int32_t m_min, int32_t m_max
     launch_fill_u32(s->nupd, 1, 0u, s->hs);
     launch_fill_u32(s->hist, kSelBins, 0u, s->hs);
     launch_fill_u64((uint64_t *)s->sel.st, sizeof(SelState) / 8, 0ull, s->hs);
-    launch_fill_u64((uint64_t *)s->counters, kStreamCounters, 0ull, s->hs);
+    launch_fill_u64((uint64_t *)s->counters, kCtrSlots * kCtrStride, 0ull, s->hs);
     launch_iota_u32(s->cellid, cb, s->hs);
     if ((rc = hchk(hipGetLastError(), "launch"))) return rc;
     if ((rc = hchk(hipStreamSynchronize(s->hs), "hipStreamSynchronize"))) return rc;
@@ -543,9 +552,12 @@ int pmp_stream_info(pmp_stream *s, pmp_stream_stats *st, int32_t *lengths, int32
     clear_error();
     if (!s || !st) return fail(PMP_EINVAL, "bad arguments");
     HIPCHK(hipSetDevice(s->device));
-    unsigned long long c[kStreamCounters] = {};
-    HIPCHK(hipMemcpyAsync(c, s->counters, sizeof(c), hipMemcpyDeviceToHost, s->hs));
+    std::vector<unsigned long long> sets(kCtrSlots * kCtrStride);
+    HIPCHK(hipMemcpyAsync(sets.data(), s->counters, sets.size() * 8, hipMemcpyDeviceToHost, s->hs));
     HIPCHK(hipStreamSynchronize(s->hs));
+    unsigned long long c[kStreamCounters] = {};
+    for (int x = 0; x < kCtrSlots; ++x)
+        for (int y = 0; y < kStreamCounters; ++y) c[y] += sets[x * kCtrStride + y];
     std::memset(st, 0, sizeof(*st));
     st->appended = (uint64_t)s->n_in;
     st->processed = (uint64_t)s->n_done;

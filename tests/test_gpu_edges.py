@@ -121,3 +121,22 @@ def test_width_matches_the_host(gpu, ws, kind):  # noqa: F811
         t = t[:150]
     _, st = run(gpu, ws, t, 20, 100, 10, 5)
     assert st["K"] == gpu.calibrate_width(t, 20, 100)
+
+
+@pytest.mark.parametrize("batch,n", [(64, 5000), (63, 700), (1300, 5200)])
+def test_stream_every_pair(gpu, oracle, batch, n):  # noqa: F811
+    """A budget that takes in every earlier window: the profile is then exact.
+    Turns of 64 candidates with remainders, merges in one block and of more
+    entries than it holds (4096), and batches of more windows than it has
+    threads (1024)."""
+    m, excl = 32, batch
+    t = np.cumsum(np.random.default_rng(batch).standard_normal(n))
+    with gpu.Stream(n, m, m, 5, excl, budget=n, batch=batch, opts=gpu.options(gamma=1)) as s:
+        s.append(t)
+        s.flush()
+        assert s.info()["dropped"] == 0
+        P, _ = s.profile(0)
+    ref = oracle.profile(t, m, excl)[0]
+    assert len(P) == len(ref)
+    for q, (a, b) in enumerate(zip(P, ref)):
+        assert parity.dist_close(float(a), float(b)), (q, a, b)
