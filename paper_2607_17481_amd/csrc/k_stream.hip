@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kBlock) void k_stream_basis(const SAnchor *__restri
 // chains over the window bound it (the moments' and the features' sums, whose
 // order is part of the result); the features' table is laid out by sample, so
 // that a step reads one line instead of one per feature (ECG-like batches of
-// 500 windows: 26 us).
+// 500 windows: 23 us).
 __global__ __launch_bounds__(kWave) void k_stream_windows(StreamDev S) {
     extern __shared__ double ys[];                 // the window's samples, then y = x - mu
     __shared__ double s_mu, s_is;
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kWave) void k_stream_windows(StreamDev S) {
         const double *b = S.basis + A.bbase + lane;
         const int ld = 2 * kp;
         double x = 0.0;
-#pragma unroll 8
+#pragma unroll 24
         for (int r = 0; r < m; ++r) x = fma(ys[r], b[(int64_t)r * ld], x);
         f = x * is;
     }
@@ -164,20 +164,25 @@ __global__ __launch_bounds__(kWave) void k_stream_windows(StreamDev S) {
 }
 
 // One completed window per block of kProbeWaves wavefronts: candidates, prune,
-// verify.  Every wavefront follows the same candidates, 64 a turn, of which each
-// group of eight lanes takes two: it reads their records and evaluates its
-// survivors; the block's best goes through LDS after every turn.
+// verify.  The search is defined as a chain of turns: a turn is up to 64 entries
+// of one bucket, pruned against max(best, P[c]) as it stood before the turn.
+// Only that bound ties the turns together, and it only falls.  So the block
+// lists the candidates of several turns, bounds all of them at once, verifies
+// the first turn's, then everything that its best leaves of the later ones, and
+// replays the turns over these values: which pairs count as verified, which
+// improve a cell and the query's best are those of the chain.
 //
 // A chain of dependent loads bounds it (a batch completes a few hundred windows,
 // too few to hide one behind another): bounds of the buckets in the runs, entry,
-// cell value, record, samples.  With one wavefront a window that searched a
-// bucket's runs when it came to the bucket, read a record per lane and took up
-// to eight turns of verification per 64 candidates, an ECG-like batch of 500
-// windows took 97 us; with all buckets searched at once, records read by groups
-// and 32 pairs verified at a time it takes 53.
+// record and cell, samples twice.  ECG-like batches of 500 windows: 97 us with
+// one wavefront a window that looked up a bucket when it came to it, 53 with a
+// block, all buckets looked up at once and nine turns one after the other, 40
+// now.
 constexpr int kProbeWaves = 4;
-constexpr int kTurn = kWave;                          // candidates per turn
-constexpr int kPerGroup = kTurn / (kProbeWaves * kPerRound);   // of them per group of lanes
+constexpr int kTurn = kWave;                          // entries per turn
+constexpr int kList = kProbeWaves * kWave;            // candidates listed at a time
+constexpr int kGroups = kList / kGroup;
+constexpr int kPreload = 64;                          // entries per bucket read ahead
 
 __global__ __launch_bounds__(kProbeWaves *kWave) void k_stream_probe(StreamDev S) {
     extern __shared__ double qwin[];               // the query's samples
@@ -185,9 +190,17 @@ __global__ __launch_bounds__(kProbeWaves *kWave) void k_stream_probe(StreamDev S
     __shared__ uint32_t rlo[kProbeSlots + 1][kStreamMaxRuns];    // and its first position in the run
     __shared__ uint32_t tot[kProbeSlots + 1], pre[kProbeSlots + 1];
     __shared__ int nbk;
-    __shared__ double wbest[2][kProbeWaves];
-    __shared__ int32_t wbestc[2][kProbeWaves];
-    __shared__ uint32_t wver[kProbeWaves];
+    __shared__ int32_t ent[kProbeSlots + 1][kPreload];
+    // the listed candidates: start, bound, cell value, distance, whether it
+    // improves the cell; first candidate of each turn
+    __shared__ int32_t lc[kList];
+    __shared__ float llb[kList];
+    __shared__ double lP[kList], ld[kList];
+    __shared__ uint8_t lup[kList];
+    __shared__ uint16_t lturn[kList], tstart[kList + 1];
+    __shared__ double wbest[kProbeWaves];
+    __shared__ double qbest;
+    __shared__ int32_t qbestc;
     const int j = blockIdx.x;
     const int tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
     const int g = lane & (kGroup - 1), grp = lane / kGroup;
@@ -269,153 +282,210 @@ __global__ __launch_bounds__(kProbeWaves *kWave) void k_stream_probe(StreamDev S
     }
     __syncthreads();
 
+    // bucket position (runs oldest first) -> window start
+    auto entry = [&](int pi, uint32_t pos) -> int32_t {
+        int rl = 0, rh = nr - 1;
+        while (rl < rh) {
+            const int mid = (rl + rh + 1) >> 1;
+            if (roff[pi][mid] <= pos) rl = mid; else rh = mid - 1;
+        }
+        return (int32_t)S.perm[cbase + rlo[pi][rl] + (pos - roff[pi][rl])];
+    };
+    // the entries of the small buckets, all at once
+    for (int x = tid; x < nb * kPreload; x += kProbeWaves * kWave) {
+        const int pi = x / kPreload, pos = x % kPreload;
+        if (tot[pi] <= (uint32_t)kPreload && (uint32_t)pos < tot[pi]) ent[pi][pos] = entry(pi, pos);
+    }
+    __syncthreads();
+
     double best = INFINITY;                         // the same in the whole block
     int32_t bestc = -1;
     unsigned long long n_cand = 0;
-    uint32_t n_ver = 0;
-    int brem = S.R, turn = 0;
+    uint32_t n_ver = 0;                             // (wavefront 0)
+    int brem = S.R, n = 0, turns = 0;               // listed candidates, their turns
     struct QueryA {
         const double *w;
         int64_t base;
         __device__ __forceinline__ double operator()(int64_t x) const { return w[x - base]; }
     };
     const QueryA qa{qwin, q};
-
-    // one turn: one candidate per lane, the same in every wavefront (c < 0:
-    // none); returns how many are valid
-    auto inspect = [&](int32_t c) -> int {
-        const uint64_t vmask = __ballot(c >= 0 && q - (int64_t)c >= S.excl);
-        const int nv = __popcll(vmask);
-        if (nv == 0) return 0;                      // (uniform in the block)
-        n_cand += (unsigned long long)nv;
-        // this lane's candidate: the g-th of its group's kPerGroup
-        const int src = (w * kPerRound + grp) * kPerGroup + (g < kPerGroup ? g : 0);
-        const int32_t cm = __shfl(c, src, kWave);
-        const bool mine = g < kPerGroup && ((vmask >> src) & 1ull);
-        double Pc = INFINITY, thr = INFINITY, muc = 0.0, isc = 0.0;
-        if (mine) {
-            Pc = bitsd(S.P[cbase + cm]);
-            thr = fmax(best, Pc);
-        }
-        auto group_bits = [&](bool b) -> uint32_t {
-            return (uint32_t)(__ballot(b) >> (grp * kGroup)) & 0xFFu;
-        };
-        const uint32_t m8 = group_bits(mine);
-        float lb = 0.0f;
-        if (m8) lb = group_lb<double>(F, fq, eq, (uint32_t)cm, mine, m8, g, sqrt2m);
-        const bool prop = mine && (double)lb < thr;
-        if (prop) {
-            muc = S.mu[cbase + cm];
-            isc = S.isig[cbase + cm];
-        }
-        const uint32_t p8 = group_bits(prop);
-        double lb_d = INFINITY;
-        int32_t lb_c = -1;
-#pragma unroll
-        for (int x = 0; x < kPerGroup; ++x) {
-            if (__ballot((p8 >> x) & 1u) == 0) continue;
-            const bool go = (p8 >> x) & 1u;
-            const int32_t vc = __shfl(cm, x, kGroup);
-            const double vP = __shfl(Pc, x, kGroup), vthr = __shfl(thr, x, kGroup);
-            const double vmu = __shfl(muc, x, kGroup), vis = __shfl(isc, x, kGroup);
-            const double dd = snap(group_zdist_a(qa, S.t, q, muq, isq, go ? (int64_t)vc : q, vmu, vis,
-                                                 go ? m : 0, exit_bound(vthr)));
-            if (go && g == 0) {
-                ++n_ver;
-                if (dd < vP) {
-                    const uint32_t slot = atomicAdd(S.nupd, 1u);
-                    if (slot < S.updcap)
-                        S.upd[slot] = SUpdate{(uint32_t)(cbase + vc), (int32_t)q, dbits(dd)};
-                    else
-                        count_add(S.counters, CS_DROP, 1ull);
-                }
-                if (dd < lb_d || (dd < INFINITY && dd == lb_d && vc < lb_c)) {
-                    lb_d = dd;
-                    lb_c = vc;
-                }
-            }
-        }
-        // the query's best over the turn: smallest (distance, start)
-        auto take = [](double &bd, int32_t &bc, double od, int32_t oc) {
-            if (od < bd || (od == bd && (uint32_t)oc < (uint32_t)bc)) {
-                bd = od;
-                bc = oc;
-            }
-        };
-#pragma unroll
-        for (int off = kGroup; off < kWave; off <<= 1)
-            take(lb_d, lb_c, __shfl_xor(lb_d, off, kWave), __shfl_xor(lb_c, off, kWave));
-        // (two sets in turn: one barrier a turn)
-        if (lane == 0) {
-            wbest[turn & 1][w] = lb_d;
-            wbestc[turn & 1][w] = lb_c;
-        }
-        __syncthreads();
-        lb_d = wbest[turn & 1][0];
-        lb_c = wbestc[turn & 1][0];
-#pragma unroll
-        for (int v = 1; v < kProbeWaves; ++v) take(lb_d, lb_c, wbest[turn & 1][v], wbestc[turn & 1][v]);
-        ++turn;
-        if (lb_c >= 0 && (lb_d < best || (lb_d == best && lb_c < bestc))) {
-            best = lb_d;
-            bestc = lb_c;
-        }
-        return nv;
+    auto group_bits = [&](bool b) -> uint32_t {
+        return (uint32_t)(__ballot(b) >> (grp * kGroup)) & 0xFFu;
     };
 
-    for (int pi = 0; pi < nb && brem > 0; ++pi) {
-        const uint32_t total = tot[pi];
-        if (total == 0) continue;
-        // bucket position (runs oldest first) -> window start
-        auto entry = [&](uint32_t pos) -> int32_t {
-            int rl = 0, rh = nr - 1;
-            while (rl < rh) {
-                const int mid = (rl + rh + 1) >> 1;
-                if (roff[pi][mid] <= pos) rl = mid; else rh = mid - 1;
+    // the bucket at work: all of its entries, or (more than budget) half of the
+    // rest of the budget on the most recent and half at even intervals over the
+    // older ones
+    int pi = 0, part = 0;                           // part: all, recent, spread
+    uint32_t base = 0, used = 0, nrec = 0;
+    for (;;) {
+        // the next turn: an entry per lane, the same in every wavefront
+        int32_t c = -1;
+        bool have = false;
+        while (!have && pi < nb && brem > 0) {
+            const uint32_t total = tot[pi], pos = base + lane;
+            if (part == 0 && base == 0 && total > (uint32_t)brem) {
+                part = 1;
+                nrec = (uint32_t)(brem / 2);
             }
-            return (int32_t)S.perm[cbase + rlo[pi][rl] + (pos - roff[pi][rl])];
-        };
-        if (total <= (uint32_t)brem) {
-            int used = 0;
-            for (uint32_t base = 0; base < total; base += kTurn) {
-                const uint32_t pos = base + lane;
-                used += inspect(pos < total ? entry(pos) : -1);
+            const uint32_t end = part == 0 ? total : part == 1 ? nrec : (uint32_t)brem - nrec;
+            if (base >= end) {
+                base = 0;
+                if (part == 1) {
+                    part = 2;
+                    continue;
+                }
+                brem = part == 0 ? brem - (int)used : 0;
+                used = 0;
+                ++pi;
+                continue;
             }
-            brem -= used;
-        } else {
-            // more entries than budget: half on the most recent, half at
-            // even intervals over the older rest
-            const int nrec = brem / 2, nstr = brem - nrec;
-            for (int base = 0; base < nrec; base += kTurn) {
-                const int x = base + lane;
-                inspect(x < nrec ? entry(total - 1u - (uint32_t)x) : -1);
-            }
-            const uint64_t span = total - (uint32_t)nrec;
-            for (int base = 0; base < nstr; base += kTurn) {
-                const int x = base + lane;
-                inspect(x < nstr ? entry((uint32_t)((uint64_t)x * span / (uint64_t)nstr)) : -1);
-            }
-            brem = 0;
+            have = true;
+            base += kTurn;
+            if (pos >= end) continue;
+            uint32_t at = pos;
+            if (part == 1) at = total - 1u - pos;
+            if (part == 2) at = (uint32_t)((uint64_t)pos * (total - nrec) / (uint64_t)end);
+            c = total <= (uint32_t)kPreload ? ent[pi][at] : entry(pi, at);
         }
-    }
+        const bool valid = c >= 0 && q - (int64_t)c >= S.excl;
+        const uint64_t vmask = __ballot(valid);
+        const int nv = __popcll(vmask);
+        if (n > 0 && (!have || n + nv > kList)) {
+            // ---- the listed turns (uniform in the block)
+            if (w == 0 && lane == 0) tstart[turns] = (uint16_t)n;
+            __syncthreads();
+            // candidates over the groups in turn, so that every group has as few
+            const int i = g * kGroups + w * kPerRound + grp;
+            const bool mine = i < n;
+            const int32_t cm = mine ? lc[i] : 0;
+            const bool first = mine && lturn[i] == 0;
+            double Pc = INFINITY, muc = 0.0, isc = 0.0;
+            if (mine) {
+                Pc = bitsd(S.P[cbase + cm]);
+                muc = S.mu[cbase + cm];
+                isc = S.isig[cbase + cm];
+            }
+            const uint32_t m8 = group_bits(mine);
+            float lb = 0.0f;
+            if (m8) lb = group_lb<double>(F, fq, eq, (uint32_t)cm, mine, m8, g, sqrt2m);
+            // the distances of the group's lanes with `prop`, one after the other
+            double dist = INFINITY;
+            auto verify = [&](bool prop, double thr) {
+                const uint32_t p8 = group_bits(prop);
+                for (int x = 0; x < kGroup; ++x) {
+                    if (__ballot((p8 >> x) & 1u) == 0) continue;
+                    const bool go = (p8 >> x) & 1u;
+                    const int32_t vc = __shfl(cm, x, kGroup);
+                    const double vthr = __shfl(thr, x, kGroup);
+                    const double vmu = __shfl(muc, x, kGroup), vis = __shfl(isc, x, kGroup);
+                    const double dd = snap(group_zdist_a(qa, S.t, q, muq, isq, go ? (int64_t)vc : q, vmu,
+                                                         vis, go ? m : 0, exit_bound(vthr)));
+                    if (go && g == x) dist = dd;
+                }
+            };
+            double thr = fmax(best, Pc);
+            verify(first && (double)lb < thr, thr);
+            if (turns > 1) {
+                double v = dist;
 #pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) n_ver += __shfl_xor(n_ver, off, kWave);
-    if (lane == 0) wver[w] = n_ver;
-    __syncthreads();
+                for (int off = kWave / 2; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off, kWave));
+                if (lane == 0) wbest[w] = v;
+                __syncthreads();
+                double b1 = best;
+#pragma unroll
+                for (int x = 0; x < kProbeWaves; ++x) b1 = fmin(b1, wbest[x]);
+                thr = fmax(b1, Pc);
+                verify(mine && !first && (double)lb < thr, thr);
+            }
+            if (mine) {
+                llb[i] = lb;
+                lP[i] = Pc;
+                ld[i] = dist;
+            }
+            __syncthreads();
+            // the turns in order, on one wavefront
+            if (w == 0) {
+                for (int u = 0; u < turns; ++u) {
+                    const int x = tstart[u] + lane;
+                    const bool in = x < (int)tstart[u + 1];
+                    double d1 = INFINITY;
+                    int32_t c1 = -1;
+                    bool prop = false, up = false;
+                    if (in) {
+                        const double p = lP[x];
+                        prop = (double)llb[x] < fmax(best, p);
+                        if (prop) {
+                            d1 = ld[x];
+                            if (d1 < INFINITY) c1 = lc[x];
+                            up = d1 < p;
+                        }
+                        lup[x] = up;
+                    }
+                    n_ver += (uint32_t)__popcll(__ballot(prop));
+                    // the query's best over the turn: smallest (distance, start)
+                    if (__ballot(c1 >= 0 && (d1 < best || (d1 == best && c1 < bestc))) == 0) continue;
+#pragma unroll
+                    for (int off = kWave / 2; off > 0; off >>= 1) {
+                        const double od = __shfl_xor(d1, off, kWave);
+                        const int32_t oc = __shfl_xor(c1, off, kWave);
+                        if (od < d1 || (od == d1 && (uint32_t)oc < (uint32_t)c1)) {
+                            d1 = od;
+                            c1 = oc;
+                        }
+                    }
+                    best = d1;
+                    bestc = c1;
+                }
+                if (lane == 0) {
+                    qbest = best;
+                    qbestc = bestc;
+                }
+            }
+            __syncthreads();
+            best = qbest;
+            bestc = qbestc;
+            // the improvements, one reservation per wavefront
+            const bool up = mine && lup[i];
+            const uint64_t um = __ballot(up);
+            if (um) {
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(S.nupd, (uint32_t)__popcll(um));
+                at = (uint32_t)__shfl((int)at, 0, kWave) + (uint32_t)__popcll(um & lanemask_lt());
+                if (up) {
+                    if (at < S.updcap) S.upd[at] = SUpdate{(uint32_t)(cbase + cm), (int32_t)q, dbits(dist)};
+                    else count_add(S.counters, CS_DROP, 1ull);
+                }
+            }
+            n = turns = 0;
+        }
+        if (!have) break;
+        if (nv == 0) continue;
+        n_cand += (unsigned long long)nv;
+        used += (uint32_t)nv;
+        if (w == 0) {
+            if (valid) {
+                const int x = n + __popcll(vmask & lanemask_lt());
+                lc[x] = c;
+                lturn[x] = (uint16_t)turns;
+            }
+            if (lane == 0) tstart[turns] = (uint16_t)n;
+        }
+        n += nv;
+        ++turns;
+    }
     if (tid == 0) {
         S.P[cq] = dbits(best);
         S.I[cq] = bestc;
-        uint32_t v = 0;
-        for (int x = 0; x < kProbeWaves; ++x) v += wver[x];
         if (n_cand) count_add(S.counters, CS_CAND, n_cand);
-        if (v) count_add(S.counters, CS_VER, (unsigned long long)v);
+        if (n_ver) count_add(S.counters, CS_VER, (unsigned long long)n_ver);
     }
 }
 
 // The end of a batch, a block per anchor and one more, all independent: the
 // anchors' directories and the buffered improvements.  As launches of their own
 // the new runs, merges, copies back and improvements took 9 + 8 + 5 + 5.5 us of
-// an ECG-like batch, and 5 us of host time each; together KSF.
+// an ECG-like batch, and 5 us of host time each; together 9.
 constexpr int kFinish = 1024;
 
 // The buffered improvements into the profile.  Every buffered distance is
@@ -462,22 +532,28 @@ __global__ __launch_bounds__(kFinish) void k_stream_finish(StreamDev S, int na,
         return;
     }
     const SAnchor &A = S.anc[blockIdx.x];
-    const int nn = A.nnew;
-    for (int i0 = 0; i0 < nn; i0 += kFinish) {
-        const int i = i0 + threadIdx.x;
+    const int nn = A.nnew, g = threadIdx.x & (kGroup - 1);
+    // eight lanes per window count the keys before its own
+    for (int i0 = 0; i0 < nn; i0 += kFinish / kGroup) {
+        const int i = i0 + threadIdx.x / kGroup;
         const uint32_t ki = i < nn ? S.bkey[A.j0 + i] : 0u;
         int rank = 0;
         for (int x0 = 0; x0 < nn; x0 += (int)kStreamMergeLds) {
             const int xn = min(nn - x0, (int)kStreamMergeLds);
-            __syncthreads();
-            for (int x = threadIdx.x; x < xn; x += kFinish) mk[x] = S.bkey[A.j0 + x0 + x];
-            __syncthreads();
-            for (int x = 0; x < xn; ++x) {
+            if (i0 == 0 || nn > (int)kStreamMergeLds) {
+                __syncthreads();
+                for (int x = threadIdx.x; x < xn; x += kFinish) mk[x] = S.bkey[A.j0 + x0 + x];
+                __syncthreads();
+            }
+            for (int x = g; x < xn; x += kGroup) {
                 const uint32_t kx = mk[x];
                 rank += kx < ki || (kx == ki && x0 + x < i);
             }
         }
-        if (i < nn) {
+        rank += xor_lane<1>(rank);
+        rank += xor_lane<2>(rank);
+        rank += xor_lane<4>(rank);
+        if (i < nn && g == 0) {
             const int64_t pos = A.cbase + A.nidx + rank;
             S.skey[pos] = ki;
             S.perm[pos] = (uint32_t)S.lq[A.j0 + i];

@@ -210,6 +210,12 @@ int run_batch(pmp_stream *s, int64_t end) {
         }
         if ((int)rb.size() - 1 > kStreamMaxRuns) return fail(PMP_EINTERNAL, "stream run table overflow");
     }
+    // (a batch of constant windows only changes nothing on the device)
+    if (nlist == 0) {
+        s->batches += 1;
+        s->n_done = end;
+        return PMP_OK;
+    }
     const int nlarge = (int)merges.size();
     for (SAnchor &A : s->anc)
         if (A.merge >= 0) A.merge += nlarge;
