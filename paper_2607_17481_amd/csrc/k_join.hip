@@ -55,16 +55,6 @@ constexpr int kCovLd = 32 + 528;              // one block's sums and products (
 
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
-
-// acc + a . b of two fp16 pairs (exact products, FP32 sums).
-__device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float acc) {
-    f16x2 x, y;
-    __builtin_memcpy(&x, &a, 4);
-    __builtin_memcpy(&y, &b, 4);
-    acc = fmaf((float)x[0], (float)y[0], acc);
-    return fmaf((float)x[1], (float)y[1], acc);
-}
 
 __device__ __forceinline__ f16x8 as_f16x8(uint4 v) {
     union {
@@ -459,20 +449,14 @@ __device__ __forceinline__ uint32_t join_exact(const Req &q, bool valid, uint32_
 // Then it walks the runs 32 candidates at a time: two 16-byte operand words
 // and one Gram term per lane (the next tile's loads in flight through the
 // current one's products), two products per query tile.  The query's filter
-// term rides in the two operand slots past the features, so a pair is kept
-// iff its accumulator reaches the candidate's Gram term, and most tiles end
-// at one comparison of their largest accumulator.
-//
-// The accumulators are tested four rows at a time (the largest of the four,
-// one bit per lane and group), and the groups that hold a passing pair go to a
-// queue in LDS as (first row, candidate): a step of 4096 pairs keeps about
-// five at noisy data, and resolving them row by row from the accumulators took
-// more issue slots than the products and the test together.  A full queue is
-// resolved one pair per lane: coordinates, order (a candidate that is a query
-// earlier in the order leaves the pair to its own block), then the pair's own
-// product against the same term, by fp16 dot products.  The pairs left become
-// window indices and go to the pair buffer, whose pairs k_join_verify takes
-// after the launch.  A wavefront that finds the buffer
+// term rides in the two operand slots past the features and the accumulators
+// start at minus the candidate's Gram term, so a pair is kept iff its
+// accumulator's sign is clear: one shift per row packs a lane's 64 signs into
+// two words.  The passing pairs (about five of a step's 4096 at noisy data) go to
+// a queue in LDS, less those of a candidate that is a query earlier in the order
+// (its own block has them).  A full queue is tested one pair per lane on the
+// stored coordinates; the pairs left become window indices and go to the pair
+// buffer, whose pairs k_join_verify takes after the launch.  A wavefront that finds the buffer
 // full puts its block on the list of overflowed blocks and stops; those are
 // taken again from their start with an emptied buffer (the pairs of the first
 // attempt that reached the buffer are then verified twice, which changes no
@@ -486,10 +470,10 @@ __device__ __forceinline__ uint32_t join_exact(const Req &q, bool valid, uint32_
 // took six bf16 products a tile; it was bound by its barriers, by a row filter
 // of about 100 VALU instructions a tile and by the mirror image of every pair.
 // Measured (FP32 form, ECG-like, 51 lengths of 100..400): 250,000 samples 27 ->
-// 5.8 ms for all tiles, 1,000,000 samples 280 -> 64 ms.  What bounds it now is
-// the first-level cache: of about 200 accesses a step of 4096 pairs, 36 are the
-// candidates' operands and the rest the rows that resolve() gathers; the matrix
-// cores are busy 15% of the time, the vector units 40%.
+// 5.8 ms for all tiles, 1,000,000 samples 280 -> 64 ms; with rows tested four at
+// a time against the term, and the row found again by the pair's own product
+// (gathers of both operands: four fifths of the cache accesses) 47 in FP64; with
+// the signs 38.
 constexpr int kJB = kJoinBlock;               // query tiles per wavefront
 constexpr int kJQ = kJB * kJT;                // queries per wavefront
 constexpr int kXcds = 8;
@@ -497,10 +481,9 @@ constexpr int64_t kJSeg = 128;                // consecutive blocks per XCD (16,
 constexpr int kJWaves = 4;                    // wavefronts per SIMD the registers are held to
 
 struct JoinSmem {
-    uint2 queue[kQueueCap];                   // (first row, candidate) of groups of four rows
+    uint2 queue[kQueueCap];                   // passing pairs (positions of query, candidate)
     uint2 outq[kOutCap];                      // kept pairs (k_q, k_c)
     uint32_t qkey[kJQ];                       // the queries' cells (kNone: not a query)
-    float qv[kJQ];                            // the queries' filter terms
     uint32_t rbeg[kWave], rend[kWave];        // the non-empty runs of 64 grid rows
 };
 
@@ -552,10 +535,9 @@ __device__ __forceinline__ void join_block(const Req &q, const GridLen *__restri
         const bool isq = validq && qf[kq];
         any |= __ballot(isq) != 0ull;
         const uint4 z = make_uint4(0, 0, 0, 0);
-        float vq = -INFINITY;                             // not a query: keeps nothing
         uint4 w0 = isq ? op0[(int64_t)pq * 2 + hh] : z, w1 = isq ? op1[(int64_t)pq * 2 + hh] : z;
         if (hh == 1) {
-            // a pair is kept iff <G_q, G_c> + v >= 0.5 |G_c|^2, with v at
+            // a pair is kept iff <G_q, G_c> + v - 0.5 |G_c|^2 >= 0, with v at
             // least 0.5 (R^2 - |G_q|^2) plus every rounding of the left side
             float hi = -65504.0f, lo = 0.0f;
             if (isq) {
@@ -564,13 +546,15 @@ __device__ __forceinline__ void join_block(const Req &q, const GridLen *__restri
                 const double nG2 = (double)mt.x * (1.0 - 0x1.0p-23);
                 double v = 0.5 * (R * R * (1.0 + 1e-9) - nG2) + G.eps_c * (double)mt.z + 1e-30;
                 v += 0x1.0p-22 * (fabs(v) + G.nmax2);
+                // the sums start at -0.5 |G_c|^2: at most 34 additions that
+                // round by up to 2^-23 of it
+                v += 4.5e-6 * G.nmax2;
                 // the slots' share of the accumulation (at most 34 additions)
                 // and of the split into hi + lo
                 v += 5e-6 * fabs(v) + 0x1.0p-12 * (double)scale;
                 // (past the range every pair passes: |v| / scale is below
                 // 32768 wherever the test decides anything)
                 const float x = (float)fmin(fmax(v / (double)scale, -60000.0), 60000.0);
-                vq = x * scale;
                 hi = half_float(half_bits(x));
                 lo = x - hi;
                 if (fabsf(hi) < 0x1.0p-14f) hi = 0.0f;
@@ -581,7 +565,6 @@ __device__ __forceinline__ void join_block(const Req &q, const GridLen *__restri
         a0[t] = as_f16x8(w0);
         a1[t] = as_f16x8(w1);
         if (hh == 0) qkey[t * kJT + i] = isq ? (gkey[pq] & kmask) : kNone;
-        if (hh == 1) sm.qv[t * kJT + i] = vq;
     }
     if (!any) return;                                     // uniform
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -621,44 +604,23 @@ __device__ __forceinline__ void join_block(const Req &q, const GridLen *__restri
         lds_sync();
         on = 0;
     };
-    // resolve the queued groups: lane 4 e + r takes row r of entry e
+    // test the queued pairs on their coordinates
     auto resolve = [&]() {
         lds_sync();
-        for (int b = 0; b < qn; b += kWave / 4) {
-            const int e = b + (lane >> 2);
+        for (int b = 0; b < qn; b += kWave) {
+            const int e = b + lane;
             bool keep = false;
-            uint32_t pq = 0, pc = 0;
+            uint2 pr = make_uint2(0u, 0u);
             if (e < qn) {
-                const uint2 pr = queue[e];
-                pq = pr.x + (uint32_t)(lane & 3);
-                pc = pr.y;
-                if (pq < pend) {
-                    const float4 gq = gp_s[pq], gc = gp_s[pc];
-                    const float v = sm.qv[pq - p0];
-                    keep = fabsf(gq.x - gc.x) <= G.rp && fabsf(gq.y - gc.y) <= G.rp &&
-                           fabsf(gq.z - gc.z) <= G.rp && pq != pc &&
-                           !(signbit(gc.w) && pc < pq);
-                    if (keep) {
-                        // the pair's own product: exact fp16 products summed
-                        // in FP32, within the same rounding bound as the
-                        // matrix products' (the slots past the features out)
-                        float dot = 0.0f;
-#pragma unroll
-                        for (int w = 0; w < 4; ++w) {
-                            const uint4 x = (w < 2 ? op0 : op1)[(int64_t)pq * 2 + (w & 1)];
-                            const uint4 y = (w < 2 ? op0 : op1)[(int64_t)pc * 2 + (w & 1)];
-                            dot = dot2(x.x, y.x, dot);
-                            dot = dot2(x.y, y.y, dot);
-                            dot = dot2(x.z, y.z, dot);
-                            if (w < 3) dot = dot2(x.w, y.w, dot);
-                        }
-                        keep = dot + v >= fabsf(gc.w);
-                    }
-                }
+                pr = queue[e];
+                const float4 gq = gp_s[pr.x], gc = gp_s[pr.y];
+                // (all three at once: one wait)
+                keep = fmaxf(fmaxf(fabsf(gq.x - gc.x), fabsf(gq.y - gc.y)), fabsf(gq.z - gc.z)) <=
+                       G.rp;
             }
             const uint64_t mk = __ballot(keep);
             if (mk == 0ull) continue;
-            if (keep) outq[on + __popcll(mk & lanemask_lt())] = make_uint2(gval[pq], gval[pc]);
+            if (keep) outq[on + __popcll(mk & lanemask_lt())] = make_uint2(gval[pr.x], gval[pr.y]);
             on += __popcll(mk);
             if (on > kOutCap - kWave) hand_on();
         }
@@ -783,12 +745,10 @@ __device__ __forceinline__ void join_block(const Req &q, const GridLen *__restri
         bool more = true;
         while (more) {
             const f16x8 b0 = as_f16x8(nb0), b1 = as_f16x8(nb1);
-            // the candidate's Gram term (its sign is the query flag), less
-            // one unit of its bits.  Terms are >= 0, so an accumulator reaches
-            // one iff their bits compare so as signed integers (no NaN occurs,
-            // and an accumulator of -0 needs a filter term of 0, which its
-            // margins exclude)
-            const int bj = (c + (uint32_t)i < e ? __float_as_int(nw) & 0x7FFFFFFF : 0x7F800000) - 1;
+            // the candidate's Gram term (its sign is the query flag), negative;
+            // +0 for a term of 0, and -inf past the run's end
+            const float term = c + (uint32_t)i < e ? 0.0f - fabsf(nw) : -INFINITY;
+            const bool cq = signbit(nw);
             const uint32_t tc = c;
             c += kJT;
             if (c >= e) {
@@ -801,40 +761,51 @@ __device__ __forceinline__ void join_block(const Req &q, const GridLen *__restri
             }
             load_tile(c, nb0, nb1, nw);                   // (past the last: read and dropped)
             n_tiles += kJB;
-            f32x16 acc[kJB];
+            f32x16 z;
 #pragma unroll
-            for (int t = 0; t < kJB; ++t) {
-                f32x16 z = {};
-                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0[t], b0, z, 0, 0, 0);
+            for (int r = 0; r < 16; ++r) z[r] = term;
+            // two query tiles at a time; bit 16 t + r of a word: row r of tile
+            // t fails (the accumulator's sign)
+            uint32_t pass[kJB / 2];
+#pragma unroll
+            for (int u = 0; u < kJB / 2; ++u) {
+                f32x16 acc[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0[2 * u + t], b0, z, 0, 0, 0);
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1[2 * u + t], b1, acc[t], 0, 0, 0);
+                uint32_t fail = 0;
+#pragma unroll
+                for (int t = 1; t >= 0; --t)
+#pragma unroll
+                    for (int r = 15; r >= 0; --r)
+                        fail = __builtin_amdgcn_alignbit(fail, (uint32_t)__float_as_int(acc[t][r]), 31);
+                pass[u] = ~fail;
             }
 #pragma unroll
-            for (int t = 0; t < kJB; ++t)
-                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1[t], b1, acc[t], 0, 0, 0);
-            // the groups of four rows with a passing pair: bit 4 t + g (the
-            // sign of term - 1 - accumulator as integers, shifted in; negative
-            // accumulators count as 0, so the difference does not wrap)
-            uint32_t hit = 0;
-#pragma unroll
-            for (int t = kJB - 1; t >= 0; --t)
-#pragma unroll
-                for (int g = 3; g >= 0; --g) {
-                    int top = 0;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) top = max(top, __float_as_int(acc[t][4 * g + r]));
-                    hit = __builtin_amdgcn_alignbit(hit, (uint32_t)(bj - top), 31);
+            for (int u = 0; u < kJB / 2; ++u) {
+                uint32_t hit = pass[u];
+                uint64_t mk = __ballot(hit != 0u);
+                while (mk) {
+                    if (qn > kQueueCap - kWave) resolve();
+                    bool put = false;
+                    uint32_t pq = 0;
+                    const uint32_t pc = tc + (uint32_t)i;
+                    if (hit) {
+                        // row r of tile t: 32 t + 8 (r / 4) + 4 hh + r % 4
+                        const uint32_t x = (uint32_t)__builtin_ctz(hit);
+                        pq = p0 + 64u * u + 32u * (x >> 4) + 8u * ((x >> 2) & 3u) + 4u * (uint32_t)hh +
+                             (x & 3u);
+                        hit &= hit - 1u;
+                        put = pq != pc && !(cq && pc < pq);
+                    }
+                    const uint64_t pm = __ballot(put);
+                    if (put) queue[qn + __popcll(pm & lanemask_lt())] = make_uint2(pq, pc);
+                    qn += __popcll(pm);
+                    mk = __ballot(hit != 0u);
                 }
-            uint64_t mk = __ballot(hit != 0u);
-            while (mk) {
-                if (qn > kQueueCap - kWave) resolve();
-                if (hit) {
-                    // group g of tile t: rows 32 t + 8 g + 4 hh .. + 3
-                    const uint32_t tg = (uint32_t)__builtin_ctz(hit);
-                    queue[qn + __popcll(mk & lanemask_lt())] =
-                        make_uint2(p0 + 8u * tg + 4u * (uint32_t)hh, tc + (uint32_t)i);
-                    hit &= hit - 1u;
-                }
-                qn += __popcll(mk);
-                mk = __ballot(hit != 0u);
             }
             if (over) break;
         }
