@@ -167,6 +167,11 @@ int pmp_open(const double *series, int64_t n, int32_t m_min, int32_t m_max,
              int32_t k, int32_t exclusion, int32_t budget,
              pmp_motif *out, int32_t *n_out);
 
+/* The device memory and stream of a pmp_open call stay for the next one on the
+ * same device (one block of at most 1 GiB while no call runs).  This frees
+ * them. */
+void pmp_trim(void);
+
 /* Same, with options (NULL = defaults) and optional stats (NULL = none). */
 int pmp_open_ex(const double *series, int64_t n, int32_t m_min, int32_t m_max,
                 int32_t k, int32_t exclusion, int32_t budget,

@@ -1574,6 +1574,70 @@ static int scratch_address(void **out) {
     return PMP_OK;
 }
 
+// ------------------------------------ device memory of pmp_open
+// Allocating and freeing the series and workspace of a call took 2 to 17 ms
+// (640 MB for 30,000 samples, whose own work is below 1 ms), so the
+// last block and its stream stay for the next call on that device: one idle
+// block a device, of at most kHostKeep bytes.  It is owned by one call at a time
+// (calls that overlap find it gone and allocate); it is freed when a call needs
+// more, when an allocation of pmp_open fails, and by pmp_trim.
+namespace {
+constexpr size_t kHostKeep = (size_t)1 << 30;
+struct HostMem {
+    void *p = nullptr;
+    size_t bytes = 0;
+    hipStream_t s = nullptr;
+    void release() {
+        if (p) (void)hipFree(p);
+        if (s) (void)hipStreamDestroy(s);
+        *this = HostMem{};
+    }
+};
+std::mutex g_idle_mu;
+HostMem g_idle[kMaxDevices];
+
+HostMem take_idle(int dev) {
+    std::lock_guard<std::mutex> lock(g_idle_mu);
+    HostMem b = g_idle[dev];
+    g_idle[dev] = HostMem{};
+    return b;
+}
+
+struct HostBlock {
+    HostMem b;
+    int dev = 0;
+    bool good = false;
+
+    int take(size_t bytes) {
+        HIPCHK(hipGetDevice(&dev));
+        const bool pooled = dev >= 0 && dev < kMaxDevices;
+        if (pooled) b = take_idle(dev);
+        if (b.bytes < bytes) b.release();
+        if (!b.p && hipMalloc(&b.p, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            b.p = nullptr;
+            // (one that another call has put back meanwhile)
+            if (pooled) take_idle(dev).release();
+            if (hipMalloc(&b.p, bytes) != hipSuccess) {
+                (void)hipGetLastError();
+                b.p = nullptr;
+                return fail(PMP_ENOMEM, "device allocation of %zu bytes failed", bytes);
+            }
+        }
+        if (b.bytes < bytes) b.bytes = bytes;
+        if (!b.s) HIPCHK(hipStreamCreateWithFlags(&b.s, hipStreamNonBlocking));
+        return PMP_OK;
+    }
+    ~HostBlock() {
+        if (good && dev >= 0 && dev < kMaxDevices && b.bytes <= kHostKeep) {
+            std::lock_guard<std::mutex> lock(g_idle_mu);
+            std::swap(b, g_idle[dev]);
+        }
+        b.release();
+    }
+};
+}  // namespace
+
 extern "C" {
 
 void pmp_default_options(pmp_options *o) {
@@ -1660,35 +1724,39 @@ int pmp_open_ex(const double *series, int64_t n, int32_t m_min, int32_t m_max, i
     for (int64_t i = 0; i < n; ++i)
         if (!std::isfinite(series[i])) return fail(PMP_EINVAL, "series contains a non-finite sample");
     const size_t ws = upper_bytes(n, m_min, m_max, o, k);
-    hipStream_t s;
-    HIPCHK(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
-    double *d_t = nullptr;
-    void *d_ws = nullptr;
-    if (hipMalloc(&d_t, (size_t)n * sizeof(double)) != hipSuccess) {
-        (void)hipStreamDestroy(s);
-        return fail(PMP_ENOMEM, "device allocation of the series failed");
-    }
-    if (hipMalloc(&d_ws, ws) != hipSuccess) {
-        (void)hipFree(d_t);
-        (void)hipStreamDestroy(s);
-        return fail(PMP_ENOMEM, "device allocation of %zu workspace bytes failed", ws);
-    }
-    rc = PMP_OK;
+    // the series, then the workspace
+    const size_t bt = ((size_t)n * sizeof(double) + 255) & ~(size_t)255;
+    HostBlock blk;
+    rc = blk.take(bt + ws);
+    if (rc) return rc;
+    const hipStream_t s = blk.b.s;
+    double *d_t = (double *)blk.b.p;
+    void *d_ws = (char *)blk.b.p + bt;
     if (hipMemcpyAsync(d_t, series, (size_t)n * sizeof(double), hipMemcpyHostToDevice, s) != hipSuccess)
         rc = fail(PMP_EDEVICE, "copy of the series failed");
     if (!rc)
         rc = run_device(d_t, n, m_min, m_max, k, exclusion, budget, opt, d_ws, ws, (void *)s, out,
                         n_out, stats, nullptr);
-    (void)hipStreamSynchronize(s);
-    (void)hipFree(d_ws);
-    (void)hipFree(d_t);
-    (void)hipStreamDestroy(s);
+    // (a block goes back only once nothing uses it)
+    blk.good = hipStreamSynchronize(s) == hipSuccess;
     return rc;
 }
 
 int pmp_open(const double *series, int64_t n, int32_t m_min, int32_t m_max, int32_t k,
              int32_t exclusion, int32_t budget, pmp_motif *out, int32_t *n_out) {
     return pmp_open_ex(series, n, m_min, m_max, k, exclusion, budget, nullptr, out, n_out, nullptr);
+}
+
+void pmp_trim(void) {
+    int cur = 0;
+    const bool known = hipGetDevice(&cur) == hipSuccess;
+    for (int dev = 0; dev < kMaxDevices; ++dev) {
+        HostMem b = take_idle(dev);
+        if (!b.p) continue;
+        (void)hipSetDevice(dev);
+        b.release();
+    }
+    if (known) (void)hipSetDevice(cur);
 }
 
 double pmp_projection(uint64_t seed, int32_t m, int32_t l, int32_t c) { return gauss(seed, m, l, c); }

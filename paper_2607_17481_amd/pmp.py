@@ -178,6 +178,11 @@ def open_host(series, m_min: int, m_max: int, k: int, exclusion: int, budget: in
     return (res, st.as_dict()) if stats else res
 
 
+def trim() -> None:
+    """Free the device memory that pmp_open keeps for its next call."""
+    lib().pmp_trim()
+
+
 def workspace_bytes(n: int, m_min: int, m_max: int, k: int = 20,
                     opts: Options | None = None) -> int:
     return int(lib().pmp_workspace_bytes(n, m_min, m_max, k,

@@ -140,3 +140,25 @@ def test_stream_every_pair(gpu, oracle, batch, n):  # noqa: F811
     assert len(P) == len(ref)
     for q, (a, b) in enumerate(zip(P, ref)):
         assert parity.dist_close(float(a), float(b)), (q, a, b)
+
+
+def test_open_memory_is_reused(gpu, oracle):  # noqa: F811
+    """pmp_open calls of growing, shrinking and equal sizes, overlapping ones
+    from several threads, and after pmp_trim: every answer is the same as
+    with fresh memory."""
+    from concurrent.futures import ThreadPoolExecutor
+    series = {n: np.cumsum(np.random.default_rng(n).standard_normal(n)) for n in (300, 2000, 900)}
+    want = {n: oracle.topk(oracle.pan_profile(t, range(16, 25), 8), 5) for n, t in series.items()}
+
+    def one(n):
+        res = gpu.open_host(series[n], 16, 24, 5, 8)
+        ok, msg = parity.canonical_equal(res, want[n])
+        assert ok, (n, msg)
+
+    for n in (300, 2000, 900, 900, 300):
+        one(n)
+    with ThreadPoolExecutor(4) as ex:
+        list(ex.map(one, [300, 2000, 900, 2000] * 3))
+    gpu.trim()
+    gpu.trim()
+    one(900)
