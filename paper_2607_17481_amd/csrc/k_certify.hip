@@ -285,32 +285,43 @@ __device__ __forceinline__ void min_step(unsigned long long &v) {
         dpp_u32<kCtrl, kRows>((uint32_t)v);
     v = o < v ? o : v;
 }
-template <typename T>
+// kRows: only over each row of 16 lanes (the result in its last lane).
+template <bool kRows, typename T>
 __device__ __forceinline__ void wave_min_steps(T &v) {
     min_step<0x111, 0xF>(v);
     min_step<0x112, 0xF>(v);
     min_step<0x114, 0xF>(v);
     min_step<0x118, 0xF>(v);
+    if (kRows) return;
     min_step<0x142, 0xA>(v);
     min_step<0x143, 0xC>(v);
 }
+template <bool kRows>
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-    wave_min_steps(v);
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+    wave_min_steps<kRows>(v);
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, kRows ? 15 : 63);
 }
+template <bool kRows>
 __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v) {
-    wave_min_steps(v);
-    return (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), 63) << 32 |
-           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
+    wave_min_steps<kRows>(v);
+    constexpr int kLast = kRows ? 15 : 63;
+    return (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), kLast) << 32 |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, kLast);
 }
 
 constexpr int kGreedyPer = kGreedyMax / kGreedyThreads;
 
 __global__ __launch_bounds__(kGreedyThreads) void k_select_greedy(
     Select in, int k, SelCell *__restrict__ acc, const unsigned long long *__restrict__ counts) {
-    __shared__ unsigned long long wv[2][kGreedyThreads / kWave];
-    __shared__ uint32_t wp[2][kGreedyThreads / kWave];
-    __shared__ int4 win[2];                                // cell, length index, m
+    // the smallest entry of each wavefront, in two sets used in turn
+    struct Best {
+        unsigned long long v;
+        uint32_t p, c;
+        int lm;
+    };
+    constexpr int kWaves = kGreedyThreads / kWave;
+    static_assert(kWaves == 16, "a row of lanes takes the wavefronts' entries");
+    __shared__ Best wbest[2][kWaves], own[kWaves];
     __shared__ unsigned long long kept;
     const int tid = threadIdx.x, lane = lane_id(), w = tid / kWave;
     SelState *st = in.st;
@@ -329,7 +340,8 @@ __global__ __launch_bounds__(kGreedyThreads) void k_select_greedy(
     // every entry with its cell and length, in registers
     unsigned long long v[kGreedyPer];
     uint32_t p[kGreedyPer], c[kGreedyPer];
-    int l[kGreedyPer], m[kGreedyPer];
+    int lm[kGreedyPer];                                    // length index << 12 | window length
+    static_assert(kMaxM < 4096, "a window length fits 12 bits");
     const int nu = (int)((nl + kGreedyThreads - 1) / kGreedyThreads);     // entries per thread
 #pragma unroll
     for (int u = 0; u < kGreedyPer; ++u) {
@@ -337,68 +349,85 @@ __global__ __launch_bounds__(kGreedyThreads) void k_select_greedy(
         v[u] = ~0ull;                                      // none
         p[u] = kNone;
         c[u] = 0;
-        l[u] = -1;
-        m[u] = 0;
+        lm[u] = -1;
         if (x < nl) {
             v[u] = in.sel_val[x];
             p[u] = in.sel[x];
             c[u] = in.sel_cell[x];
-            const int2 lm = in.sel_len[x];
-            l[u] = lm.x;
-            m[u] = lm.y;
+            const int2 y = in.sel_len[x];
+            lm[u] = y.x << 12 | y.y;
         }
     }
-    for (int r = 0; r < k; ++r) {
-        unsigned long long bv = ~0ull;
-        uint32_t bp = kNone;
+    // the wavefront's smallest entry, kept until an entry of it goes
+    unsigned long long ov = ~0ull;
+    uint32_t op = kNone, oc = 0u;
+    int ol = -1;
+    bool stale = true;
+    int r = 0;
+    for (; r < k; ++r) {
+        if (stale) {                                       // (uniform in the wavefront)
+            unsigned long long bv = ~0ull;
+            uint32_t bp = kNone;
 #pragma unroll
-        for (int u = 0; u < kGreedyPer; ++u)
-            if (u < nu && (v[u] < bv || (v[u] == bv && p[u] < bp))) {
-                bv = v[u];
-                bp = p[u];
-            }
-        const unsigned long long mv = wave_min_u64(bv);
-        const uint32_t mp = wave_min_u32(bv == mv ? bp : kNone);
-        // (two sets of the wavefronts' results in turn: one barrier a round
-        // suffices for them)
-        if (lane == 0) {
-            wv[r & 1][w] = mv;
-            wp[r & 1][w] = mp;
+            for (int u = 0; u < kGreedyPer; ++u)
+                if (u < nu && (v[u] < bv || (v[u] == bv && p[u] < bp))) {
+                    bv = v[u];
+                    bp = p[u];
+                }
+            const unsigned long long mv = wave_min_u64<false>(bv);
+            const uint32_t mp = wave_min_u32<false>(bv == mv ? bp : kNone);
+            if (lane == 0) own[w] = Best{~0ull, kNone, 0u, -1};
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int u = 0; u < kGreedyPer; ++u)
+                if (u < nu && mp != kNone && p[u] == mp) own[w] = Best{mv, mp, c[u], lm[u]};
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            ov = own[w].v;
+            op = own[w].p;
+            oc = own[w].c;
+            ol = own[w].lm;
         }
+        if (lane == 0) wbest[r & 1][w] = Best{ov, op, oc, ol};
         __syncthreads();
-        const unsigned long long xv = lane < kGreedyThreads / kWave ? wv[r & 1][lane] : ~0ull;
-        bv = wave_min_u64(xv);
-        bp = wave_min_u32(lane < kGreedyThreads / kWave && xv == bv ? wp[r & 1][lane] : kNone);
+        const Best &x = wbest[r & 1][lane & (kWaves - 1)];
+        const unsigned long long xv = x.v;
+        const uint32_t xp = x.p, xc = x.c;
+        const int xl = x.lm;
+        const unsigned long long bv = wave_min_u64<true>(xv);
+        const uint32_t bp = wave_min_u32<true>(xv == bv ? xp : kNone);
         if (bp == kNone) break;                            // (uniform) nothing is left
-        // the thread that holds the cell publishes it
-#pragma unroll
-        for (int u = 0; u < kGreedyPer; ++u)
-            if (u < nu && p[u] == bp) {
-                win[r & 1] = make_int4((int)c[u], l[u], m[u], 0);
-                acc[r] = SelCell{bv, bp, c[u]};
-                st->naccept = r + 1;
-            }
-        __syncthreads();
-        const int4 x = win[r & 1];
+        const int src = __ffsll((unsigned long long)__ballot(xp == bp)) - 1;
+        const uint32_t bc = (uint32_t)__builtin_amdgcn_readlane((int)xc, src);
+        const int bl = __builtin_amdgcn_readlane(xl, src), bm = bl & 0xFFF;
+        if (tid == 0) acc[r] = SelCell{bv, bp, bc};
+        bool gone = false;
 #pragma unroll
         for (int u = 0; u < kGreedyPer; ++u) {
-            const int64_t d = (int64_t)c[u] - (int64_t)(uint32_t)x.x;
-            if (u < nu && l[u] == x.y && 2 * (d < 0 ? -d : d) <= x.z) {
+            const int64_t d = (int64_t)c[u] - (int64_t)bc;
+            if (u < nu && lm[u] == bl && 2 * (d < 0 ? -d : d) <= bm) {
                 v[u] = ~0ull;
                 p[u] = kNone;
-                l[u] = -1;
+                lm[u] = -1;
+                gone = true;
             }
         }
+        stale = __ballot(gone) != 0ull;
     }
+    if (tid == 0) st->naccept = r;
 }
 
 // ------------------------------------------------------------------ rows
 
 // One pass over each requested row c: out_min[c] = min over valid j of the
-// snapped distance (the certificate's check), and out_arg[c] = smallest
-// valid j whose snapped distance equals req[c].target (the reported
-// neighbour when the check holds).  Constant windows are not indexed and
-// never scanned.
+// snapped distance where that lies at or below req[c].target, else +inf or a
+// value above it (the certificate's check), and out_arg[c] = smallest valid j
+// whose snapped distance equals req[c].target (the reported neighbour when the
+// check holds).  Constant windows are not indexed and never scanned.  A sum
+// past the target stops.  At most 128 blocks a row, and one pair of atomics a
+// block: with one per wavefront, 20 rows queued 300,000 atomics
+// on 20 addresses and took 926 us for 981,000 windows a row, 512 now.
 // Each lane takes every (threads)-th window of the length and evaluates the
 // canonical distance on its own (lane_zdist): neighbouring lanes read
 // neighbouring windows, and the row's own window is shared by all.
@@ -412,12 +441,14 @@ __global__ __launch_bounds__(kBlock) void k_rows(Req q, const RowReq *__restrict
     const double mui = q.mu[R.k], isi = q.isig[R.k];
     const int64_t nt = (int64_t)gridDim.x * kBlock;
     unsigned long long best = (unsigned long long)kInfBits, arg = ~0ull;
+    // (well above the target: only values above it stop early)
+    const double lim2 = exit_bound(fmax(bitsd(R.target), kEps0) * (1.0 + 1e-9));
     for (int64_t x = (int64_t)blockIdx.x * kBlock + threadIdx.x; x < L.n_index; x += nt) {
         const int64_t kc = L.kbase + x;
         const int64_t j = (int64_t)q.cell[kc] - L.cell_base;
         const int64_t gap = j > i ? j - i : i - j;
         if (gap < q.excl) continue;
-        const double dd = snap(lane_zdist(q.t, i, mui, isi, j, q.mu[kc], q.isig[kc], m));
+        const double dd = snap(lane_zdist(q.t, i, mui, isi, j, q.mu[kc], q.isig[kc], m, lim2));
         const unsigned long long b = (unsigned long long)dbits(dd);
         best = b < best ? b : best;
         if (b == R.target && (unsigned long long)j < arg) arg = (unsigned long long)j;
@@ -428,7 +459,17 @@ __global__ __launch_bounds__(kBlock) void k_rows(Req q, const RowReq *__restrict
         best = o < best ? o : best;
         arg = a < arg ? a : arg;
     }
+    __shared__ unsigned long long wb[kBlock / kWave], wa[kBlock / kWave];
     if (lane_id() == 0) {
+        wb[threadIdx.x / kWave] = best;
+        wa[threadIdx.x / kWave] = arg;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int v = 1; v < kBlock / kWave; ++v) {
+            best = wb[v] < best ? wb[v] : best;
+            arg = wa[v] < arg ? wa[v] : arg;
+        }
         atomicMin(&out_min[blockIdx.y], best);
         if (arg != ~0ull) atomicMin(&out_arg[blockIdx.y], arg);
     }
@@ -499,7 +540,7 @@ void launch_select(const Select &x, const uint64_t *P, int64_t n, const uint32_t
 void launch_rows(const Req &q, const RowReq *rr, int nrows, int64_t maxN,
                  unsigned long long *out_min, unsigned long long *out_arg, hipStream_t s) {
     if (nrows <= 0) return;
-    hipLaunchKernelGGL(k_rows, dim3(gridcap(maxN, 1024), (unsigned)nrows), dim3(kBlock), 0, s,
+    hipLaunchKernelGGL(k_rows, dim3(gridcap(maxN, 128), (unsigned)nrows), dim3(kBlock), 0, s,
                        q, rr, out_min, out_arg);
 }
 

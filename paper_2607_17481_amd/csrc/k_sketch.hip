@@ -180,6 +180,21 @@ __device__ __forceinline__ void sketch_record(const Req &q, int m, int kprime,
     emax = fmaxf(emax, e);
 }
 
+// The length and tile of a sketch block, or -1 (uniform): tile blockIdx.x of all
+// lengths' tiles, or, for the anchors (every stride-th length and the last),
+// tile x of anchor y.
+__device__ __forceinline__ int sketch_tile(const Req &q, int mode, int stride, int64_t &tile) {
+    if (mode == kSketchAnchors) {
+        const int l = min((int)blockIdx.y * stride, q.L - 1);
+        if ((int64_t)blockIdx.x * kTileW >= q.len[l].W) return -1;
+        tile = q.len[l].tile_base + blockIdx.x;
+        return l;
+    }
+    tile = blockIdx.x;
+    const int l = find_tile_len(q.len, q.L, tile);
+    return mode == kSketchBetween && q.len[l].anchor ? -1 : l;   // (done by the first pass)
+}
+
 // A tile's samples into LDS: st[r] = t[i0 + r] for r < nvalid, 0 up to
 // ntotal.  Every load of a thread is issued before the first LDS write, so a
 // tile waits for memory once, not once per 256 samples.
@@ -200,16 +215,36 @@ __device__ __forceinline__ void load_tile_samples(const double *__restrict__ t, 
     }
 }
 
+// One non-constant window (x: its samples in LDS, k: its position): the
+// two-pass moments (Sec. 3.2), its cell, and no value and no hint yet.
+__device__ __forceinline__ void window_entry(const Req &q, const double *x, int m, uint32_t cell,
+                                             int64_t k, double &mu, double &is) {
+    const double sg = window_moments(x, m, mu);
+    is = 1.0 / sg;
+    if (!(sg > 0.0) || !isfinite(sg) || !(is > 0.0) || !isfinite(is)) {
+        // samples differ but sigma underflows or overflows: outside the
+        // range the library represents; the window stays indexed so
+        // every count stays consistent, and the call fails
+        atomicOr(q.bad, 2);
+        is = 1.0;
+    }
+    q.cell[k] = cell;
+    q.mu[k] = mu;
+    q.isig[k] = is;
+    q.P[k] = kInfBits;
+    q.hint[k] = kNone;
+}
+
 // Shared first steps of a sketch tile (samples already in LDS): the
 // compacted position k of every non-constant window (thread tid takes
 // windows 4 tid .. 4 tid + 3; a block scan) and the list of those windows,
-// then their two-pass moments (Sec. 3.2), dealt evenly over the threads from
-// the list, with their cell and the initial profile value.  Ends with the
-// block synchronized and kpos final (and, when given, smu / sis: the mean
-// and 1 / sigma of each non-constant window by its place in the tile).
+// then, unless k_moments made them (`made`), their entries, dealt evenly over
+// the threads from the list.  Ends with the block synchronized and kpos final
+// (and, when given, smu / sis: the mean and 1 / sigma of each non-constant
+// window by its place in the tile).
 __device__ __forceinline__ void tile_positions_and_moments(
     const Req &q, const LenInfo &L, int64_t i0, int nw, int64_t tile, const double *st,
-    const uint32_t *__restrict__ E, const uint32_t *__restrict__ tile_off, int32_t *kpos,
+    const uint32_t *__restrict__ E, const uint32_t *__restrict__ tile_off, bool made, int32_t *kpos,
     uint16_t *widx, uint32_t *wsum, double *smu = nullptr, double *sis = nullptr) {
     const int m = L.m;
     const int tid = threadIdx.x;
@@ -254,31 +289,22 @@ __device__ __forceinline__ void tile_positions_and_moments(
     }
     __syncthreads();
     // the cell -> indexed position map (anchors and hints need it)
-    if (q.kmap)
+    if (q.kmap && !made)
         for (int w = tid; w < nw; w += kBlock)
             q.kmap[L.cell_base + i0 + w] = kpos[w] < 0 ? kNone : (uint32_t)kpos[w];
     int nix = 0;                                        // non-constant windows of the tile
     for (int v = 0; v < kBlock / kWave; ++v) nix += (int)wsum[v];
 
-    // ---- moments (two-pass, population; Sec. 3.2), one thread per
-    // non-constant window
-    for (int xi = tid; xi < nix; xi += kBlock) {
+    for (int xi = tid; xi < nix && !(made && !smu); xi += kBlock) {
         const int w = widx[xi];
         const int32_t kk = kpos[w];
-        double mu;
-        const double sg = window_moments(st + w, m, mu);
-        double is = 1.0 / sg;
-        if (!(sg > 0.0) || !isfinite(sg) || !(is > 0.0) || !isfinite(is)) {
-            // samples differ but sigma underflows or overflows: outside the
-            // range the library represents; the window stays indexed so
-            // every count stays consistent, and the call fails
-            atomicOr(q.bad, 2);
-            is = 1.0;
+        double mu, is;
+        if (made) {
+            mu = q.mu[kk];
+            is = q.isig[kk];
+        } else {
+            window_entry(q, st + w, m, (uint32_t)(L.cell_base + i0 + w), kk, mu, is);
         }
-        q.cell[kk] = (uint32_t)(L.cell_base + i0 + w);
-        q.mu[kk] = mu;
-        q.isig[kk] = is;
-        q.P[kk] = kInfBits;
         if (smu) {
             smu[w] = mu;
             sis[w] = is;
@@ -288,6 +314,99 @@ __device__ __forceinline__ void tile_positions_and_moments(
 }
 
 }  // namespace
+
+// Positions and entries of the windows of the lengths between anchors, which get
+// their records later, or never.  Block (x, y): the starts [x, x + 1) * kTileW
+// at up to `group` lengths, whose samples and change-point counts it stages
+// once; the windows of all of them are listed in LDS and dealt evenly over the
+// threads, so that a few windows per length (a series of mostly constant
+// stretches) still keep every lane busy.
+//
+// Bounded by the two serial sums of m samples per window, read from LDS.  As
+// tiles of the sketch itself (one length a block, three blocks a compute unit
+// because of the staging rows, a fifth of the threads busy) 5M samples of a
+// Wafer-like series at 51 lengths took 3.5 ms with the anchors' records; this
+// takes 1.8, and those 1.2.
+constexpr int kMomentList = 2 * kTileW;
+
+__global__ __launch_bounds__(kBlock) void k_moments(Req q, const uint32_t *__restrict__ E,
+                                                    const uint32_t *__restrict__ tile_off, int group,
+                                                    int st_len) {
+    extern __shared__ double dyn[];
+    __shared__ uint2 list[kMomentList];                  // position; length and window
+    __shared__ uint32_t cnt[2][kBlock / kWave];
+    double *st = dyn;                                    // samples
+    uint32_t *e = (uint32_t *)(dyn + st_len);            // change-point counts
+    const int l0 = blockIdx.y * group, l1 = min(q.L, l0 + group);
+    const int64_t i0 = (int64_t)blockIdx.x * kTileW;
+    if (i0 >= q.len[l0].W) return;                       // (window counts descend)
+    const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
+    const int64_t n1 = q.len[l0].W + q.len[l0].m;        // entries of E: n + 1
+    const int span = (int)min<int64_t>(kTileW + q.len[l1 - 1].m, n1 - i0);
+    for (int x = tid; x < span; x += kBlock) {
+        e[x] = E[i0 + x];
+        if (i0 + x < n1 - 1) st[x] = q.t[i0 + x];
+    }
+    __syncthreads();
+    int n = 0, turn = 0;
+    auto flush = [&]() {
+        __syncthreads();
+        for (int x = tid; x < n; x += kBlock) {
+            const uint2 u = list[x];
+            const int l = l0 + (int)(u.y >> 16), w = (int)(u.y & 0xFFFFu);
+            double mu, is;
+            window_entry(q, st + w, q.len[l].m, (uint32_t)(q.len[l].cell_base + i0 + w), u.x, mu, is);
+        }
+        __syncthreads();
+        n = 0;
+    };
+    for (int l = l0; l < l1; ++l) {
+        const LenInfo &L = q.len[l];
+        if (L.anchor || i0 >= L.W) continue;             // (uniform)
+        const int m = L.m, nw = (int)min<int64_t>(kTileW, L.W - i0);
+        if (n + kTileW > kMomentList) flush();
+        // wavefront wv takes the windows [256 wv, 256 wv + 256) of the tile
+        constexpr int kRounds = kTileW / kBlock;
+        const int w0 = wv * (kTileW / (kBlock / kWave)) + lane;
+        uint64_t bal[kRounds];
+        int mine = 0;
+#pragma unroll
+        for (int j = 0; j < kRounds; ++j) {
+            const int w = w0 + j * kWave;
+            bal[j] = __ballot(w < nw && e[w + m] != e[w + 1]);
+            mine += __popcll(bal[j]);
+        }
+        if (lane == 0) cnt[turn][wv] = (uint32_t)mine;
+        // (two sets of counts in turn: one barrier a length)
+        __syncthreads();
+        uint32_t at = 0, total = 0;
+#pragma unroll
+        for (int v = 0; v < kBlock / kWave; ++v) {
+            at += v < wv ? cnt[turn][v] : 0u;
+            total += cnt[turn][v];
+        }
+        turn ^= 1;
+        at = __builtin_amdgcn_readfirstlane(at);
+        const uint32_t base = tile_off[L.tile_base + blockIdx.x];
+        uint32_t *const km = q.kmap ? q.kmap + L.cell_base + i0 : nullptr;
+#pragma unroll
+        for (int j = 0; j < kRounds; ++j) {
+            const int w = w0 + j * kWave;
+            uint32_t k = kNone;
+            if (bal[j]) {                                // (uniform)
+                if ((bal[j] >> lane) & 1ull) {
+                    const uint32_t r = at + (uint32_t)__popcll(bal[j] & lanemask_lt());
+                    k = base + r;
+                    list[n + r] = make_uint2(k, (uint32_t)(l - l0) << 16 | (uint32_t)w);
+                }
+                at += (uint32_t)__popcll(bal[j]);
+            }
+            if (km && w < nw) km[w] = k;
+        }
+        n += (int)total;
+    }
+    flush();
+}
 
 // One block per tile of 1024 consecutive windows of one length.
 //  1. samples into LDS; compacted position of every non-constant window;
@@ -305,13 +424,13 @@ __device__ __forceinline__ void tile_positions_and_moments(
 template <typename FT>
 __global__ __launch_bounds__(kBlock, 3) void k_sketch(Req q, const uint32_t *__restrict__ E,
                                                       const uint32_t *__restrict__ tile_off,
-                                                      int st_len, int mode) {
+                                                      int st_len, int mode, int stride) {
     extern __shared__ double dyn[];
     __shared__ SketchSmem sm;
-    const int64_t tile = blockIdx.x;
-    const int l = find_tile_len(q.len, q.L, tile);
+    int64_t tile;
+    const int l = sketch_tile(q, mode, stride, tile);
+    if (l < 0) return;
     const LenInfo L = q.len[l];
-    if (mode == kSketchBetween && L.anchor) return;       // done by the first pass
     const int m = L.m;
     const int kp = L.kprime;
     const int64_t i0 = (tile - L.tile_base) * kTileW;
@@ -328,8 +447,8 @@ __global__ __launch_bounds__(kBlock, 3) void k_sketch(Req q, const uint32_t *__r
     for (int x = tid; x < kRowsC * (kFD - 2 * kp); x += kBlock)
         stage[x / (kFD - 2 * kp)][2 * kp + x % (kFD - 2 * kp)] = 0.0;
 
-    tile_positions_and_moments(q, L, i0, nw, tile, st, E, tile_off, sm.kpos, sm.widx, sm.wsum);
-    if (mode == kSketchAnchors && !L.anchor) return;      // records later, if needed
+    tile_positions_and_moments(q, L, i0, nw, tile, st, E, tile_off, mode == kSketchBetween, sm.kpos,
+                               sm.widx, sm.wsum);
     // ---- sliding DFT in FP64: thread (segment g, bin b)
     const int b = tid & 15;
     const int g = tid >> 4;
@@ -518,17 +637,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                                                         const int64_t *__restrict__ bbase,
                                                         const uint16_t *__restrict__ bh,
                                                         const uint16_t *__restrict__ bm,
-                                                        const uint16_t *__restrict__ bl, int mode) {
+                                                        const uint16_t *__restrict__ bl, int mode,
+                                                        int stride) {
     extern __shared__ double dyn[];
     __shared__ int32_t kpos[kTileW];
     __shared__ uint16_t widx[kTileW];
     __shared__ uint32_t wsum[kBlock / kWave];
     __shared__ double smu[kTileW], sis[kTileW];
     __shared__ int emax_s;
-    const int64_t tile = blockIdx.x;
-    const int l = find_tile_len(q.len, q.L, tile);
+    int64_t tile;
+    const int l = sketch_tile(q, mode, stride, tile);
+    if (l < 0) return;
     const LenInfo L = q.len[l];
-    if (mode == kSketchBetween && L.anchor) return;       // done by the first pass
     const int m = L.m;
     const int mp = (m + 15) & ~15;
     const int64_t i0 = (tile - L.tile_base) * kTileW;
@@ -540,8 +660,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 
     if (tid == 0) emax_s = 0;
     load_tile_samples(q.t, i0, nw + m - 1, nw + mp + kMBlk, st);
-    tile_positions_and_moments(q, L, i0, nw, tile, st, E, tile_off, kpos, widx, wsum, smu, sis);
-    if (mode == kSketchAnchors && !L.anchor) return;      // records later, if needed
+    tile_positions_and_moments(q, L, i0, nw, tile, st, E, tile_off, mode == kSketchBetween, kpos, widx,
+                               wsum, smu, sis);
 
     const uint4 *Bh = (const uint4 *)(bh + bbase[l]);
     const uint4 *Bm = (const uint4 *)(bm + bbase[l]);
@@ -692,38 +812,40 @@ namespace {
 
 // The FP32 copy f of a window's stored features (zeros when !valid), with
 // the record's error bound and norm.
+constexpr int kFRow = 33;                     // floats per staged record (odd: lanes' rows
+                                              // fall in different banks)
+
+// The FP32 copies of the records of the n <= 64 windows from k0 on into the
+// wavefront's LDS rows (feature c at [c], the error at [kSlotErr], the norm,
+// raised by its rounding, behind it), 16 bytes a lane in memory order: a lane
+// reading its own record touches 64 lines per load and, at 16 wavefronts a
+// compute unit, fetched each of them four times.
 template <typename FT>
-__device__ __forceinline__ void load_fcopy(const Req &q, int64_t kk, bool valid, float f[kFD],
-                                           float &erec, float &nrec) {
-    const FT *rec = (const FT *)q.F + kk * kRec;
-    erec = nrec = 0.0f;
+__device__ __forceinline__ void stage_records(const Req &q, int64_t k0, int n, float *rows) {
+    const int lane = lane_id();
+    constexpr int kPer = 16 / sizeof(FT);     // slots per 16 bytes
+    constexpr int kVec = kRec / kPer;         // loads per record
+    const FT *src = (const FT *)q.F + k0 * kRec;
+    typedef __attribute__((ext_vector_type(kPer))) FT vec;
+    vec v[kVec];
 #pragma unroll
-    for (int c = 0; c < kFD; ++c) f[c] = 0.0f;
-    if (valid && sizeof(FT) == 8) {
-#pragma unroll
-        for (int p = 0; p < kFD / 2; ++p) {
-            const double2 v = *(const double2 *)(rec + 2 * p);
-            f[2 * p] = (float)v.x;
-            f[2 * p + 1] = (float)v.y;
-        }
-        const double2 v = *(const double2 *)(rec + kSlotErr);
-        erec = (float)v.x;
-        nrec = (float)(v.y * (1.0 + 1e-7));
-    } else if (valid) {
-#pragma unroll
-        for (int p = 0; p < 7; ++p) {
-            const float4 v = *(const float4 *)(rec + 4 * p);
-            f[4 * p] = v.x;
-            f[4 * p + 1] = v.y;
-            f[4 * p + 2] = v.z;
-            f[4 * p + 3] = v.w;
-        }
-        const float4 v = *(const float4 *)(rec + 28);
-        f[28] = v.x;
-        f[29] = v.y;
-        erec = v.z;
-        nrec = v.w;
+    for (int u = 0; u < kVec; ++u) {
+        const int x = u * kWave + lane;       // record x / kVec, slots from (x % kVec) kPer on
+        v[u] = x / kVec < n ? *(const vec *)(src + (int64_t)x * kPer) : vec{};
     }
+#pragma unroll
+    for (int u = 0; u < kVec; ++u) {
+        const int x = u * kWave + lane;
+        float *r = rows + (x / kVec) * kFRow + (x % kVec) * kPer;
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+            const int slot = (x % kVec) * kPer + e;
+            r[e] = slot == kSlotNorm ? (sizeof(FT) == 8 ? (float)((double)v[u][e] * (1.0 + 1e-7)) : (float)v[u][e])
+                                     : (float)v[u][e];
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 // The FP32 copy as bf16 pairs: hi = bf16(f), lo = bf16(f - hi); hi + lo is
@@ -755,17 +877,47 @@ __device__ __forceinline__ void bf16_pairs(const float f[kFD], uint32_t hw[16], 
 // normal range as 0), their metadata and the principal coordinates of the FP32
 // copy (FP64 dots) that place the grid.
 template <typename FT>
-__global__ __launch_bounds__(kBlock) void k_join_ops(Req q, int64_t k0, int64_t k1) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
+void k_join_ops(Req q, const double *__restrict__ udir, int64_t k0, int64_t k1) {
     const int64_t kk = k0 + (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const bool live = kk < k1;
     const int64_t k_first = k0 + (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~(kWave - 1));
     if (k_first >= k1) return;
     const int l = find_len_k_wave(q.len, q.L, k_first, live ? kk : k_first);
+    __shared__ float rows[kBlock / kWave][kWave * kFRow];
+    __shared__ double dirs[kBlock / kWave][kJoinDirs * 32];
+    const int lane = lane_id(), wv = threadIdx.x / kWave;
+    stage_records<FT>(q, k_first, (int)min(k1 - k_first, (int64_t)kWave), rows[wv]);
+    const float *const fr = rows[wv] + lane * kFRow;
+    // the principal coordinates, for the windows of one length at a time
+    // (usually the wavefront's only one), its directions in LDS
+    double p0 = 0.0, p1 = 0.0, p2 = 0.0;
+    for (uint64_t todo = __ballot(live); todo;) {
+        const int lu = __builtin_amdgcn_readlane(l, __ffsll((unsigned long long)todo) - 1);
+        todo &= ~__ballot(live && l == lu);
+        const double *u = udir + (int64_t)lu * kJoinDirs * 32;
+        dirs[wv][lane] = u[lane];
+        if (lane < kJoinDirs * 32 - kWave) dirs[wv][kWave + lane] = u[kWave + lane];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (l == lu) {
+#pragma unroll 6
+            for (int c = 0; c < kFD; ++c) {
+                const double x = (double)fr[c];
+                p0 = fma(dirs[wv][c], x, p0);
+                p1 = fma(dirs[wv][32 + c], x, p1);
+                p2 = fma(dirs[wv][64 + c], x, p2);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
     float ep = 0.0f;
     if (live) {
         float f[kFD];
-        float erec, nrec;
-        load_fcopy<FT>(q, kk, true, f, erec, nrec);
+#pragma unroll
+        for (int c = 0; c < kFD; ++c) f[c] = fr[c];
+        const float erec = fr[kSlotErr], nrec = fr[kSlotNorm];
         const uint32_t cw = half_bits(join_scale(q.len[l].m));
         uint32_t hw[16];
         double n2 = 0.0, r2 = 0.0;
@@ -784,14 +936,6 @@ __global__ __launch_bounds__(kBlock) void k_join_ops(Req q, int64_t k0, int64_t 
             hw[w] = hp;
         }
         hw[15] = cw | (cw << 16);
-        const double *u = q.udir + (int64_t)l * kJoinDirs * 32;
-        double p0 = 0.0, p1 = 0.0, p2 = 0.0;
-#pragma unroll
-        for (int c = 0; c < kFD; ++c) {
-            p0 = fma(u[c], (double)f[c], p0);
-            p1 = fma(u[32 + c], (double)f[c], p1);
-            p2 = fma(u[64 + c], (double)f[c], p2);
-        }
         // f is within u32 |F~| of the stored record F~, itself within e of F;
         // so e' = e + u32 |F~| + |G - f| bounds |G - F|
         uint4 *jo = q.jop + kk * kJoinOp;
@@ -858,9 +1002,15 @@ __global__ __launch_bounds__(kBlock) void k_keys(Req q, const float *__restrict_
     const bool valid = j < L.n_index;
     const int64_t kk = L.kbase + (valid ? j : 0);
 
+    // (the staged records lie where the projections go)
+    float *const rows = &sm.dots[tid / kWave][0][0][0];
+    const int64_t jw = ((int64_t)blockIdx.x - L.blk_base) * kBlock + (tid & ~(kWave - 1));
+    stage_records<FT>(q, L.kbase + jw, (int)max(min(L.n_index - jw, (int64_t)kWave), (int64_t)0), rows);
     float f[kFD];
-    float erec = 0.0f, nrec = 0.0f;
-    load_fcopy<FT>(q, kk, valid, f, erec, nrec);
+#pragma unroll
+    for (int c = 0; c < kFD; ++c) f[c] = rows[(tid & (kWave - 1)) * kFRow + c];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     uint32_t hw[16], lw[16];
     bf16_pairs(f, hw, lw);
 
@@ -953,20 +1103,33 @@ __global__ __launch_bounds__(kBlock) void k_keys(Req q, const float *__restrict_
 // First slot of every bucket from the sorted keys: between two consecutive
 // sorted entries, every bucket index in (previous, current] starts at the
 // current slot (empty buckets included); the entry past the end closes the
-// last buckets.  Also the slot map: slot -> cell.
+// last buckets.  Also the slot map: slot -> cell.  Runs of more than a few
+// empty buckets (a series of few shapes leaves most of a deep directory empty)
+// are filled by the whole wavefront: one lane's 10^5 stores in turn took 176 us
+// at Wafer-like 5M, 68 now.
 __global__ __launch_bounds__(kBlock) void k_bucket_bounds(Req q, int64_t N, int64_t nbuckets,
                                                           uint32_t *__restrict__ bstart) {
     const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (s > N) return;
     const uint32_t mask = (1u << q.key_shift) - 1u;
     auto gidx = [&](uint32_t key) -> int64_t {
         const int l = (int)(key >> q.key_shift);
         const int d = q.len[l].depth;
         return q.len[l].bucket_base + (int64_t)((key & mask) >> (q.key_shift - d));
     };
-    const int64_t cur = s < N ? gidx(q.skey[s]) : nbuckets;
-    const int64_t prev = s > 0 ? gidx(q.skey[s - 1]) : -1;
-    for (int64_t b = prev + 1; b <= cur; ++b) bstart[b] = (uint32_t)s;
+    int64_t cur = -1, prev = -1;                         // (past N: nothing)
+    if (s <= N) {
+        cur = s < N ? gidx(q.skey[s]) : nbuckets;
+        prev = s > 0 ? gidx(q.skey[s - 1]) : -1;
+    }
+    const bool wide = cur - prev > 8;
+    if (!wide)
+        for (int64_t b = prev + 1; b <= cur; ++b) bstart[b] = (uint32_t)s;
+    for (uint64_t todo = __ballot(wide); todo; todo &= todo - 1) {
+        const int src = __ffsll((unsigned long long)todo) - 1;
+        const int64_t p1 = __shfl(prev, src, kWave), c1 = __shfl(cur, src, kWave);
+        const uint32_t v = (uint32_t)(s - lane_id() + src);
+        for (int64_t b = p1 + 1 + lane_id(); b <= c1; b += kWave) bstart[b] = v;
+    }
     if (s < N) q.pcell[s] = q.cell[q.perm[s]];
 }
 
@@ -986,9 +1149,26 @@ void launch_tile_counts(const LenInfo *len, int L, const uint32_t *E, int64_t st
                        dim3(kBlock), 0, s, len, L, E, group, ntiles, tile_cnt);
 }
 
-void launch_sketch(int precision, const Req &q, const uint32_t *E, const uint32_t *tile_off,
-                   int64_t ntiles, int max_m, int mode, hipStream_t s) {
-    if (ntiles <= 0) return;
+static dim3 sketch_grid(const SketchGrid &g, int mode) {
+    if (mode == kSketchAnchors)
+        return dim3((unsigned)((g.starts + kTileW - 1) / kTileW), (unsigned)g.anchors);
+    return dim3((unsigned)g.ntiles);
+}
+
+// Lengths per block: as many as leave the chip 2048 blocks, up to 8 (samples,
+// counts and list fit four blocks a compute unit up to windows of 500).
+void launch_moments(const Req &q, const uint32_t *E, const uint32_t *tile_off, const SketchGrid &g,
+                    int max_m, hipStream_t s) {
+    const int64_t tiles = (g.starts + kTileW - 1) / kTileW;
+    const int group = (int)std::min<int64_t>(std::max<int64_t>(g.ntiles / 2048, 1), 8);
+    const int st_len = (kTileW + max_m + 1) & ~1;
+    hipLaunchKernelGGL(k_moments, dim3((unsigned)tiles, (unsigned)((q.L + group - 1) / group)),
+                       dim3(kBlock), (size_t)st_len * 12, s, q, E, tile_off, group, st_len);
+}
+
+void launch_sketch(const Req &q, const uint32_t *E, const uint32_t *tile_off, const SketchGrid &g,
+                   int max_m, int mode, hipStream_t s) {
+    if (g.ntiles <= 0) return;
     // samples (1024 + m - 1 doubles, rounded up to an even count so the
     // staging rows that follow are 16-byte aligned), then the staging rows,
     // sized for the longest window of the request
@@ -996,9 +1176,8 @@ void launch_sketch(int precision, const Req &q, const uint32_t *E, const uint32_
     const size_t dyn = (size_t)(st_len + kRowsC * kStageLd) * sizeof(double);
     // the FP64 form only: the precision forms sketch on the matrix cores
     // (k_sketch_mfma)
-    (void)precision;
-    hipLaunchKernelGGL((k_sketch<double>), dim3((unsigned)ntiles), dim3(kBlock), dyn, s, q, E,
-                       tile_off, st_len, mode);
+    hipLaunchKernelGGL((k_sketch<double>), sketch_grid(g, mode), dim3(kBlock), dyn, s, q, E,
+                       tile_off, st_len, mode, g.stride);
 }
 
 int64_t basis_elems(const LenInfo *len_host, int L, std::vector<int64_t> &base) {
@@ -1015,26 +1194,25 @@ void launch_basis(const LenInfo *len, int L, const int64_t *base, uint16_t *bh, 
                        bl);
 }
 
-void launch_sketch_mfma(int precision, const Req &q, const uint32_t *E, const uint32_t *tile_off,
-                        int64_t ntiles, int max_m, const int64_t *bbase, const uint16_t *bh,
+void launch_sketch_mfma(const Req &q, const uint32_t *E, const uint32_t *tile_off,
+                        const SketchGrid &g, int max_m, const int64_t *bbase, const uint16_t *bh,
                         const uint16_t *bm, const uint16_t *bl, int mode, hipStream_t s) {
-    if (ntiles <= 0) return;
-    // samples of the tile, padded with zeros for the last block's reads
+    if (g.ntiles <= 0) return;
+    // samples of the tile, padded with zeros for the last block's reads; both
+    // precision forms take FP32-grade features (form 2 differs in its keys
+    // only)
     const size_t dyn = (size_t)(kTileW + ((max_m + 15) & ~15) + kMBlk) * sizeof(double);
-    // both precision forms take FP32-grade features (form 2 differs in its
-    // keys only)
-    (void)precision;
-    hipLaunchKernelGGL(k_sketch_mfma, dim3((unsigned)ntiles), dim3(kBlock), dyn, s, q, E,
-                       tile_off, bbase, bh, bm, bl, mode);
+    hipLaunchKernelGGL(k_sketch_mfma, sketch_grid(g, mode), dim3(kBlock), dyn, s, q, E, tile_off,
+                       bbase, bh, bm, bl, mode, g.stride);
 }
 
 void launch_join_ops(int precision, const Req &q, int64_t k0, int64_t k1, hipStream_t s) {
     if (k1 <= k0) return;
     const unsigned g = (unsigned)((k1 - k0 + kBlock - 1) / kBlock);
     if (precision == 0)
-        hipLaunchKernelGGL(k_join_ops<double>, dim3(g), dim3(kBlock), 0, s, q, k0, k1);
+        hipLaunchKernelGGL(k_join_ops<double>, dim3(g), dim3(kBlock), 0, s, q, q.udir, k0, k1);
     else
-        hipLaunchKernelGGL(k_join_ops<float>, dim3(g), dim3(kBlock), 0, s, q, k0, k1);
+        hipLaunchKernelGGL(k_join_ops<float>, dim3(g), dim3(kBlock), 0, s, q, q.udir, k0, k1);
 }
 
 void launch_keys(int precision, const Req &q, int64_t nblocks, hipStream_t s) {

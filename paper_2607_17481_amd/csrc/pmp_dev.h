@@ -447,6 +447,8 @@ __device__ __forceinline__ int find_len_k_wave(const LenInfo *len, int L, int64_
 __device__ __forceinline__ double window_moments(const double *x, int m, double &mu) {
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
     int r = 0;
+    // (the sums are chains; unrolled so that their reads are in flight together)
+#pragma unroll 4
     for (; r + 4 <= m; r += 4) {
         a0 += x[r];
         a1 += x[r + 1];
@@ -456,6 +458,7 @@ __device__ __forceinline__ double window_moments(const double *x, int m, double 
     for (; r < m; ++r) a0 += x[r];
     mu = ((a0 + a1) + (a2 + a3)) / (double)m;
     a0 = a1 = a2 = a3 = 0.0;
+#pragma unroll 4
     for (r = 0; r + 4 <= m; r += 4) {
         const double c0 = x[r] - mu, c1 = x[r + 1] - mu;
         const double c2 = x[r + 2] - mu, c3 = x[r + 3] - mu;
@@ -739,22 +742,29 @@ void launch_changepoints(const double *t, int64_t n, uint32_t *flag, int *bad, h
 // (also clears tile_cnt[ntiles]; starts = windows of the shortest length)
 void launch_tile_counts(const LenInfo *len, int L, const uint32_t *E, int64_t starts, int max_m,
                         int64_t ntiles, uint32_t *tile_cnt, hipStream_t s);
-// Which tiles of [0, ntiles) the sketch gives records: every length
-// (kSketchAll), the anchor lengths only, the moments and positions of every
-// tile still written (kSketchAnchors), or the lengths between anchors, whose
-// moments and positions a kSketchAnchors pass already wrote (kSketchBetween;
-// it re-writes them with the same values and resets their cells to +inf, so
-// it runs before anything lowers a cell of those lengths)
+// Which tiles the sketch gives records (and, but for kSketchBetween, positions
+// and moments): every length (kSketchAll), the anchor lengths (kSketchAnchors),
+// or the lengths between anchors, after k_moments (kSketchBetween)
 enum { kSketchAll = 0, kSketchAnchors = 1, kSketchBetween = 2 };
-void launch_sketch(int precision, const Req &q, const uint32_t *E, const uint32_t *tile_off,
-                   int64_t ntiles, int max_m, int mode, hipStream_t s);
+// The tiles of a sketch launch: all tiles [0, ntiles) of the lengths in turn, or
+// the anchors' (every stride-th length and the last; starts: windows of the
+// shortest length).
+struct SketchGrid {
+    int64_t ntiles, starts;
+    int stride, anchors;
+};
+// Positions, moments and initial values of the lengths between anchors.
+void launch_moments(const Req &q, const uint32_t *E, const uint32_t *tile_off, const SketchGrid &g,
+                    int max_m, hipStream_t s);
+void launch_sketch(const Req &q, const uint32_t *E, const uint32_t *tile_off, const SketchGrid &g,
+                   int max_m, int mode, hipStream_t s);
 void launch_keys(int precision, const Req &q, int64_t nblocks, hipStream_t s);
 void launch_join_ops(int precision, const Req &q, int64_t k0, int64_t k1, hipStream_t s);
 int64_t basis_elems(const LenInfo *len_host, int L, std::vector<int64_t> &base);
 void launch_basis(const LenInfo *len, int L, const int64_t *base, uint16_t *bh, uint16_t *bm,
                   uint16_t *bl, int max_m, hipStream_t s);
-void launch_sketch_mfma(int precision, const Req &q, const uint32_t *E, const uint32_t *tile_off,
-                        int64_t ntiles, int max_m, const int64_t *bbase, const uint16_t *bh,
+void launch_sketch_mfma(const Req &q, const uint32_t *E, const uint32_t *tile_off,
+                        const SketchGrid &g, int max_m, const int64_t *bbase, const uint16_t *bh,
                         const uint16_t *bm, const uint16_t *bl, int mode, hipStream_t s);
 void launch_bucket_bounds(const Req &q, int64_t N, int64_t nbuckets, uint32_t *bstart,
                           hipStream_t s);

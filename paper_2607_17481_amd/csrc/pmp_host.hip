@@ -745,11 +745,12 @@ static int run_sieve(const Plan &p, Bufs &b, const Req &q, const Opt &o, hipStre
 // tiles get records, kSketch*).
 static void launch_records(const Plan &p, Bufs &b, const Req &q, const Opt &o, int64_t ntiles,
                            int mode, hipStream_t s) {
+    const SketchGrid g{ntiles, p.n - p.ms[0] + 1, o.stride, p.anchors};
+    if (mode == kSketchAnchors) launch_moments(q, b.E, b.tile_off, g, p.max_m, s);
     if (o.precision == 0)
-        launch_sketch(o.precision, q, b.E, b.tile_off, ntiles, p.max_m, mode, s);
+        launch_sketch(q, b.E, b.tile_off, g, p.max_m, mode, s);
     else
-        launch_sketch_mfma(o.precision, q, b.E, b.tile_off, ntiles, p.max_m, b.bbase, b.bh, b.bm,
-                           b.bl, mode, s);
+        launch_sketch_mfma(q, b.E, b.tile_off, g, p.max_m, b.bbase, b.bh, b.bm, b.bl, mode, s);
 }
 
 // rec_lim: with `lazy` (the first pass gave records to the anchor lengths
@@ -1038,7 +1039,6 @@ static int run_pipeline(Run &R, Arena &ar) {
     }
     launch_bucket_bounds(q, p.Na, p.nbuckets, b.bstart, s);
     launch_hot_buckets(b.bstart, p.nbuckets, q.budget_R, &b.counters[C_HOT], s);
-    launch_fill_u32(b.hint, N, kNone, s);
     tm.mark(3, s);
     tm.mark(4, s);
     // the selection after the first anchor's probe, when it settled the top-k
@@ -1576,7 +1576,7 @@ static int scratch_address(void **out) {
 
 // ------------------------------------ device memory of pmp_open
 // Allocating and freeing the series and workspace of a call took 2 to 17 ms
-// (640 MB for 30,000 samples, whose own work is below 1 ms), so the
+// (640 MB for 30,000 samples at 101 lengths, whose own work is 1.5 ms), so the
 // last block and its stream stay for the next call on that device: one idle
 // block a device, of at most kHostKeep bytes.  It is owned by one call at a time
 // (calls that overlap find it gone and allocate); it is freed when a call needs
