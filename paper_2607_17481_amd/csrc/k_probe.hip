@@ -80,7 +80,8 @@ struct QwinA {
 template <typename FT, bool kCut, int kTeam>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 void k_probe(Req q, const uint32_t *__restrict__ bstart, int qcap, int64_t blk0, double cut,
-             Quant x) {
+             Quant x, ProbeIf go) {
+    if (go.zeros && *go.zeros >= go.limit) return;           // (uniform)
     // the anchor length of this block (blocks [blk0, blk0 + gridDim.x) of
     // the probe): the last length whose first probe block is at or below it
     // (uniform)
@@ -329,33 +330,34 @@ constexpr int64_t kProbeWaves = 4096;
 
 template <typename FT, int kTeam>
 static void launch_probe_team(const Req &q, const uint32_t *bstart, int64_t blk0, int64_t nblocks,
-                              int qcap, const Quant &x, hipStream_t s) {
+                              int qcap, const Quant &x, const ProbeIf &go, hipStream_t s) {
     hipLaunchKernelGGL((k_probe<FT, false, kTeam>), dim3((unsigned)(nblocks * (kTeam / kGroup))),
                        dim3(kWave), (size_t)qcap * sizeof(double), s, q, bstart, qcap, blk0,
-                       INFINITY, x);
+                       INFINITY, x, go);
 }
 template <typename FT>
 static void launch_probe_ft(const Req &q, const uint32_t *bstart, int64_t blk0, int64_t nblocks,
-                            int qcap, double cut, const Quant &x, hipStream_t s) {
+                            int qcap, double cut, const Quant &x, const ProbeIf &go, hipStream_t s) {
     if (x.x16)                    // (over 2^20 windows: the queries fill the chip)
         hipLaunchKernelGGL((k_probe<FT, true, kGroup>), dim3((unsigned)nblocks), dim3(kWave),
-                           (size_t)qcap * sizeof(double), s, q, bstart, qcap, blk0, cut, x);
+                           (size_t)qcap * sizeof(double), s, q, bstart, qcap, blk0, cut, x, go);
     else if (nblocks * 8 <= kProbeWaves)
-        launch_probe_team<FT, 64>(q, bstart, blk0, nblocks, qcap, x, s);
+        launch_probe_team<FT, 64>(q, bstart, blk0, nblocks, qcap, x, go, s);
     else if (nblocks * 4 <= kProbeWaves)
-        launch_probe_team<FT, 32>(q, bstart, blk0, nblocks, qcap, x, s);
+        launch_probe_team<FT, 32>(q, bstart, blk0, nblocks, qcap, x, go, s);
     else if (nblocks * 2 <= kProbeWaves)
-        launch_probe_team<FT, 16>(q, bstart, blk0, nblocks, qcap, x, s);
+        launch_probe_team<FT, 16>(q, bstart, blk0, nblocks, qcap, x, go, s);
     else
-        launch_probe_team<FT, 8>(q, bstart, blk0, nblocks, qcap, x, s);
+        launch_probe_team<FT, 8>(q, bstart, blk0, nblocks, qcap, x, go, s);
 }
 
 void launch_probe(int precision, const Req &q, const uint32_t *bstart, int64_t blk0,
-                  int64_t nblocks, int max_m, double cut, const Quant &x, hipStream_t s) {
+                  int64_t nblocks, int max_m, double cut, const Quant &x, const ProbeIf &go,
+                  hipStream_t s) {
     if (nblocks <= 0) return;
     const int qcap = kQwinExtra + max_m;
-    if (precision == 0) launch_probe_ft<double>(q, bstart, blk0, nblocks, qcap, cut, x, s);
-    else launch_probe_ft<float>(q, bstart, blk0, nblocks, qcap, cut, x, s);
+    if (precision == 0) launch_probe_ft<double>(q, bstart, blk0, nblocks, qcap, cut, x, go, s);
+    else launch_probe_ft<float>(q, bstart, blk0, nblocks, qcap, cut, x, go, s);
 }
 
 void launch_hot_buckets(const uint32_t *bstart, int64_t nb, int R, unsigned long long *cnt,

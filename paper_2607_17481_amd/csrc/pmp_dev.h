@@ -768,13 +768,20 @@ void launch_sketch_mfma(const Req &q, const uint32_t *E, const uint32_t *tile_of
                         const uint16_t *bm, const uint16_t *bl, int mode, hipStream_t s);
 void launch_bucket_bounds(const Req &q, int64_t N, int64_t nbuckets, uint32_t *bstart,
                           hipStream_t s);
+// A probe that the device may call off: nothing runs once *zeros >= limit (null:
+// always).
+struct ProbeIf {
+    const unsigned long long *zeros;
+    unsigned long long limit;
+};
 // (k_probe.hip)
 // one wavefront per kProbeQ indexed windows of each anchor length (LenInfo.pblk_base):
 // the probe blocks [blk0, blk0 + nblocks)
 // cut: pairs above it are of no interest (+inf: none), x: the prefilter for
 // them (x16 null with cut = +inf)
 void launch_probe(int precision, const Req &q, const uint32_t *bstart, int64_t blk0,
-                  int64_t nblocks, int max_m, double cut, const Quant &x, hipStream_t s);
+                  int64_t nblocks, int max_m, double cut, const Quant &x, const ProbeIf &go,
+                  hipStream_t s);
 void launch_hot_buckets(const uint32_t *bstart, int64_t nb, int R, unsigned long long *cnt,
                         hipStream_t s);
 // (k_complete.hip): the emit stage

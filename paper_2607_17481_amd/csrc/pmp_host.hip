@@ -397,9 +397,11 @@ struct Bufs {
     char *head;
     uint32_t *loff;            // [L + 1] indexed windows before each length
     int *bad;
+    unsigned long long *zeros; // cells at 0 of the first anchor
     unsigned long long *counters;
     int bad_h = 0;             // the host's copies
-    unsigned long long improved_h = 0;
+    unsigned long long zeros_h = 0, improved_h = 0;
+    bool emax_new = true;      // records were made since the host's copy
     std::vector<float> emax_h;
     float *emax, *gproj;
     double *cov, *udir;
@@ -503,8 +505,8 @@ int select_result(const Select &x, const char *host, SelState &st, std::vector<S
     return PMP_OK;
 }
 
-// bad (8 bytes), then both lists of feature errors
-static size_t head_bytes(int L) { return 8 + (size_t)L * 8; }
+// bad and zeros (16 bytes), then both lists of feature errors
+static size_t head_bytes(int L) { return 16 + (size_t)L * 8; }
 
 static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
     b.len = take<LenInfo>(a, p.L);
@@ -515,7 +517,7 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
     // buckets (at most 2 W + 1 per length)
     b.scan_tmp = (uint32_t *)a.take(scan_temp_bytes(std::max<int64_t>(
         {p.n + 1, p.ntiles + 1, 2 * p.cells + p.L + 1})));
-    // [wsums | loff | bad | emax | the selection's results]
+    // [wsums | loff | bad, zeros | emax | the selection's results]
     const size_t hw = kWidthSets * (kMaxK - kWidthMin + 1) * sizeof(WidthSums);
     const size_t ho = ((size_t)(p.L + 1) * 4 + 7) & ~(size_t)7, he = head_bytes(p.L);
     const int64_t need = need_select(k, p.max_m);
@@ -523,7 +525,8 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
     b.wsums = (WidthSums *)b.head;
     b.loff = (uint32_t *)(b.head + hw);
     b.bad = (int *)(b.head + hw + ho);
-    b.emax = (float *)(b.bad + 2);           // then the join operands' (jemax)
+    b.zeros = (unsigned long long *)(b.bad + 2);
+    b.emax = (float *)(b.zeros + 1);         // then the join operands' (jemax)
     b.selblk = (char *)b.bad + he;
     b.emax_h.assign(p.L, 0.0f);
     // the rows' requests and results, then the counters (read with the results)
@@ -647,6 +650,13 @@ static hipError_t upload(void *dst, const void *src, size_t bytes, hipStream_t s
 // given) receives the join's kept pairs and overflowed blocks.  Only the first n
 // positions are looked at (0: all), for callers that know that no cell after
 // them can be accepted.
+// The host's copies of what lies from b.bad on.
+static void read_head(const Plan &p, Bufs &b, const char *host) {
+    memcpy(&b.bad_h, host, sizeof(int));
+    memcpy(&b.zeros_h, host + 8, 8);
+    memcpy(b.emax_h.data(), host + 16, p.L * sizeof(float));
+    b.emax_new = false;
+}
 struct JoinCounts {
     unsigned long long kept;
     uint32_t nredo, pad;
@@ -665,8 +675,7 @@ static int select_topk(const Plan &p, Bufs &b, int k, hipStream_t s, std::vector
     std::vector<char> host(he + select_read_bytes(b.sel));
     HIPCHK(hipMemcpyAsync(host.data(), b.bad, host.size(), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    memcpy(&b.bad_h, host.data(), sizeof(int));
-    memcpy(b.emax_h.data(), host.data() + 8, p.L * sizeof(float));
+    read_head(p, b, host.data());
     SelState st;
     std::vector<SelCell> acc;
     const int rc = select_result(b.sel, host.data() + he, st, acc,
@@ -746,6 +755,7 @@ static int run_sieve(const Plan &p, Bufs &b, const Req &q, const Opt &o, hipStre
 static void launch_records(const Plan &p, Bufs &b, const Req &q, const Opt &o, int64_t ntiles,
                            int mode, hipStream_t s) {
     const SketchGrid g{ntiles, p.n - p.ms[0] + 1, o.stride, p.anchors};
+    b.emax_new = true;
     if (mode == kSketchAnchors) launch_moments(q, b.E, b.tile_off, g, p.max_m, s);
     if (o.precision == 0)
         launch_sketch(q, b.E, b.tile_off, g, p.max_m, mode, s);
@@ -1054,16 +1064,28 @@ static int run_pipeline(Run &R, Arena &ar) {
         for (int l = 1; l < p.L && a1 < 0; ++l)
             if (p.len[l].anchor) a1 = l;
         const int64_t first = a1 < 0 ? p.nprobe_blocks : p.len[a1].pblk_base;
-        launch_probe(o.precision, q, b.bstart, 0, first, p.max_m, INFINITY, Quant{}, s);
+        launch_probe(o.precision, q, b.bstart, 0, first, p.max_m, INFINITY, Quant{}, ProbeIf{}, s);
         bool rest = first < p.nprobe_blocks;
-        if (rest && o.certify) {
-            // fewer than k zeros at the first length (counted on the device,
-            // in the join's pair counter, free until the certificate) cannot
-            // give k accepted ones; otherwise the selection decides
+        if (rest && o.certify && N < kQuantMin && o.sieve_w == 0) {
+            // small requests ask the device: the other anchors' probe calls
+            // itself off when the first has k zeros, and the selection that
+            // follows either way tells (a round trip less, 45 us of 1.3 ms at
+            // Wafer-like 100,000; large ones would select among all lengths'
+            // cells where the first one's do)
+            launch_count_zero(b.P + p.len[0].kbase, p.len[0].n_index, b.zeros, s);
+            launch_probe(o.precision, q, b.bstart, first, p.nprobe_blocks - first, p.max_m, INFINITY,
+                         Quant{}, ProbeIf{b.zeros, (unsigned long long)R.k}, s);
+            const int rc = select_topk(p, b, R.k, s, acc0);
+            if (rc) return rc;
+            rest = b.zeros_h >= (unsigned long long)R.k &&
+                   !(acc0.size() == (size_t)R.k && acc0.back().d == 0.0);
+            have_acc0 = !rest;
+        } else if (rest && o.certify) {
+            // fewer than k zeros at the first length (counted on the device)
+            // cannot give k accepted ones; otherwise the selection decides
             unsigned long long zeros = 0;
-            launch_fill_u64((uint64_t *)b.jcount, 1, 0ull, s);
-            launch_count_zero(b.P + p.len[0].kbase, p.len[0].n_index, b.jcount, s);
-            HIPCHK(hipMemcpyAsync(&zeros, b.jcount, 8, hipMemcpyDeviceToHost, s));
+            launch_count_zero(b.P + p.len[0].kbase, p.len[0].n_index, b.zeros, s);
+            HIPCHK(hipMemcpyAsync(&zeros, b.zeros, 8, hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
             if (zeros >= (unsigned long long)R.k) {
                 // (no other length has a value yet)
@@ -1091,7 +1113,7 @@ static int run_pipeline(Run &R, Arena &ar) {
         }
         if (rest)
             launch_probe(o.precision, q, b.bstart, first, p.nprobe_blocks - first, p.max_m, cut,
-                         cut < INFINITY ? qx : Quant{}, s);
+                         cut < INFINITY ? qx : Quant{}, ProbeIf{}, s);
     }
     tm.mark(5, s);
     HIPCHK(hipGetLastError());
@@ -1120,13 +1142,12 @@ static int run_pipeline(Run &R, Arena &ar) {
     if (!selected) {
         rc = select_topk(p, b, R.k, s, acc);
         if (rc) return rc;
-    } else {
+    } else if (b.emax_new) {
         // the feature errors again, with the records the emit stage added
-        std::vector<char> host(8 + p.L * sizeof(float));
+        std::vector<char> host(head_bytes(p.L));
         HIPCHK(hipMemcpyAsync(host.data(), b.bad, host.size(), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
-        memcpy(&b.bad_h, host.data(), sizeof(int));
-        memcpy(b.emax_h.data(), host.data() + 8, p.L * sizeof(float));
+        read_head(p, b, host.data());
     }
     const std::vector<float> &emax = b.emax_h;
     if (b.bad_h) return fail(PMP_EINVAL, "series has windows whose standard deviation underflows");
@@ -1255,7 +1276,9 @@ static int run_pipeline(Run &R, Arena &ar) {
             // of the pairs it kept (a kernel of its own, at full occupancy).
             // A chunk is sized to fill three quarters of the pair buffer at
             // the last chunk's rate of kept pairs per block (the first at 16
-            // pairs per window): rates change slowly over the lengths, and
+            // pairs per window; below 2^20 windows at 4, which is all of them:
+            // another chunk costs 60 us there, the blocks that overflow less):
+            // rates change slowly over the lengths, and
             // each chunk's last wavefronts leave the chip part idle.  Blocks that still found
             // the buffer full are listed and taken again, in chunks too; if
             // that leaves as many, each overflows the buffer alone and their
@@ -1272,7 +1295,7 @@ static int run_pipeline(Run &R, Arena &ar) {
                 auto chunk = [&](int64_t left) {
                     const int64_t lim =
                         rate > 0.0 ? std::max<int64_t>(64, (int64_t)std::min(0.75 * (double)b.jcap / rate, 1e15))
-                                   : std::max<int64_t>(64, b.jcap / (16 * win_per_blk));
+                                   : std::max<int64_t>(64, b.jcap / ((Nq < kQuantMin ? 4 : 16) * win_per_blk) + 1);
                     return std::min(left, lim);
                 };
                 auto take_chunk = [&](int64_t b0, const uint32_t *list) {
