@@ -23,9 +23,13 @@ namespace pmp {
 // ---------------------------------------------------------------- select
 
 // The radix select runs on the device from start to end: up to six passes of a
-// histogram over 11 (the last 9) bits of the FP64 bit pattern, whose last block
+// histogram over 11 (the last 2) bits of a key of the value, whose last block
 // picks the bin holding the `remaining`-th smallest value and narrows the
-// prefix `high`.  It is over as soon as the cells at or below that bin fit the
+// prefix `high`.  The key counts the bit pattern from 2^-20 on, below every value
+// but 0, so that the first pass's 2048 bins divide 1e-6 to 128 (distances are at
+// most 2 sqrt(m), 90.5) sixty-four to the octave: the pattern's own top bits fill
+// about twenty of them, which took a second pass and put a wavefront's counts on
+// the same few addresses.  It is over as soon as the cells at or below that bin fit the
 // output (usually after two or three passes; the greedy sorts out the rest),
 // and the passes after that return at once.  The state lives in a SelState,
 // whose ticket and histogram every pass leaves cleared for the next.
@@ -100,9 +104,18 @@ __device__ __forceinline__ SelPick pick_bin(const unsigned int *hist, int nbins)
     return p;
 }
 
-// Histogram of bits [shift, shift + nbits) of P over cells whose bits above
-// shift + nbits equal the state's prefix, then (last block) the bin of the
-// remaining-th value.  Pass 0 also settles two cases: fewer finite values than
+constexpr int kSelShift = 46;                              // of the first pass
+constexpr uint64_t kSelLo = 0x3EB0000000000000ull;         // 2^-20
+__device__ __forceinline__ uint64_t sel_key(uint64_t v) {
+    return v < kSelLo ? 0ull : v - kSelLo + (1ull << kSelShift);
+}
+__device__ __forceinline__ uint64_t sel_value(uint64_t key) {
+    return key < (1ull << kSelShift) ? 0ull : key - (1ull << kSelShift) + kSelLo;
+}
+
+// Histogram of bits [shift, shift + nbits) of the keys of P over cells whose
+// bits above shift + nbits equal the state's prefix, then (last block) the bin
+// of the remaining-th value.  Pass 0 also settles two cases: fewer finite values than
 // wanted (take them all), and a first bin of 0, whose values are exact zeros
 // (the snap leaves nothing between 0 and 1e-6).
 __global__ __launch_bounds__(kBlock) void k_select_hist(const uint64_t *__restrict__ P,
@@ -119,8 +132,10 @@ __global__ __launch_bounds__(kBlock) void k_select_hist(const uint64_t *__restri
          i += (int64_t)gridDim.x * kBlock) {
         const uint64_t v = P[i];
         if (v >= kInfBits) continue;                       // no value
-        if (top < 64 && (v >> top) != high) continue;
-        atomicAdd(&h[(v >> shift) & ((1ull << nbits) - 1)], 1u);
+        const uint64_t u = sel_key(v);
+        if (pass > 0 && (u >> top) != high) continue;
+        atomicAdd(&h[pass > 0 ? (u >> shift) & ((1ull << nbits) - 1)
+                              : min(u >> shift, (uint64_t)(kSelBins - 1))], 1u);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < (1 << nbits); i += kBlock)
@@ -161,11 +176,11 @@ __global__ __launch_bounds__(kBlock) void k_select_hist(const uint64_t *__restri
                 st->need_eq = (int64_t)r2;
                 st->done = 1;
             } else if (last) {
-                st->pivot = hi;
+                st->pivot = sel_value(hi);
                 st->need_eq = (int64_t)r2;
                 st->done = 1;
             } else if (below + (int64_t)in_bin <= cap) {
-                st->pivot = (hi + 1) << shift;             // the whole bin
+                st->pivot = sel_value((hi + 1) << shift);  // the whole bin
                 st->done = 1;
             }
         }
@@ -519,8 +534,8 @@ static inline unsigned gridcap(int64_t n, int64_t cap) {
 
 void launch_select(const Select &x, const uint64_t *P, int64_t n, const uint32_t *cell,
                    const LenView &lv, const unsigned long long *counts, hipStream_t s) {
-    static const int shifts[6] = {53, 42, 31, 20, 9, 0};
-    static const int widths[6] = {11, 11, 11, 11, 11, 9};
+    static const int shifts[6] = {kSelShift, 35, 24, 13, 2, 0};
+    static const int widths[6] = {11, 11, 11, 11, 11, 2};
     if (n <= 0) return;
     // (each block ends with a fence and a ticket: eight turns a thread at
     // least, and no more blocks than fill the chip)

@@ -5,8 +5,9 @@
 // The host keeps what decides each batch's shape without reading the device
 // back: the change-point counts of the samples (a window is constant when
 // none lies inside it, Sec. 2), every anchor's indexed count, depth and run
-// bounds.  A batch is then one upload of its descriptor and five to seven
-// launches on the session's stream.
+// bounds.  A group of batches is then one upload of their descriptors and one
+// launch for all their windows, and a batch two launches more (four with a
+// large merge) on the session's stream.
 #include "pmp_dev.h"
 #include "pmp_host.h"
 
@@ -16,6 +17,9 @@
 #include <vector>
 
 using namespace pmp;
+
+// Batches whose windows one launch makes.
+constexpr int kBatchGroup = 16;
 
 struct pmp_stream {
     int device = 0;
@@ -42,13 +46,11 @@ struct pmp_stream {
     float *gproj = nullptr;
     unsigned long long *counters = nullptr;
     // per batch
-    SAnchor *d_anc = nullptr;
-    int32_t *d_list = nullptr;            // la[listcap], lq[listcap]
+    char *d_desc = nullptr;               // a group's descriptors (run_group)
     uint32_t *bkey = nullptr;
     float *bmarg = nullptr;
     SUpdate *upd = nullptr;
     uint32_t *nupd = nullptr;
-    SMerge *d_merge = nullptr;
     int listcap = 0;
     uint32_t updcap = 0;
     // pinned staging for the per-batch uploads (a ring, each slot reused
@@ -119,9 +121,6 @@ StreamDev dev_args(pmp_stream *s, int nlist) {
     S.ktmp = s->ktmp;
     S.basis = s->basis;
     S.gproj = s->gproj;
-    S.anc = s->d_anc;
-    S.la = s->d_list;
-    S.lq = s->d_list + s->listcap;
     S.nlist = nlist;
     S.B = s->o.B;
     S.R = s->R;
@@ -146,18 +145,25 @@ void depth_of(const pmp_stream *s, int64_t n, int &d, int &h) {
     h = std::min(h, std::min(d, s->o.probe_cap));
 }
 
-// One batch: the samples [n_done, end) (already resident and counted in E).
-int run_batch(pmp_stream *s, int64_t end) {
+// What one batch of a group launches.
+struct Batch {
+    int nlist, off;                       // its windows in the group's list
+    int nlarge, mg;                       // its merges: the large ones, the first of them
+    int64_t nthreads;
+};
+
+// The batch [t0, t1) (already resident and counted in E): its windows, its
+// anchors' descriptors and its merges, appended to the group's.
+int plan_batch(pmp_stream *s, int64_t t0, int64_t t1, std::vector<int32_t> &la,
+               std::vector<int32_t> &lq, std::vector<SAnchor> &ancs, std::vector<SMerge> &mgs,
+               Batch &bt) {
     const int na = (int)s->anc.size();
-    const int64_t t0 = s->n_done, t1 = end;             // sample range of the batch
-    std::vector<int32_t> la, lq;
-    la.reserve((size_t)na * (t1 - t0));
-    lq.reserve((size_t)na * (t1 - t0));
+    bt = Batch{0, (int)la.size(), 0, (int)mgs.size(), 0};
     std::vector<SMerge> merges, small;               // launches of their own; in one block
     for (int a = 0; a < na; ++a) {
         SAnchor &A = s->anc[a];
         const int m = A.m;
-        A.j0 = (int32_t)la.size();
+        A.j0 = (int32_t)la.size() - bt.off;
         int nn = 0;
         // windows completed by samples t0..t1-1: starts tau - m + 1 >= 0
         for (int64_t tau = std::max<int64_t>(t0, m - 1); tau < t1; ++tau) {
@@ -176,12 +182,11 @@ int run_batch(pmp_stream *s, int64_t end) {
         A.nruns = (int32_t)rb.size() - 1;
         std::copy(rb.begin(), rb.end(), A.runs);
     }
-    const int nlist = (int)la.size();
-    if (nlist > s->listcap) return fail(PMP_EINTERNAL, "stream batch list overflow");
+    bt.nlist = (int)la.size() - bt.off;
+    if (bt.nlist > s->listcap) return fail(PMP_EINTERNAL, "stream batch list overflow");
     // the runs after this batch: the new run, then the binary-counter merge
     // of the newest runs (a run absorbs the newer ones once they are as
     // large), at most one merge per anchor
-    int64_t nthreads = 0;
     for (int a = 0; a < na; ++a) {
         SAnchor &A = s->anc[a];
         A.merge = -1;
@@ -196,64 +201,104 @@ int run_batch(pmp_stream *s, int64_t end) {
         if (first < last) {
             SMerge M{};
             M.cbase = A.cbase;
-            M.first = nthreads;
+            M.first = bt.nthreads;
             M.nruns = last - first + 1;
             for (int r = 0; r <= M.nruns; ++r) M.runs[r] = rb[first + r];
             if (M.runs[M.nruns] - M.runs[0] <= kStreamMergeLds) {
                 A.merge = (int32_t)small.size();         // (after the others, below)
                 small.push_back(M);
             } else {
-                nthreads += M.runs[M.nruns] - M.runs[0];
+                bt.nthreads += M.runs[M.nruns] - M.runs[0];
                 merges.push_back(M);
             }
             rb.erase(rb.begin() + first + 1, rb.end() - 1);
         }
         if ((int)rb.size() - 1 > kStreamMaxRuns) return fail(PMP_EINTERNAL, "stream run table overflow");
     }
-    // (a batch of constant windows only changes nothing on the device)
-    if (nlist == 0) {
-        s->batches += 1;
-        s->n_done = end;
-        return PMP_OK;
-    }
-    const int nlarge = (int)merges.size();
+    bt.nlarge = (int)merges.size();
     for (SAnchor &A : s->anc)
-        if (A.merge >= 0) A.merge += nlarge;
-    merges.insert(merges.end(), small.begin(), small.end());
-    // one upload: anchors, list, merges
-    const size_t b_anc = (size_t)na * sizeof(SAnchor);
-    const size_t b_list = (size_t)2 * s->listcap * sizeof(int32_t);
-    const size_t b_mg = merges.size() * sizeof(SMerge);
-    char *st = s->stage[s->slot];
-    HIPCHK(hipEventSynchronize(s->stage_ev[s->slot]));
-    std::memcpy(st, s->anc.data(), b_anc);
-    int32_t *sl = (int32_t *)(st + b_anc);
-    std::memcpy(sl, la.data(), (size_t)nlist * sizeof(int32_t));
-    std::memcpy(sl + s->listcap, lq.data(), (size_t)nlist * sizeof(int32_t));
-    std::memcpy(st + b_anc + b_list, merges.data(), b_mg);
-    // the device descriptor block is laid out the same way
-    HIPCHK(hipMemcpyAsync(s->d_anc, st, b_anc + b_list + b_mg, hipMemcpyHostToDevice, s->hs));
-    HIPCHK(hipEventRecord(s->stage_ev[s->slot], s->hs));
-    s->slot = (s->slot + 1) % pmp_stream::kSlots;
+        if (A.merge >= 0) A.merge += bt.nlarge;
+    mgs.insert(mgs.end(), merges.begin(), merges.end());
+    mgs.insert(mgs.end(), small.begin(), small.end());
+    ancs.insert(ancs.end(), s->anc.begin(), s->anc.end());
+    for (SAnchor &A : s->anc) A.nidx += A.nnew;
+    return PMP_OK;
+}
 
-    const StreamDev S = dev_args(s, nlist);
-    launch_stream_windows(S, s->max_am, s->hs);
-    launch_stream_probe(S, s->max_am, s->hs);
-    launch_stream_finish(S, na, s->d_merge, s->hs);
-    launch_stream_merge(S, s->d_merge, nlarge, nthreads, s->hs);
-    HIPCHK(hipGetLastError());
-    for (int a = 0; a < na; ++a) s->anc[a].nidx += s->anc[a].nnew;
-    s->windows += (uint64_t)nlist;
-    s->batches += 1;
-    s->n_done = end;
+// The next batches up to `ends` (at most kBatchGroup).  Windows depend on the
+// samples only, so one launch makes those of the whole group (a batch's few
+// hundred leave most of the chip idle: 24 us a batch, 3 in a group); searches
+// and what follows them go batch by batch.
+int run_group(pmp_stream *s, const std::vector<int64_t> &ends) {
+    const int na = (int)s->anc.size();
+    std::vector<int32_t> la, lq;
+    std::vector<SAnchor> ancs;
+    std::vector<SMerge> mgs;
+    std::vector<Batch> bts(ends.size());
+    int64_t t0 = s->n_done;
+    for (size_t x = 0; x < ends.size(); ++x) {
+        const int rc = plan_batch(s, t0, ends[x], la, lq, ancs, mgs, bts[x]);
+        if (rc) return rc;
+        t0 = ends[x];
+    }
+    const int nl = (int)la.size();
+    // (batches of constant windows only change nothing on the device)
+    if (nl > 0) {
+        // one upload: anchors and merges of every batch, the list
+        const size_t b_anc = ancs.size() * sizeof(SAnchor), b_mg = mgs.size() * sizeof(SMerge);
+        const size_t b_list = (size_t)nl * sizeof(int32_t);
+        char *st = s->stage[s->slot];
+        HIPCHK(hipEventSynchronize(s->stage_ev[s->slot]));
+        std::memcpy(st, ancs.data(), b_anc);
+        std::memcpy(st + b_anc, mgs.data(), b_mg);
+        std::memcpy(st + b_anc + b_mg, la.data(), b_list);
+        std::memcpy(st + b_anc + b_mg + b_list, lq.data(), b_list);
+        // the device descriptor block is laid out the same way
+        char *const dd = s->d_desc;
+        HIPCHK(hipMemcpyAsync(dd, st, b_anc + b_mg + 2 * b_list, hipMemcpyHostToDevice, s->hs));
+        HIPCHK(hipEventRecord(s->stage_ev[s->slot], s->hs));
+        s->slot = (s->slot + 1) % pmp_stream::kSlots;
+
+        StreamDev S = dev_args(s, nl);
+        S.anc = (const SAnchor *)dd;
+        S.la = (const int32_t *)(dd + b_anc + b_mg);
+        S.lq = S.la + nl;
+        launch_stream_windows(S, s->max_am, s->hs);
+        for (size_t x = 0; x < bts.size(); ++x) {
+            const Batch &bt = bts[x];
+            if (bt.nlist == 0) continue;
+            StreamDev B = S;
+            B.nlist = bt.nlist;
+            B.anc = S.anc + x * na;
+            B.la = S.la + bt.off;
+            B.lq = S.lq + bt.off;
+            B.bkey = S.bkey + bt.off;
+            B.bmarg = S.bmarg + (int64_t)bt.off * kMaxBits;
+            const SMerge *mg = (const SMerge *)(dd + b_anc) + bt.mg;
+            launch_stream_probe(B, s->max_am, s->hs);
+            launch_stream_finish(B, na, mg, s->hs);
+            launch_stream_merge(B, mg, bt.nlarge, bt.nthreads, s->hs);
+        }
+        HIPCHK(hipGetLastError());
+    }
+    s->windows += (uint64_t)nl;
+    s->batches += ends.size();
+    s->n_done = ends.back();
     return PMP_OK;
 }
 
 int ingest(pmp_stream *s, bool partial) {
     HIPCHK(hipEventRecord(s->ev0, s->hs));
-    while (s->n_in - s->n_done >= s->beta || (partial && s->n_in > s->n_done)) {
-        const int64_t end = std::min(s->n_done + s->beta, s->n_in);
-        const int rc = run_batch(s, end);
+    for (;;) {
+        std::vector<int64_t> ends;
+        int64_t at = s->n_done;
+        while ((int)ends.size() < kBatchGroup &&
+               (s->n_in - at >= s->beta || (partial && s->n_in > at))) {
+            at = std::min(at + s->beta, s->n_in);
+            ends.push_back(at);
+        }
+        if (ends.empty()) break;
+        const int rc = run_group(s, ends);
         if (rc) return rc;
     }
     HIPCHK(hipEventRecord(s->ev1, s->hs));
@@ -353,19 +398,14 @@ int pmp_stream_create(int device, int64_t capacity, int32_t m_min, int32_t m_max
     SCHK(dalloc(s, &s->gproj, (int64_t)na * kMaxBits * kFD));
     SCHK(dalloc(s, &s->counters, kCtrSlots * kCtrStride));
     {
-        // anchors, batch list and merge descriptors in one block
-        char *blk = nullptr;
-        const size_t bytes = (size_t)na * sizeof(SAnchor) + (size_t)2 * s->listcap * sizeof(int32_t) +
-                             (size_t)na * sizeof(SMerge);
-        SCHK(dalloc(s, &blk, (int64_t)bytes));
-        s->d_anc = (SAnchor *)blk;
-        s->d_list = (int32_t *)(blk + (size_t)na * sizeof(SAnchor));
-        s->d_merge = (SMerge *)(blk + (size_t)na * sizeof(SAnchor) +
-                                (size_t)2 * s->listcap * sizeof(int32_t));
+        // a group's anchors, merges and list in one block
+        const size_t bytes = (size_t)kBatchGroup * ((size_t)na * (sizeof(SAnchor) + sizeof(SMerge)) +
+                                                    (size_t)2 * s->listcap * sizeof(int32_t));
+        SCHK(dalloc(s, &s->d_desc, (int64_t)bytes));
         s->stage_bytes = bytes;
     }
-    SCHK(dalloc(s, &s->bkey, s->listcap));
-    SCHK(dalloc(s, &s->bmarg, (int64_t)s->listcap * kMaxBits));
+    SCHK(dalloc(s, &s->bkey, (int64_t)kBatchGroup * s->listcap));
+    SCHK(dalloc(s, &s->bmarg, (int64_t)kBatchGroup * s->listcap * kMaxBits));
     SCHK(dalloc(s, &s->upd, s->updcap));
     SCHK(dalloc(s, &s->nupd, 1));
     SCHK(dalloc(s, &s->selblk, (int64_t)select_block_bytes(need, k)));
@@ -396,12 +436,12 @@ int pmp_stream_create(int device, int64_t capacity, int32_t m_min, int32_t m_max
     if ((rc = hchk(hipMemcpyAsync(s->gproj, gp.data(), gp.size() * sizeof(float),
                                   hipMemcpyHostToDevice, s->hs), "hipMemcpyAsync")))
         return rc;
-    if ((rc = hchk(hipMemcpyAsync(s->d_anc, s->anc.data(), (size_t)na * sizeof(SAnchor),
+    if ((rc = hchk(hipMemcpyAsync(s->d_desc, s->anc.data(), (size_t)na * sizeof(SAnchor),
                                   hipMemcpyHostToDevice, s->hs), "hipMemcpyAsync")))
         return rc;
     int64_t max_elems = 0;
     for (const SAnchor &A : s->anc) max_elems = std::max<int64_t>(max_elems, 2 * A.kprime * A.m);
-    launch_stream_basis(s->d_anc, na, max_elems, s->basis, s->hs);
+    launch_stream_basis((const SAnchor *)s->d_desc, na, max_elems, s->basis, s->hs);
     launch_fill_u64(s->P, cb, kInfBits, s->hs);
     launch_fill_u32((uint32_t *)s->I, cb, 0xFFFFFFFFu, s->hs);
     launch_fill_u32(s->nupd, 1, 0u, s->hs);
@@ -449,7 +489,7 @@ int pmp_stream_topk(pmp_stream *s, pmp_motif *out, int32_t *n_out) {
     if (!s || !out || !n_out) return fail(PMP_EINVAL, "bad arguments");
     HIPCHK(hipSetDevice(s->device));
     *n_out = 0;
-    const LenView lv{(const char *)s->d_anc, (int64_t)sizeof(SAnchor),
+    const LenView lv{s->d_desc, (int64_t)sizeof(SAnchor),
                      (int32_t)offsetof(SAnchor, cbase), (int32_t)offsetof(SAnchor, m),
                      (int32_t)s->anc.size()};
     launch_select(s->sel, s->P, s->cells, s->cellid, lv, nullptr, s->hs);
