@@ -561,15 +561,21 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
 
 static bool needs_kmap(const Opt &o) { return o.stride > 1; }
 
-// Kept pairs of the join buffered between its tiles and its exact stage:
-// four per indexed window (32 bytes a window), at least 2^16.
 // Indexed windows from which a request uses the 16-bit prefilter: below, its
 // data and the selection for the cut (about 0.1 ms) cost more than the exact
 // distances they save.
 constexpr int64_t kQuantMin = (int64_t)1 << 20;
 constexpr double kProbeCut = 1.25;   // the probe's cut over the first anchor's k-th value
 constexpr int kJoinCounts = kCtrSlots * kCtrStride + 1;
-static int64_t join_pair_cap(int64_t N) { return std::max<int64_t>(int64_t(1) << 16, 4 * N); }
+// Kept pairs of the join buffered between its tiles and its exact stage, at
+// least 2^16: fourteen per indexed window while there are fewer than 2^20 cells, so
+// that nearly every such request takes its tiles in one chunk (a further chunk
+// costs 60 us, blocks that overflow more), four above, where chunks are long.
+// (By the cells, which the bound before any data knows too.)
+static bool join_one_chunk(const Plan &p) { return p.cells < kQuantMin; }
+static int64_t join_pair_cap(const Plan &p, int64_t N) {
+    return std::max<int64_t>(int64_t(1) << 16, (join_one_chunk(p) ? 14 : 4) * N);
+}
 
 // Blocks of the join over N windows in L lengths, at most.
 static int64_t join_blocks_max(int64_t N, int L) { return N / (kJoinTile * kJoinBlock) + L + 1; }
@@ -603,7 +609,7 @@ static void carve2(Arena &a, Bufs &b, const Plan &p, const Opt &o) {
     b.jk2 = take<uint32_t>(a, N);
     b.jv2 = take<uint32_t>(a, N);
     b.xw = take<float4>(a, N);
-    b.jcap = join_pair_cap(N);
+    b.jcap = join_pair_cap(p, N);
     b.jpairs = take<uint2>(a, b.jcap);
     // the segments' pair counts, the number of overflowed blocks, nonq (u32 per length)
     b.jcount = take<unsigned long long>(a, kJoinCounts + (p.L + 1) / 2);
@@ -1276,12 +1282,10 @@ static int run_pipeline(Run &R, Arena &ar) {
             // of the pairs it kept (a kernel of its own, at full occupancy).
             // A chunk is sized to fill three quarters of the pair buffer at
             // the last chunk's rate of kept pairs per block (the first at 16
-            // pairs per window; below 2^20 windows at 4, which is all of them:
-            // another chunk costs 60 us there, the blocks that overflow less):
-            // rates change slowly over the lengths, and
+            // pairs per window; all of a small request): rates change slowly over the lengths, and
             // each chunk's last wavefronts leave the chip part idle.  Blocks that still found
             // the buffer full are listed and taken again, in chunks too; if
-            // that leaves as many, each overflows the buffer alone and their
+            // a block overflows with a segment of the buffer to itself, its
             // pairs are verified in place.  The counts of the last chunk come
             // back with the selection, which is then repeated if some of its
             // blocks are still to be taken.
@@ -1292,11 +1296,21 @@ static int run_pipeline(Run &R, Arena &ar) {
                 JoinCounts cnt{};
                 double rate = 0.0;                       // kept pairs per block
                 int64_t nb = 0;
+                // (64 blocks have a segment of the buffer each: fewer at a
+                // time would not let one of them keep more)
                 auto chunk = [&](int64_t left) {
                     const int64_t lim =
                         rate > 0.0 ? std::max<int64_t>(64, (int64_t)std::min(0.75 * (double)b.jcap / rate, 1e15))
-                                   : std::max<int64_t>(64, b.jcap / ((Nq < kQuantMin ? 4 : 16) * win_per_blk) + 1);
+                        : join_one_chunk(p) ? left
+                                   : std::max<int64_t>(64, b.jcap / (16 * win_per_blk));
                     return std::min(left, lim);
+                };
+                // the rate after a chunk of which `over` blocks found the
+                // buffer full: those that ended say too little, so twice theirs
+                // and no less than before
+                auto new_rate = [&](uint32_t over) {
+                    const double r = (double)(cnt.kept + 1) / (double)std::max<int64_t>(nb - (int64_t)over, 1);
+                    rate = over ? std::max(2.0 * r, 2.0 * rate) : r;
                 };
                 auto take_chunk = [&](int64_t b0, const uint32_t *list) {
                     const JoinOut out{b.jpairs, b.jcount, std::max<int64_t>(1, b.jcap / kCtrSlots), nxt,
@@ -1311,8 +1325,9 @@ static int run_pipeline(Run &R, Arena &ar) {
                     HIPCHK(hipStreamSynchronize(s));
                     cnt.kept = 0;
                     for (int x = 0; x < kCtrSlots; ++x) cnt.kept += v[x * kCtrStride];
+                    const uint32_t before = cnt.nredo;
                     cnt.nredo = (uint32_t)v[kJoinCounts - 1];
-                    rate = (double)(cnt.kept + 1) / (double)nb;
+                    new_rate(cnt.nredo - before);
                     launch_fill_u64((uint64_t *)b.jcount, kJoinCounts - 1, 0ull, s);
                     return PMP_OK;
                 };
@@ -1327,22 +1342,26 @@ static int run_pipeline(Run &R, Arena &ar) {
                 }
                 // (a k-th value of 0 keeps the answer within the round's
                 // lengths; synchronizes: gl may be rewritten next)
+                const uint32_t before = cnt.nredo;
                 rc = select_topk(p, b, R.k, s, acc, Nq, &cnt);
                 if (rc) return rc;
                 const bool again = cnt.nredo > 0;
+                if (again) new_rate(cnt.nredo - before);
                 while (cnt.nredo > 0) {
                     const uint32_t n = cnt.nredo;
-                    rate = (double)(cnt.kept + 1) / (double)std::max<int64_t>(nb, 1);
                     std::swap(cur, nxt);
                     launch_fill_u64((uint64_t *)b.jcount, kJoinCounts, 0ull, s);
+                    cnt.nredo = 0;
+                    bool alone = true;                   // every block had its own segment
                     for (int64_t b0 = 0; b0 < (int64_t)n; b0 += nb) {
                         nb = chunk((int64_t)n - b0);
+                        alone = alone && nb <= kCtrSlots;
                         take_chunk(0, cur + b0);
                         HIPCHK(hipGetLastError());
                         rc = read_counts();
                         if (rc) return rc;
                     }
-                    if (cnt.nredo >= n) {
+                    if (alone && cnt.nredo > 0) {
                         launch_join_redo(in, nxt, cnt.nredo, s);
                         HIPCHK(hipGetLastError());
                         break;
