@@ -322,11 +322,14 @@ __global__ __launch_bounds__(kBlock) void k_hot_buckets(const uint32_t *__restri
 
 static inline unsigned nblk(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-// Lanes per query: the fewest that give every SIMD of the chip four wavefronts.
-// Measured on random walks with 51 lengths, one anchor's launch: 4,000 queries
-// 249 us at 8 lanes, 87 at 64; above 32,768 queries more lanes only add the
-// verifications that another would have spared.
-constexpr int64_t kProbeWaves = 4096;
+// Lanes per query by the launch's blocks of eight queries.  Measured in whole
+// requests, fewer lanes against more at the same size: random walk 4,000 (500
+// blocks, then 1,500 of the other anchors) 249 us at 8 lanes, 87 at 64, and 1.71
+// ms against 1.60 with 32 lanes for the others, 1.70 with 64; ECG-like 50,000
+// at 24..67 (6,250 blocks) 3.83 -> 3.60 ms with 16 lanes; Wafer-like 5M (123,000
+// blocks) 6.06 ms with 8 lanes, 6.45 with 16: queries that fill the chip only
+// add the verifications that another would have spared.
+constexpr int64_t kTeam64 = 1024, kTeam32 = 4096, kTeam16 = 65536;
 
 template <typename FT, int kTeam>
 static void launch_probe_team(const Req &q, const uint32_t *bstart, int64_t blk0, int64_t nblocks,
@@ -341,11 +344,11 @@ static void launch_probe_ft(const Req &q, const uint32_t *bstart, int64_t blk0, 
     if (x.x16)                    // (over 2^20 windows: the queries fill the chip)
         hipLaunchKernelGGL((k_probe<FT, true, kGroup>), dim3((unsigned)nblocks), dim3(kWave),
                            (size_t)qcap * sizeof(double), s, q, bstart, qcap, blk0, cut, x, go);
-    else if (nblocks * 8 <= kProbeWaves)
+    else if (nblocks <= kTeam64)
         launch_probe_team<FT, 64>(q, bstart, blk0, nblocks, qcap, x, go, s);
-    else if (nblocks * 4 <= kProbeWaves)
+    else if (nblocks <= kTeam32)
         launch_probe_team<FT, 32>(q, bstart, blk0, nblocks, qcap, x, go, s);
-    else if (nblocks * 2 <= kProbeWaves)
+    else if (nblocks <= kTeam16)
         launch_probe_team<FT, 16>(q, bstart, blk0, nblocks, qcap, x, go, s);
     else
         launch_probe_team<FT, 8>(q, bstart, blk0, nblocks, qcap, x, go, s);
