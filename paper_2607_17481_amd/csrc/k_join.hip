@@ -41,6 +41,8 @@
 #include "pmp_dev.h"
 #include "quant.h"
 
+#include <algorithm>
+
 namespace pmp {
 
 namespace {
@@ -498,7 +500,7 @@ __device__ __forceinline__ void join_block(const Req &q, const GridLen *__restri
                                            const float *__restrict__ gw_s, int64_t nwin,
                                            const uint32_t *__restrict__ nonq, int cb1, int cb2,
                                            int cb3, double T, int64_t gb, const JoinOut &out,
-                                           JoinSmem &sm) {
+                                           JoinSmem &sm, uint32_t part = 0, uint32_t parts = 1) {
     uint2 *const queue = sm.queue, *const outq = sm.outq;
     uint32_t *const qkey = sm.qkey, *const rbeg = sm.rbeg, *const rend = sm.rend;
     const int lane = lane_id();
@@ -741,15 +743,9 @@ __device__ __forceinline__ void join_block(const Req &q, const GridLen *__restri
         uint32_t e = __builtin_amdgcn_readfirstlane(rend[0]);
         uint4 nb0, nb1;
         float nw;
-        load_tile(c, nb0, nb1, nw);
         bool more = true;
-        while (more) {
-            const f16x8 b0 = as_f16x8(nb0), b1 = as_f16x8(nb1);
-            // the candidate's Gram term (its sign is the query flag), negative;
-            // +0 for a term of 0, and -inf past the run's end
-            const float term = c + (uint32_t)i < e ? 0.0f - fabsf(nw) : -INFINITY;
-            const bool cq = signbit(nw);
-            const uint32_t tc = c;
+        // one tile on (all uniform)
+        auto next = [&]() {
             c += kJT;
             if (c >= e) {
                 if (++run < nrun) {
@@ -758,6 +754,23 @@ __device__ __forceinline__ void join_block(const Req &q, const GridLen *__restri
                 } else {
                     more = false;
                 }
+            }
+        };
+        if (kRedo) {
+            // this part's tiles: every parts-th from the part-th on
+            for (uint32_t x = 0; x < part && more; ++x) next();
+        }
+        load_tile(c, nb0, nb1, nw);
+        while (more) {
+            const f16x8 b0 = as_f16x8(nb0), b1 = as_f16x8(nb1);
+            // the candidate's Gram term (its sign is the query flag), negative;
+            // +0 for a term of 0, and -inf past the run's end
+            const float term = c + (uint32_t)i < e ? 0.0f - fabsf(nw) : -INFINITY;
+            const bool cq = signbit(nw);
+            const uint32_t tc = c;
+            next();
+            if (kRedo) {
+                for (uint32_t x = 1; x < parts && more; ++x) next();
             }
             load_tile(c, nb0, nb1, nw);                   // (past the last: read and dropped)
             n_tiles += kJB;
@@ -849,8 +862,10 @@ void k_join_tiles(Req q, const GridLen *__restrict__ gl, const uint32_t *__restr
                           cb3, T, gb, out, sm);
 }
 
-// Blocks that overflow an empty buffer, wavefronts striding over their list:
-// their pairs are verified in place.
+// Blocks that overflow a segment of the buffer to themselves: their pairs are
+// verified in place.  Each block's tiles go to `parts` wavefronts in turn: one
+// wavefront took 3.2 ms for the few hundred thousand pairs of such a block (random
+// walk, 4,443 samples at 259..396), 1.0 with up to 32.
 template <typename FT>
 __global__ __launch_bounds__(kWave)
 void k_join_redo(Req q, const GridLen *__restrict__ gl, const uint32_t *__restrict__ gkey,
@@ -858,11 +873,11 @@ void k_join_redo(Req q, const GridLen *__restrict__ gl, const uint32_t *__restri
                  const uint4 *__restrict__ jop_s, const float4 *__restrict__ jmeta,
                  const float4 *__restrict__ gp_s, const float *__restrict__ gw_s, int64_t nwin,
                  const uint32_t *__restrict__ nonq, int cb1, int cb2, int cb3, double T,
-                 const uint32_t *__restrict__ list, uint32_t n, JoinOut out) {
+                 const uint32_t *__restrict__ list, uint32_t n, uint32_t parts, JoinOut out) {
     __shared__ JoinSmem sm;
-    for (uint32_t x = blockIdx.x; x < n; x += gridDim.x)
+    for (uint32_t x = blockIdx.x; x < n * parts; x += gridDim.x)
         join_block<FT, true>(q, gl, gkey, gval, qf, jop_s, jmeta, gp_s, gw_s, nwin, nonq, cb1, cb2,
-                             cb3, T, (int64_t)list[x], out, sm);
+                             cb3, T, (int64_t)list[x / parts], out, sm, x % parts, parts);
 }
 
 // The exact stage of the pairs in the buffer, one pair per lane, each block
@@ -1086,15 +1101,17 @@ void launch_join_tiles(const JoinIn &in, int64_t blk0, int64_t nblocks, const ui
 
 void launch_join_redo(const JoinIn &in, const uint32_t *list, uint32_t n, hipStream_t s) {
     if (n == 0) return;
-    const dim3 grid(n < 2048u ? n : 2048u);
+    // (two wavefronts a SIMD fit)
+    const uint32_t parts = std::min(std::max(2048u / n, 1u), 32u);
+    const dim3 grid(std::min(n * parts, 2048u));
     if (in.precision == 0)
         hipLaunchKernelGGL(k_join_redo<double>, grid, dim3(kWave), 0, s, in.q, in.gl, in.gkey,
                            in.gval, in.qf, in.jop_s, in.jmeta, in.gp_s, in.gw_s, in.nwin, in.nonq,
-                           in.cb1, in.cb2, in.cb3, in.T, list, n, JoinOut{});
+                           in.cb1, in.cb2, in.cb3, in.T, list, n, parts, JoinOut{});
     else
         hipLaunchKernelGGL(k_join_redo<float>, grid, dim3(kWave), 0, s, in.q, in.gl, in.gkey,
                            in.gval, in.qf, in.jop_s, in.jmeta, in.gp_s, in.gw_s, in.nwin, in.nonq,
-                           in.cb1, in.cb2, in.cb3, in.T, list, n, JoinOut{});
+                           in.cb1, in.cb2, in.cb3, in.T, list, n, parts, JoinOut{});
 }
 
 void launch_join_verify(int precision, const Req &q, const GridLen *gl, const JoinOut &out,
