@@ -522,6 +522,11 @@ __device__ __forceinline__ void join_block(const Req &q, const GridLen *__restri
     const uint32_t p0 = pbeg + (uint32_t)((gb - G.blk_base) * kJQ);
     const int i = lane % kJT, hh = lane / kJT;
     const float scale = join_scale(m);
+    // the largest e' of the length, over the sets
+    static_assert((kJeSets & (kJeSets - 1)) == 0 && kJeSets <= kWave, "a set per lane");
+    float je = q.jemax[(int64_t)(lane % kJeSets) * je_pitch(q.L) + l];
+#pragma unroll
+    for (int off = kJeSets / 2; off > 0; off >>= 1) je = fmaxf(je, __shfl_xor(je, off, kWave));
 
     const uint4 *const op0 = jop_s, *const op1 = jop_s + 2 * nwin;
 
@@ -544,7 +549,7 @@ __device__ __forceinline__ void join_block(const Req &q, const GridLen *__restri
             float hi = -65504.0f, lo = 0.0f;
             if (isq) {
                 const float4 mt = jmeta[kq];              // |G|^2, e', |G| bound, 0
-                const double R = (G.Tr + (double)mt.y + (double)q.jemax[l]) * (1.0 + 1e-9);
+                const double R = (G.Tr + (double)mt.y + (double)je) * (1.0 + 1e-9);
                 const double nG2 = (double)mt.x * (1.0 - 0x1.0p-23);
                 double v = 0.5 * (R * R * (1.0 + 1e-9) - nG2) + G.eps_c * (double)mt.z + 1e-30;
                 v += 0x1.0p-22 * (fabs(v) + G.nmax2);

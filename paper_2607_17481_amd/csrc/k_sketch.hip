@@ -952,14 +952,15 @@ void k_join_ops(Req q, const double *__restrict__ udir, int64_t k0, int64_t k1) 
         q.jmeta[kk] = make_float4((float)n2, ep, (float)(sqrt(n2) * (1.0 + 1e-12)) * (1.0f + 2.4e-7f),
                                   0.0f);
     }
-    // the largest e' of the length (one atomic per wavefront within a length;
-    // positive floats order like their bits)
+    // the largest e' of the length, one atomic per wavefront within a length
+    // (positive floats order like their bits; a stale read only costs an atomic)
+    int *const je = (int *)q.jemax + (int64_t)(blockIdx.x % kJeSets) * je_pitch(q.L);
+    int eb = __float_as_int(ep);
     if (__ballot(live && l != __shfl(l, 0, kWave)) == 0) {
-        for (int off = kWave / 2; off > 0; off >>= 1) ep = fmaxf(ep, __shfl_xor(ep, off, kWave));
-        // (a stale read only costs an atomic)
-        if (lane_id() == 0 && ep > q.jemax[l]) atomicMax((int *)&q.jemax[l], __float_as_int(ep));
+        for (int off = kWave / 2; off > 0; off >>= 1) eb = max(eb, __shfl_xor(eb, off, kWave));
+        if (lane == 0 && eb > je[l]) atomicMax(&je[l], eb);
     } else if (live) {
-        atomicMax((int *)&q.jemax[l], __float_as_int(ep));
+        atomicMax(&je[l], eb);
     }
 }
 

@@ -94,7 +94,7 @@ struct Req {
     uint32_t *hint;        // [N] start of a partner that lowered the cell
                            // (kNone: none), written when a cell is lowered
     float   *emax;         // [L] largest e_i of each length
-    float   *jemax;        // [L] largest e' of each length's join operands
+    float   *jemax;        // [kJeSets][je_pitch] largest e' of each length's join operands
     unsigned long long *counters;   // stats counters: kCtrSlots sets, kCtrStride apart
     int     *bad;          // raised on inputs the library cannot represent
 };
@@ -114,6 +114,13 @@ constexpr uint32_t kNone = 0xFFFFFFFFu;      // no entry (kmap, hint)
 // to the eight XCDs in turn, so a set belongs to one of them.
 constexpr int kCtrSlots = 64;
 constexpr int kCtrStride = 16;               // in 64-bit words: 128 bytes
+// Likewise the largest feature error of a length's join operands, which every
+// wavefront of k_join_ops may raise: kJeSets sets of a float per length, on
+// lines of their own.  With one set its atomics queued: 2.1 million windows of
+// 51 lengths took 265 to 298 us, 200,000 took 69; with 16 sets 157 and 30, with
+// 64 132 and 23, but they lie in the head that is read back.
+constexpr int kJeSets = 32;
+__host__ __device__ inline int64_t je_pitch(int L) { return ((int64_t)L + 31) & ~(int64_t)31; }
 
 // ------------------------------------------------------------- helpers
 

@@ -403,7 +403,7 @@ struct Bufs {
     unsigned long long zeros_h = 0, improved_h = 0;
     bool emax_new = true;      // records were made since the host's copy
     std::vector<float> emax_h;
-    float *emax, *gproj;
+    float *emax, *jemax, *gproj;
     double *cov, *udir;
     GridLen *gl;
     int64_t *bbase;            // MFMA sketch basis: offsets per length, then hi / mid / lo tables
@@ -505,8 +505,8 @@ int select_result(const Select &x, const char *host, SelState &st, std::vector<S
     return PMP_OK;
 }
 
-// bad and zeros (16 bytes), then both lists of feature errors
-static size_t head_bytes(int L) { return 16 + (size_t)L * 8; }
+// bad and zeros (16 bytes), then the feature errors
+static size_t head_bytes(int L) { return (16 + (size_t)L * 4 + 7) & ~(size_t)7; }
 
 static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
     b.len = take<LenInfo>(a, p.L);
@@ -517,16 +517,18 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
     // buckets (at most 2 W + 1 per length)
     b.scan_tmp = (uint32_t *)a.take(scan_temp_bytes(std::max<int64_t>(
         {p.n + 1, p.ntiles + 1, 2 * p.cells + p.L + 1})));
-    // [wsums | loff | bad, zeros | emax | the selection's results]
+    // [wsums | loff | jemax | bad, zeros | emax | the selection's results]
     const size_t hw = kWidthSets * (kMaxK - kWidthMin + 1) * sizeof(WidthSums);
     const size_t ho = ((size_t)(p.L + 1) * 4 + 7) & ~(size_t)7, he = head_bytes(p.L);
     const int64_t need = need_select(k, p.max_m);
-    b.head = (char *)a.take(hw + ho + he + select_block_bytes(need, k));
+    const size_t hj = (size_t)kJeSets * je_pitch(p.L) * sizeof(float);
+    b.head = (char *)a.take(hw + ho + hj + he + select_block_bytes(need, k));
     b.wsums = (WidthSums *)b.head;
     b.loff = (uint32_t *)(b.head + hw);
-    b.bad = (int *)(b.head + hw + ho);
+    b.jemax = (float *)(b.head + hw + ho);    // cleared from here on
+    b.bad = (int *)(b.head + hw + ho + hj);
     b.zeros = (unsigned long long *)(b.bad + 2);
-    b.emax = (float *)(b.zeros + 1);         // then the join operands' (jemax)
+    b.emax = (float *)(b.zeros + 1);
     b.selblk = (char *)b.bad + he;
     b.emax_h.assign(p.L, 0.0f);
     // the rows' requests and results, then the counters (read with the results)
@@ -944,8 +946,8 @@ static int run_pipeline(Run &R, Arena &ar) {
     tm.mark(0, s);
 
     // ---- validation, change points, index counts per tile
-    HIPCHK(upload(b.len, p.len.data(), p.L * sizeof(LenInfo), s, (uint32_t *)b.bad,
-                  (int64_t)(head_bytes(p.L) + sizeof(SelState)) / 4));
+    HIPCHK(upload(b.len, p.len.data(), p.L * sizeof(LenInfo), s, (uint32_t *)b.jemax,
+                  (int64_t)((b.selblk - (char *)b.jemax) + sizeof(SelState)) / 4));
     launch_changepoints(R.t, R.n, b.flags, b.bad, s);
     scan_exclusive_u32(b.flags, b.E, R.n + 1, nullptr, b.scan_tmp, s);
     launch_tile_counts(b.len, p.L, b.E, p.n - p.ms[0] + 1, p.max_m, p.ntiles, b.tile_off, s);
@@ -1018,7 +1020,7 @@ static int run_pipeline(Run &R, Arena &ar) {
     q.pcell = b.pcell;
     q.gproj = b.gproj;
     q.emax = b.emax;
-    q.jemax = b.emax + p.L;
+    q.jemax = b.jemax;
     q.counters = b.counters;
     q.bad = b.bad;
     q.kmap = b.kmap;
