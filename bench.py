@@ -167,21 +167,21 @@ def algorithmic_bytes(n, lengths, st, fs):
     probe = (nq * (REC * fs + 4 + 4 + 8 + 8 + 8 + 8 + 4)
              + st["pass_candidates"] * (REC * fs + 4 + 4 + 8)
              + st["pass_verified"] * (16 + 16) + 8 * n)
-    # the join: its queried windows' operands (record read; 128 + 16 + 16
+    # the join: its queried windows' operands (record read; 64 + 16 + 16
     # written), grid keys and sort, then per kept pair ...
     nj = st.get("join_windows", nx)
-    join = (nj * (REC * fs + 128 + 16 + 16) + nx * 32 + st["join_candidates"] * (REC * fs + 4)
+    join = (nj * (REC * fs + 64 + 16 + 16) + nx * 32 + st["join_candidates"] * (REC * fs + 4)
             + st["join_verified"] * (16 + 16) + 8 * n)
     return {"k_sketch": float(sketch), "k_keys": float(keys), "k_probe": float(probe),
             "k_join": float(join)}
 
 
-# the source files of each timed kernel: the sketch kernel; the keys; the
+# the source files of each timed kernel: the moments and the sketch; the keys; the
 # probe; the join phase (the join's operands and principal directions, the
 # grid keys and the tile join)
 KERNEL_SOURCES = {"k_sketch": ("k_sketch.hip",), "k_keys": ("k_sketch.hip",),
-                  "k_probe": ("k_probe.hip",),
-                  "k_join": ("k_join.hip", "k_certify.hip", "k_sketch.hip")}
+                  "k_probe": ("k_probe.hip", "quant.h"),
+                  "k_join": ("k_join.hip", "k_certify.hip", "k_sketch.hip", "quant.h")}
 
 
 def source_digest(kernel):
@@ -595,9 +595,9 @@ def main():
     traffic = measured_traffic(dom, args.workload, args.precision)
     if dom == "k_join":
         # the threshold join's ceiling is its filter on the matrix cores: per
-        # filtered pair three split-bf16 products of the 32-wide feature
-        # vectors (hi.hi, hi.lo, lo.hi), 3 x 32 x 2 = 192 flop
-        flops = float(last["join_pairs"]) * 192.0
+        # filtered pair one fp16 product of the 32-wide feature vectors,
+        # 32 x 2 = 64 flop (the dense fp16 rate is that of bf16)
+        flops = float(last["join_pairs"]) * 64.0
         achieved = flops / (kern_ms[dom] * 1e-3) / 1e12
         roof = {"kernel": dom, "bound": "mfma", "achieved": achieved, "peak": BF16_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": achieved / BF16_PEAK_TFLOPS, "traffic": traffic,

@@ -21,12 +21,13 @@
 // top-k built on it by the certificate does not (the role of the fixed merge
 // order of Prop. 5).
 //
-// GPU mapping: eight lanes per query, eight queries per wavefront.  A query
-// inspects eight candidates at a time, one per lane; their records are read
-// by the eight lanes together (one contiguous row per load) and the eight
-// bounds summed by a transposed reduction.  The survivors are verified by the
-// eight lanes together, smallest bound first, each result tightening the
-// prune of the rest; queries without survivors search on meanwhile.
+// GPU mapping: a team of 8 to 64 lanes per query, the more the fewer queries a
+// launch has (launch_probe gives the thresholds).  Every group of eight lanes
+// of a team inspects eight candidates at a time, one per lane; their records
+// are read by the eight lanes together (one contiguous row per load) and the
+// eight bounds summed by a transposed reduction.  The survivors are verified
+// smallest bound first, each result tightening the prune of the rest; queries
+// without survivors search on meanwhile.
 //
 // One departure from the paper: a query stops once its own cell reaches 0
 // (the smallest possible value); the remaining candidates could only lower

@@ -19,9 +19,11 @@
 // magnitude (replacing the paper's relative (1 - lambda) shrink, Lemma 4,
 // which it proves only above a threshold).
 //
-// One pass writes, for every non-constant window k (compacted, in (length,
-// start) order): its cell, moments, feature record, key word (signature +
-// Hamming-1 probe order), join record and bucket sort key.  Records are
+// k_moments writes, for every non-constant window k (compacted, in (length,
+// start) order), its cell and moments; the sketch kernels the records of the
+// lengths they are launched for (the anchors first, the others where they are
+// read); k_keys the anchor windows' key words (signature + Hamming-1 probe
+// order) and bucket sort keys; k_join_ops the join's operands.  Records are
 // staged in LDS and leave in whole, coalesced rows.
 #include "pmp_dev.h"
 

@@ -50,6 +50,25 @@ def test_probe_groups(gpu, ws, oracle, windows, prec):  # noqa: F811
     check(gpu, ws, oracle, gaps, lo, hi, excl, k=5, precision=PRECS[prec])
 
 
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("windows", [8192, 8193, 32768, 32769])
+def test_probe_teams(gpu, ws, oracle, windows, prec):  # noqa: F811
+    """The probe's 64, 32 and 16 lanes per query: at and one past the largest
+    launch of the first two."""
+    m, excl = 8, 4
+    t = np.random.default_rng(windows).standard_normal(windows + m - 1)
+    check(gpu, ws, oracle, t, m, m, excl, precision=PRECS[prec])
+
+
+@pytest.mark.parametrize("lengths", [255, 256, 257, 600])
+def test_many_lengths(gpu, ws, oracle, lengths):  # noqa: F811
+    """Tables of more lengths than one launch's arguments or one block of
+    lengths hold."""
+    lo, excl = 8, 20
+    t = np.cumsum(np.random.default_rng(lengths).standard_normal(lengths + 60))
+    check(gpu, ws, oracle, t, lo, lo + lengths - 1, excl)
+
+
 _LARGE_ROWS: dict = {}
 
 
