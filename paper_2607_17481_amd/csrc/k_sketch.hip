@@ -217,36 +217,144 @@ __device__ __forceinline__ void load_tile_samples(const double *__restrict__ t, 
     }
 }
 
-// One non-constant window (x: its samples in LDS, k: its position): the
-// two-pass moments (Sec. 3.2), its cell, and no value and no hint yet.
-__device__ __forceinline__ void window_entry(const Req &q, const double *x, int m, uint32_t cell,
-                                             int64_t k, double &mu, double &is) {
-    const double sg = window_moments(x, m, mu);
-    is = 1.0 / sg;
+// 1 / sigma of a non-constant window.
+__device__ __forceinline__ double window_isig(const Req &q, double sg) {
+    const double is = 1.0 / sg;
     if (!(sg > 0.0) || !isfinite(sg) || !(is > 0.0) || !isfinite(is)) {
         // samples differ but sigma underflows or overflows: outside the
         // range the library represents; the window stays indexed so
         // every count stays consistent, and the call fails
         atomicOr(q.bad, 2);
-        is = 1.0;
+        return 1.0;
     }
-    q.cell[k] = cell;
-    q.mu[k] = mu;
-    q.isig[k] = is;
-    q.P[k] = kInfBits;
-    q.hint[k] = kNone;
+    return is;
+}
+
+// The entries of the non-constant windows (`in`, a bit each) of a quad, at
+// positions k on: moments, cells, no value and no hint yet.  Usually all four,
+// stored 16 bytes at a time (a lane's own four in turn would write every line
+// of the wavefront in four parts).
+__device__ __forceinline__ void quad_entries(const Req &q, const double mu[4], const double sg[4],
+                                             uint32_t cell, uint32_t in, int64_t k) {
+    if (in == 15u) {
+        typedef __attribute__((ext_vector_type(2), aligned(8))) double d2;
+        typedef __attribute__((ext_vector_type(2), aligned(8))) uint64_t l2;
+        typedef __attribute__((ext_vector_type(4), aligned(4))) uint32_t u4;
+        double is[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) is[j] = window_isig(q, sg[j]);
+        *(u4 *)(q.cell + k) = u4{cell, cell + 1u, cell + 2u, cell + 3u};
+        *(u4 *)(q.hint + k) = u4{kNone, kNone, kNone, kNone};
+#pragma unroll
+        for (int j = 0; j < 4; j += 2) {
+            *(d2 *)(q.mu + k + j) = d2{mu[j], mu[j + 1]};
+            *(d2 *)(q.isig + k + j) = d2{is[j], is[j + 1]};
+            *(l2 *)(q.P + k + j) = l2{kInfBits, kInfBits};
+        }
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if ((in >> j) & 1u) {
+            q.cell[k] = cell + (uint32_t)j;
+            q.hint[k] = kNone;
+            q.mu[k] = mu[j];
+            q.isig[k] = window_isig(q, sg[j]);
+            q.P[k] = kInfBits;
+            ++k;
+        }
+}
+
+// The moments of four consecutive windows w .. w + 3 (w a multiple of 4), with
+// the bits of window_moments: every window's four partial sums take its samples
+// in the same order, but a sample is read once for all four.  even / odd: the
+// samples 4 i, 4 i + 1 and 4 i + 2, 4 i + 3, so that neighbouring lanes read
+// neighbouring 16 bytes.
+__device__ __forceinline__ void quad_moments(const double2 *even, const double2 *odd, int w, int m,
+                                             double mu[4], double sg[4]) {
+    even += w / 4;
+    odd += w / 4;
+    auto at = [&](int r) -> double {
+        const double2 v = (r & 2) ? odd[r >> 2] : even[r >> 2];
+        return (r & 1) ? v.y : v.x;
+    };
+    if (m < 4) {
+        // (three samples: the remainder's sums only)
+        for (int j = 0; j < 4; ++j) {
+            double a = 0.0;
+            for (int r = 0; r < m; ++r) a += at(r + j);
+            mu[j] = a / (double)m;
+            a = 0.0;
+            for (int r = 0; r < m; ++r) {
+                const double c = at(r + j) - mu[j];
+                a = fma(c, c, a);
+            }
+            sg[j] = sqrt(a / (double)m);
+        }
+        return;
+    }
+    const int m4 = m & ~3, rest = m - m4;
+    double acc[4][4];
+    auto clear = [&]() {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int p = 0; p < 4; ++p) acc[j][p] = 0.0;
+    };
+    // sample t of the quad is sample t - j of window j
+    auto pass = [&](auto add) {
+        clear();
+        {
+            const double2 x = even[0], y = odd[0];
+            const double v[4] = {x.x, x.y, y.x, y.y};
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int j = 0; j <= t; ++j) add(acc[j][t - j], v[t], j);
+        }
+#pragma unroll 2
+        for (int t4 = 1; t4 < m4 / 4; ++t4) {
+            const double2 x = even[t4], y = odd[t4];
+            const double v[4] = {x.x, x.y, y.x, y.y};
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) add(acc[j][(t - j) & 3], v[t], j);
+        }
+        // the last samples of windows 1 .. 3, then every window's remainder
+        // (all in its first sum)
+        {
+            const double2 x = even[m4 / 4], y = odd[m4 / 4], z = even[m4 / 4 + 1];
+            const double v[6] = {x.x, x.y, y.x, y.y, z.x, z.y};
+#pragma unroll
+            for (int t = 0; t < 6; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (t < j) add(acc[j][(t - j) & 3], v[t], j);
+                    else if (t - j < rest) add(acc[j][0], v[t], j);
+                }
+        }
+    };
+    pass([&](double &a, double x, int) { a += x; });
+#pragma unroll
+    for (int j = 0; j < 4; ++j) mu[j] = ((acc[j][0] + acc[j][1]) + (acc[j][2] + acc[j][3])) / (double)m;
+    pass([&](double &a, double x, int j) {
+        const double c = x - mu[j];
+        a = fma(c, c, a);
+    });
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sg[j] = sqrt(((acc[j][0] + acc[j][1]) + (acc[j][2] + acc[j][3])) / (double)m);
 }
 
 // Shared first steps of a sketch tile (samples already in LDS): the
 // compacted position k of every non-constant window (thread tid takes
-// windows 4 tid .. 4 tid + 3; a block scan) and the list of those windows,
-// then, unless k_moments made them (`made`), their entries, dealt evenly over
-// the threads from the list.  Ends with the block synchronized and kpos final
-// (and, when given, smu / sis: the mean and 1 / sigma of each non-constant
-// window by its place in the tile).
-__device__ __forceinline__ void tile_positions_and_moments(
-    const Req &q, const LenInfo &L, int64_t i0, int nw, int64_t tile, const double *st,
-    const uint32_t *__restrict__ E, const uint32_t *__restrict__ tile_off, bool made, int32_t *kpos,
+// windows 4 tid .. 4 tid + 3; a block scan) and the list of those windows.
+// Ends with the block synchronized and kpos final (and, when given, smu / sis:
+// the mean and 1 / sigma of each non-constant window by its place in the tile,
+// which k_moments made).
+__device__ __forceinline__ void tile_positions(
+    const Req &q, const LenInfo &L, int64_t i0, int nw, int64_t tile,
+    const uint32_t *__restrict__ E, const uint32_t *__restrict__ tile_off, int32_t *kpos,
     uint16_t *widx, uint32_t *wsum, double *smu = nullptr, double *sis = nullptr) {
     const int m = L.m;
     const int tid = threadIdx.x;
@@ -290,26 +398,14 @@ __device__ __forceinline__ void tile_positions_and_moments(
         }
     }
     __syncthreads();
-    // the cell -> indexed position map (anchors and hints need it)
-    if (q.kmap && !made)
-        for (int w = tid; w < nw; w += kBlock)
-            q.kmap[L.cell_base + i0 + w] = kpos[w] < 0 ? kNone : (uint32_t)kpos[w];
-    int nix = 0;                                        // non-constant windows of the tile
-    for (int v = 0; v < kBlock / kWave; ++v) nix += (int)wsum[v];
-
-    for (int xi = tid; xi < nix && !(made && !smu); xi += kBlock) {
-        const int w = widx[xi];
-        const int32_t kk = kpos[w];
-        double mu, is;
-        if (made) {
-            mu = q.mu[kk];
-            is = q.isig[kk];
-        } else {
-            window_entry(q, st + w, m, (uint32_t)(L.cell_base + i0 + w), kk, mu, is);
-        }
-        if (smu) {
-            smu[w] = mu;
-            sis[w] = is;
+    if (smu) {
+        int nix = 0;                                    // non-constant windows of the tile
+        for (int v = 0; v < kBlock / kWave; ++v) nix += (int)wsum[v];
+        for (int xi = tid; xi < nix; xi += kBlock) {
+            const int w = widx[xi];
+            const int32_t kk = kpos[w];
+            smu[w] = q.mu[kk];
+            sis[w] = q.isig[kk];
         }
     }
     __syncthreads();
@@ -317,102 +413,112 @@ __device__ __forceinline__ void tile_positions_and_moments(
 
 }  // namespace
 
-// Positions and entries of the windows of the lengths between anchors, which get
-// their records later, or never.  Block (x, y): the starts [x, x + 1) * kTileW
-// at up to `group` lengths, whose samples and change-point counts it stages
-// once; the windows of all of them are listed in LDS and dealt evenly over the
-// threads, so that a few windows per length (a series of mostly constant
-// stretches) still keep every lane busy.
+// Positions and entries of all windows.  Block (x, y): the starts [x, x + 1) *
+// kTileW at `group` lengths, whose samples and change-point counts it stages
+// once; the aligned quads of windows that hold a non-constant one are listed in
+// LDS for all of them and dealt evenly over the threads, so that a few windows
+// per length (a series of mostly constant stretches) still keep every lane busy.
 //
-// Bounded by the two serial sums of m samples per window, read from LDS.  As
-// tiles of the sketch itself (one length a block, three blocks a compute unit
-// because of the staging rows, a fifth of the threads busy) 5M samples of a
-// Wafer-like series at 51 lengths took 3.5 ms with the anchors' records; this
-// takes 1.8, and those 1.2.
-constexpr int kMomentList = 2 * kTileW;
+// With a window per thread the LDS was busy all the time (two sums of m samples
+// a window, 8 bytes a lane): hence the quads, which read a sample once for four
+// windows and leave the FP64 sums and the 32 bytes written a window (4 a cell) to
+// bound it.  51 million windows of 100..400 samples took 2.8 ms, now 1.6; the
+// 75.4 million of 50..100 of a Wafer-like series of 5M samples, with the anchors'
+// records in the sketch, 3.1, now 1.7 and 1.1.  (The 16-byte reads need an aligned
+// base: from one 8 bytes off they kept the LDS busy for 5.5 ms.)
+constexpr int kMomentGroup = 8;                          // lengths per block at most
 
 __global__ __launch_bounds__(kBlock) void k_moments(Req q, const uint32_t *__restrict__ E,
                                                     const uint32_t *__restrict__ tile_off, int group,
                                                     int st_len) {
-    extern __shared__ double dyn[];
-    __shared__ uint2 list[kMomentList];                  // position; length and window
+    extern __shared__ double2 quads[];                   // (16-byte reads need the alignment)
+    __shared__ uint2 list[kMomentGroup * kTileW / 4];    // first position; length, quad, windows
     __shared__ uint32_t cnt[2][kBlock / kWave];
-    double *st = dyn;                                    // samples
-    uint32_t *e = (uint32_t *)(dyn + st_len);            // change-point counts
+    __shared__ uint32_t nlist;
+    double2 *const even = quads, *const odd = even + st_len / 4;   // samples
+    uint32_t *const e = (uint32_t *)(odd + st_len / 4);  // change-point counts
     const int l0 = blockIdx.y * group, l1 = min(q.L, l0 + group);
     const int64_t i0 = (int64_t)blockIdx.x * kTileW;
     if (i0 >= q.len[l0].W) return;                       // (window counts descend)
     const int tid = threadIdx.x, lane = lane_id(), wv = tid / kWave;
     const int64_t n1 = q.len[l0].W + q.len[l0].m;        // entries of E: n + 1
     const int span = (int)min<int64_t>(kTileW + q.len[l1 - 1].m, n1 - i0);
-    for (int x = tid; x < span; x += kBlock) {
-        e[x] = E[i0 + x];
-        if (i0 + x < n1 - 1) st[x] = q.t[i0 + x];
+    if (tid == 0) nlist = 0;
+    for (int x = tid; x < st_len; x += kBlock) {
+        if (x < span) e[x] = E[i0 + x];
+        // (0 past the last sample: the windows there belong to no length)
+        ((double *)((x & 2) ? odd : even))[(x >> 2) * 2 + (x & 1)] =
+            i0 + x < n1 - 1 ? q.t[i0 + x] : 0.0;
     }
     __syncthreads();
-    int n = 0, turn = 0;
-    auto flush = [&]() {
-        __syncthreads();
-        for (int x = tid; x < n; x += kBlock) {
-            const uint2 u = list[x];
-            const int l = l0 + (int)(u.y >> 16), w = (int)(u.y & 0xFFFFu);
-            double mu, is;
-            window_entry(q, st + w, q.len[l].m, (uint32_t)(q.len[l].cell_base + i0 + w), u.x, mu, is);
-        }
-        __syncthreads();
-        n = 0;
-    };
+    int turn = 0;
     for (int l = l0; l < l1; ++l) {
         const LenInfo &L = q.len[l];
-        if (L.anchor || i0 >= L.W) continue;             // (uniform)
+        if (i0 >= L.W) break;                            // (uniform)
         const int m = L.m, nw = (int)min<int64_t>(kTileW, L.W - i0);
-        if (n + kTileW > kMomentList) flush();
         // wavefront wv takes the windows [256 wv, 256 wv + 256) of the tile
         constexpr int kRounds = kTileW / kBlock;
-        const int w0 = wv * (kTileW / (kBlock / kWave)) + lane;
+        const int w0 = wv * kRounds * kWave;
         uint64_t bal[kRounds];
         int mine = 0;
 #pragma unroll
         for (int j = 0; j < kRounds; ++j) {
-            const int w = w0 + j * kWave;
+            const int w = w0 + j * kWave + lane;
             bal[j] = __ballot(w < nw && e[w + m] != e[w + 1]);
             mine += __popcll(bal[j]);
         }
         if (lane == 0) cnt[turn][wv] = (uint32_t)mine;
         // (two sets of counts in turn: one barrier a length)
         __syncthreads();
-        uint32_t at = 0, total = 0;
+        uint32_t at = tile_off[L.tile_base + blockIdx.x];
 #pragma unroll
-        for (int v = 0; v < kBlock / kWave; ++v) {
-            at += v < wv ? cnt[turn][v] : 0u;
-            total += cnt[turn][v];
-        }
+        for (int v = 0; v < kBlock / kWave; ++v) at += v < wv ? cnt[turn][v] : 0u;
+        at = __builtin_amdgcn_readfirstlane(at);         // the wavefront's first position
         turn ^= 1;
-        at = __builtin_amdgcn_readfirstlane(at);
-        const uint32_t base = tile_off[L.tile_base + blockIdx.x];
-        uint32_t *const km = q.kmap ? q.kmap + L.cell_base + i0 : nullptr;
+        if (q.kmap) {
+            uint32_t *const km = q.kmap + L.cell_base + i0;
+            uint32_t k = at;
 #pragma unroll
-        for (int j = 0; j < kRounds; ++j) {
-            const int w = w0 + j * kWave;
-            uint32_t k = kNone;
-            if (bal[j]) {                                // (uniform)
-                if ((bal[j] >> lane) & 1ull) {
-                    const uint32_t r = at + (uint32_t)__popcll(bal[j] & lanemask_lt());
-                    k = base + r;
-                    list[n + r] = make_uint2(k, (uint32_t)(l - l0) << 16 | (uint32_t)w);
-                }
-                at += (uint32_t)__popcll(bal[j]);
+            for (int j = 0; j < kRounds; ++j) {
+                const int w = w0 + j * kWave + lane;
+                const bool in = (bal[j] >> lane) & 1ull;
+                if (w < nw) km[w] = in ? k + (uint32_t)__popcll(bal[j] & lanemask_lt()) : kNone;
+                k += (uint32_t)__popcll(bal[j]);
             }
-            if (km && w < nw) km[w] = k;
         }
-        n += (int)total;
+        if (mine == 0) continue;                         // (uniform in the wavefront)
+        // lane i: quad i of the wavefront's 64
+        uint64_t b = bal[0];
+        uint32_t k = at;
+#pragma unroll
+        for (int j = 1; j < kRounds; ++j)
+            if (lane >= j * (kWave / 4)) {
+                b = bal[j];
+                k += (uint32_t)__popcll(bal[j - 1]);
+            }
+        const int sh = 4 * (lane & (kWave / 4 - 1));
+        const uint32_t in4 = (uint32_t)(b >> sh) & 15u;
+        k += (uint32_t)__popcll(b & ((1ull << sh) - 1ull));
+        const uint64_t mk = __ballot(in4 != 0u);
+        uint32_t p = 0;
+        if (lane == 0) p = atomicAdd(&nlist, (uint32_t)__popcll(mk));
+        p = __builtin_amdgcn_readfirstlane(p);
+        if (in4)
+            list[p + (uint32_t)__popcll(mk & lanemask_lt())] =
+                make_uint2(k, (uint32_t)(l - l0) << 16 | (uint32_t)(w0 / 4 + lane) << 4 | in4);
     }
-    flush();
+    __syncthreads();
+    for (uint32_t x = tid; x < nlist; x += kBlock) {
+        const uint2 u = list[x];
+        const int l = l0 + (int)(u.y >> 16), w = (int)((u.y >> 4) & 0xFFFu) * 4;
+        double mu[4], sg[4];
+        quad_moments(even, odd, w, q.len[l].m, mu, sg);
+        quad_entries(q, mu, sg, (uint32_t)(q.len[l].cell_base + i0 + w), u.y & 15u, (int64_t)u.x);
+    }
 }
 
 // One block per tile of 1024 consecutive windows of one length.
 //  1. samples into LDS; compacted position of every non-constant window;
-//     two-pass moments of those windows (one thread per window);
 //  2. thread (segment g = tid / 16, bin b = tid % 16) owns bin k = b + 1 of
 //     the 64 windows of segment g: it computes the bin directly at the
 //     segment start (four independent phasor chains, so the sum is not one
@@ -449,8 +555,7 @@ __global__ __launch_bounds__(kBlock, 3) void k_sketch(Req q, const uint32_t *__r
     for (int x = tid; x < kRowsC * (kFD - 2 * kp); x += kBlock)
         stage[x / (kFD - 2 * kp)][2 * kp + x % (kFD - 2 * kp)] = 0.0;
 
-    tile_positions_and_moments(q, L, i0, nw, tile, st, E, tile_off, mode == kSketchBetween, sm.kpos,
-                               sm.widx, sm.wsum);
+    tile_positions(q, L, i0, nw, tile, E, tile_off, sm.kpos, sm.widx, sm.wsum);
     // ---- sliding DFT in FP64: thread (segment g, bin b)
     const int b = tid & 15;
     const int g = tid >> 4;
@@ -662,8 +767,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 
     if (tid == 0) emax_s = 0;
     load_tile_samples(q.t, i0, nw + m - 1, nw + mp + kMBlk, st);
-    tile_positions_and_moments(q, L, i0, nw, tile, st, E, tile_off, mode == kSketchBetween, kpos, widx,
-                               wsum, smu, sis);
+    tile_positions(q, L, i0, nw, tile, E, tile_off, kpos, widx, wsum, smu, sis);
 
     const uint4 *Bh = (const uint4 *)(bh + bbase[l]);
     const uint4 *Bm = (const uint4 *)(bm + bbase[l]);
@@ -1158,13 +1262,13 @@ static dim3 sketch_grid(const SketchGrid &g, int mode) {
     return dim3((unsigned)g.ntiles);
 }
 
-// Lengths per block: as many as leave the chip 2048 blocks, up to 8 (samples,
-// counts and list fit four blocks a compute unit up to windows of 500).
+// Lengths per block: as many as leave the chip 2048 blocks, up to kMomentGroup.
 void launch_moments(const Req &q, const uint32_t *E, const uint32_t *tile_off, const SketchGrid &g,
                     int max_m, hipStream_t s) {
     const int64_t tiles = (g.starts + kTileW - 1) / kTileW;
-    const int group = (int)std::min<int64_t>(std::max<int64_t>(g.ntiles / 2048, 1), 8);
-    const int st_len = (kTileW + max_m + 1) & ~1;
+    const int group = (int)std::min<int64_t>(std::max<int64_t>(g.ntiles / 2048, 1), kMomentGroup);
+    // (a quad reads up to six samples past the last window's start + m)
+    const int st_len = (kTileW + max_m + 12) & ~3;
     hipLaunchKernelGGL(k_moments, dim3((unsigned)tiles, (unsigned)((q.L + group - 1) / group)),
                        dim3(kBlock), (size_t)st_len * 12, s, q, E, tile_off, group, st_len);
 }

@@ -749,9 +749,8 @@ void launch_changepoints(const double *t, int64_t n, uint32_t *flag, int *bad, h
 // (also clears tile_cnt[ntiles]; starts = windows of the shortest length)
 void launch_tile_counts(const LenInfo *len, int L, const uint32_t *E, int64_t starts, int max_m,
                         int64_t ntiles, uint32_t *tile_cnt, hipStream_t s);
-// Which tiles the sketch gives records (and, but for kSketchBetween, positions
-// and moments): every length (kSketchAll), the anchor lengths (kSketchAnchors),
-// or the lengths between anchors, after k_moments (kSketchBetween)
+// Which tiles the sketch gives records: every length (kSketchAll), the anchor
+// lengths (kSketchAnchors), or the lengths between anchors (kSketchBetween)
 enum { kSketchAll = 0, kSketchAnchors = 1, kSketchBetween = 2 };
 // The tiles of a sketch launch: all tiles [0, ntiles) of the lengths in turn, or
 // the anchors' (every stride-th length and the last; starts: windows of the
@@ -760,7 +759,7 @@ struct SketchGrid {
     int64_t ntiles, starts;
     int stride, anchors;
 };
-// Positions, moments and initial values of the lengths between anchors.
+// Positions, moments and initial values of every window.
 void launch_moments(const Req &q, const uint32_t *E, const uint32_t *tile_off, const SketchGrid &g,
                     int max_m, hipStream_t s);
 void launch_sketch(const Req &q, const uint32_t *E, const uint32_t *tile_off, const SketchGrid &g,

@@ -764,7 +764,7 @@ static void launch_records(const Plan &p, Bufs &b, const Req &q, const Opt &o, i
                            int mode, hipStream_t s) {
     const SketchGrid g{ntiles, p.n - p.ms[0] + 1, o.stride, p.anchors};
     b.emax_new = true;
-    if (mode == kSketchAnchors) launch_moments(q, b.E, b.tile_off, g, p.max_m, s);
+    if (mode != kSketchBetween) launch_moments(q, b.E, b.tile_off, g, p.max_m, s);
     if (o.precision == 0)
         launch_sketch(q, b.E, b.tile_off, g, p.max_m, mode, s);
     else

@@ -60,6 +60,19 @@ def test_probe_teams(gpu, ws, oracle, windows, prec):  # noqa: F811
     check(gpu, ws, oracle, t, m, m, excl, precision=PRECS[prec])
 
 
+@pytest.mark.parametrize("stride", [1, 16])
+@pytest.mark.parametrize("lo", [3, 4, 17])
+@pytest.mark.parametrize("windows", [5, 1023, 1024, 1026, 2049])
+def test_moment_quads(gpu, ws, oracle, windows, lo, stride):  # noqa: F811
+    """Moments of four windows a thread: windows of 3 samples and of every
+    remainder, the last window in each place of its quad and tile, and flat
+    stretches that leave one to three windows of a quad."""
+    t = np.random.default_rng(windows + lo).standard_normal(windows + lo + 2)
+    for a, w in ((37, lo), (90, lo + 1), (151, lo + 5), (700, 2 * lo + 3)):
+        t[a:a + w] = t[a:a + 1] if a < len(t) else 0.0
+    check(gpu, ws, oracle, t, lo, lo + 3, lo, k=5, anchor_stride=stride)
+
+
 @pytest.mark.parametrize("lengths", [255, 256, 257, 600])
 def test_many_lengths(gpu, ws, oracle, lengths):  # noqa: F811
     """Tables of more lengths than one launch's arguments or one block of
