@@ -68,6 +68,10 @@ int pmp_run_device_debug(const double *d_series, int64_t n, int32_t m_min,
                          pmp_motif *out, int32_t *n_out, pmp_stats *stats,
                          pmp_debug *dbg);
 
+/* Work-items (blocks times threads) of the largest launch that a probe of that
+ * many queries makes: below 2^32, the most that a launch takes. */
+int64_t pmp_probe_work_items(int64_t queries);
+
 /* The Gaussian projection g_{m,l}[c] the library draws for seed `seed`
  * (Sec. 3.4: seeded Gaussian vectors, independent per length): Box-Muller on
  * the SplitMix64 counter stream, counter ((m*64 + l)*64 + c)*2 + {0,1}. */

@@ -332,6 +332,14 @@ static inline unsigned nblk(int64_t n) { return (unsigned)((n + kBlock - 1) / kB
 // add the verifications that another would have spared.
 constexpr int64_t kTeam64 = 1024, kTeam32 = 4096, kTeam16 = 65536;
 
+// A launch has fewer than 2^32 work-items (blocks times threads), and a block of
+// eight queries has 64 at least: 2^29 queries and more take several launches.
+// Pieces of 2^20 blocks keep every launch far below that and still fill the
+// chip a hundred times over.
+constexpr int64_t kProbePiece = (int64_t)1 << 20;
+static_assert(kTeam16 <= kProbePiece, "the larger teams take one launch");
+static_assert(kProbePiece * kWave < (int64_t)1 << 32, "work-items of a launch");
+
 template <typename FT, int kTeam>
 static void launch_probe_team(const Req &q, const uint32_t *bstart, int64_t blk0, int64_t nblocks,
                               int qcap, const Quant &x, const ProbeIf &go, hipStream_t s) {
@@ -342,17 +350,22 @@ static void launch_probe_team(const Req &q, const uint32_t *bstart, int64_t blk0
 template <typename FT>
 static void launch_probe_ft(const Req &q, const uint32_t *bstart, int64_t blk0, int64_t nblocks,
                             int qcap, double cut, const Quant &x, const ProbeIf &go, hipStream_t s) {
-    if (x.x16)                    // (over 2^20 windows: the queries fill the chip)
-        hipLaunchKernelGGL((k_probe<FT, true, kGroup>), dim3((unsigned)nblocks), dim3(kWave),
-                           (size_t)qcap * sizeof(double), s, q, bstart, qcap, blk0, cut, x, go);
-    else if (nblocks <= kTeam64)
+    if (!x.x16 && nblocks <= kTeam64)
         launch_probe_team<FT, 64>(q, bstart, blk0, nblocks, qcap, x, go, s);
-    else if (nblocks <= kTeam32)
+    else if (!x.x16 && nblocks <= kTeam32)
         launch_probe_team<FT, 32>(q, bstart, blk0, nblocks, qcap, x, go, s);
-    else if (nblocks <= kTeam16)
+    else if (!x.x16 && nblocks <= kTeam16)
         launch_probe_team<FT, 16>(q, bstart, blk0, nblocks, qcap, x, go, s);
     else
-        launch_probe_team<FT, 8>(q, bstart, blk0, nblocks, qcap, x, go, s);
+        for (int64_t at = 0; at < nblocks; at += kProbePiece) {
+            const int64_t n = nblocks - at < kProbePiece ? nblocks - at : kProbePiece;
+            if (x.x16)            // (over 2^20 windows: the queries fill the chip)
+                hipLaunchKernelGGL((k_probe<FT, true, kGroup>), dim3((unsigned)n), dim3(kWave),
+                                   (size_t)qcap * sizeof(double), s, q, bstart, qcap, blk0 + at,
+                                   cut, x, go);
+            else
+                launch_probe_team<FT, 8>(q, bstart, blk0 + at, n, qcap, x, go, s);
+        }
 }
 
 void launch_probe(int precision, const Req &q, const uint32_t *bstart, int64_t blk0,
@@ -362,6 +375,12 @@ void launch_probe(int precision, const Req &q, const uint32_t *bstart, int64_t b
     const int qcap = kQwinExtra + max_m;
     if (precision == 0) launch_probe_ft<double>(q, bstart, blk0, nblocks, qcap, cut, x, go, s);
     else launch_probe_ft<float>(q, bstart, blk0, nblocks, qcap, cut, x, go, s);
+}
+
+int64_t probe_work_items(int64_t nblocks) {
+    const int64_t n = nblocks < kProbePiece ? nblocks : kProbePiece;
+    const int team = nblocks <= kTeam64 ? 64 : nblocks <= kTeam32 ? 32 : nblocks <= kTeam16 ? 16 : 8;
+    return n * (team / kGroup) * kWave;
 }
 
 void launch_hot_buckets(const uint32_t *bstart, int64_t nb, int R, unsigned long long *cnt,

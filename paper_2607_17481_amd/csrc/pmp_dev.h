@@ -788,6 +788,8 @@ struct ProbeIf {
 void launch_probe(int precision, const Req &q, const uint32_t *bstart, int64_t blk0,
                   int64_t nblocks, int max_m, double cut, const Quant &x, const ProbeIf &go,
                   hipStream_t s);
+// the work-items of the largest launch of a probe of that many blocks
+int64_t probe_work_items(int64_t nblocks);
 void launch_hot_buckets(const uint32_t *bstart, int64_t nb, int R, unsigned long long *cnt,
                         hipStream_t s);
 // (k_complete.hip): the emit stage

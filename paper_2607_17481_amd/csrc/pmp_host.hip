@@ -1803,6 +1803,10 @@ void pmp_trim(void) {
     if (known) (void)hipSetDevice(cur);
 }
 
+int64_t pmp_probe_work_items(int64_t queries) {
+    return probe_work_items((queries + kProbeQ - 1) / kProbeQ);
+}
+
 double pmp_projection(uint64_t seed, int32_t m, int32_t l, int32_t c) { return gauss(seed, m, l, c); }
 
 int pmp_calibrate_width(const double *series, int64_t n, int32_t m_min, int32_t m_max,
