@@ -650,10 +650,22 @@ void launch_stream_windows(const StreamDev &S, int max_m, hipStream_t s) {
                        (size_t)max_m * sizeof(double), s, S);
 }
 
+// Windows per launch of the search.  A launch has fewer than 2^32 work-items,
+// which a batch of 2^24 windows has at 256 threads each; 2^16 windows fill the
+// chip thirty times over.
+constexpr int kStreamPiece = 1 << 16;
+static_assert((int64_t)kStreamPiece * kProbeWaves * kWave < (int64_t)1 << 32, "work-items of a launch");
+
 void launch_stream_probe(const StreamDev &S, int max_m, hipStream_t s) {
-    if (S.nlist <= 0) return;
-    hipLaunchKernelGGL(k_stream_probe, dim3((unsigned)S.nlist), dim3(kProbeWaves * kWave),
-                       (size_t)max_m * sizeof(double), s, S);
+    for (int64_t at = 0; at < S.nlist; at += kStreamPiece) {
+        StreamDev B = S;
+        B.la += at;
+        B.lq += at;
+        B.bkey += at;
+        B.bmarg += at * kMaxBits;
+        hipLaunchKernelGGL(k_stream_probe, dim3((unsigned)std::min<int64_t>(S.nlist - at, kStreamPiece)),
+                           dim3(kProbeWaves * kWave), (size_t)max_m * sizeof(double), s, B);
+    }
 }
 
 void launch_stream_finish(const StreamDev &S, int na, const SMerge *mg, hipStream_t s) {

@@ -1,7 +1,9 @@
 """Calls at the edges of what one launch, one buffer or one allocation holds."""
+import numpy as np
 import pytest
 
 from paper_2607_17481_amd import synth
+from tests import parity
 from tests.test_gpu_parity import gpu, run  # noqa: F401  (fixtures)
 
 pytestmark = pytest.mark.gpu
@@ -17,3 +19,23 @@ def test_probe_in_pieces(gpu):  # noqa: F811
     runs = [run(gpu, own, t, lo, hi, excl, 10, budget=4, anchor_stride=s) for s in (16, 1)]
     assert runs[1][1]["probe_queries"] - runs[1][1]["indexed_cells"] // 16 > 8 << 20
     assert runs[0][0] == runs[1][0]
+
+
+def test_stream_probe_in_pieces(gpu, oracle):  # noqa: F811
+    """A batch of more windows (51 anchors of 1,300) than one launch of the
+    search takes (2^16), at a budget that takes in every earlier window: the
+    profile of the last anchors, whose windows the second launch has, is exact."""
+    lo, hi, batch, n = 20, 70, 1300, 3900
+    t = np.cumsum(np.random.default_rng(batch).standard_normal(n))
+    opts = gpu.options(gamma=1, anchor_stride=1)
+    with gpu.Stream(n, lo, hi, 5, batch, budget=n, batch=batch, opts=opts) as s:
+        s.append(t)
+        s.flush()
+        st = s.info()
+        assert st["anchors"] == 51 and st["dropped"] == 0
+        rows = {m: s.profile(m - lo)[0] for m in (lo, 69, 70)}
+    for m, P in rows.items():
+        ref = oracle.profile(t, m, batch)[0]
+        assert len(P) == len(ref)
+        for q, (a, b) in enumerate(zip(P, ref)):
+            assert parity.dist_close(float(a), float(b)), (m, q, a, b)
