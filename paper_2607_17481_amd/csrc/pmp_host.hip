@@ -665,6 +665,10 @@ static void read_head(const Plan &p, Bufs &b, const char *host) {
     memcpy(b.emax_h.data(), host + 16, p.L * sizeof(float));
     b.emax_new = false;
 }
+// Fails once a window was seen whose deviation the library cannot represent.
+static int check_windows(const Bufs &b) {
+    return b.bad_h ? fail(PMP_EINVAL, "series has windows whose standard deviation underflows") : PMP_OK;
+}
 struct JoinCounts {
     unsigned long long kept;
     uint32_t nredo, pad;
@@ -684,11 +688,15 @@ static int select_topk(const Plan &p, Bufs &b, int k, hipStream_t s, std::vector
     HIPCHK(hipMemcpyAsync(host.data(), b.bad, host.size(), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     read_head(p, b, host.data());
+    // (before the selection is looked at: its keys hold every distance of
+    // windows with a deviation, 2 sqrt(m) at most, and no others)
+    int rc = check_windows(b);
+    if (rc) return rc;
     SelState st;
     std::vector<SelCell> acc;
-    const int rc = select_result(b.sel, host.data() + he, st, acc,
-                                 [&](uint32_t c) { return len_of_cell(p, c); },
-                                 [&](int l) { return p.ms[l]; });
+    rc = select_result(b.sel, host.data() + he, st, acc,
+                       [&](uint32_t c) { return len_of_cell(p, c); },
+                       [&](int l) { return p.ms[l]; });
     if (counts) *counts = {st.kept, st.nredo, 0u};
     b.improved_h = st.improved;
     if (rc) return rc;
@@ -1158,7 +1166,8 @@ static int run_pipeline(Run &R, Arena &ar) {
         read_head(p, b, host.data());
     }
     const std::vector<float> &emax = b.emax_h;
-    if (b.bad_h) return fail(PMP_EINVAL, "series has windows whose standard deviation underflows");
+    rc = check_windows(b);
+    if (rc) return rc;
     int rounds = 0;
     double T = acc.size() == (size_t)R.k ? acc.back().d : INFINITY;
     if (R.dbg && R.dbg->t_start_scale > 0.0 && std::isfinite(T)) T *= R.dbg->t_start_scale;

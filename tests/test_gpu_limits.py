@@ -4,7 +4,7 @@ import pytest
 
 from paper_2607_17481_amd import synth
 from tests import parity
-from tests.test_gpu_parity import gpu, run  # noqa: F401  (fixtures)
+from tests.test_gpu_parity import gpu, run, ws  # noqa: F401  (fixtures)
 
 pytestmark = pytest.mark.gpu
 
@@ -39,3 +39,16 @@ def test_stream_probe_in_pieces(gpu, oracle):  # noqa: F811
         assert len(P) == len(ref)
         for q, (a, b) in enumerate(zip(P, ref)):
             assert parity.dist_close(float(a), float(b)), (m, q, a, b)
+
+
+@pytest.mark.parametrize("scale", [1e155, 1e-170])
+@pytest.mark.parametrize("k", [1, 20])
+def test_deviation_out_of_range_is_an_argument_error(gpu, ws, k, scale):  # noqa: F811
+    """Windows whose variance overflows (or underflows) are refused as an
+    argument error, also where their one-pass distances are far above every
+    distance that the selection's keys tell apart."""
+    rng = np.random.default_rng(6)
+    t = scale * (np.sin(np.arange(3000) * (2 * np.pi / 60)) + 1e-5 * rng.standard_normal(3000))
+    with pytest.raises(gpu.PMPError) as e:
+        run(gpu, ws, t, 60, 64, 30, k)
+    assert e.value.code == gpu.PMP_EINVAL
