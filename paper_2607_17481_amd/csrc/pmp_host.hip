@@ -570,13 +570,15 @@ constexpr int64_t kQuantMin = (int64_t)1 << 20;
 constexpr double kProbeCut = 1.25;   // the probe's cut over the first anchor's k-th value
 constexpr int kJoinCounts = kCtrSlots * kCtrStride + 1;
 // Kept pairs of the join buffered between its tiles and its exact stage, at
-// least 2^16: fourteen per indexed window while there are fewer than 2^20 cells, so
-// that nearly every such request takes its tiles in one chunk (a further chunk
-// costs 60 us, blocks that overflow more), four above, where chunks are long.
-// (By the cells, which the bound before any data knows too.)
+// least 2^16: fourteen per indexed window up to 2^20 of them, so that nearly
+// every request of fewer cells takes its tiles in one chunk (a further chunk
+// costs 60 us, blocks that overflow more), then as many until they are four per
+// window: there chunks are long.  Never fewer for more windows, so that a
+// workspace that holds a request holds every smaller one.
 static bool join_one_chunk(const Plan &p) { return p.cells < kQuantMin; }
-static int64_t join_pair_cap(const Plan &p, int64_t N) {
-    return std::max<int64_t>(int64_t(1) << 16, (join_one_chunk(p) ? 14 : 4) * N);
+static int64_t join_pair_cap(int64_t N) {
+    const int64_t few = 14 * std::min(N, kQuantMin);
+    return std::max({int64_t(1) << 16, few, 4 * N});
 }
 
 // Blocks of the join over N windows in L lengths, at most.
@@ -611,7 +613,7 @@ static void carve2(Arena &a, Bufs &b, const Plan &p, const Opt &o) {
     b.jk2 = take<uint32_t>(a, N);
     b.jv2 = take<uint32_t>(a, N);
     b.xw = take<float4>(a, N);
-    b.jcap = join_pair_cap(p, N);
+    b.jcap = join_pair_cap(N);
     b.jpairs = take<uint2>(a, b.jcap);
     // the segments' pair counts, the number of overflowed blocks, nonq (u32 per length)
     b.jcount = take<unsigned long long>(a, kJoinCounts + (p.L + 1) / 2);
