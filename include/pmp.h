@@ -168,8 +168,8 @@ int pmp_open(const double *series, int64_t n, int32_t m_min, int32_t m_max,
              pmp_motif *out, int32_t *n_out);
 
 /* The device memory and stream of a pmp_open call stay for the next one on the
- * same device (one block of at most 1 GiB while no call runs).  This frees
- * them. */
+ * same device (one block of at most 1 GiB while no call runs), until this call
+ * or an allocation of the library that fails frees them. */
 void pmp_trim(void);
 
 /* Same, with options (NULL = defaults) and optional stats (NULL = none). */

@@ -68,6 +68,10 @@ int pmp_run_device_debug(const double *d_series, int64_t n, int32_t m_min,
                          pmp_motif *out, int32_t *n_out, pmp_stats *stats,
                          pmp_debug *dbg);
 
+/* The next `count` attempts of this thread to allocate device memory fail as if
+ * none were left. */
+void pmp_debug_fail_allocs(int32_t count);
+
 /* Work-items (blocks times threads) of the largest launch that a probe of that
  * many queries makes: below 2^32, the most that a launch takes. */
 int64_t pmp_probe_work_items(int64_t queries);

@@ -25,6 +25,10 @@ void clear_error();
             return fail(PMP_EDEVICE, "%s failed: %s", #x, hipGetErrorString(e_));       \
     } while (0)
 
+// hipMalloc on the current device; when it fails, again without the block that
+// pmp_open keeps there.
+hipError_t device_malloc(void **p, size_t bytes);
+
 // ------------------------------------------------------------ options
 
 struct Opt {

@@ -1635,7 +1635,8 @@ static int scratch_address(void **out) {
 // last block and its stream stay for the next call on that device: one idle
 // block a device, of at most kHostKeep bytes.  It is owned by one call at a time
 // (calls that overlap find it gone and allocate); it is freed when a call needs
-// more, when an allocation of pmp_open fails, and by pmp_trim.
+// more, when any allocation of the library fails (device_malloc), and by
+// pmp_trim.
 namespace {
 constexpr size_t kHostKeep = (size_t)1 << 30;
 struct HostMem {
@@ -1658,6 +1659,32 @@ HostMem take_idle(int dev) {
     return b;
 }
 
+// Test hook (pmp_debug_fail_allocs): attempts of this thread still to fail.
+thread_local int32_t t_fail_allocs = 0;
+
+hipError_t try_malloc(void **p, size_t bytes) {
+    hipError_t e = hipErrorOutOfMemory;
+    if (t_fail_allocs > 0) --t_fail_allocs;
+    else e = hipMalloc(p, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+    }
+    return e;
+}
+}  // namespace
+
+hipError_t pmp::device_malloc(void **p, size_t bytes) {
+    hipError_t e = try_malloc(p, bytes);
+    int dev = 0;
+    if (e == hipSuccess || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return e;
+    HostMem idle = take_idle(dev);
+    if (!idle.p) return e;
+    idle.release();
+    return try_malloc(p, bytes);
+}
+
+namespace {
 struct HostBlock {
     HostMem b;
     int dev = 0;
@@ -1668,17 +1695,9 @@ struct HostBlock {
         const bool pooled = dev >= 0 && dev < kMaxDevices;
         if (pooled) b = take_idle(dev);
         if (b.bytes < bytes) b.release();
-        if (!b.p && hipMalloc(&b.p, bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            b.p = nullptr;
-            // (one that another call has put back meanwhile)
-            if (pooled) take_idle(dev).release();
-            if (hipMalloc(&b.p, bytes) != hipSuccess) {
-                (void)hipGetLastError();
-                b.p = nullptr;
-                return fail(PMP_ENOMEM, "device allocation of %zu bytes failed", bytes);
-            }
-        }
+        // (a failure gives back what another call has put there meanwhile)
+        if (!b.p && device_malloc(&b.p, bytes) != hipSuccess)
+            return fail(PMP_ENOMEM, "device allocation of %zu bytes failed", bytes);
         if (b.bytes < bytes) b.bytes = bytes;
         if (!b.s) HIPCHK(hipStreamCreateWithFlags(&b.s, hipStreamNonBlocking));
         return PMP_OK;
@@ -1813,6 +1832,8 @@ void pmp_trim(void) {
     }
     if (known) (void)hipSetDevice(cur);
 }
+
+void pmp_debug_fail_allocs(int32_t count) { t_fail_allocs = count; }
 
 int64_t pmp_probe_work_items(int64_t queries) {
     return probe_work_items((queries + kProbeQ - 1) / kProbeQ);

@@ -32,6 +32,7 @@
 #include <vector>
 
 #include "pmp.h"
+#include "pmp_host.h"
 
 namespace {
 
@@ -229,8 +230,7 @@ pmp_server *pmp_server_create(int device, size_t hbm_budget_bytes, int32_t max_s
     srv->device = device;
     srv->budget = hbm_budget_bytes & ~(kAlign - 1);
     srv->slots = max_slots;
-    if (hipMalloc((void **)&srv->arena, srv->budget) != hipSuccess) {
-        srv->arena = nullptr;
+    if (pmp::device_malloc((void **)&srv->arena, srv->budget) != hipSuccess) {
         release(srv);
         return nullptr;
     }

@@ -81,10 +81,8 @@ template <typename T>
 int dalloc(pmp_stream *s, T **p, int64_t count) {
     void *v = nullptr;
     const size_t bytes = std::max<size_t>(256, (size_t)count * sizeof(T));
-    if (hipMalloc(&v, bytes) != hipSuccess) {
-        (void)hipGetLastError();
+    if (device_malloc(&v, bytes) != hipSuccess)
         return fail(PMP_ENOMEM, "stream: hipMalloc of %zu bytes failed", bytes);
-    }
     s->allocs.push_back(v);
     s->dev_bytes += bytes;
     *p = (T *)v;
@@ -562,10 +560,8 @@ int pmp_stream_exact(pmp_stream *s, pmp_motif *out, int32_t *n_out, pmp_stats *s
         if (s->ws) HIPCHK(hipFree(s->ws));
         s->ws = nullptr;
         s->ws_bytes = 0;
-        if (hipMalloc(&s->ws, need) != hipSuccess) {
-            (void)hipGetLastError();
+        if (device_malloc(&s->ws, need) != hipSuccess)
             return fail(PMP_ENOMEM, "stream: exact query workspace of %zu bytes", need);
-        }
         s->ws_bytes = need;
     }
     return pmp_run_device(s->t, s->n_in, s->m_min, s->m_max, s->k, s->excl, s->alpha, &po, s->ws,

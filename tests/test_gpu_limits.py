@@ -52,3 +52,36 @@ def test_deviation_out_of_range_is_an_argument_error(gpu, ws, k, scale):  # noqa
     with pytest.raises(gpu.PMPError) as e:
         run(gpu, ws, t, 60, 64, 30, k)
     assert e.value.code == gpu.PMP_EINVAL
+
+
+def test_kept_memory_is_given_back_when_an_allocation_fails(gpu):  # noqa: F811
+    """pmp_open keeps a block of device memory.  A stream session, its exact
+    query and a server give it back when there is no memory left for them, and
+    go on; without a block to give back they fail."""
+    import torch
+    t = np.cumsum(np.random.default_rng(9).standard_normal(30_000))
+    args = (32, 82, 5, 32)
+    fail = gpu.lib().pmp_debug_fail_allocs
+    block = gpu.workspace_bytes(len(t), 32, 82, 5)
+    assert 400 << 20 < block < 1 << 30
+    st = gpu.Stream(3000, *args)
+    st.append(t[:3000])
+
+    def free():
+        return torch.cuda.mem_get_info(0)[0]
+
+    calls = [lambda: gpu.Stream(3000, *args).close(), lambda: gpu.Server(0, 64 << 20, 1).close(),
+             st.exact]
+    for call in calls:
+        gpu.open_host(t, *args, 16)
+        a = free()
+        fail(1)
+        call()
+        fail(0)
+        assert free() - a > block // 2
+    for call in calls[:2] + [lambda: gpu.open_host(t, *args, 16)]:
+        fail(1)
+        with pytest.raises(gpu.PMPError):
+            call()
+        fail(0)
+    st.close()
