@@ -18,8 +18,13 @@
 
 using namespace pmp;
 
-// Batches whose windows one launch makes.
+// Batches whose windows one launch makes: at most sixteen, and only while they
+// have at most 2^14 windows together (one wavefront each), twice what fills the
+// chip.  Every buffer of a group is sized by it: with sixteen batches whatever
+// their size, a session with batches of 20,000 samples at five anchors held 471
+// MB, and 309 with one, for nothing.
 constexpr int kBatchGroup = 16;
+constexpr int64_t kGroupWindows = 1 << 14;
 
 struct pmp_stream {
     int device = 0;
@@ -51,7 +56,8 @@ struct pmp_stream {
     float *bmarg = nullptr;
     SUpdate *upd = nullptr;
     uint32_t *nupd = nullptr;
-    int listcap = 0;
+    int listcap = 0;                      // windows of a batch at most
+    int group = 1;                        // batches of a group at most
     uint32_t updcap = 0;
     // pinned staging for the per-batch uploads (a ring, each slot reused
     // only after its copy finished)
@@ -223,7 +229,7 @@ int plan_batch(pmp_stream *s, int64_t t0, int64_t t1, std::vector<int32_t> &la,
     return PMP_OK;
 }
 
-// The next batches up to `ends` (at most kBatchGroup).  Windows depend on the
+// The next batches up to `ends` (at most s->group).  Windows depend on the
 // samples only, so one launch makes those of the whole group (a batch's few
 // hundred leave most of the chip idle: 24 us a batch, 3 in a group); searches
 // and what follows them go batch by batch.
@@ -290,7 +296,7 @@ int ingest(pmp_stream *s, bool partial) {
     for (;;) {
         std::vector<int64_t> ends;
         int64_t at = s->n_done;
-        while ((int)ends.size() < kBatchGroup &&
+        while ((int)ends.size() < s->group &&
                (s->n_in - at >= s->beta || (partial && s->n_in > at))) {
             at = std::min(at + s->beta, s->n_in);
             ends.push_back(at);
@@ -369,6 +375,7 @@ int pmp_stream_create(int device, int64_t capacity, int32_t m_min, int32_t m_max
     }
     s->E.assign((size_t)capacity + 1, 0u);
     s->listcap = std::max(1, na * batch);
+    s->group = (int)std::clamp<int64_t>(kGroupWindows / s->listcap, 1, kBatchGroup);
     s->updcap = (uint32_t)std::min<int64_t>((int64_t)s->listcap * s->R, UINT32_MAX);
     const int64_t need = need_select(k, s->max_am);
 
@@ -397,13 +404,13 @@ int pmp_stream_create(int device, int64_t capacity, int32_t m_min, int32_t m_max
     SCHK(dalloc(s, &s->counters, kCtrSlots * kCtrStride));
     {
         // a group's anchors, merges and list in one block
-        const size_t bytes = (size_t)kBatchGroup * ((size_t)na * (sizeof(SAnchor) + sizeof(SMerge)) +
+        const size_t bytes = (size_t)s->group * ((size_t)na * (sizeof(SAnchor) + sizeof(SMerge)) +
                                                     (size_t)2 * s->listcap * sizeof(int32_t));
         SCHK(dalloc(s, &s->d_desc, (int64_t)bytes));
         s->stage_bytes = bytes;
     }
-    SCHK(dalloc(s, &s->bkey, (int64_t)kBatchGroup * s->listcap));
-    SCHK(dalloc(s, &s->bmarg, (int64_t)kBatchGroup * s->listcap * kMaxBits));
+    SCHK(dalloc(s, &s->bkey, (int64_t)s->group * s->listcap));
+    SCHK(dalloc(s, &s->bmarg, (int64_t)s->group * s->listcap * kMaxBits));
     SCHK(dalloc(s, &s->upd, s->updcap));
     SCHK(dalloc(s, &s->nupd, 1));
     SCHK(dalloc(s, &s->selblk, (int64_t)select_block_bytes(need, k)));

@@ -85,3 +85,17 @@ def test_kept_memory_is_given_back_when_an_allocation_fails(gpu):  # noqa: F811
             call()
         fail(0)
     st.close()
+
+
+def test_stream_batches_share_buffers_only_while_small(gpu):  # noqa: F811
+    """The per-window buffers of a session follow its batch: a key, the margins,
+    the list and the improvements of one batch, not of sixteen, once a batch
+    fills a launch."""
+    n, lo, budget = 60_000, 100, 1
+    opts = gpu.options(gamma=8)
+    held = []
+    for batch in (20_000, 40_000):
+        with gpu.Stream(n, lo, lo, 5, batch, budget=budget, batch=batch, opts=opts) as s:
+            held.append(s.info()["device_bytes"])
+    per_window = 8 * budget * 16 + 4 + 24 * 4 + 8
+    assert held[1] - held[0] <= 20_000 * per_window + 4096
