@@ -72,6 +72,11 @@ int pmp_run_device_debug(const double *d_series, int64_t n, int32_t m_min,
  * none were left. */
 void pmp_debug_fail_allocs(int32_t count);
 
+/* The workgroups of a launch of `nblocks` blocks of the threshold join, and the
+ * block that one of them takes (-1: none). */
+int64_t pmp_join_workgroups(int64_t nblocks);
+int64_t pmp_join_block_of(int64_t nblocks, int64_t workgroup);
+
 /* Work-items (blocks times threads) of the largest launch that a probe of that
  * many queries makes: below 2^32, the most that a launch takes. */
 int64_t pmp_probe_work_items(int64_t queries);

@@ -478,8 +478,6 @@ __device__ __forceinline__ uint32_t join_exact(const Req &q, bool valid, uint32_
 // the signs 38.
 constexpr int kJB = kJoinBlock;               // query tiles per wavefront
 constexpr int kJQ = kJB * kJT;                // queries per wavefront
-constexpr int kXcds = 8;
-constexpr int64_t kJSeg = 128;                // consecutive blocks per XCD (16,384 queries)
 constexpr int kJWaves = 4;                    // wavefronts per SIMD the registers are held to
 
 struct JoinSmem {
@@ -854,13 +852,10 @@ void k_join_tiles(Req q, const GridLen *__restrict__ gl, const uint32_t *__restr
                   const uint4 *__restrict__ jop_s, const float4 *__restrict__ jmeta,
                   const float4 *__restrict__ gp_s, const float *__restrict__ gw_s, int64_t nwin,
                   const uint32_t *__restrict__ nonq, int cb1, int cb2, int cb3, double T,
-                  int64_t blk0, int64_t nblocks, const uint32_t *__restrict__ list, JoinOut out) {
+                  int64_t blk0, int64_t nblocks, const uint32_t *__restrict__ list, int run,
+                  JoinOut out) {
     __shared__ JoinSmem sm;
-    // consecutive blocks share most of their candidates: workgroups go to the
-    // XCDs in turn, so each XCD takes segments of kJSeg consecutive blocks,
-    // whose candidates its L2 then serves again
-    const int64_t seq = (int64_t)(blockIdx.x / kXcds);
-    const int64_t b = ((seq / kJSeg) * kXcds + blockIdx.x % kXcds) * kJSeg + seq % kJSeg;
+    const int64_t b = join_block_of((int64_t)blockIdx.x, run);
     if (b >= nblocks) return;
     const int64_t gb = list ? (int64_t)list[b] : blk0 + b;
     join_block<FT, false>(q, gl, gkey, gval, qf, jop_s, jmeta, gp_s, gw_s, nwin, nonq, cb1, cb2,
@@ -1090,18 +1085,16 @@ void launch_join_gather(const uint32_t *gval, const uint4 *jop, const float4 *gp
 void launch_join_tiles(const JoinIn &in, int64_t blk0, int64_t nblocks, const uint32_t *list,
                        const JoinOut &out, hipStream_t s) {
     if (nblocks <= 0) return;
-    // whole groups of one segment per XCD (workgroups past the last block end
-    // at once); fewer blocks than that spread over the XCDs with the grid
-    const int64_t group = kXcds * kJSeg;
-    const dim3 grid((unsigned)((nblocks + group - 1) / group * group));
+    const int run = join_run(nblocks);
+    const dim3 grid((unsigned)join_workgroups(nblocks));
     if (in.precision == 0)
         hipLaunchKernelGGL(k_join_tiles<double>, grid, dim3(kWave), 0, s, in.q, in.gl, in.gkey,
                            in.gval, in.qf, in.jop_s, in.jmeta, in.gp_s, in.gw_s, in.nwin, in.nonq,
-                           in.cb1, in.cb2, in.cb3, in.T, blk0, nblocks, list, out);
+                           in.cb1, in.cb2, in.cb3, in.T, blk0, nblocks, list, run, out);
     else
         hipLaunchKernelGGL(k_join_tiles<float>, grid, dim3(kWave), 0, s, in.q, in.gl, in.gkey,
                            in.gval, in.qf, in.jop_s, in.jmeta, in.gp_s, in.gw_s, in.nwin, in.nonq,
-                           in.cb1, in.cb2, in.cb3, in.T, blk0, nblocks, list, out);
+                           in.cb1, in.cb2, in.cb3, in.T, blk0, nblocks, list, run, out);
 }
 
 void launch_join_redo(const JoinIn &in, const uint32_t *list, uint32_t n, hipStream_t s) {

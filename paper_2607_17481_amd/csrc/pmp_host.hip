@@ -1833,6 +1833,12 @@ void pmp_trim(void) {
     if (known) (void)hipSetDevice(cur);
 }
 
+int64_t pmp_join_workgroups(int64_t nblocks) { return join_workgroups(nblocks); }
+int64_t pmp_join_block_of(int64_t nblocks, int64_t workgroup) {
+    const int64_t b = join_block_of(workgroup, join_run(nblocks));
+    return b < nblocks ? b : -1;
+}
+
 void pmp_debug_fail_allocs(int32_t count) { t_fail_allocs = count; }
 
 int64_t pmp_probe_work_items(int64_t queries) {

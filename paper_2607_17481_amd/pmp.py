@@ -120,6 +120,10 @@ def lib():
         L.pmp_run_device_noalloc.argtypes = [vp, i64, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp]
         L.pmp_debug_fail_allocs.argtypes = [i32]
         L.pmp_debug_fail_allocs.restype = None
+        L.pmp_join_workgroups.argtypes = [i64]
+        L.pmp_join_workgroups.restype = i64
+        L.pmp_join_block_of.argtypes = [i64, i64]
+        L.pmp_join_block_of.restype = i64
         L.pmp_probe_work_items.argtypes = [i64]
         L.pmp_probe_work_items.restype = i64
         L.pmp_projection.argtypes = [u64, i32, i32, i32]
