@@ -54,10 +54,12 @@ typedef struct {
        first, which real data reaches only rarely.  Other values: EINVAL. */
     double   t_start_scale;
     /* in: 0 = off.  A positive value caps the threshold join's buffer of
-       kept pairs (between its tiles and its exact stage) at that many pairs,
-       so that the tiles verify the pairs past the cap themselves, as they do
-       when a round keeps more pairs than the buffer holds.  The result is
-       the same.  Negative values: EINVAL. */
+       kept pairs (between its tiles and its exact stage) at that many pairs
+       (at least one in each of its 64 segments), so that blocks of the join
+       find their segment full, as they do when a round keeps more pairs than
+       the buffer holds: they are listed and taken again with an emptied
+       buffer, and verify their pairs themselves if one alone overflows a
+       segment.  The result is the same.  Negative values: EINVAL. */
     int64_t  join_pair_cap;
 } pmp_debug;
 
@@ -67,6 +69,10 @@ int pmp_run_device_debug(const double *d_series, int64_t n, int32_t m_min,
                          void *d_workspace, size_t ws_bytes, void *stream,
                          pmp_motif *out, int32_t *n_out, pmp_stats *stats,
                          pmp_debug *dbg);
+
+/* The join's blocks that this thread's requests took again and that they verified
+ * in place, since the last call. */
+void pmp_debug_join_blocks(int64_t *again, int64_t *in_place);
 
 /* The next `count` attempts of this thread to allocate device memory fail as if
  * none were left. */

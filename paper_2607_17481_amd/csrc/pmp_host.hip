@@ -862,6 +862,9 @@ static int emit_stage(const Plan &p, Bufs &b, Req &q, const Opt &o, int k, hipSt
 
 // ------------------------------------------------------------- pipeline
 
+// Test counters (pmp_debug_join_blocks).
+static thread_local int64_t t_join_again = 0, t_join_in_place = 0;
+
 // The sampled lengths: the first, the middle and the last.
 static WidthSets width_sets(const Plan &p) {
     WidthSets w{};
@@ -1362,6 +1365,7 @@ static int run_pipeline(Run &R, Arena &ar) {
                 if (again) new_rate(cnt.nredo - before);
                 while (cnt.nredo > 0) {
                     const uint32_t n = cnt.nredo;
+                    t_join_again += n;
                     std::swap(cur, nxt);
                     launch_fill_u64((uint64_t *)b.jcount, kJoinCounts, 0ull, s);
                     cnt.nredo = 0;
@@ -1375,6 +1379,7 @@ static int run_pipeline(Run &R, Arena &ar) {
                         if (rc) return rc;
                     }
                     if (alone && cnt.nredo > 0) {
+                        t_join_in_place += cnt.nredo;
                         launch_join_redo(in, nxt, cnt.nredo, s);
                         HIPCHK(hipGetLastError());
                         break;
@@ -1837,6 +1842,12 @@ int64_t pmp_join_workgroups(int64_t nblocks) { return join_workgroups(nblocks); 
 int64_t pmp_join_block_of(int64_t nblocks, int64_t workgroup) {
     const int64_t b = join_block_of(workgroup, join_run(nblocks));
     return b < nblocks ? b : -1;
+}
+
+void pmp_debug_join_blocks(int64_t *again, int64_t *in_place) {
+    *again = t_join_again;
+    *in_place = t_join_in_place;
+    t_join_again = t_join_in_place = 0;
 }
 
 void pmp_debug_fail_allocs(int32_t count) { t_fail_allocs = count; }

@@ -1,10 +1,12 @@
 """Calls at the edges of what one launch, one buffer or one allocation holds."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
 from paper_2607_17481_amd import synth
 from tests import parity
-from tests.test_gpu_parity import gpu, run, ws  # noqa: F401  (fixtures)
+from tests.test_gpu_parity import PRECS, gpu, run, ws  # noqa: F401  (fixtures)
 
 pytestmark = pytest.mark.gpu
 
@@ -99,3 +101,45 @@ def test_stream_batches_share_buffers_only_while_small(gpu):  # noqa: F811
             held.append(s.info()["device_bytes"])
     per_window = 8 * budget * 16 + 4 + 24 * 4 + 8
     assert held[1] - held[0] <= 20_000 * per_window + 4096
+
+
+def join_blocks(gpu):  # noqa: F811
+    again, in_place = C.c_int64(), C.c_int64()
+    gpu.lib().pmp_debug_join_blocks(C.byref(again), C.byref(in_place))
+    return again.value, in_place.value
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("n,lo,hi,fewest,most,shared", [
+    # a few blocks, each with a segment of its own from the start: taken again
+    # for nothing, then in place with many wavefronts to each
+    (900, 40, 42, 1, 60, False),
+    # forty blocks a segment, and more of them in place than half the wavefronts
+    # of that launch: one wavefront each
+    (6000, 30, 90, 1100, 10**9, True),
+])
+def test_overflowed_join_blocks(gpu, ws, oracle, n, lo, hi, fewest, most, shared, prec):  # noqa: F811
+    """Blocks of the join that find their segment of the pair buffer full.  With
+    one pair a segment they are verified in place; with room for a quarter of
+    all pairs a segment holds several blocks' but not its forty's: those that
+    overflowed are done when they are taken again."""
+    excl, k = 20, 20
+    t = np.cumsum(np.random.default_rng(n).standard_normal(n))
+    rows = oracle.pan_profile_v2(t, range(lo, hi + 1), excl)
+    join_blocks(gpu)
+    res, st = run(gpu, ws, t, lo, hi, excl, k, precision=PRECS[prec])
+    assert join_blocks(gpu) == (0, 0)
+    ok, msg = parity.check_topk(res, rows, k, oracle, t, excl=excl)
+    assert ok, msg
+    dbg = gpu.Debug()
+    dbg.size = C.sizeof(gpu.Debug)
+    seen = []
+    for cap in (1, st["join_candidates"] // 4):
+        dbg.join_pair_cap = cap
+        got, _ = run(gpu, ws, t, lo, hi, excl, k, debug=dbg, precision=PRECS[prec])
+        assert got == res
+        seen.append(join_blocks(gpu))
+        print(cap, seen[-1])
+    assert fewest <= seen[0][1] <= most
+    if shared:
+        assert seen[1][0] > seen[1][1]
