@@ -982,6 +982,12 @@ __device__ __forceinline__ void bf16_pairs(const float f[kFD], uint32_t hw[16], 
 // (lengths up to the key bound): the features rounded to fp16 (parts below its
 // normal range as 0), their metadata and the principal coordinates of the FP32
 // copy (FP64 dots) that place the grid.
+//
+// The filter's terms and its fp16 numbers are ranged for |G| <= nmax.  True
+// features keep that (|F| <= m / sqrt 2), computed ones need not: behind a sample
+// of 1e20 the FP64 slide is off by 1e5 times a unit deviation, and the record's
+// error bound says so.  Such a window gets G = 0, whose distance from F is at
+// most m / sqrt 2.
 template <typename FT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
 void k_join_ops(Req q, const double *__restrict__ udir, int64_t k0, int64_t k1) {
@@ -1027,6 +1033,8 @@ void k_join_ops(Req q, const double *__restrict__ udir, int64_t k0, int64_t k1) 
         const uint32_t cw = half_bits(join_scale(q.len[l].m));
         uint32_t hw[16];
         double n2 = 0.0, r2 = 0.0;
+        const double fmost = (double)q.len[l].m * 0.70710678118654757;   // |F| at most
+        const double nmax = (fmost * 1.01 + 1.0) * (1.0 - 1e-6);
 #pragma unroll
         for (int w = 0; w < 15; ++w) {
             uint32_t hp = 0;
@@ -1041,6 +1049,13 @@ void k_join_ops(Req q, const double *__restrict__ udir, int64_t k0, int64_t k1) 
             }
             hw[w] = hp;
         }
+        // (n2 is infinite or not a number when a feature overflows)
+        const bool in_range = n2 <= nmax * nmax;
+        if (!in_range) {
+#pragma unroll
+            for (int w = 0; w < 15; ++w) hw[w] = 0u;
+            n2 = 0.0;
+        }
         hw[15] = cw | (cw << 16);
         // f is within u32 |F~| of the stored record F~, itself within e of F;
         // so e' = e + u32 |F~| + |G - f| bounds |G - F|
@@ -1050,10 +1065,14 @@ void k_join_ops(Req q, const double *__restrict__ udir, int64_t k0, int64_t k1) 
             jo[part] = make_uint4(hw[4 * part], hw[4 * part + 1], hw[4 * part + 2], hw[4 * part + 3]);
         // w: the join's candidate Gram term 0.5 |G|^2, rounded down (its sign
         // bit is set per certify round by the grid keys)
-        q.gp[kk] = make_float4((float)p0, (float)p1, (float)p2,
+        // (coordinates past the range of a float: their error bound takes every
+        // other along)
+        auto coord = [](double p) { return fabs(p) < 1e38 ? (float)p : 0.0f; };
+        q.gp[kk] = make_float4(coord(p0), coord(p1), coord(p2),
                                (float)(0.5 * (double)(float)n2 * (1.0 - 0x1.0p-23)));
-        const double epd = ((double)erec + 5.9604644775390625e-08 * (double)nrec +
-                            sqrt(r2) * (1.0 + 1e-12)) * (1.0 + 1e-6) + 1e-30;
+        const double epd = (in_range ? (double)erec + 5.9604644775390625e-08 * (double)nrec +
+                                           sqrt(r2) * (1.0 + 1e-12)
+                                     : fmost) * (1.0 + 1e-6) + 1e-30;
         ep = (float)epd * (1.0f + 2.4e-7f);
         q.jmeta[kk] = make_float4((float)n2, ep, (float)(sqrt(n2) * (1.0 + 1e-12)) * (1.0f + 2.4e-7f),
                                   0.0f);

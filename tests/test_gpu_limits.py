@@ -143,3 +143,24 @@ def test_overflowed_join_blocks(gpu, ws, oracle, n, lo, hi, fewest, most, shared
     assert fewest <= seen[0][1] <= most
     if shared:
         assert seen[1][0] > seen[1][1]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("stride", [1, 16])
+@pytest.mark.parametrize("fill", [1e9, 1e17, 1e18, 1e20, 1e25, 1e36, 1e100])
+def test_windows_behind_a_fill_value(gpu, ws, oracle, fill, stride, prec):  # noqa: F811
+    """A huge sample (a fill value of missing data) leaves the sliding DFT of the
+    windows after it, up to the end of their segment of 64, with errors far
+    above the features themselves, as their records' bounds say.  The best pairs
+    lie just there: the certificate has to find them, whatever the value."""
+    n, lo, hi, excl, k = 3000, 32, 33, 16, 3
+    rng = np.random.default_rng(11)
+    t = rng.standard_normal(n)
+    # windows 1002 .. 1023, the last of the segment at 960, are near copies
+    t[1002:1055] = t[2102:2155] + 0.02 * rng.standard_normal(53)
+    t[1000] = fill
+    rows = oracle.pan_profile(t, range(lo, hi + 1), excl)
+    res, _ = run(gpu, ws, t, lo, hi, excl, k, budget=1, precision=PRECS[prec], anchor_stride=stride)
+    assert {x.i // 100 for x in res} <= {10, 21} and res[0].dist < 0.5
+    ok, msg = parity.check_topk(res, rows, k, oracle, t, excl=excl)
+    assert ok, msg
