@@ -70,6 +70,12 @@ int pmp_run_device_debug(const double *d_series, int64_t n, int32_t m_min,
                          pmp_motif *out, int32_t *n_out, pmp_stats *stats,
                          pmp_debug *dbg);
 
+/* The threshold join's filter term of a query: its fp16 vector's squared norm,
+ * e' and the bound on its norm, the length's largest e', the radius Tr on the
+ * true features; and the scale of the two operand slots that carry the term. */
+double pmp_join_filter_term(int32_t m, double Tr, float n2, float ep, float gnorm, float je);
+double pmp_join_scale(int32_t m);
+
 /* The join's blocks that this thread's requests took again and that they verified
  * in place, since the last call. */
 void pmp_debug_join_blocks(int64_t *again, int64_t *in_place);

@@ -543,21 +543,10 @@ __device__ __forceinline__ void join_block(const Req &q, const GridLen *__restri
         const uint4 z = make_uint4(0, 0, 0, 0);
         uint4 w0 = isq ? op0[(int64_t)pq * 2 + hh] : z, w1 = isq ? op1[(int64_t)pq * 2 + hh] : z;
         if (hh == 1) {
-            // a pair is kept iff <G_q, G_c> + v - 0.5 |G_c|^2 >= 0, with v at
-            // least 0.5 (R^2 - |G_q|^2) plus every rounding of the left side
             float hi = -65504.0f, lo = 0.0f;
             if (isq) {
                 const float4 mt = jmeta[kq];              // |G|^2, e', |G| bound, 0
-                const double R = (G.Tr + (double)mt.y + (double)je) * (1.0 + 1e-9);
-                const double nG2 = (double)mt.x * (1.0 - 0x1.0p-23);
-                double v = 0.5 * (R * R * (1.0 + 1e-9) - nG2) + G.eps_c * (double)mt.z + 1e-30;
-                v += 0x1.0p-22 * (fabs(v) + G.nmax2);
-                // the sums start at -0.5 |G_c|^2: at most 34 additions that
-                // round by up to 2^-23 of it
-                v += 4.5e-6 * G.nmax2;
-                // the slots' share of the accumulation (at most 34 additions)
-                // and of the split into hi + lo
-                v += 5e-6 * fabs(v) + 0x1.0p-12 * (double)scale;
+                const double v = join_filter_term(G.Tr, G.eps_c, G.nmax2, mt.x, mt.y, mt.z, je, scale);
                 // (past the range every pair passes: |v| / scale is below
                 // 32768 wherever the test decides anything)
                 const float x = (float)fmin(fmax(v / (double)scale, -60000.0), 60000.0);

@@ -1034,7 +1034,7 @@ void k_join_ops(Req q, const double *__restrict__ udir, int64_t k0, int64_t k1) 
         uint32_t hw[16];
         double n2 = 0.0, r2 = 0.0;
         const double fmost = (double)q.len[l].m * 0.70710678118654757;   // |F| at most
-        const double nmax = (fmost * 1.01 + 1.0) * (1.0 - 1e-6);
+        const double nmax = join_nmax(q.len[l].m) * (1.0 - 1e-6);
 #pragma unroll
         for (int w = 0; w < 15; ++w) {
             uint32_t hp = 0;

@@ -228,11 +228,39 @@ struct GridLen {
 // 2.5 nmax^2 in absolute value (nmax: the largest |G| of length m), into the
 // range of an fp16 number: the two operand slots past the features hold c on
 // the candidate's side and the term over c, as hi + lo, on the query's.
-__device__ __forceinline__ float join_scale(int m) {
+__host__ __device__ inline float join_scale(int m) {
     const float nmax2 = 0.5f * (float)m * (float)m * 1.03f + 2.0f * (float)m + 2.0f;
     float c = 1.0f;
     while (32768.0f * c < 2.5f * nmax2) c *= 2.0f;
     return c;
+}
+
+// The largest |G| of windows of m samples, and the join's dot-product error per
+// unit |G_q| (times that |G_c|): at most 34 additions of its products that round
+// by up to 2^-23, four times over.
+__host__ __device__ inline double join_nmax(int m) {
+    return (double)m / 1.4142135623730951 * 1.01 + 1.0;
+}
+__host__ __device__ inline double join_eps(double nmax) { return 1.6e-5 * nmax; }
+
+// The query's filter term v: a pair is kept iff <G_q, G_c> + v - 0.5 |G_c|^2 >= 0
+// as the tiles sum it, so v is at least 0.5 (R^2 - |G_q|^2) plus every rounding
+// of the left side.  Tr: radius on the true features; eps_c, nmax2: of the length
+// (GridLen); n2, ep, gn: |G|^2, e' and the bound on |G| of the query; je: the
+// length's largest e'.
+__host__ __device__ inline double join_filter_term(double Tr, double eps_c, double nmax2, float n2,
+                                                   float ep, float gn, float je, float scale) {
+    const double R = (Tr + (double)ep + (double)je) * (1.0 + 1e-9);
+    const double nG2 = (double)n2 * (1.0 - 0x1.0p-23);
+    double v = 0.5 * (R * R * (1.0 + 1e-9) - nG2) + eps_c * (double)gn + 1e-30;
+    v += 0x1.0p-22 * (fabs(v) + nmax2);
+    // the sums start at -0.5 |G_c|^2: at most 34 additions that round by up to
+    // 2^-23 of it
+    v += 4.5e-6 * nmax2;
+    // the slots' share of the accumulation (at most 34 additions) and of the
+    // split into hi + lo
+    v += 5e-6 * fabs(v) + 0x1.0p-12 * (double)scale;
+    return v;
 }
 
 // State of the device-side radix select (k_certify.hip).

@@ -1224,7 +1224,7 @@ static int run_pipeline(Run &R, Arena &ar) {
             bool two_d = true, three_d = true;
             for (int l = 0; l < p.L; ++l) {
                 const double m = p.ms[l];
-                const double nmax = m / std::sqrt(2.0) * 1.01 + 1.0;
+                const double nmax = join_nmax(p.ms[l]);
                 const double efmax = ((double)emax[l] + 5.9604644775390625e-08 * nmax * 1.01) *
                                          (1.0 + 1e-6) + 1e-30;
                 const double Tr = Teff * std::sqrt(m / 2.0) * (1.0 + 1e-9);
@@ -1241,7 +1241,7 @@ static int run_pipeline(Run &R, Arena &ar) {
             const int cb3 = three_d ? cb3d : 0;
             for (int l = 0; l < p.L; ++l) {
                 const double m = p.ms[l];
-                const double nmax = m / std::sqrt(2.0) * 1.01 + 1.0;
+                const double nmax = join_nmax(p.ms[l]);
                 GridLen &G = gl[l];
                 G.qlo = -(nmax * 1.001 + 1e-9);
                 // each coordinate's cells span [qlo, -qlo] in 2^bits cells at
@@ -1259,7 +1259,7 @@ static int run_pipeline(Run &R, Arena &ar) {
                     G.hinv = 1.0 / std::max(hr / kJoinNb, hmin);
                     G.hinv2 = 1.0 / std::max(hr / kJoinNb, hmin2);
                 }
-                G.eps_c = 1.6e-5 * nmax;
+                G.eps_c = join_eps(nmax);
                 // per-pair test on the stored coordinates (floats, each within
                 // 2^-24 nmax of its FP64 value)
                 G.rp = std::isinf(Rf[l]) ? INFINITY
@@ -1843,6 +1843,12 @@ int64_t pmp_join_block_of(int64_t nblocks, int64_t workgroup) {
     const int64_t b = join_block_of(workgroup, join_run(nblocks));
     return b < nblocks ? b : -1;
 }
+
+double pmp_join_filter_term(int32_t m, double Tr, float n2, float ep, float gnorm, float je) {
+    const double nmax = join_nmax(m);
+    return join_filter_term(Tr, join_eps(nmax), nmax * nmax, n2, ep, gnorm, je, join_scale(m));
+}
+double pmp_join_scale(int32_t m) { return join_scale(m); }
 
 void pmp_debug_join_blocks(int64_t *again, int64_t *in_place) {
     *again = t_join_again;

@@ -118,6 +118,10 @@ def lib():
         L.pmp_run_device_debug.argtypes = [vp, i64, i32, i32, i32, i32, i32, vp, vp, sz, vp, vp,
                                            vp, vp, vp]
         L.pmp_run_device_noalloc.argtypes = [vp, i64, i32, i32, i32, i32, i32, vp, vp, vp, vp, vp]
+        L.pmp_join_filter_term.argtypes = [i32, C.c_double] + [C.c_float] * 4
+        L.pmp_join_filter_term.restype = C.c_double
+        L.pmp_join_scale.argtypes = [i32]
+        L.pmp_join_scale.restype = C.c_double
         L.pmp_debug_join_blocks.argtypes = [vp, vp]
         L.pmp_debug_join_blocks.restype = None
         L.pmp_debug_fail_allocs.argtypes = [i32]
