@@ -11,7 +11,8 @@
 // FP32.  With z = (t - mu) / sigma = x s / sigma + (c - mu) / sigma up to
 //   delta = (2^-16 (1 + 1e-4) + 2^-21) max|t - c| / sigma
 // per sample (the rounding of x; the second term covers the FP32 factors and
-// the FP32 evaluation of the difference), the sum S over the window obeys
+// the FP32 evaluation of the difference: six units of 2^-24 max|t - c| / sigma on
+// one side and seven on the other, of eight each), the sum S over the window obeys
 //   sqrt(S) <= d + sqrt(m) (delta_i + delta_j),  S's own roundings < 1e-4,
 // so a pair whose S reaches (thr + sqrt(m) (delta_i + delta_j))^2 (1 + 2e-4)
 // has d > thr and can lower no cell from above thr.  Every other pair goes on
