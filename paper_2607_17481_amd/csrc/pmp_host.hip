@@ -563,18 +563,28 @@ static void carve1(Arena &a, Bufs &b, const Plan &p, int k) {
 
 static bool needs_kmap(const Opt &o) { return o.stride > 1; }
 
-// Indexed windows from which a request uses the 16-bit prefilter: below, its
-// data and the selection for the cut (about 0.1 ms) cost more than the exact
-// distances they save.
+// Indexed windows from which a request uses the 16-bit prefilter, and below which
+// it takes the small requests' forms (the probe called off on the device, the join
+// in one chunk).  With the line at 2^18, 2^20 and 2^22, ms a request: ECG-like at 51
+// lengths of 100..400, 10,000 samples (0.5 million windows) 2.3, 2.6, 2.6; 20,000
+// (1.0) 2.75, 4.0, 4.0; 26,000 (1.3) 3.2, 3.2, 5.0; 80,000 (4.1) 6.8, 6.8, 13.3;
+// random walk 16,000 at 50..100 (0.8) 2.65, 3.0, 3.0; Wafer-like the same.  So 2^20
+// is well below what loses and still above the best line.
 constexpr int64_t kQuantMin = (int64_t)1 << 20;
-constexpr double kProbeCut = 1.25;   // the probe's cut over the first anchor's k-th value
+// The probe's cut over the first anchor's k-th value.  1, 1.25, 1.5, 2 and none, ms
+// a request: ECG-like 1M 89.3, 90.0, 91.2, 94.3, 128; 250,000 18.2, 18.8, 19.5,
+// 21.0, 32.0; random walk 30,000 at 50..100 3.6, 3.7, 3.3, 3.9, 4.9.
+constexpr double kProbeCut = 1.25;
 constexpr int kJoinCounts = kCtrSlots * kCtrStride + 1;
 // Kept pairs of the join buffered between its tiles and its exact stage, at
 // least 2^16: fourteen per indexed window up to 2^20 of them, so that nearly
 // every request of fewer cells takes its tiles in one chunk (a further chunk
 // costs 60 us, blocks that overflow more), then as many until they are four per
-// window: there chunks are long.  Never fewer for more windows, so that a
-// workspace that holds a request holds every smaller one.
+// window: there chunks are long.  Fourteen is what the workspace's bound before
+// such buffers left room for; with 4, 8, 14 and 28 ECG-like series of 10,000 to
+// 1M samples and random walks take the same within 3 % (26,000: 3.25, 3.2, 3.2,
+// 3.1 ms).  Never fewer for more windows, so that a workspace that holds a
+// request holds every smaller one.
 static bool join_one_chunk(const Plan &p) { return p.cells < kQuantMin; }
 static int64_t join_pair_cap(int64_t N) {
     const int64_t few = 14 * std::min(N, kQuantMin);
