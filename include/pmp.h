@@ -275,8 +275,9 @@ void pmp_server_destroy(pmp_server *srv);
  * first sample (pmp_stream_flush cuts one early).
  * Sessions are not thread-safe; one session uses one device.
  *
- * Memory: about 330 bytes per (sample, anchor length) of `capacity` on the
- * device, 4 bytes per sample on the host; an exact query adds the
+ * Memory: about 330 bytes per (sample, anchor length) of `capacity` and
+ * 16 gamma budget + 108 per (sample, anchor length) of a batch on the device, 4
+ * bytes per sample on the host; an exact query adds the
  * workspace pmp_run_device needs for the samples held. */
 typedef struct pmp_stream pmp_stream;
 
