@@ -917,9 +917,9 @@ struct JoinIn {
 // Where the tiles' kept pairs go: kCtrSlots segments of segcap pairs each,
 // their fill counts kCtrStride apart in pcount (a block writes to the segment
 // of its workgroup, workgroup % kCtrSlots, so that reservations do not queue on
-// one address: the blocks of a launch of up to kCtrSlots have a segment each);
-// blocks that find theirs full go to `redo` (*nredo of them, one entry per block
-// of a launch).
+// one address: a launch of up to kCtrSlots blocks has as many workgroups, and a
+// segment each); blocks that find theirs full go to `redo` (*nredo of them, one entry per block of a
+// launch).
 struct JoinOut {
     uint2 *pairs;
     unsigned long long *pcount;
@@ -929,18 +929,18 @@ struct JoinOut {
 };
 // Which of a launch's blocks a workgroup takes.  Consecutive blocks share most of
 // their candidates and workgroups go to the eight XCDs in turn, so each XCD takes
-// runs of consecutive blocks, whose candidates its L2 then serves again: up to 128
-// (16,384 queries), but only so long that every XCD has 64 of them, for heavy blocks
-// lie together too.  Runs of 1, 16, 128 and 1024 at ECG-like 1M (launches of 65,000
-// blocks): 91.6, 91.3, 91.1 and 100.6 ms a request; 250,000 (FP64) 19.0, 18.9, 19.0,
-// 20.1; 200,000 at one length (1,563 blocks) 6.9, 6.9, 7.4, 7.6; random walk 9,000
-// at 250..460 4.6, 4.7, 5.2, 4.7.  (128 whatever the launch put up to 128 blocks on
-// one XCD and 64 into eight segments of the pair buffer, so that lists of overflowed
-// blocks overflowed again: 13.9 ms at 200,000, 5.9 for the walk.)
+// runs of consecutive blocks, whose candidates its L2 then serves again: sixteen
+// (2,048 queries), or an eighth of a launch of fewer than 128 blocks.  Runs of
+// 1, 16, 128 and 1024 at ECG-like 1M: 91.6, 91.3, 91.1 and 100.6 ms a request;
+// 250,000 (FP64) 19.0, 18.9, 19.0, 20.1; 200,000 at one length 6.9, 6.9, 7.4, 7.6;
+// random walk 9,000 at 250..460 4.6, 4.7, 5.2, 4.7: long runs leave XCDs waiting
+// for the one with the heavy blocks.  (128 whatever the launch put up to 128
+// blocks on one XCD and 64 into eight segments of the pair buffer, so that lists
+// of overflowed blocks overflowed again: 13.9 ms at 200,000, 5.9 for the walk.)
 constexpr int kXcds = 8;
-constexpr int64_t kJoinRun = 128, kJoinRuns = 64;
+constexpr int64_t kJoinRun = 16;
 inline int join_run(int64_t nblocks) {
-    const int64_t r = nblocks / (kXcds * kJoinRuns);
+    const int64_t r = (nblocks + kXcds - 1) / kXcds;
     return (int)(r < 1 ? 1 : r < kJoinRun ? r : kJoinRun);
 }
 // (whole rounds of runs: workgroups past the last block end at once)
