@@ -929,16 +929,15 @@ struct JoinOut {
 };
 // Which of a launch's blocks a workgroup takes.  Consecutive blocks share most of
 // their candidates and workgroups go to the eight XCDs in turn, so each XCD takes
-// runs of consecutive blocks, whose candidates its L2 then serves again: sixteen
-// (2,048 queries), or an eighth of a launch of fewer than 128 blocks.  Runs of
-// 1, 16, 128 and 1024 at ECG-like 1M: 91.6, 91.3, 91.1 and 100.6 ms a request;
-// 250,000 (FP64) 19.0, 18.9, 19.0, 20.1; 200,000 at one length 6.9, 6.9, 7.4, 7.6;
-// random walk 9,000 at 250..460 4.6, 4.7, 5.2, 4.7: long runs leave XCDs waiting
-// for the one with the heavy blocks.  (128 whatever the launch put up to 128
-// blocks on one XCD and 64 into eight segments of the pair buffer, so that lists
-// of overflowed blocks overflowed again: 13.9 ms at 200,000, 5.9 for the walk.)
+// runs of consecutive blocks, whose candidates its L2 then serves again: 128 (16,384
+// queries) where there are enough, else as many as spread the blocks over all
+// XCDs.  With 128 whatever their number, up to 128 blocks ran on one XCD and 64
+// shared eight segments of the pair buffer, so that lists of overflowed blocks
+// overflowed again: ECG-like 200,000 at one length of 100 samples 13.9 -> 7.5 ms a
+// request, 30,000 at 41 lengths and four bins 30.2 -> 9.2, random walk 9,000 at
+// 250..460 5.93 -> 5.06.
 constexpr int kXcds = 8;
-constexpr int64_t kJoinRun = 16;
+constexpr int64_t kJoinRun = 128;
 inline int join_run(int64_t nblocks) {
     const int64_t r = (nblocks + kXcds - 1) / kXcds;
     return (int)(r < 1 ? 1 : r < kJoinRun ? r : kJoinRun);

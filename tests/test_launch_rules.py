@@ -31,11 +31,11 @@ def test_join_blocks_are_placed_over_the_chip(n):
         if b >= 0:
             assert b not in at
             at[b] = w
-    assert len(at) == n and groups < n + 8 * 16
+    assert len(at) == n and groups < n + 8 * 128
     load = [0] * 8
     for w in at.values():
         load[w % 8] += 1
-    run = min(16, -(-n // 8))
+    run = min(128, -(-n // 8))
     assert max(load) - min(load) <= run and max(load) <= -(-n // (8 * run)) * run
     assert sum(x > 0 for x in load) == min(8, -(-n // run))
     segments = {w % 64 for w in at.values()}
