@@ -917,9 +917,9 @@ struct JoinIn {
 // Where the tiles' kept pairs go: kCtrSlots segments of segcap pairs each,
 // their fill counts kCtrStride apart in pcount (a block writes to the segment
 // of its workgroup, workgroup % kCtrSlots, so that reservations do not queue on
-// one address: a launch of up to kCtrSlots blocks has as many workgroups, and a
-// segment each); blocks that find theirs full go to `redo` (*nredo of them, one entry per block of a
-// launch).
+// one address: the blocks of a launch of up to kCtrSlots have a segment each);
+// blocks that find theirs full go to `redo` (*nredo of them, one entry per block
+// of a launch).
 struct JoinOut {
     uint2 *pairs;
     unsigned long long *pcount;
@@ -929,13 +929,17 @@ struct JoinOut {
 };
 // Which of a launch's blocks a workgroup takes.  Consecutive blocks share most of
 // their candidates and workgroups go to the eight XCDs in turn, so each XCD takes
-// runs of consecutive blocks, whose candidates its L2 then serves again: 128 (16,384
-// queries) where there are enough, else as many as spread the blocks over all
-// XCDs.  With 128 whatever their number, up to 128 blocks ran on one XCD and 64
-// shared eight segments of the pair buffer, so that lists of overflowed blocks
-// overflowed again: ECG-like 200,000 at one length of 100 samples 13.9 -> 7.5 ms a
-// request, 30,000 at 41 lengths and four bins 30.2 -> 9.2, random walk 9,000 at
-// 250..460 5.93 -> 5.06.
+// runs of consecutive blocks: 128 (16,384 queries), or an eighth of a launch of
+// fewer than 1024, so that every XCD has some.  The tiles themselves hardly care
+// (ECG-like 1M with runs of 1, 16 and 128: 91.6, 91.3, 91.1 ms a request), but the
+// pairs of a segment are then neighbours and k_join_verify takes them on the XCD
+// that found them: with runs of 8 instead of 128 it took 372 us instead of 270 for
+// a random walk of 20,714 at 292..317 (4,150 blocks).  Longer runs leave XCDs
+// waiting for the one with the heavy blocks: 100.6 ms with 1024 at ECG-like 1M;
+// 128 themselves cost 200,000 samples of one length (1,563 blocks) 7.4 ms against
+// 6.9 with 16.  (128 whatever the launch put up to 128 blocks on one XCD and 64 into
+// eight segments of the pair buffer, so that lists of overflowed blocks overflowed
+// again: 13.9 ms there, 30.2 instead of 9.2 at 30,000, 41 lengths and four bins.)
 constexpr int kXcds = 8;
 constexpr int64_t kJoinRun = 128;
 inline int join_run(int64_t nblocks) {
