@@ -7,7 +7,8 @@
 //   R = T sqrt(m/2) + e'_i + e'_j,     e' >= ||G - F||
 // (the record's bound, the FP32 rounding and the fp16 rounding itself, which
 // k_join_ops measures window by window; features off by more than their range
-// give way to G = 0, which is within the largest possible norm of any F).  The join finds every such pair:
+// give way to G = 0, which is within the largest possible norm of any F).  The
+// join finds every such pair:
 //
 //  * grid: each length's windows get coordinates, the projections of their
 //    FP32 feature copies f on the leading principal directions of that
